@@ -125,7 +125,13 @@ struct PipeCfg {
     static constexpr int NT = 64 * WM * WN;
     static constexpr int WTM = BMC / WM, WTN = BN / WN;
     static constexpr int MF = MFO_ ? MFO_ : ((!FP8 && WTM >= 32) ? 32 : 16);   // MFMA block edge
-    static constexpr int KS = MF == 32 ? 16 : 32;              // k elements per MFMA
+    // fp8 tiles of 64 rows and more ([K][N] weights) are MFMA-bound: they run on the deep instructions
+    // (16x16x128, 32x32x64: 4.3 and 3.9 PFLOP/s on random operands where 16x16x32 sustains 2.4).  The error of a sum
+    // against 64 bits is that of the 16x16x32 form (measured on four distributions, K = 128 ... 8192), and on the fp8
+    // layer (64 experts, top-6, 2048 -> 2816) the outputs are the same bits.  There the product went from 283 to 176 us at
+    // 4096 tokens and from 473 to 303 us at 8192; with the fused activation from 263 to 177 us at 4096.
+    static constexpr bool F8W = FP8_ && !WKC_ && BM_ >= 64;
+    static constexpr int KS = F8W ? (MF == 32 ? 64 : 128) : (MF == 32 ? 16 : 32);   // k elements per MFMA
     static constexpr int KSTEPS = BK / KS;
     static constexpr int NBW = WTN / MF, MBW = WTM / MF;
     static constexpr int MBW_BODY = BM / WM / MF;              // row blocks per wavefront without the slack rows
@@ -138,7 +144,7 @@ struct PipeCfg {
     // ... and with at least four weight blocks per wavefront the fragments are reloaded in place (see reads_after)
     static constexpr bool XROLL = PERWAVE && WTN / MF >= 4;
     // ... and the bf16 [K][N] ones run their k loop in two alternating roles (see run_pp in pipe_tile)
-    static constexpr bool PP = XROLL && !WKC_ && !FP8_ && NS_ == 2 && BK_ / KS == 2;
+    static constexpr bool PP = XROLL && !WKC_ && (!FP8_ || F8W) && NS_ == 2 && BK_ / KS <= 2;
     static constexpr int XROW = BK * ES, CPR = XROW / 16;
     static constexpr int WROW = BN * ES, CPRW = WROW / 16;
     // the token tile in LDS is rounded up so that every wavefront issues the same number of DMA instructions
@@ -149,12 +155,14 @@ struct PipeCfg {
     static constexpr int LDS_BYTES = NS * XS_BYTES + (WHALF ? NSWH * WH_BYTES : NSW * WS_BYTES);
     static_assert(!WHALF || (NS_ == 2 && !FP8_ && !WKC_ && BK_ / (MFO_ == 16 ? 32 : 16) == 2 && NSWH_ % 2 == 1),
                   "half-stage weight ring: two k-steps per k-tile, two token stages, an odd number of half-stages");
-    // weight-fragment LDS reads per k-step (two 4-k halves for bf16, one 8-k piece for fp8)
-    static constexpr int WREADS = NBW * ((FP8 || WKC) ? 1 : 2);
+    // weight-fragment LDS reads per k-step and block (two 4-k halves for bf16, 8-k pieces for fp8: one, or four for
+    // the deep instructions)
+    static constexpr int WPIECES = F8W ? 4 : ((FP8 || WKC) ? 1 : 2);
+    static constexpr int WREADS = NBW * WPIECES;
     // memory-bound tiles start the weight stream before the token rows are known
     static constexpr bool EARLY_W = MF == 16;
     static_assert(XROW == 64 || XROW == 128, "token tile rows are 64 or 128 bytes");
-    static_assert(WTM % MF == 0 && WTN % MF == 0 && KSTEPS >= 2 && BK % KS == 0, "wave tile");
+    static_assert(WTM % MF == 0 && WTN % MF == 0 && (KSTEPS >= 2 || PP) && BK % KS == 0, "wave tile");
     static_assert(BM % (WM * MF) == 0 && SLACK % (WM * MF) == 0, "body and slack rows split evenly over the wavefront rows");
     static_assert(WROW <= 1024, "weight tile row");
     static_assert(XS_BYTES % 1024 == 0 && WS_BYTES % 1024 == 0, "DMA granularity");
@@ -177,7 +185,12 @@ __device__ __forceinline__ int pswz_x(int row) {
 template <class C>
 __device__ __forceinline__ int pswz_w(int krow) {
     int s;
-    if constexpr (C::FP8) s = C::CPRW >= 16 ? (krow & 15) : ((krow >> 1) & 7);
+    if constexpr (C::F8W) {
+        // a half-wavefront of a transposing read covers 16 k-rows (8 and the 8 sixteen further on) of one 16-column
+        // chunk (16-row MFMA blocks), or 8 k-rows of two adjacent chunks (32-row blocks)
+        static_assert(!C::F8W || C::CPRW == 16, "deep fp8 tiles are 256 columns wide");
+        s = C::MF == 32 ? (krow & 7) << 1 : ((krow & 7) | ((krow >> 1) & 8));
+    } else if constexpr (C::FP8) s = C::CPRW >= 16 ? (krow & 15) : ((krow >> 1) & 7);
     else if constexpr (C::MF == 32) s = (krow & 3) << 2;
     else s = ((krow & 3) | ((krow >> 1) & 4)) << 1;
     return s & (C::CPRW - 1);
@@ -409,14 +422,23 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     mb_live = mb_live < 0 ? 0 : (mb_live > MBW ? MBW : mb_live);
 
     // ---- fragment registers, double-buffered across k-steps; per-lane LDS offsets of k-step 0
-    u32x2_t wq[2][NBW][2];       // (XROLL: [1][nb < NBW / 2] is never used)
-    u32x4_t xq[C::XROLL ? 1 : 2][MBW];
+    // Deep fp8 instructions: 32 bytes per lane and operand, in 16-byte chunks of k.  The instruction pairs byte j of lane
+    // group i of one operand with byte j of lane group i of the other, so any assignment of k to (group, byte) serves
+    // as long as both operands use the same one; this one keeps the token reads at 16 bytes.
+    using wfrag_t = typename std::conditional<C::F8W, u32x2_t[4], u32x2_t[2]>::type;
+    using xfrag_t = typename std::conditional<C::F8W, u32x4_t[2], u32x4_t[1]>::type;
+    wfrag_t wq[2][NBW];          // (XROLL: [1][nb < NBW / 2] is never used)
+    xfrag_t xq[C::XROLL ? 1 : 2][MBW];
     int w_rd[NBW];
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb) {
         int kr0, ncol, c, within;
-        if constexpr (C::FP8) {
-            kr0 = 8 * g + (li >> 1);
+        if constexpr (C::F8W && MF == 32) {
+            kr0 = 16 * (g >> 1) + (li >> 1);
+            ncol = wn * C::WTN + nb * 32 + 16 * (g & 1) + 8 * (li & 1);
+            c = ncol >> 4; within = ncol & 15;
+        } else if constexpr (C::FP8) {
+            kr0 = (C::F8W ? 16 : 8) * g + (li >> 1);
             ncol = wn * C::WTN + nb * 16 + 8 * (li & 1);
             c = ncol >> 4; within = ncol & 15;
         } else if constexpr (MF == 32) {
@@ -465,6 +487,11 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                     const int wb = wbuf(buf, nb);
                     wq[wb][nb][0].x = v.x; wq[wb][nb][0].y = v.y; wq[wb][nb][1].x = v.z; wq[wb][nb][1].y = v.w;
                 }
+            } else if constexpr (C::F8W) {
+                // piece (s, q) of a fragment: k = 16 (lane group) + 8 q + s * (the k of all groups' 16-byte chunks)
+                const int nb = (r - 1) >> 2, s = ((r - 1) >> 1) & 1, q = (r - 1) & 1;
+                const char* p = ws + w_rd[nb] + (kk * C::KS + s * (C::KS / 2) + q * 8) * C::WROW;
+                wq[wbuf(buf, nb)][nb][2 * s + q] = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr8_b64_v2i32((MOE_LDS(i32x2_t)*)(p)));
             } else if constexpr (C::FP8) {
                 const int nb = r - 1;
                 const char* p = ws + w_rd[nb] + (kk * 32) * C::WROW;
@@ -478,13 +505,19 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             const int mb = r == 0 ? 0 : r - WREADS;
             if (tail && mb >= mb_live) return;
             const char* xrow = xs + x_rd + mb * X_BLOCK_STRIDE;
-            if constexpr (C::FP8) {
+            if constexpr (C::F8W) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const int c = MF == 32 ? kk * 4 + s * 2 + (lane >> 5) : s * 4 + g;
+                    xq[C::XROLL ? 0 : buf][mb][s] = *reinterpret_cast<const u32x4_t*>(xrow + ((c ^ xswz) << 4));
+                }
+            } else if constexpr (C::FP8) {
                 const int c = kk * 2 + (g >> 1);
                 const u32x2_t v = *reinterpret_cast<const u32x2_t*>(xrow + ((c ^ xswz) << 4) + (g & 1) * 8);
-                xq[C::XROLL ? 0 : buf][mb].x = v.x; xq[C::XROLL ? 0 : buf][mb].y = v.y;
+                xq[C::XROLL ? 0 : buf][mb][0].x = v.x; xq[C::XROLL ? 0 : buf][mb][0].y = v.y;
             } else {
                 const int c = MF == 32 ? kk * 2 + (lane >> 5) : kk * 4 + g;
-                xq[C::XROLL ? 0 : buf][mb] = *reinterpret_cast<const u32x4_t*>(xrow + ((c ^ xswz) << 4));
+                xq[C::XROLL ? 0 : buf][mb][0] = *reinterpret_cast<const u32x4_t*>(xrow + ((c ^ xswz) << 4));
             }
         }
     };
@@ -492,14 +525,22 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // for every row block and then the second half, which lets the first half's fragments be reloaded in place
     auto mfma_at = [&](int mb, int nb, int buf, bool tail) __attribute__((always_inline)) {
         if (tail && mb >= mb_live) return;
-        if constexpr (C::FP8) {
-            const u32x2_t xv = {xq[C::XROLL ? 0 : buf][mb].x, xq[C::XROLL ? 0 : buf][mb].y};
+        if constexpr (C::F8W) {
+            const u32x2_t* w = wq[wbuf(buf, nb)][nb];
+            const u32x4_t* x = xq[C::XROLL ? 0 : buf][mb];
+            const i32x8_t wf = {(int)w[0].x, (int)w[0].y, (int)w[1].x, (int)w[1].y, (int)w[2].x, (int)w[2].y, (int)w[3].x, (int)w[3].y};
+            const i32x8_t xf = {(int)x[0].x, (int)x[0].y, (int)x[0].z, (int)x[0].w, (int)x[1].x, (int)x[1].y, (int)x[1].z, (int)x[1].w};
+            if constexpr (C::PP) asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+v"(acc[nb][mb]) : "v"(wf), "v"(xf));
+            else if constexpr (MF == 32) acc[nb][mb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wf, xf, acc[nb][mb], 0, 0, 0, 0, 0, 0);
+            else acc[nb][mb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf, xf, acc[nb][mb], 0, 0, 0, 0, 0, 0);
+        } else if constexpr (C::FP8) {
+            const u32x2_t xv = {xq[C::XROLL ? 0 : buf][mb][0].x, xq[C::XROLL ? 0 : buf][mb][0].y};
             acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(__builtin_bit_cast(long, wq[wbuf(buf, nb)][nb][0]),
                                                                      __builtin_bit_cast(long, xv), acc[nb][mb], 0, 0, 0);
         } else {
             const int wb = wbuf(buf, nb);
             const u32x4_t wv = {wq[wb][nb][0].x, wq[wb][nb][0].y, wq[wb][nb][1].x, wq[wb][nb][1].y};
-            const bf16x8_t wf = __builtin_bit_cast(bf16x8_t, wv), xf = __builtin_bit_cast(bf16x8_t, xq[C::XROLL ? 0 : buf][mb]);
+            const bf16x8_t wf = __builtin_bit_cast(bf16x8_t, wv), xf = __builtin_bit_cast(bf16x8_t, xq[C::XROLL ? 0 : buf][mb][0]);
             if constexpr (C::PP) {
                 // Written out so that the sum stays in its registers: left to itself the register allocator moves
                 // accumulators into fragment registers that have just become free and copies them back at the end
@@ -657,7 +698,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
         // is rounded up to whole instructions per wavefront; the upper wavefronts' last one may be all padding)
         constexpr int XI_ROLE = (C::BMC + XROWS_PER_INST * NW - 1 - ROLE * (NW / 2) * XROWS_PER_INST) / (XROWS_PER_INST * NW);
         constexpr int XIL = decltype(xil_tag)::value < XI_ROLE ? decltype(xil_tag)::value : XI_ROLE;
-        static_assert(KSTEPS == 2 && NS == 2 && NSW == 3 && WI % 2 == 0 && !STREAM && C::EARLY_W && C::XROLL, "alternating roles");
+        static_assert(KSTEPS <= 2 && NS == 2 && NSW == 3 && WI % 2 == 0 && !STREAM && C::EARLY_W && C::XROLL, "alternating roles");
         auto bar = []() __attribute__((always_inline)) {
             MOE_SCHED_FENCE();
             __builtin_amdgcn_s_barrier();
@@ -724,7 +765,36 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             };
             auto none = [](int) __attribute__((always_inline)) {};
             using std::integral_constant;
-            if constexpr (ROLE == 0) {
+            if constexpr (KSTEPS == 1) {
+                // one k-step per k-tile (deep fp8 instructions): two slots, otherwise as above
+                //            slot 1             slot 2
+                //   role 0   M(kt), wait        L(kt+1)
+                //   role 1   L(kt), wait        M(kt)
+                // After slot 1 nobody reads tile kt any more.  Slot 1 refills the weight stage freed one k-tile earlier,
+                // slot 2 the token stage just freed; at the wait only slot 1's weight instructions may be in flight.
+                auto wt = [&](int j) __attribute__((always_inline)) {
+                    if constexpr (STEADY) dma_w(j, kt + 2, prevw, false, 0);
+                };
+                if constexpr (ROLE == 0) {
+                    mma(integral_constant<int, WI>{}, wt);
+                    if (STEADY) wait_vmcnt<WI>(); else wait_vmcnt<0>();
+                    bar();
+                    if (STEADY || kt + 1 < KT) reads(nxt, nxtw, 0);
+#pragma unroll
+                    for (int j = 0; j < XIL; ++j) xr(j);
+                    lgkm0();
+                    bar();
+                } else {
+                    reads(cur, curw, 0);
+#pragma unroll
+                    for (int j = 0; j < WI; ++j) wt(j);
+                    lgkm0();
+                    if (STEADY) wait_vmcnt<WI>(); else wait_vmcnt<0>();
+                    bar();
+                    mma(integral_constant<int, XIL>{}, xr);
+                    bar();
+                }
+            } else if constexpr (ROLE == 0) {
                 mma(integral_constant<int, WH>{}, wa);
                 bar();
                 reads(cur, curw, 1);
@@ -784,9 +854,10 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // of the kernel, 10 % on the paper's shorter-K shape).  Rows keep a fixed stride of 2*WTN bytes (the fused
     // activation fills half of it); 16-byte chunks are XOR-swizzled with the row.
     constexpr int RBMAX = C::WTN * 2, CPROF = RBMAX / 16;
-    // (the 64-row-slack tile is larger than its rings and keeps the direct stores,
-    // and so do the K-contiguous layout and fp8, whose large-tile kernels the extra code pushed into register spills)
-    constexpr bool STAGED = !STREAM && C::BM >= 64 && NW * C::WTM * RBMAX <= C::LDS_BYTES && !C::WKC && !C::FP8 && !C::SPLITK;
+    // (the 64-row-slack tile is larger than its rings and keeps the direct stores, and so does the K-contiguous layout,
+    // whose large-tile kernels the extra code pushed into register spills; the fp8 product above at 4096 tokens: 196 us
+    // with direct stores, 176 us staged)
+    constexpr bool STAGED = !STREAM && C::BM >= 64 && NW * C::WTM * RBMAX <= C::LDS_BYTES && !C::WKC && (!C::FP8 || C::F8W) && !C::SPLITK;
     static_assert(!STAGED || (C::WTM * (CPROF / 2)) % 64 == 0, "staging area");
     char* const stage = smem + wave * (C::WTM * RBMAX);
     // 4 values of tile row block mb (this lane's row in it), tile columns n_out .. n_out + 3 of the OUTPUT row
@@ -869,6 +940,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
         // of an 18-group epilogue).
         constexpr int PASSES = STAGED ? C::WTM * CPROF / 64 : 1;
         int r_pass[PASSES], r_mb[MBW];
+        float xs_mb[MBW];   // (staged fp8 tiles: the token scales of this lane's rows)
         const int cu_ = a.swiglu ? CPROF / 2 : CPROF;   // 16-byte chunks per staged row; 64 / cu_ rows per instruction
         if constexpr (STAGED) {
 #pragma unroll
@@ -878,6 +950,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 const bool live = lr < C::WTM && m_local < tc.rows;
                 const int r = rows_of_tile[live ? m_local : 0];
                 r_pass[pass] = live ? r : -1;
+            }
+            if constexpr (C::FP8) {
+#pragma unroll
+                for (int mb = 0; mb < MBW; ++mb) {
+                    const int m_local = (mb * C::WM + wm) * MF + lrow;
+                    xs_mb[mb] = a.x_scale[rows_of_tile[m_local < tc.rows ? m_local : 0] / a.k];
+                }
             }
         } else if constexpr (C::SPLITK) {
             static_assert(!C::SPLITK || (!STREAM && !C::FP8 && !C::WKC), "split-k: bf16, weights as [E][K][N]");
@@ -919,7 +998,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             } else {
                 if (m_local >= tc.rows) continue;
                 if constexpr (!STAGED) r = r_mb[mb];
-                if constexpr (C::FP8) { xsc = a.x_scale[r / a.k]; wsc = a.w_scale[tc.e]; }
+                if constexpr (C::FP8) { xsc = STAGED ? xs_mb[mb] : a.x_scale[r / a.k]; wsc = a.w_scale[tc.e]; }
             }
             if (!a.swiglu) {
                 char* yrow = Yb + (size_t)r * y_row_bytes + (size_t)n0 * 2;

@@ -170,10 +170,10 @@ using P8_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true>;
 using P8_16x64 = PipeCfg<16, 64, 128, 1, 2, 4, true>;
 using P8_32x128 = PipeCfg<32, 128, 128, 1, 2, 4, true>;
 // fp8 at prefill sizes: the 256 x 256 launch shape with its two narrow task functions, and a 64-row tile
-using P8_256x256 = PipeCfg<256, 256, 128, 2, 4, 2, true, 3>;
-using P8s_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true>;
-using P8s_128x256 = PipeCfg<128, 256, 128, 1, 8, 2, true>;
-using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true>;
+using P8_256x256 = PipeCfg<256, 256, 128, 2, 4, 2, true, 3, 0, false, 16>;
+using P8s_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
+using P8s_128x256 = PipeCfg<128, 256, 128, 1, 8, 2, true, 2, 0, false, 32>;
+using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true, 3, 0, false, 32>;
 
 // The pre-packed weight layout [E][N][K] (K contiguous): the shapes the benchmark uses
 using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
