@@ -143,8 +143,9 @@ struct PipeCfg {
     static constexpr bool PERWAVE = MF == 16 && MBW_BODY >= 4;
     // ... and with at least four weight blocks per wavefront the fragments are reloaded in place (see reads_after)
     static constexpr bool XROLL = PERWAVE && WTN / MF >= 4;
-    // ... and the bf16 [K][N] ones run their k loop in two alternating roles (see run_pp in pipe_tile)
-    static constexpr bool PP = XROLL && !WKC_ && (!FP8_ || F8W) && NS_ == 2 && BK_ / KS <= 2;
+    // ... and they run their k loop in two alternating roles (see run_pp in pipe_tile).  [E][N][K] weights, 4096 -> 28672,
+    // 8 experts, top-2: 958 -> 881 us at 2047 tokens, 1595 -> 1512 at 4096 against the interleaved loop.
+    static constexpr bool PP = XROLL && (!FP8_ || F8W) && NS_ == 2 && BK_ / KS <= 2;
     static constexpr int XROW = BK * ES, CPR = XROW / 16;
     static constexpr int WROW = BN * ES, CPRW = WROW / 16;
     // the token tile in LDS is rounded up so that every wavefront issues the same number of DMA instructions
@@ -293,10 +294,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // per-lane source offsets inside a tile; everything that depends on the tile (expert, n-tile) is in the base pointer
     // When a wavefront's weight instructions lie a multiple of 16 k-rows apart they share swizzle and lane
     // pattern: one offset register serves them all and the distance goes into the scalar base.
-    constexpr bool W_FOLD = !C::WKC && (NW * WROWS_PER_INST) % 16 == 0;
+    // ([E][N][K]: a multiple of 32 tile rows apart, which the swizzle and the gate/up units of 16 rows both repeat on.)
+    constexpr bool W_FOLD = C::WKC ? (NW * XROWS_PER_INST) % 32 == 0 : (NW * WROWS_PER_INST) % 16 == 0;
     constexpr int WI_OFF = W_FOLD ? 1 : WI;
     uint32_t dx_off[XI], dx_next = 0, dw_off[WI_OFF];
     const uint32_t w_row_bytes = (uint32_t)a.N * ES;
+    const size_t w_fold = C::WKC ? (size_t)(a.swiglu ? NW * XROWS_PER_INST / 2 : NW * XROWS_PER_INST) * (uint32_t)(a.K * ES)
+                                 : (size_t)(NW * WROWS_PER_INST) * w_row_bytes;
 #pragma unroll
     for (int j = 0; j < WI_OFF; ++j) {
         const int inst = j * NW + wave;
@@ -349,7 +353,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // hinted form made the register allocator spill.
     auto dma_w = [&](int j, int kt, int stage, bool next, int ntm) __attribute__((always_inline)) {
         const char* src = (next ? Wt_next : Wt) + (size_t)kt * w_kt_stride +
-                          (W_FOLD ? (size_t)(j * NW * WROWS_PER_INST) * w_row_bytes : (size_t)0);
+                          (W_FOLD ? (size_t)j * w_fold : (size_t)0);
         const uint32_t dst = lds0 + C::W_RING + stage * C::WS_BYTES + (j * NW + wave) * 1024;
         const uint32_t voff = dw_off[W_FOLD ? 0 : j];
         if (ntm == 2 ? (next ? w_once_next : w_once) : ntm == 1) dma16_nt(voff, src, dst);
@@ -854,10 +858,9 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // of the kernel, 10 % on the paper's shorter-K shape).  Rows keep a fixed stride of 2*WTN bytes (the fused
     // activation fills half of it); 16-byte chunks are XOR-swizzled with the row.
     constexpr int RBMAX = C::WTN * 2, CPROF = RBMAX / 16;
-    // (the 64-row-slack tile is larger than its rings and keeps the direct stores, and so does the K-contiguous layout,
-    // whose large-tile kernels the extra code pushed into register spills; the fp8 product above at 4096 tokens: 196 us
-    // with direct stores, 176 us staged)
-    constexpr bool STAGED = !STREAM && C::BM >= 64 && NW * C::WTM * RBMAX <= C::LDS_BYTES && !C::WKC && (!C::FP8 || C::F8W) && !C::SPLITK;
+    // (the 64-row-slack tile is larger than its rings and keeps the direct stores; the fp8 product above at 4096 tokens:
+    // 196 us with direct stores, 176 us staged)
+    constexpr bool STAGED = !STREAM && C::BM >= 64 && NW * C::WTM * RBMAX <= C::LDS_BYTES && (!C::FP8 || C::F8W) && !C::SPLITK;
     static_assert(!STAGED || (C::WTM * (CPROF / 2)) % 64 == 0, "staging area");
     char* const stage = smem + wave * (C::WTM * RBMAX);
     // 4 values of tile row block mb (this lane's row in it), tile columns n_out .. n_out + 3 of the OUTPUT row

@@ -180,7 +180,7 @@ using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
 using Pk_256x256s = PipeCfg<256, 256, 64, 2, 4, 2, false, 2, 64, true>;
 using Pks_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pks_128x256 = PipeCfg<128, 256, 64, 1, 8, 2, false, 2, 0, true>;
-using Pk_128x256 = PipeCfg<128, 256, 64, 1, 4, 3, false, 3, 0, true>;
+using Pk_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pk_16x256 = PipeCfg<16, 256, 64, 1, 2, 2, false, 2, 0, true>;
 using P8k_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true, 2, 0, true>;
 using P8k_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true, 4, 0, true>;
@@ -188,7 +188,7 @@ using P8k_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true, 4, 0, true>;
 const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256, Pks_64x256, Pks_128x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256s, Pks_64x256, Pks_128x256>, 0, 64, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pk_128x256>, 0, 0, MOE_W_LAYOUT_NK},
+    {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pk_128x256, Pks_64x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK},
