@@ -127,7 +127,7 @@ int64_t moe_grid_upper_bound(int T, int k, int E, int tile_m, int tile_n, int N)
  *   topk_ids  DEVICE int32 [T, k] row-major: expert chosen for token t, slot j.
  *   T >= 0 tokens (0 gives a valid empty map), 1 <= k <= E, 1 <= E <= 1024,
  *   T*k <= 2^24, tile_m in {16,32,64,128,256}, tile_n in {64,128,256}, N >= 1.
- *   task_map  DEVICE, >= moe_task_map_bytes(T,...) bytes, written entirely.  The allocation must really be
+ *   task_map  DEVICE, >= moe_task_map_bytes(T,...) bytes, written entirely (but for the scratch part).  The allocation must really be
  *             that large: the kernels read a few words past sorted_rows (into the scratch part).
  * Deterministic: the same input gives the same bytes.  Ids outside [0,E) are
  * counted in header[MOE_HDR_STATUS] and force total_tiles = 0.

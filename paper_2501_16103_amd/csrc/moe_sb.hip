@@ -527,22 +527,24 @@ int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, c
     const MapLayout L = map_layout(E);
     const int64_t R = (int64_t)T * k;
     if (R <= kChunkRows) {
-        const size_t lds = ((size_t)kWaves * L.E64 + L.E64 + 32 + 2 * (size_t)L.E64) * sizeof(int);
+        const int threads = small_build_threads(R, L.E64);
         static unsigned long long attr_done = 0;
-        if (ensure_lds_attr(reinterpret_cast<const void*>(&map_build_small),
-                            (int)(((size_t)kWaves * kMaxE + 3 * (size_t)kMaxE + 32) * sizeof(int)), &attr_done) != MOE_OK)
+        if (ensure_lds_attr(reinterpret_cast<const void*>(&map_build_small), (int)small_build_lds(kMapThreads, kMaxE), &attr_done) != MOE_OK)
             return MOE_ERR_HIP;
-        map_build_small<<<1, kMapThreads, lds, s>>>(topk_ids, map, T, k, E, N, g);
+        map_build_small<<<1, threads, small_build_lds(threads, L.E64), s>>>(topk_ids, map, T, k, E, N, g);
     } else {
         const int nchunks = nchunks_for(R);
-        int32_t* chunk_hist = map + L.off_rows + round_up64((size_t)R);
         const int hs = hist_stride(L.E64);
-        map_hist<<<nchunks, 256, hs * sizeof(int), s>>>(topk_ids, (int)R, E, L.E64, chunk_hist);
+        int32_t* chunk_hist = nullptr;
+        if (nchunks > kFusedChunks) {
+            chunk_hist = map + L.off_rows + round_up64((size_t)R);
+            map_hist<<<nchunks, kMapThreads, hs * sizeof(int), s>>>(topk_ids, (int)R, E, L.E64, chunk_hist);
+        }
         static unsigned long long attr_done2 = 0;
         if (ensure_lds_attr(reinterpret_cast<const void*>(&map_scan_scatter),
-                            (int)(((size_t)kWaves * kMaxE + kMaxE) * sizeof(int)), &attr_done2) != MOE_OK)
+                            (int)(((size_t)(kWaves + 1) * kMaxE + 2 * hist_stride(kMaxE)) * sizeof(int)), &attr_done2) != MOE_OK)
             return MOE_ERR_HIP;
-        map_scan_scatter<<<nchunks, kMapThreads, ((size_t)kWaves * L.E64 + L.E64) * sizeof(int), s>>>(
+        map_scan_scatter<<<nchunks, kMapThreads, ((size_t)(kWaves + 1) * L.E64 + 2 * hs) * sizeof(int), s>>>(
             topk_ids, map, chunk_hist, nchunks, T, k, E, N, g);
     }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;

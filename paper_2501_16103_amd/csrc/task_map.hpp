@@ -139,7 +139,7 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
-// Inclusive scan across the 1024 threads of the block (s_tmp: >= 16 ints of LDS).
+// Inclusive scan across the threads of the block (at most kMapThreads; s_tmp: >= kWaves ints of LDS).
 __device__ __forceinline__ int block_incl_scan(int v, int* s_tmp) {
     const int w = threadIdx.x >> 6, lane = __lane_id();
     const int incl = wave_incl_scan(v);
@@ -153,102 +153,123 @@ __device__ __forceinline__ int block_incl_scan(int v, int* s_tmp) {
 
 __device__ __forceinline__ int bit_reverse(int r, int nbits) { return nbits ? (int)(__brev((unsigned)r) >> (32 - nbits)) : 0; }
 
-// From the per-expert count held by thread e (< E64; 0 beyond E): write counts, offsets,
-// sigma, tile_prefix and the header.  Executed by all kMapThreads threads of one block.
-// order 0: sigma ascending in expert index.  order 1 (spread, our reading of the interval-halving placement of
-// Sec. 4.2): non-empty experts ranked by tile count (largest first, ties by lower index), rank r
-// keyed by bitrev(r) over ceil(log2 M) bits, sigma by increasing key.
-// s_work: >= 2*E64 ints of LDS.  Returns this thread's exclusive row offset (valid for tid < E).
+// Ints of LDS finish_map needs: three totals per wavefront, then the heavy-tile sum of order 2.
+constexpr int kTmpInts = 3 * kWaves + 8;
+
+// From the per-expert count held by thread e (< E64; 0 beyond E): write counts, offsets, sigma, tile_prefix, the task
+// records and the header.  Executed by all threads of one block of at least E64 threads.
+// The build is a few microseconds of latency, so what counts is the chain of barriers and memory round trips:
+//   - order 0: sigma is ascending, so the TilePrefix of a non-empty expert is the plain inclusive scan of the tile counts
+//     in expert order (empty experts add nothing), and its position the scan of the non-empty flags: the three scans
+//     (rows, non-empty, tiles) run together, with one barrier, or none at E <= 64, where they are one wavefront's;
+//   - every word is written once, by the thread that knows it: an empty expert's thread writes one of the pads.
+// order 1 (spread, our reading of the interval-halving placement of Sec. 4.2): non-empty experts ranked by tile count
+// (largest first, ties by lower index), rank r keyed by bitrev(r) over ceil(log2 M) bits, sigma by increasing key.
+// order 2: heavy experts (more than a quarter of an m-tile) by falling tile count, ties by lower index, then the light ones
+// by rising index; the tiles of the heavy part are summed for the header.
+// s_tmp: kTmpInts ints, s_work: >= 2*E64 ints of LDS (orders 1 and 2 only).  Returns this thread's exclusive row offset
+// (valid for tid < E).  `write` is false for the workgroups that only need that (every scatter workgroup repeats this
+// function; the first one stores its results).
 __device__ __forceinline__ int finish_map(int32_t* __restrict__ map, const MapLayout& L, int cnt, int bad, int T, int k,
                                           int E, int N, const moe_tiling& g, int* s_tmp, int* s_work, bool write = true) {
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, w = tid >> 6;
     const int R = T * k;
     const int nt = (N + g.tile_n - 1) / g.tile_n;
-    const int nonempty = cnt > 0;
+    const bool nonempty = cnt > 0;
     const int tiles = expert_m_tiles(cnt, g) * nt;
     const int order = g.order;
-    const int off_incl = block_incl_scan(cnt, s_tmp);
-    const int ne_incl = block_incl_scan(nonempty, s_tmp);
-    __syncthreads();
-    if (tid == kMapThreads - 1) s_tmp[16] = ne_incl;
-    __syncthreads();
-    const int M = s_tmp[16];
-    // position of this expert in sigma
-    int pos = ne_incl - 1;
-    if (order == 1) {
-        if (tid < L.E64) s_work[tid] = nonempty ? tiles : -1;
+    int rows_incl = wave_incl_scan(cnt);
+    int ne_incl = __popcll(__ballot(nonempty) & (~0ull >> (63 - __lane_id())));
+    int tile_incl = wave_incl_scan(tiles);
+    int M, total;
+    if (L.E64 > 64 || order != 0) {
+        if (__lane_id() == 63) {
+            s_tmp[3 * w] = rows_incl;
+            s_tmp[3 * w + 1] = ne_incl;
+            s_tmp[3 * w + 2] = tile_incl;
+        }
+        if (tid == 0) s_tmp[3 * kWaves] = 0;
         __syncthreads();
-        int rank = 0;
-        if (nonempty)
-            for (int j = 0; j < L.E64; ++j) {
-                const int tj = s_work[j];
-                rank += (tj > tiles) || (tj == tiles && j < tid);
-            }
-        int nbits = 0;
-        while ((1 << nbits) < M) ++nbits;
-        const int key = bit_reverse(rank, nbits);
-        if (tid < L.E64) s_work[L.E64 + tid] = nonempty ? key : 0x7fffffff;
-        __syncthreads();
-        pos = 0;
-        if (nonempty)
-            for (int j = 0; j < L.E64; ++j) pos += s_work[L.E64 + j] < key;
-        __syncthreads();
+        M = 0;
+        total = 0;
+        for (int i = 0; i < (L.E64 >> 6); ++i) {
+            const int r = s_tmp[3 * i], n = s_tmp[3 * i + 1], t = s_tmp[3 * i + 2];
+            if (i < w) { rows_incl += r; ne_incl += n; tile_incl += t; }
+            M += n;
+            total += t;
+        }
+    } else {   // (only the first wavefront holds experts, and only it uses these)
+        M = __builtin_amdgcn_readlane(ne_incl, 63);
+        total = __builtin_amdgcn_readlane(tile_incl, 63);
     }
-    // order 2: heavy experts (more than a quarter of an m-tile) by falling tile count, ties by lower index, then the
-    // light ones by rising index; the tiles of the heavy part are summed for the header
-    const bool light = 4 * cnt <= g.tile_m;
-    if (tid == 0) s_tmp[18] = 0;
-    if (order == 2) {
-        const int heavy_key = light ? 0 : tiles;   // every heavy expert has at least one tile
-        if (tid < L.E64) s_work[tid] = nonempty ? heavy_key : -1;
-        __syncthreads();
-        pos = 0;
-        if (nonempty) {
-            for (int j = 0; j < L.E64; ++j) {
-                const int tj = s_work[j];
-                pos += (tj > heavy_key) || (tj == heavy_key && j < tid);
+    const int off = rows_incl - cnt;
+    int heavy_tiles = 0;
+    if (order == 0) {
+        if (write && tid < L.E64) {
+            // position in sigma; empty experts take the pads behind the M tasks, in order
+            const int pos = nonempty ? ne_incl - 1 : M + tid - ne_incl;
+            const int prefix = nonempty ? tile_incl : 0x7fffffff, ex = nonempty ? tid : -1;
+            map[L.off_sigma + pos] = ex;
+            map[L.off_prefix + pos] = prefix;
+            reinterpret_cast<int4*>(map + L.off_records)[pos] = make_int4(prefix, ex, cnt, nonempty ? off : 0);
+        }
+    } else {
+        int pos = 0;
+        if (order == 1) {
+            if (tid < L.E64) s_work[tid] = nonempty ? tiles : -1;
+            __syncthreads();
+            int rank = 0;
+            if (nonempty)
+                for (int j = 0; j < L.E64; ++j) {
+                    const int tj = s_work[j];
+                    rank += (tj > tiles) || (tj == tiles && j < tid);
+                }
+            int nbits = 0;
+            while ((1 << nbits) < M) ++nbits;
+            const int key = bit_reverse(rank, nbits);
+            if (tid < L.E64) s_work[L.E64 + tid] = nonempty ? key : 0x7fffffff;
+            __syncthreads();
+            if (nonempty)
+                for (int j = 0; j < L.E64; ++j) pos += s_work[L.E64 + j] < key;
+        } else {
+            const bool light = 4 * cnt <= g.tile_m;
+            const int heavy_key = light ? 0 : tiles;   // every heavy expert has at least one tile
+            if (tid < L.E64) s_work[tid] = nonempty ? heavy_key : -1;
+            __syncthreads();
+            if (nonempty) {
+                for (int j = 0; j < L.E64; ++j) {
+                    const int tj = s_work[j];
+                    pos += (tj > heavy_key) || (tj == heavy_key && j < tid);
+                }
+                if (!light) atomicAdd(&s_tmp[3 * kWaves], tiles);   // integer sum: the order of the adds does not matter
             }
-            if (!light) atomicAdd(&s_tmp[18], tiles);   // integer sum: the order of the adds does not matter
         }
         __syncthreads();
+        heavy_tiles = s_tmp[3 * kWaves];
+        if (!nonempty) pos = M + tid - ne_incl;
+        if (tid < L.E64) {
+            s_work[pos] = nonempty ? tiles : 0;
+            if (write) {
+                map[L.off_sigma + pos] = nonempty ? tid : -1;
+                map[L.off_records + 4 * pos + 1] = nonempty ? tid : -1;
+                map[L.off_records + 4 * pos + 2] = cnt;
+                map[L.off_records + 4 * pos + 3] = nonempty ? off : 0;
+            }
+        }
+        __syncthreads();
+        // Alg. 1 over the non-empty experts in sigma order
+        const int prefix = block_incl_scan(tid < M ? s_work[tid] : 0, s_tmp);
+        if (write && tid < L.E64) {
+            map[L.off_prefix + tid] = tid < M ? prefix : 0x7fffffff;
+            map[L.off_records + 4 * tid] = tid < M ? prefix : 0x7fffffff;
+        }
     }
-    // `write` is false for the workgroups that only need the returned offsets (every scatter workgroup repeats
-    // this function; the first one stores its results)
+    if (!write) return off;
     if (tid < L.E64) {
-        if (write) {
-            map[L.off_counts + tid] = cnt;
-            map[L.off_sigma + tid] = -1;
-            map[L.off_records + 4 * tid + 1] = -1;
-            map[L.off_records + 4 * tid + 2] = 0;
-            map[L.off_records + 4 * tid + 3] = 0;
-        }
-        s_work[tid] = 0;
+        map[L.off_counts + tid] = cnt;
+        map[L.off_offsets + tid] = tid < E ? off : (tid == E ? R - bad : R);
     }
-    if (write)
-        for (int i = tid; i < L.E64 + 64; i += kMapThreads) map[L.off_offsets + i] = i <= E ? 0 : R;
-    __syncthreads();
-    if (write && tid < E) map[L.off_offsets + tid] = off_incl - cnt;
-    if (write && tid == 0) map[L.off_offsets + E] = R - bad;
-    if (nonempty) {
-        if (write) {
-            map[L.off_sigma + pos] = tid;
-            map[L.off_records + 4 * pos + 1] = tid;
-            map[L.off_records + 4 * pos + 2] = cnt;
-            map[L.off_records + 4 * pos + 3] = off_incl - cnt;
-        }
-        s_work[pos] = tiles;
-    }
-    __syncthreads();
-    // Alg. 1 over the non-empty experts in sigma order
-    const int tile_incl = block_incl_scan(tid < M ? s_work[tid] : 0, s_tmp);
-    if (write && tid < L.E64) {
-        map[L.off_prefix + tid] = tid < M ? tile_incl : 0x7fffffff;
-        map[L.off_records + 4 * tid] = tid < M ? tile_incl : 0x7fffffff;
-    }
-    __syncthreads();
-    if (tid == kMapThreads - 1) s_tmp[17] = tile_incl;
-    __syncthreads();
-    const int total = s_tmp[17];
+    if (tid < 64) map[L.off_offsets + L.E64 + tid] = L.E64 + tid == E ? R - bad : R;
     if (tid < MOE_MAP_HDR_WORDS) {
         int v = 0;
         switch (tid) {
@@ -270,12 +291,12 @@ __device__ __forceinline__ int finish_map(int32_t* __restrict__ map, const MapLa
             case MOE_HDR_TILE_M_SMALL: v = g.tile_m_small; break;
             case MOE_HDR_SMALL_MAX_ROWS: v = g.small_max_rows; break;
             case MOE_HDR_TILE_M_SLACK: v = g.tile_m_slack; break;
-            case MOE_HDR_HEAVY_TILES: v = (order == 2 && !bad) ? s_tmp[18] : 0; break;
+            case MOE_HDR_HEAVY_TILES: v = (order == 2 && !bad) ? heavy_tiles : 0; break;
             default: v = 0;
         }
-        if (write) map[tid] = v;
+        map[tid] = v;
     }
-    return off_incl - cnt;
+    return off;
 }
 
 __device__ __forceinline__ int key_bits(int E) {
@@ -284,115 +305,147 @@ __device__ __forceinline__ int key_bits(int E) {
     return nb;
 }
 
-// One-workgroup build for R <= kChunkRows: histogram, scans and stable scatter fused.
-// Dynamic LDS: kWaves * E64 ints (per-wavefront counts) + E64 ints (offsets) + 32 + 2 * E64 (ordering).
+// Exclusive scan of the per-wavefront counts of expert `e` in row order, in place; returns their sum.
+__device__ __forceinline__ int scan_waves(int* s_wave, int E64, int nwaves, int e) {
+    int run = 0;
+    for (int i = 0; i < nwaves; ++i) {
+        const int c = s_wave[i * E64 + e];
+        s_wave[i * E64 + e] = run;
+        run += c;
+    }
+    return run;
+}
+
+// One-workgroup build for R <= kChunkRows: histogram, scans and stable scatter fused.  As many wavefronts as rows or
+// experts need: a decode step's few rows are one wavefront's work, and a barrier of one wavefront costs nothing
+// (R = 6, E = 64: 6.2 -> 3.1 us against a workgroup of 16).
+// Dynamic LDS: (wavefronts + 1) * E64 ints (per-wavefront counts, offsets) + kTmpInts + 1 + 2 * E64 (ordering).
+__host__ __device__ inline int small_build_threads(int64_t R, int E64) { return (int)(R > E64 ? (R + 63) / 64 * 64 : E64); }
+__host__ __device__ inline size_t small_build_lds(int threads, int E64) {
+    return ((size_t)(threads / 64 + 3) * E64 + kTmpInts + 1) * sizeof(int);
+}
 __global__ __launch_bounds__(kMapThreads) void map_build_small(const int32_t* __restrict__ ids, int32_t* __restrict__ map,
                                                                 int T, int k, int E, int N, moe_tiling g) {
     extern __shared__ int s_mem[];
     const MapLayout L = map_layout(E);
-    int* s_wave = s_mem;                   // [kWaves][E64]
-    int* s_off = s_mem + kWaves * L.E64;   // [E64]
-    int* s_tmp = s_off + L.E64;            // [32]
-    int* s_work = s_tmp + 32;              // [2*E64]
+    const int nwaves = blockDim.x >> 6;
+    int* s_wave = s_mem;                   // [nwaves][E64]
+    int* s_off = s_mem + nwaves * L.E64;   // [E64]
+    int* s_work = s_off + L.E64;           // [2*E64]
+    int* s_tmp = s_work + 2 * L.E64;       // [kTmpInts], then the count of bad ids
     const int tid = threadIdx.x, w = tid >> 6;
     const int R = T * k;
-    for (int i = tid; i < kWaves * L.E64; i += kMapThreads) s_wave[i] = 0;
-    if (tid == 0) s_tmp[31] = 0;
-    __syncthreads();
     const bool in_range = tid < R;
     const int e = in_range ? ids[tid] : 0;
+    for (int i = tid; i < nwaves * L.E64; i += blockDim.x) s_wave[i] = 0;
+    if (tid == 0) s_tmp[kTmpInts] = 0;
+    __syncthreads();
     const bool valid = in_range && e >= 0 && e < E;
     int rank, size;
     wave_match(e, valid, key_bits(E), rank, size);
     if (valid && rank == 0) s_wave[w * L.E64 + e] = size;
     const int nbad = __popcll(__ballot(in_range && !valid));
-    if (nbad && __lane_id() == 0) atomicAdd(&s_tmp[31], nbad);
+    if (nbad && __lane_id() == 0) atomicAdd(&s_tmp[kTmpInts], nbad);
     __syncthreads();
-    const int bad = s_tmp[31];
-    int cnt = 0;
-    if (tid < L.E64) {
-        for (int i = 0; i < kWaves; ++i) {  // exclusive scan over wavefronts, in row order
-            const int c = s_wave[i * L.E64 + tid];
-            s_wave[i * L.E64 + tid] = cnt;
-            cnt += c;
-        }
-    }
+    const int bad = s_tmp[kTmpInts];
+    const int cnt = tid < L.E64 ? scan_waves(s_wave, L.E64, nwaves, tid) : 0;
     const int off = finish_map(map, L, cnt, bad, T, k, E, N, g, s_tmp, s_work);
     if (tid < L.E64) s_off[tid] = off;
     __syncthreads();
     if (valid) map[L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank] = tid;
 }
 
-// Multi-chunk path, step 1: per-chunk histogram (integer LDS atomics: order-free).
-__global__ __launch_bounds__(256) void map_hist(const int32_t* __restrict__ ids, int R, int E, int E64,
-                                                 int32_t* __restrict__ chunk_hist) {
+// Larger builds: one workgroup per chunk of kChunkRows rows.  Every workgroup needs the counts of all experts over all
+// rows and over the rows before its own chunk; it then repeats the scans (the first one writes counts / offsets / sigma /
+// TilePrefix / task records / header) and scatters its chunk of rows, stably, into the token index arrays.
+// Up to kFusedChunks chunks every workgroup counts all ids itself (R * 4 bytes out of L2, one LDS add per id), which
+// costs less than a second launch; beyond that a first launch leaves one histogram per chunk.  Measured, one launch
+// against two, back to back: 5 chunks, E = 64: 5.1 / 6.6 us; 16 chunks, E = 256: 7.3 / 8.3; 24 chunks, E = 64: 7.5 / 7.2;
+// 64 chunks, E = 256: 13.6 / 9.5.  (One row after another summed the chunk histograms before, and every scan had its own
+// pair of barriers: 13, 18, 17 and 35 us.)
+constexpr int kFusedChunks = 16;
+
+// Per-chunk histogram (integer LDS atomics: order-free).
+__global__ __launch_bounds__(kMapThreads) void map_hist(const int32_t* __restrict__ ids, int R, int E, int E64,
+                                                         int32_t* __restrict__ chunk_hist) {
     extern __shared__ int s_mem[];
     const int hs = hist_stride(E64);
-    for (int i = threadIdx.x; i < hs; i += 256) s_mem[i] = 0;
+    const int r = blockIdx.x * kChunkRows + threadIdx.x;
+    const int e = r < R ? ids[r] : 0;
+    for (int i = threadIdx.x; i < hs; i += kMapThreads) s_mem[i] = 0;
     __syncthreads();
-    const int base = blockIdx.x * kChunkRows;
-    for (int i = threadIdx.x; i < kChunkRows; i += 256) {
-        const int r = base + i;
-        if (r < R) {
-            const int e = ids[r];
-            atomicAdd(&s_mem[(e >= 0 && e < E) ? e : E64], 1);
-        }
-    }
+    if (r < R) atomicAdd(&s_mem[(e >= 0 && e < E) ? e : E64], 1);
     __syncthreads();
-    for (int i = threadIdx.x; i < hs; i += 256) chunk_hist[(size_t)blockIdx.x * hs + i] = s_mem[i];
+    for (int i = threadIdx.x; i < hs; i += kMapThreads) chunk_hist[(size_t)blockIdx.x * hs + i] = s_mem[i];
 }
 
-// Multi-chunk path, step 2: every workgroup turns the chunk histograms into counts, offsets and its own chunk's
-// bases (plain loads, no stores in between, so they pipeline), the first one also writes counts / offsets /
-// sigma / TilePrefix / task records / header; then each scatters its chunk of rows, stably, into the token
-// index arrays.  Repeating the scans in every workgroup costs less than a third kernel launch.
-// Dynamic LDS: kWaves * E64 ints (per-wavefront counts) + E64 ints (this chunk's destination per expert).
+// chunk_hist == nullptr: count the ids here.  Dynamic LDS: kWaves * E64 ints (per-wavefront counts) + E64 ints (this
+// chunk's destination per expert) + 2 * hist_stride(E64) ints (counts of the rows before this chunk, of the others).
 __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* __restrict__ ids, int32_t* __restrict__ map,
                                                                 const int32_t* __restrict__ chunk_hist, int nchunks,
                                                                 int T, int k, int E, int N, moe_tiling g) {
     extern __shared__ int s_mem[];
-    __shared__ int s_tmp[32];
-    __shared__ int s_work[2 * kMaxE];
+    __shared__ int s_tmp[kTmpInts];
     const MapLayout L = map_layout(E);
     const int hs = hist_stride(L.E64);
     int* s_wave = s_mem;                  // [kWaves][E64]
     int* s_off = s_mem + kWaves * L.E64;  // [E64]
+    int* s_hist = s_off + L.E64;          // [2][hs]: before this chunk, not before it; column E64 counts bad ids
     const int tid = threadIdx.x, w = tid >> 6;
     const int R = T * k;
-    for (int i = tid; i < kWaves * L.E64; i += kMapThreads) s_wave[i] = 0;
-    __syncthreads();
-    const int r = blockIdx.x * kChunkRows + tid;
+    const int chunk = blockIdx.x;
+    const int r = chunk * kChunkRows + tid;
     const bool in_range = r < R;
     const int e = in_range ? ids[r] : 0;
+    for (int i = tid; i < kWaves * L.E64; i += kMapThreads) s_wave[i] = 0;
+    for (int i = tid; i < 2 * hs; i += kMapThreads) s_hist[i] = 0;
+    __syncthreads();
     const bool valid = in_range && e >= 0 && e < E;
     int rank, size;
     wave_match(e, valid, key_bits(E), rank, size);
     if (valid && rank == 0) s_wave[w * L.E64 + e] = size;
-    int cnt = 0, base = 0;
-    if (tid < L.E64) {
-        for (int c = 0; c < nchunks; ++c) {
-            const int v = chunk_hist[(size_t)c * hs + tid];
-            if (c < (int)blockIdx.x) base += v;
-            cnt += v;
+    if (chunk_hist) {
+        // thread (column, part): the parts share out the chunks
+        const int cols = L.E64 + 1, parts = kMapThreads / L.E64;
+        const int col = tid % L.E64, part = tid / L.E64;
+        if (part < parts) {
+            int before = 0, rest = 0;
+#pragma unroll 4
+            for (int c = part; c < nchunks; c += parts) {
+                const int v = chunk_hist[(size_t)c * hs + col];
+                if (c < chunk) before += v; else rest += v;
+            }
+            if (before) atomicAdd(&s_hist[col], before);
+            if (rest) atomicAdd(&s_hist[hs + col], rest);
         }
-    }
-    if (tid == kMapThreads - 1) {
         int b = 0;
-        for (int c = 0; c < nchunks; ++c) b += chunk_hist[(size_t)c * hs + L.E64];
-        s_tmp[31] = b;
+        for (int c = tid; c < nchunks; c += kMapThreads) b += chunk_hist[(size_t)c * hs + cols - 1];
+        if (b) atomicAdd(&s_hist[L.E64], b);
+    } else {
+        const int batch = 4;
+        for (int c0 = 0; c0 < nchunks; c0 += batch) {
+            int v[batch];
+#pragma unroll
+            for (int j = 0; j < batch; ++j) {
+                const int rr = (c0 + j) * kChunkRows + tid;
+                v[j] = c0 + j < nchunks && rr < R ? ids[rr] : -2;
+            }
+#pragma unroll
+            for (int j = 0; j < batch; ++j) {
+                const int rr = (c0 + j) * kChunkRows + tid;
+                if (c0 + j < nchunks && rr < R)
+                    atomicAdd(&s_hist[(c0 + j < chunk ? 0 : hs) + ((v[j] >= 0 && v[j] < E) ? v[j] : L.E64)], 1);
+            }
+        }
     }
     __syncthreads();
-    const int bad = s_tmp[31];
-    const int off = finish_map(map, L, cnt, bad, T, k, E, N, g, s_tmp, s_work, blockIdx.x == 0);
-    if (tid < L.E64) {
-        s_off[tid] = off + base;
-        int run = 0;
-        for (int i = 0; i < kWaves; ++i) {  // exclusive scan over wavefronts, in row order
-            const int c = s_wave[i * L.E64 + tid];
-            s_wave[i * L.E64 + tid] = run;
-            run += c;
-        }
-    }
+    const int bad = s_hist[L.E64] + s_hist[hs + L.E64];
+    const int before = tid < L.E64 ? s_hist[tid] : 0;
+    const int cnt = tid < L.E64 ? before + s_hist[hs + tid] : 0;
+    if (tid < L.E64) scan_waves(s_wave, L.E64, kWaves, tid);
+    __syncthreads();   // (the ordering work below reuses s_hist)
+    const int off = finish_map(map, L, cnt, bad, T, k, E, N, g, s_tmp, s_hist, chunk == 0);
+    if (tid < L.E64) s_off[tid] = off + before;
     __syncthreads();
     if (valid) map[L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank] = r;
 }
