@@ -161,7 +161,9 @@ using Pb_32x128 = PipeCfg<32, 128, 64, 1, 4, 6>;
 // Narrow task functions that share the launch shape (512 threads, 256-wide n-tiles) of Pb_256x256: used for its
 // partly filled tiles and as the small-expert strategy of a two-strategy launch
 using Ps_64x256 = PipeCfg<64, 256, 64, 1, 8, 3>;
-using Ps_128x256 = PipeCfg<128, 256, 64, 1, 8, 2>;
+// (three stages, as the 128-row launch has them: with two, one stage of weights was in flight; 64 experts, 2048 -> 2816, 73 rows
+// each: 156 -> 138 us, 8 experts, 4096 -> 28672, 83 rows each: 420 -> 367 us, now the same as the 128-row launch)
+using Ps_128x256 = PipeCfg<128, 256, 64, 1, 8, 3>;
 // 16-row tiles (two wavefronts) and fp8: the weight stream starts before the token rows are known
 using Pb_16x256 = PipeCfg<16, 256, 64, 1, 2, 2>;
 using Pb_16x128 = PipeCfg<16, 128, 64, 1, 2, 4>;
@@ -172,14 +174,14 @@ using P8_32x128 = PipeCfg<32, 128, 128, 1, 2, 4, true>;
 // fp8 at prefill sizes: the 256 x 256 launch shape with its two narrow task functions, and a 64-row tile
 using P8_256x256 = PipeCfg<256, 256, 128, 2, 4, 2, true, 3, 0, false, 16>;
 using P8s_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
-using P8s_128x256 = PipeCfg<128, 256, 128, 1, 8, 2, true, 2, 0, false, 32>;
+using P8s_128x256 = PipeCfg<128, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
 using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true, 3, 0, false, 32>;
 
 // The pre-packed weight layout [E][N][K] (K contiguous): the shapes the benchmark uses
 using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
 using Pk_256x256s = PipeCfg<256, 256, 64, 2, 4, 2, false, 2, 64, true>;
 using Pks_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, true>;
-using Pks_128x256 = PipeCfg<128, 256, 64, 1, 8, 2, false, 2, 0, true>;
+using Pks_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pk_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pk_16x256 = PipeCfg<16, 256, 64, 1, 2, 2, false, 2, 0, true>;
 using P8k_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true, 2, 0, true>;
@@ -441,8 +443,11 @@ int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling*
     const int cus = 256;
     moe_tiling g = {16, 128, MOE_ORDER_ASCENDING, 0, 0, 0};
     if (dtype == MOE_DTYPE_FP8_E4M3 && mean_rows > 24) {
-        // prefill sizes
-        g.tile_m = mean_rows > 96 ? 256 : 64; g.tile_n = 256;
+        // prefill sizes.  The 256-row launch runs its partly filled tiles with narrower functions, so below 96 rows per
+        // expert it costs nothing there and reads every weight panel once (64 experts, 2048 -> 2816: 66 us against 68
+        // for 64-row tiles at 31 rows per expert, 87 against 107 at 73) -- unless one tile per expert and 256 columns
+        // leaves CUs without a tile.
+        g.tile_m = mean_rows > 96 || active * ((N + 255) / 256) >= cus ? 256 : 64; g.tile_n = 256;
     } else if (dtype == MOE_DTYPE_FP8_E4M3) {
         // expected tiles under a uniform routing: E * (1 - (1 - 1/E)^R) experts are hit, plus full extra m-tiles
         const double hit = E * (1.0 - pow(1.0 - 1.0 / E, (double)R));
@@ -465,8 +470,9 @@ int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling*
         };
         bool short_grid;
         if (mean_rows > 48 && mean_rows <= 96) {
-            // counts straddle 64: the four-wave 64- and 128-row functions of the 128-row launch
-            g.tile_m = active * ((N + 255) / 256) >= 3 * cus ? 128 : 64;
+            // counts straddle 64: the 64- and 128-row functions of the 128-row launch, which read every weight panel once
+            // (64 experts, 73 rows each: 2048 -> 2816 137 us against 180 for 64-row tiles, 1408 -> 2048 75 against 91)
+            g.tile_m = 128;
             g.tile_n = 256;
             short_grid = active * ((N + 255) / 256) < cus;
         } else {
