@@ -208,7 +208,8 @@ int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, c
  *   fp8: up to 24 rows per expert (the decode regime) 16-row tiles, 256 wide when that gives between one and two
  *   workgroups per CU, else 128; above that 256 x 256 (64 x 256 up to 96 rows per expert where one tile per expert
  *   and 256 columns would leave CUs without one);
- *   bf16: up to 48 rows per expert 128 x 128 when 256-wide tiles would leave CUs without one; else up to
+ *   bf16: up to half a row per expert (a token or two) 16-row tiles, 256 wide when that covers half of the CUs, else
+ *   128; up to 48 rows per expert 128 x 128 when 256-wide tiles would leave CUs without one; else up to
  *   8 rows 16 x 256; from 48 to 96 rows 128 x 256; otherwise 256 x 256 (its launch handles tiles of at most 64 and
  *   128 rows with narrower task functions), with 32 slack rows above 192 rows per expert.  Where that choice
  *   would give fewer than three quarters of the CUs a tile under a balanced routing (few experts and a narrow N:
@@ -254,7 +255,8 @@ typedef struct moe_gemm_desc {
 /* How moe_grouped_gemm maps workgroups to tiles (moe_gemm_desc.launch_mode).  The task map and the results are the
  * same in every mode; tests and measurements use the explicit modes.
  *   MOE_LAUNCH_AUTO      resident workgroups where a kernel for that exists and the grid bound is at least two
- *                        tiles per resident workgroup, else one workgroup per tile
+ *                        tiles per resident workgroup (or, for 128-wide tiles that can be run in pairs, one pair per
+ *                        CU), else one workgroup per tile
  *   MOE_LAUNCH_PER_TILE  always one workgroup per tile
  *   MOE_LAUNCH_RESIDENT  resident workgroups (each runs a contiguous share of its XCD's tiles back to back) wherever
  *                        a kernel for that exists: 16-row tiles with E <= 256 (fp8: T + E <= 2048); elsewhere the

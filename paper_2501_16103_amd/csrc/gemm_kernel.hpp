@@ -204,13 +204,16 @@ struct TileStream {
     static constexpr int MAX_GROUPS = 4;  // E <= 256
     int4 rec[MAX_GROUPS];                 // lane-held task records, group by group
     int next_B, end_B;                    // tiles still to run: [next_B, end_B)
+    int pair;                             // tiles of the map per tile here: 2 = two neighbouring n-tiles run as one
     moe_tiling tiling;
     const float* xs_lds;                  // LDS copies of x_scale[T] and w_scale[E] (fp8)
     const float* ws_lds;
 };
 
-// Alg. 2 + 4 on registers (see decode_block): B must be below the total tile count.
-__device__ __forceinline__ TileCoord decode_from_registers(const TileStream& ts, int B) {
+// Alg. 2 + 4 on registers (see decode_block): B must be below the total tile count.  With pair = 2 (an even number of
+// n-tiles) every entry of TilePrefix is even, so tile B of the pairs belongs to the task of the map's tile 2 B.
+__device__ __forceinline__ TileCoord decode_from_registers(const TileStream& ts, int B_pair) {
+    const int B = B_pair * ts.pair;
     int h = 0;
 #pragma unroll
     for (int gi = 0; gi < TileStream::MAX_GROUPS; ++gi) h += __popcll(__ballot(B >= ts.rec[gi].x));  // pads never vote
@@ -226,7 +229,7 @@ __device__ __forceinline__ TileCoord decode_from_registers(const TileStream& ts,
         }
         if (h > 0 && ((h - 1) >> 6) == gi) kprev = __builtin_amdgcn_readlane(ts.rec[gi].x, (h - 1) & 63);
     }
-    const int l = B - kprev;
+    const int l = (B - kprev) / ts.pair;
     TileCoord c;
     c.e = rec.y;
     const int cnt = rec.z;
@@ -289,8 +292,10 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     static_assert(C::SLACK == 0 || (C::BM * C::XROW) % (1024 * NW) == 0, "slack rows start at a DMA instruction boundary");
     constexpr int XROWS_PER_INST = 1024 / C::XROW, WROWS_PER_INST = 1024 / C::WROW;
     static_assert((NS - 1) * XI + (NSW - 1) * WI < 64, "vmcnt range");
-    static_assert(!STREAM || (C::BM == 16 && MF == 16 && MBW == 1 && XI == 1 && NS == NSW && C::SLACK == 0 && KSTEPS % 2 == 0),
-                  "the streaming loop is written for 16-row tiles");
+    // 16-row tiles get their row ids through the scalar path: their wait (lgkmcnt) leaves the weight stream in flight, and
+    // the ids stay in a register for the epilogue.
+    constexpr bool ROWS16 = C::BM == 16 && MF == 16 && MBW == 1 && XI == 1 && NS == NSW && C::SLACK == 0 && !C::SPLITK;
+    static_assert(!STREAM || (ROWS16 && KSTEPS % 2 == 0), "the streaming loop is written for 16-row tiles");
     // per-lane source offsets inside a tile; everything that depends on the tile (expert, n-tile) is in the base pointer
     // When a wavefront's weight instructions lie a multiple of 16 k-rows apart they share swizzle and lane
     // pattern: one offset register serves them all and the distance goes into the scalar base.
@@ -379,7 +384,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 }
         } else {
 #pragma unroll
-            for (int s = 0; s < (C::PP ? NS : NSW); ++s)
+            for (int s = 0; s < (ROWS16 ? 1 : C::PP ? NS : NSW); ++s)
                 if (s < KT) {
 #pragma unroll
                     for (int j = 0; j < WI; ++j) dma_w(j, s, s, false, 2);
@@ -389,8 +394,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
 
     // ---- per-tile row information
     const int32_t* rows_of_tile = map + L.off_rows + tc.row_base;
-    // streaming: lane j < 16 holds the flat row id of tile row j (row 0's for j past the tile's rows) and the
-    // token's scale; fetched through the scalar path and LDS so that no vector-memory wait is ever generated
+    // 16-row tiles: lane j < 16 holds the flat row id of tile row j (row 0's for j past the tile's rows).  Streaming: the
+    // token's scale comes from LDS, so that no vector-memory wait is ever generated
     int rows_v = 0, rows_v_next = 0;
     auto stream_rows = [&](const TileCoord& t, int& rv, uint32_t& dxo) {
         i32x8_t lo, hi;
@@ -404,7 +409,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
         const int tok_of_row = __shfl(tok, row);
         dxo = (uint32_t)tok_of_row * (uint32_t)(a.K * ES) + ((pos ^ pswz_x<C>(row)) << 4);
     };
-    if constexpr (STREAM) {
+    if constexpr (ROWS16) {
         stream_rows(tc, rows_v, dx_off[0]);
     } else {
 #pragma unroll
@@ -416,6 +421,10 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             dx_off[j] = (uint32_t)(r / a.k) * (uint32_t)(a.K * ES) + ((pos ^ pswz_x<C>(row)) << 4);
         }
     }
+
+    // the token scale of this lane's row, asked for before the k loop (its wait comes with the first use, in the epilogue)
+    float xs_early = 1.f;
+    if constexpr (ROWS16 && C::FP8 && !STREAM) xs_early = a.x_scale[__shfl(rows_v, lrow) / a.k];
 
     using acc_t = typename std::conditional<MF == 32, f32x16_t, f32x4_t>::type;
     acc_t acc[NBW][MBW];
@@ -595,11 +604,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             for (int s = 0; s < NSW; ++s) {
                 if (s < KT) {
 #pragma unroll
-                    for (int d = (s < NS ? 0 : XIL); d < (C::EARLY_W ? XIL : ND); ++d) dma_one(d, s, s, s, s, true);
+                    for (int d = (s < NS ? 0 : XIL); d < (C::EARLY_W && (!ROWS16 || s == 0) ? XIL : ND); ++d) dma_one(d, s, s, s, s, true);
                 }
             }
-            // EARLY_W issued weights and token rows in two batches: wait for all of it; else only tile 0 is needed
-            if (!C::EARLY_W && NSW <= KT) wait_vmcnt<(NS - 1) * XIL + (NSW - 1) * WI>(); else wait_vmcnt<0>();
+            // EARLY_W issued weights and token rows in two batches: wait for all of it; else only tile 0 is needed (16-row
+            // tiles only issued the weights of tile 0 early, and the rest of the rings tile by tile)
+            if ((!C::EARLY_W || ROWS16) && NSW <= KT) wait_vmcnt<(NS - 1) * XIL + (NSW - 1) * WI>(); else wait_vmcnt<0>();
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < NREADS; ++r) read_one(r, 0, 0, 0, 0, TAIL);
@@ -982,7 +992,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 }
             }
             break;
-        } else if constexpr (!STREAM) {
+        } else if constexpr (!ROWS16) {
 #pragma unroll
             for (int mb = 0; mb < MBW; ++mb) {
                 const int m_local = (mb * C::WM + wm) * MF + lrow;
@@ -994,9 +1004,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             const int m_local = (mb * C::WM + wm) * MF + lrow;
             int r = 0;
             float xsc = 1.f, wsc = 1.f;
-            if constexpr (STREAM) {
+            if constexpr (ROWS16) {
                 r = __shfl(rows_v, m_local);
-                if constexpr (C::FP8) { xsc = ts->xs_lds[r / a.k]; wsc = ts->ws_lds[tc.e]; }
+                if constexpr (C::FP8) {
+                    xsc = STREAM ? ts->xs_lds[r / a.k] : xs_early;
+                    wsc = STREAM ? ts->ws_lds[tc.e] : a.w_scale[tc.e];
+                }
                 if (m_local >= tc.rows) continue;
             } else {
                 if (m_local >= tc.rows) continue;
@@ -1245,8 +1258,9 @@ __global__ __launch_bounds__(CBIG::NT) void moe_gemm_pipe2_kernel(GemmArgs a) {
 // Streaming launch for 16-row tiles (the weight-streaming regime): a fixed number of resident workgroups, each
 // running a contiguous share of its XCD's tiles through pipe_tile<C, true>, so that the weight stream of a
 // workgroup does not stop at tile boundaries.  Requires E <= 256, K / BK >= ring depth, one tiling strategy;
-// fp8 scales are staged in LDS behind the rings (T + E floats).
-template <class C>
+// fp8 scales are staged in LDS behind the rings (T + E floats).  PAIR = 2: C is twice as wide as the map's tiles and runs
+// two neighbouring n-tiles as one (the map has an even number of them).
+template <class C, int PAIR = 1>
 __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int32_t* __restrict__ map = a.map;
@@ -1257,10 +1271,10 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
 #pragma unroll
     for (int gi = 0; gi < TileStream::MAX_GROUPS; ++gi)
         ts.rec[gi] = 64 * gi < L.E64 ? recs[64 * gi + lane] : make_int4(0x7fffffff, -1, 0, 0);
-    const int total = map[MOE_HDR_TOTAL_TILES];
+    const int total = map[MOE_HDR_TOTAL_TILES] / PAIR;
     const bool hdr_ok = map[MOE_HDR_MAGIC] == MOE_MAP_MAGIC && map[MOE_HDR_T] == a.T && map[MOE_HDR_K_TOP] == a.k &&
                         map[MOE_HDR_E] == a.E && map[MOE_HDR_N] == a.N && map[MOE_HDR_TILE_M] == C::BM &&
-                        map[MOE_HDR_TILE_N] == C::BN && map[MOE_HDR_STATUS] == 0 && map[MOE_HDR_TILE_M_SMALL] == 0 &&
+                        map[MOE_HDR_TILE_N] * PAIR == C::BN && map[MOE_HDR_STATUS] == 0 && map[MOE_HDR_TILE_M_SMALL] == 0 &&
                         map[MOE_HDR_SMALL_MAX_ROWS] == 0 && a.tile_m_small == 0 && a.small_max_rows == 0 &&
                         map[MOE_HDR_TILE_M_SLACK] == 0 && a.tile_m_slack == 0;
     if (!hdr_ok) return;
@@ -1270,9 +1284,14 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     const int x0 = xcd * per_xcd;
     const int n_x = total - x0 < per_xcd ? total - x0 : per_xcd;
     if (n_x <= 0) return;
+    // Shares: the fewest workgroups that end in the same number of rounds, all with full shares -- the others would only
+    // take HBM bandwidth from the longest ones (8 experts, 4096 -> 28672, 16 tokens, 3.5 tiles per workgroup: 267 us against
+    // 279 with shares of 3 and 4; 64 experts, 2048 -> 2816, 8 tokens, 1.5 each: 62 against 65) -- unless that left close to
+    // half of them idle: below 1.5 tiles each, one for everybody and a second for some.
     const int per_wg = (n_x + slots - 1) / slots;
-    const int t0 = x0 + slot * per_wg;
-    int t1 = t0 + per_wg;
+    const bool even = 2 * n_x < 3 * slots;
+    const int t0 = x0 + (even ? (int)((long long)n_x * slot / slots) : slot * per_wg);
+    int t1 = even ? x0 + (int)((long long)n_x * (slot + 1) / slots) : t0 + per_wg;
     if (t1 > x0 + n_x) t1 = x0 + n_x;
     if (t0 >= t1) return;
     float* xs_lds = reinterpret_cast<float*>(smem + C::LDS_BYTES);
@@ -1285,6 +1304,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     ts.xs_lds = xs_lds;
     ts.ws_lds = ws_lds;
     ts.tiling = moe_tiling{C::BM, C::BN, 0, 0, 0, 0};
+    ts.pair = PAIR;
     ts.next_B = t0 + 1;
     ts.end_B = t1;
     const TileCoord tc = decode_from_registers(ts, t0);

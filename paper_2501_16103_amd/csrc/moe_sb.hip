@@ -102,21 +102,45 @@ inline int resident_workgroups(const void* fn, int threads, int lds, ResidentCac
     return MOE_OK;
 }
 
-// Streaming launch: as many workgroups as stay resident at once (grid is only an upper bound here).
-template <class C>
-int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+constexpr int kCus = 256;
+constexpr int kSpareSlots = 16;   // workgroups a launch's grid holds beyond the bound on its tiles (see grouped_gemm_impl)
+
+// Resident workgroups for at most `tiles` tiles of C, PAIR of the map's tiles each.  *launched stays false where one
+// workgroup per tile is asked for, where K is too short to fill the ring, or where single tiles are fewer than two per
+// resident workgroup: there is nothing to stream across then.
+template <class C, int PAIR>
+int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t s, bool* launched) {
     const int lds = C::LDS_BYTES + (C::FP8 ? 4 * (a.T + a.E) : 0);
     static ResidentCache cache;
     int resident = 0;
-    if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C>), C::NT, lds, &cache, &resident) != MOE_OK)
+    *launched = false;
+    if (a.K / C::BK < C::NS) return MOE_OK;
+    if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C, PAIR>), C::NT, lds, &cache, &resident) != MOE_OK)
         return MOE_ERR_HIP;
-    // with fewer than two tiles per resident workgroup there is nothing to stream across: one workgroup per tile
-    if (mode == MOE_LAUNCH_PER_TILE || (mode == MOE_LAUNCH_AUTO && grid < 2 * (int64_t)resident))
-        return launch_pipe<C>(a, grid, mode, s);
-    int64_t g = grid < resident ? grid : resident;
+    *launched = !(mode == MOE_LAUNCH_PER_TILE || (mode == MOE_LAUNCH_AUTO && PAIR == 1 && tiles < 2 * (int64_t)resident));
+    if (!*launched) return MOE_OK;
+    int64_t g = tiles < resident ? tiles : resident;
     if (mode >= 8 && g > mode) g = mode / 8 * 8;
-    moe_gemm_stream_kernel<C><<<dim3((unsigned)g), dim3(C::NT), lds, s>>>(a);
+    moe_gemm_stream_kernel<C, PAIR><<<dim3((unsigned)g), dim3(C::NT), lds, s>>>(a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
+// Streaming launch: as many workgroups as stay resident at once (grid is only an upper bound here).  CW: the same tile
+// twice as wide, for maps of 128-wide tiles whose N holds a whole number of 256-wide ones: the map's n-tiles are then run
+// in pairs wherever the pairs still give every CU one (fp8, 64 experts, 2048 -> 2816, 32 tokens: 56 -> 52 us).
+template <class C, class CW = C>
+int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    bool launched = false;
+    if constexpr (CW::BN == 2 * C::BN) {
+        const int64_t pairs = (grid - kSpareSlots) / 2;
+        if (mode != MOE_LAUNCH_PER_TILE && a.N % CW::BN == 0 && (pairs >= kCus || mode >= MOE_LAUNCH_RESIDENT)) {
+            const int rc = launch_stream_kernel<CW, 2>(a, (pairs + 7) / 8 * 8, mode, s, &launched);
+            if (rc != MOE_OK || launched) return rc;
+        }
+    }
+    const int rc = launch_stream_kernel<C, 1>(a, grid, mode, s, &launched);
+    if (rc != MOE_OK || launched) return rc;
+    return launch_pipe<C>(a, grid, mode, s);
 }
 
 template <class CBIG, class CSMALL, class... Tails>
@@ -137,7 +161,6 @@ struct GemmVariant {
     int w_layout = MOE_W_LAYOUT_KN;
     // the same tile as a streaming launch (resident workgroups run several tiles back to back), or nullptr
     gemm_launch_fn fn_stream = nullptr;
-    int ring = 0;  // ring depth of the streaming kernel: it needs K / bk >= ring
     // the same GEMM tasks batched with a reduction task in one launch (moe_grouped_gemm_batched), or nullptr
     gemm_launch_fn fn_batched = nullptr;
 };
@@ -164,11 +187,14 @@ using Ps_64x256 = PipeCfg<64, 256, 64, 1, 8, 3>;
 // (three stages, as the 128-row launch has them: with two, one stage of weights was in flight; 64 experts, 2048 -> 2816, 73 rows
 // each: 156 -> 138 us, 8 experts, 4096 -> 28672, 83 rows each: 420 -> 367 us, now the same as the 128-row launch)
 using Ps_128x256 = PipeCfg<128, 256, 64, 1, 8, 3>;
-// 16-row tiles (two wavefronts) and fp8: the weight stream starts before the token rows are known
-using Pb_16x256 = PipeCfg<16, 256, 64, 1, 2, 2>;
-using Pb_16x128 = PipeCfg<16, 128, 64, 1, 2, 4>;
-using P8_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true>;
-using P8_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true>;
+// 16-row tiles and fp8: the weight stream starts before the token rows are known.  One workgroup per CU with enough
+// wavefronts to issue a stage's DMA instructions side by side (4 each per stage: a wavefront's own 16 took longer than the
+// stage's share of the HBM rate) streams faster than two workgroups of two wavefronts: 8 experts, 4096 -> 28672,
+// 16 tokens 280 -> 267 us (7.0 TB/s), 64 experts, 2048 -> 2816, 32 tokens 121 -> 98 us, one token (128-wide) 18.8 -> 14.5 us.
+using Pb_16x256 = PipeCfg<16, 256, 64, 1, 8, 3>;
+using Pb_16x128 = PipeCfg<16, 128, 64, 1, 4, 6>;
+using P8_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true>;
+using P8_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true>;
 using P8_16x64 = PipeCfg<16, 64, 128, 1, 2, 4, true>;
 using P8_32x128 = PipeCfg<32, 128, 128, 1, 2, 4, true>;
 // fp8 at prefill sizes: the 256 x 256 launch shape with its two narrow task functions, and a 64-row tile
@@ -183,21 +209,21 @@ using Pk_256x256s = PipeCfg<256, 256, 64, 2, 4, 2, false, 2, 64, true>;
 using Pks_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pks_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pk_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
-using Pk_16x256 = PipeCfg<16, 256, 64, 1, 2, 2, false, 2, 0, true>;
-using P8k_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true, 2, 0, true>;
-using P8k_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true, 4, 0, true>;
+using Pk_16x256 = PipeCfg<16, 256, 64, 1, 8, 3, false, 3, 0, true>;
+using P8k_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true, 3, 0, true>;
+using P8k_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true, 6, 0, true>;
 
 const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256, Pks_64x256, Pks_128x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256s, Pks_64x256, Pks_128x256>, 0, 64, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pk_128x256, Pks_64x256>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256, Ps_64x256, Ps_128x256>, 0, 0, MOE_W_LAYOUT_KN, nullptr, 0,
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<Pk_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x128, P8k_16x256>},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256, Ps_64x256, Ps_128x256>, 0, 0, MOE_W_LAYOUT_KN, nullptr,
      &launch_batched<Pb_256x256, Ps_64x256, Ps_128x256>},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s, Ps_64x256, Ps_128x256>, 0, 64},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s32, Ps_64x256, Ps_128x256>, 0, 32, MOE_W_LAYOUT_KN, nullptr, 0,
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s32, Ps_64x256, Ps_128x256>, 0, 32, MOE_W_LAYOUT_KN, nullptr,
      &launch_batched<Pb_256x256s32, Ps_64x256, Ps_128x256>},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pb_128x256, Ps_64x256>},
     {MOE_DTYPE_BF16, 128, 128, 64, &launch_pipe<Pb_128x128>},
@@ -205,11 +231,11 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 64, 128, 64, &launch_pipe<Pb_64x128>},
     {MOE_DTYPE_BF16, 32, 256, 64, &launch_pipe<Pb_32x256>},
     {MOE_DTYPE_BF16, 32, 128, 64, &launch_pipe<Pb_32x128>},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pb_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256>, Pb_16x256::NS},
-    {MOE_DTYPE_BF16, 16, 128, 64, &launch_pipe<Pb_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128>, Pb_16x128::NS},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256>, P8_16x256::NS},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128>, P8_16x128::NS},
-    {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x64>, P8_16x64::NS},
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pb_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256>},
+    {MOE_DTYPE_BF16, 16, 128, 64, &launch_pipe<Pb_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pb_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x64>},
     {MOE_DTYPE_FP8_E4M3, 32, 128, 128, &launch_pipe<P8_32x128>},
     {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_pipe<P8_256x256, P8s_64x256, P8s_128x256>},
     {MOE_DTYPE_FP8_E4M3, 64, 256, 128, &launch_pipe<P8_64x256>},
@@ -288,12 +314,12 @@ int grouped_gemm_impl(const void* X, const void* W, const void* task_map, void* 
     int64_t grid = moe_grid_upper_bound_tiled(d->T, d->k, d->E, d->tile_m, d->tile_n, d->N, d->tile_m_small,
                                               d->small_max_rows) + red_tiles;
     if (grid == 0) return MOE_OK;
-    grid = (grid + 7) / 8 * 8 + 16;  // spare slots per XCD: the interleaved dealings round their shares up
+    grid = (grid + 7) / 8 * 8 + kSpareSlots;  // spare slots per XCD: the interleaved dealings round their shares up
     if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
     if (red) return v->fn_batched(a, grid, d->launch_mode, static_cast<hipStream_t>(stream));
     // weight-streaming tiles: keep the workgroups resident and stream tile after tile where the shape allows it
-    const bool can_stream = v->fn_stream && d->E <= 256 && d->K / v->bk >= v->ring &&
-                            (d->dtype != MOE_DTYPE_FP8_E4M3 || d->T + d->E <= 2048) && d->launch_mode != MOE_LAUNCH_PER_TILE;
+    const bool can_stream = v->fn_stream && d->E <= 256 && (d->dtype != MOE_DTYPE_FP8_E4M3 || d->T + d->E <= 2048) &&
+                            d->launch_mode != MOE_LAUNCH_PER_TILE;
     return (can_stream ? v->fn_stream : v->fn)(a, grid, d->launch_mode, static_cast<hipStream_t>(stream));
 }
 
@@ -454,6 +480,11 @@ int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling*
         const double t256 = (hit + (double)(R / 16)) * ((N + 255) / 256);
         g.tile_m = 16;
         g.tile_n = (N % 256 == 0 && t256 >= cus && t256 <= 2 * cus) ? 256 : 128;
+    } else if (mean_rows <= 0.5 && active * ((N + 255) / 256) < cus && N % 128 == 0) {
+        // a token or two: one row per expert that is hit.  The 16-row tiles move no padding rows; 128 wide while 256-wide
+        // ones would leave more than half of the CUs without one (64 experts, top-6, one token: 2048 -> 2816 14.5 us
+        // against 17.2 for 128 x 128, 1408 -> 2048 10.3 against 12.9; at 4 tokens the latter 19.4 us 256 wide, 27 128 wide)
+        g.tile_m = 16; g.tile_n = active * ((N + 255) / 256) >= cus / 2 ? 256 : 128;
     } else if (mean_rows <= 48 && active * ((N + 255) / 256) < cus && N % 128 == 0) {
         // too few 256-wide tiles to give every CU one: halve the tile width; 128 rows also hold a skewed
         // routing's busiest expert in one tile

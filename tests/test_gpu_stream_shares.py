@@ -1,0 +1,66 @@
+"""Resident 16-row launches against one workgroup per tile, bit for bit: shares of less than one, one to two and many tiles
+per workgroup, 128-wide tiles run in pairs (an even number of n-tiles) and singly (an odd one, or K too short for the pair's
+ring), both weight layouts."""
+import pytest
+import torch
+
+from paper_2501_16103_amd import binding as mb
+from paper_2501_16103_amd import workloads as wk
+from tests import helpers as H
+from tests.test_gpu_neighbours import _check_swiglu
+from tests.test_gpu_parity import _check_y
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, layout, tile_n, T, E, k, K, N, routing, swiglu, modes
+    ("bf16", "kn", 128, 40, 16, 2, 448, 768, "gauss_topk", False, (8, 16, 64, 96, 2)),
+    ("bf16", "kn", 128, 40, 16, 2, 448, 640, "gauss_topk", True, (8, 64, 2)),
+    ("bf16", "kn", 128, 33, 8, 2, 128, 512, "zipf", False, (8, 2)),          # two k-tiles: no ring is filled
+    ("bf16", "kn", 256, 90, 8, 2, 192, 768, "zipf", True, (8, 24, 64, 2)),   # several m-tiles per expert
+    ("bf16", "nk", 256, 90, 8, 2, 256, 768, "zipf", False, (8, 24, 2)),
+    ("fp8", "kn", 128, 32, 64, 6, 384, 512, "uniform_topk", False, (8, 128, 2)),
+    ("fp8", "nk", 128, 32, 64, 6, 512, 512, "uniform_topk", True, (8, 128, 2)),
+    ("fp8", "nk", 256, 50, 16, 2, 896, 512, "zipf", False, (8, 40, 2)),
+    ("fp8", "kn", 256, 50, 200, 2, 128, 512, "zipf", False, (8, 2)),         # one k-tile, four groups of task records
+]
+
+
+@pytest.mark.parametrize("dtype,layout,tile_n,T,E,k,K,N,routing,swiglu,modes", CASES)
+def test_stream_shares(oracle_mod, dtype, layout, tile_n, T, E, k, K, N, routing, swiglu, modes):
+    dev = torch.device("cuda:0")
+    wl = wk.Workload("stream_shares", T, E, k, K, N, dtype, routing, 16, tile_n)
+    fp8, dt = dtype == "fp8", mb.MOE_DTYPE_FP8_E4M3 if dtype == "fp8" else mb.MOE_DTYPE_BF16
+    ids, xs, ws = wk.make_routing(wl), None, None
+    if fp8:
+        (X, xs), (W, ws) = wk.make_x(wl), wk.make_w(wl)
+        ws = ws * (4.0 if swiglu else 1.0)
+    else:
+        X, W = wk.make_x(wl), wk.make_w(wl) * (4.0 if swiglu else 1.0)
+    Wd = (W.transpose(1, 2).contiguous() if layout == "nk" else W).to(dev)
+    Xd, xd, wd = X.to(dev), None if xs is None else xs.to(dev), None if ws is None else ws.to(dev)
+    tmap = mb.alloc_task_map(T, k, E, 16, tile_n, N)
+    mb.moe_build_task_map(ids.to(dev), T, k, E, 16, tile_n, N, tmap)
+
+    def run(mode):
+        Y = torch.full((T * k, N // 2 if swiglu else N), float("nan"), dtype=torch.bfloat16, device=dev)
+        mb.moe_grouped_gemm(Xd, Wd, None, tmap, Y, mb.GemmDesc(
+            dt, T, k, E, K, N, 16, tile_n, xd, wd, epilogue=mb.MOE_EPILOGUE_SWIGLU if swiglu else mb.MOE_EPILOGUE_NONE,
+            w_layout=mb.MOE_W_LAYOUT_NK if layout == "nk" else mb.MOE_W_LAYOUT_KN, launch_mode=mode))
+        torch.cuda.synchronize()
+        return H.y_bits(Y)
+
+    want = run(mb.MOE_LAUNCH_PER_TILE)
+    for mode in modes + (mb.MOE_LAUNCH_AUTO,):
+        assert (run(mode) == want).all(), f"launch mode {mode}"
+    if fp8:
+        res = oracle_mod.grouped_gemm_fp8(wk.bits(X), wk.bits(W), xs.numpy(), ws.numpy(), ids.numpy())
+        Xf, Wf = X.view(torch.float8_e4m3fn).double().numpy(), W.view(torch.float8_e4m3fn).double().numpy()
+        sc = (xs.double().numpy(), ws.double().numpy())
+    else:
+        res = oracle_mod.grouped_gemm_bf16(wk.bits(X), wk.bits(W), ids.numpy())
+        Xf, Wf, sc = X.double().numpy(), W.double().numpy(), (None, None)
+    if swiglu:
+        _check_swiglu(oracle_mod, want, res, Xf, Wf, ids.numpy(), k, K, *sc)
+    else:
+        _check_y(want, res, Xf, Wf, ids.numpy(), k, K, H.tol_fp8(K) if fp8 else H.tol_bf16(K), *sc)
