@@ -203,6 +203,15 @@ int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, c
                           void* task_map, void* stream);
 
 /*
+ * Both maps of a feed-forward layer in one build: task_map as moe_build_task_map_ex(topk_ids, T, k, E, N, tiling) gives it,
+ * and task_map2 as moe_build_task_map_ex(topk_ids, T * k, 1, E, N2, tiling2) does -- the second product sees the T * k
+ * activated rows as tokens of their own with one expert each, so its rows, counts and offsets are the first map's.  Same
+ * bytes (the scratch parts aside) and errors as those two calls; the two maps must be different buffers.
+ */
+int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map,
+                            int N2, const moe_tiling* tiling2, void* task_map2, void* stream);
+
+/*
  * A reasonable tiling for a problem shape, from the measurements behind this library (HOST, pure; the routing
  * itself is not known to the host, so the choice goes by the mean rows per expert T*k/E):
  *   fp8: up to 24 rows per expert (the decode regime) 16-row tiles, 256 wide when that gives between one and two

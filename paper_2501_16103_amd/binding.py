@@ -46,7 +46,7 @@ EXPORTS = [
     "moe_map_off_counts", "moe_map_off_offsets", "moe_map_off_sigma", "moe_map_off_tile_prefix",
     "moe_map_off_task_records", "moe_map_off_sorted_rows", "moe_task_map_bytes", "moe_grid_upper_bound", "moe_build_task_map",
     "moe_build_task_map_ordered", "moe_build_task_map_tiled", "moe_grid_upper_bound_tiled", "moe_tile_pair_supported",
-    "moe_build_task_map_ex", "moe_tiling_supported", "moe_w_layout_supported", "moe_default_tiling",
+    "moe_build_task_map_ex", "moe_build_task_map_pair", "moe_tiling_supported", "moe_w_layout_supported", "moe_default_tiling",
     "moe_task_map_status", "moe_task_map_expand", "moe_grouped_gemm", "moe_tile_supported", "moe_combine",
     "moe_grouped_gemm_splitk", "moe_splitk_workspace_bytes", "moe_default_k_parts",
     "moe_grouped_gemm_splitk_static", "moe_splitk_static_scratch_bytes",
@@ -112,6 +112,9 @@ def lib() -> ctypes.CDLL:
         L.moe_build_task_map_ex.restype = ctypes.c_int
         L.moe_build_task_map_ex.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [ctypes.POINTER(moe_tiling),
                                                                                       ctypes.c_void_p, ctypes.c_void_p]
+        L.moe_build_task_map_pair.restype = ctypes.c_int
+        L.moe_build_task_map_pair.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [
+            ctypes.POINTER(moe_tiling), ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(moe_tiling), ctypes.c_void_p, ctypes.c_void_p]
         L.moe_tiling_supported.restype = ctypes.c_int
         L.moe_tiling_supported.argtypes = [ctypes.c_int, ctypes.POINTER(moe_tiling)]
         L.moe_default_tiling.restype = ctypes.c_int
@@ -162,12 +165,19 @@ def strerror(code: int) -> str:
     return lib().moe_strerror(code).decode()
 
 
+# A step of one token is two or four calls of a few microseconds of GPU time each, so what a call costs on the host counts
+# (ctypes takes plain integers for pointers; torch.cuda.current_stream() builds a Stream object for its handle alone).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def moe_task_map_bytes(T_max: int, k: int, E: int, tile_m: int, tile_n: int, N: int) -> int:
@@ -251,6 +261,16 @@ def moe_build_task_map_ex(topk_ids: torch.Tensor, T: int, k: int, E: int, N: int
     rc = lib().moe_build_task_map_ex(_ptr(topk_ids), T, k, E, N, ctypes.byref(g), _ptr(task_map), _stream())
     if check and rc != MOE_OK:
         raise MoeError(rc, "moe_build_task_map_ex")
+    return rc
+
+
+def moe_build_task_map_pair(topk_ids: torch.Tensor, T: int, k: int, E: int, N: int, tiling: Tiling, task_map: torch.Tensor,
+                            N2: int, tiling2: Tiling, task_map2: torch.Tensor, check: bool = True) -> int:
+    g, g2 = tiling.c_struct(), tiling2.c_struct()
+    rc = lib().moe_build_task_map_pair(_ptr(topk_ids), T, k, E, N, ctypes.byref(g), _ptr(task_map), N2, ctypes.byref(g2),
+                                       _ptr(task_map2), _stream())
+    if check and rc != MOE_OK:
+        raise MoeError(rc, "moe_build_task_map_pair")
     return rc
 
 
@@ -402,11 +422,11 @@ def moe_grouped_gemm_splitk_static(X: torch.Tensor, W: torch.Tensor, task_map: t
 class MoeLayerPlan:
     """Buffers and tilings for one bf16 MoE feed-forward layer (Sec. 2.2) run with the library's calls only:
 
-        map(T, k) -> gate+up product with the fused gated activation -> map(T*k, 1) -> down product -> weighted sum.
+        maps of both products -> gate+up product with the fused gated activation -> down product -> weighted sum.
 
     The second product sees the T*k activated rows as tokens of their own, each routed to exactly one expert
-    (the flattened routing with k = 1), so the same two entry points serve both products (the second one in its
-    split-k form, with a workspace held here, where moe_default_k_parts says so).  Nothing here computes:
+    (the flattened routing with k = 1), so one build writes both maps and the same entry point serves both products (the
+    second one in its split-k form, with a workspace held here, where moe_default_k_parts says so).  Nothing here computes:
     the plan holds caller-visible device buffers and issues calls on the current stream."""
 
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):
@@ -436,9 +456,8 @@ class MoeLayerPlan:
         topk_ids int32 [T, k]; topk_weights fp32 [T, k] or None.  Returns out [T, hidden] (the plan's buffer)."""
         T, k, E = self.T, self.k, self.E
         flat = topk_ids.reshape(T * k, 1)
-        moe_build_task_map_ex(topk_ids, T, k, E, 2 * self.inter, self.g1, self.map1)
+        moe_build_task_map_pair(topk_ids, T, k, E, 2 * self.inter, self.g1, self.map1, self.hidden, self.g2, self.map2)
         moe_grouped_gemm(X, W_gate_up, topk_ids, self.map1, self.act, self.d1)
-        moe_build_task_map_ex(flat, T * k, 1, E, self.hidden, self.g2, self.map2)
         if self.k_parts > 1:
             moe_grouped_gemm_splitk(self.act, W_down, self.map2, self.down, self.d2, self.k_parts, self.workspace)
         else:

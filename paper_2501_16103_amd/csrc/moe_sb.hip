@@ -323,6 +323,53 @@ int grouped_gemm_impl(const void* X, const void* W, const void* task_map, void* 
     return (can_stream ? v->fn_stream : v->fn)(a, grid, d->launch_mode, static_cast<hipStream_t>(stream));
 }
 
+// ---- task maps
+
+int check_build_args(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, const void* task_map) {
+    if (!tiling) return MOE_ERR_INVALID_ARG;
+    const moe_tiling g = *tiling;
+    const int tile_m = g.tile_m, tile_n = g.tile_n, order = g.order;
+    if (!task_map || (T > 0 && !topk_ids)) return MOE_ERR_INVALID_ARG;
+    if (tile_m < 1) return MOE_ERR_UNSUPPORTED;
+    {
+        const int rcs = check_small_args(tile_m, g.tile_m_small, g.small_max_rows, g.tile_m_slack);
+        if (rcs != MOE_OK) return rcs;
+    }
+    if (order != MOE_ORDER_ASCENDING && order != MOE_ORDER_SPREAD && order != MOE_ORDER_INTERLEAVE) return MOE_ERR_INVALID_ARG;
+    if (((uintptr_t)task_map & 15) || ((uintptr_t)topk_ids & 3)) return MOE_ERR_INVALID_ARG;
+    return check_map_args(T, k, E, tile_m, tile_n, N);
+}
+
+// The launches of a build (arguments already checked).
+int build_maps(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling& g, void* task_map, const TwinMap& twin,
+               hipStream_t s) {
+    int32_t* map = static_cast<int32_t*>(task_map);
+    const MapLayout L = map_layout(E);
+    const int64_t R = (int64_t)T * k;
+    if (R <= kChunkRows) {
+        const int threads = small_build_threads(R, L.E64);
+        static unsigned long long attr_done = 0;
+        if (ensure_lds_attr(reinterpret_cast<const void*>(&map_build_small), (int)small_build_lds(kMapThreads, kMaxE), &attr_done) != MOE_OK)
+            return MOE_ERR_HIP;
+        map_build_small<<<1, threads, small_build_lds(threads, L.E64), s>>>(topk_ids, map, T, k, E, N, g, twin);
+    } else {
+        const int nchunks = nchunks_for(R);
+        const int hs = hist_stride(L.E64);
+        int32_t* chunk_hist = nullptr;
+        if (nchunks > kFusedChunks) {
+            chunk_hist = map + L.off_rows + round_up64((size_t)R);
+            map_hist<<<nchunks, kMapThreads, hs * sizeof(int), s>>>(topk_ids, (int)R, E, L.E64, chunk_hist);
+        }
+        static unsigned long long attr_done2 = 0;
+        if (ensure_lds_attr(reinterpret_cast<const void*>(&map_scan_scatter),
+                            (int)(((size_t)(kWaves + 1) * kMaxE + 2 * hist_stride(kMaxE)) * sizeof(int)), &attr_done2) != MOE_OK)
+            return MOE_ERR_HIP;
+        map_scan_scatter<<<nchunks, kMapThreads, ((size_t)(kWaves + 1) * L.E64 + 2 * hs) * sizeof(int), s>>>(
+            topk_ids, map, chunk_hist, nchunks, T, k, E, N, g, twin);
+    }
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 // ---- split-k: shared by the entry point that takes a workspace and by the one that allocates nothing
 
 int check_splitk_args(const moe_gemm_desc* d, int k_parts) {
@@ -546,45 +593,18 @@ int moe_tiling_supported(int dtype, const moe_tiling* g) {
 
 int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling,
                           void* task_map, void* stream) {
-    if (!tiling) return MOE_ERR_INVALID_ARG;
-    const moe_tiling g = *tiling;
-    const int tile_m = g.tile_m, tile_n = g.tile_n, order = g.order;
-    if (!task_map || (T > 0 && !topk_ids)) return MOE_ERR_INVALID_ARG;
-    if (tile_m < 1) return MOE_ERR_UNSUPPORTED;
-    {
-        const int rcs = check_small_args(tile_m, g.tile_m_small, g.small_max_rows, g.tile_m_slack);
-        if (rcs != MOE_OK) return rcs;
-    }
-    if (order != MOE_ORDER_ASCENDING && order != MOE_ORDER_SPREAD && order != MOE_ORDER_INTERLEAVE) return MOE_ERR_INVALID_ARG;
-    if (((uintptr_t)task_map & 15) || ((uintptr_t)topk_ids & 3)) return MOE_ERR_INVALID_ARG;
-    const int rc = check_map_args(T, k, E, tile_m, tile_n, N);
+    const int rc = check_build_args(topk_ids, T, k, E, N, tiling, task_map);
+    return rc != MOE_OK ? rc : build_maps(topk_ids, T, k, E, N, *tiling, task_map, TwinMap{}, static_cast<hipStream_t>(stream));
+}
+
+int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map,
+                            int N2, const moe_tiling* tiling2, void* task_map2, void* stream) {
+    int rc = check_build_args(topk_ids, T, k, E, N, tiling, task_map);
+    if (rc == MOE_OK) rc = check_build_args(topk_ids, T * k, 1, E, N2, tiling2, task_map2);
+    if (rc == MOE_OK && task_map == task_map2) rc = MOE_ERR_INVALID_ARG;
     if (rc != MOE_OK) return rc;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t* map = static_cast<int32_t*>(task_map);
-    const MapLayout L = map_layout(E);
-    const int64_t R = (int64_t)T * k;
-    if (R <= kChunkRows) {
-        const int threads = small_build_threads(R, L.E64);
-        static unsigned long long attr_done = 0;
-        if (ensure_lds_attr(reinterpret_cast<const void*>(&map_build_small), (int)small_build_lds(kMapThreads, kMaxE), &attr_done) != MOE_OK)
-            return MOE_ERR_HIP;
-        map_build_small<<<1, threads, small_build_lds(threads, L.E64), s>>>(topk_ids, map, T, k, E, N, g);
-    } else {
-        const int nchunks = nchunks_for(R);
-        const int hs = hist_stride(L.E64);
-        int32_t* chunk_hist = nullptr;
-        if (nchunks > kFusedChunks) {
-            chunk_hist = map + L.off_rows + round_up64((size_t)R);
-            map_hist<<<nchunks, kMapThreads, hs * sizeof(int), s>>>(topk_ids, (int)R, E, L.E64, chunk_hist);
-        }
-        static unsigned long long attr_done2 = 0;
-        if (ensure_lds_attr(reinterpret_cast<const void*>(&map_scan_scatter),
-                            (int)(((size_t)(kWaves + 1) * kMaxE + 2 * hist_stride(kMaxE)) * sizeof(int)), &attr_done2) != MOE_OK)
-            return MOE_ERR_HIP;
-        map_scan_scatter<<<nchunks, kMapThreads, ((size_t)(kWaves + 1) * L.E64 + 2 * hs) * sizeof(int), s>>>(
-            topk_ids, map, chunk_hist, nchunks, T, k, E, N, g);
-    }
-    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+    const TwinMap twin = {static_cast<int32_t*>(task_map2), N2, *tiling2};
+    return build_maps(topk_ids, T, k, E, N, *tiling, task_map, twin, static_cast<hipStream_t>(stream));
 }
 
 int moe_task_map_status(const void* task_map, void* stream) {

@@ -316,6 +316,14 @@ __device__ __forceinline__ int scan_waves(int* s_wave, int E64, int nwaves, int 
     return run;
 }
 
+// A second map from the same routing, flattened: T * k tokens with one expert each (the second product of a layer).  Rows,
+// counts and offsets are those of the first map; only its tiling and N differ.  map == nullptr: none.
+struct TwinMap {
+    int32_t* map;
+    int N;
+    moe_tiling g;
+};
+
 // One-workgroup build for R <= kChunkRows: histogram, scans and stable scatter fused.  As many wavefronts as rows or
 // experts need: a decode step's few rows are one wavefront's work, and a barrier of one wavefront costs nothing
 // (R = 6, E = 64: 6.2 -> 3.1 us against a workgroup of 16).
@@ -325,7 +333,7 @@ __host__ __device__ inline size_t small_build_lds(int threads, int E64) {
     return ((size_t)(threads / 64 + 3) * E64 + kTmpInts + 1) * sizeof(int);
 }
 __global__ __launch_bounds__(kMapThreads) void map_build_small(const int32_t* __restrict__ ids, int32_t* __restrict__ map,
-                                                                int T, int k, int E, int N, moe_tiling g) {
+                                                                int T, int k, int E, int N, moe_tiling g, TwinMap twin) {
     extern __shared__ int s_mem[];
     const MapLayout L = map_layout(E);
     const int nwaves = blockDim.x >> 6;
@@ -350,9 +358,17 @@ __global__ __launch_bounds__(kMapThreads) void map_build_small(const int32_t* __
     const int bad = s_tmp[kTmpInts];
     const int cnt = tid < L.E64 ? scan_waves(s_wave, L.E64, nwaves, tid) : 0;
     const int off = finish_map(map, L, cnt, bad, T, k, E, N, g, s_tmp, s_work);
+    if (twin.map) {
+        __syncthreads();   // (the two share the scratch)
+        finish_map(twin.map, L, cnt, bad, R, 1, E, twin.N, twin.g, s_tmp, s_work);
+    }
     if (tid < L.E64) s_off[tid] = off;
     __syncthreads();
-    if (valid) map[L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank] = tid;
+    if (valid) {
+        const size_t at = L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank;
+        map[at] = tid;
+        if (twin.map) twin.map[at] = tid;
+    }
 }
 
 // Larger builds: one workgroup per chunk of kChunkRows rows.  Every workgroup needs the counts of all experts over all
@@ -383,7 +399,7 @@ __global__ __launch_bounds__(kMapThreads) void map_hist(const int32_t* __restric
 // chunk's destination per expert) + 2 * hist_stride(E64) ints (counts of the rows before this chunk, of the others).
 __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* __restrict__ ids, int32_t* __restrict__ map,
                                                                 const int32_t* __restrict__ chunk_hist, int nchunks,
-                                                                int T, int k, int E, int N, moe_tiling g) {
+                                                                int T, int k, int E, int N, moe_tiling g, TwinMap twin) {
     extern __shared__ int s_mem[];
     __shared__ int s_tmp[kTmpInts];
     const MapLayout L = map_layout(E);
@@ -445,9 +461,17 @@ __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* _
     if (tid < L.E64) scan_waves(s_wave, L.E64, kWaves, tid);
     __syncthreads();   // (the ordering work below reuses s_hist)
     const int off = finish_map(map, L, cnt, bad, T, k, E, N, g, s_tmp, s_hist, chunk == 0);
+    if (twin.map && chunk == 0) {
+        __syncthreads();   // (the two share the scratch)
+        finish_map(twin.map, L, cnt, bad, R, 1, E, twin.N, twin.g, s_tmp, s_hist);
+    }
     if (tid < L.E64) s_off[tid] = off + before;
     __syncthreads();
-    if (valid) map[L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank] = r;
+    if (valid) {
+        const size_t at = L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank;
+        map[at] = r;
+        if (twin.map) twin.map[at] = r;
+    }
 }
 
 // Full per-block table from the compressed map, one wavefront per block index.

@@ -48,3 +48,25 @@ def test_map_build_chunk_edges(order, bad):
         np.testing.assert_array_equal(rec[:M], np.stack([np.cumsum(tiles[sigma]), sigma, counts[sigma], offsets[sigma]], axis=1))
         np.testing.assert_array_equal(rec[M:], np.tile([2 ** 31 - 1, -1, 0, 0], (len(rec) - M, 1)))
         assert np.all(got[o["sigma"] + M: o["tile_prefix"]] == -1) and np.all(got[o["tile_prefix"] + M: o["task_records"]] == 2 ** 31 - 1)
+
+
+@pytest.mark.parametrize("order", [0, 1, 2], ids=["ascending", "spread", "interleave"])
+def test_map_pair_equals_two_builds(order):
+    """One build of both maps of a layer: the bytes of the two separate builds, bad ids included."""
+    dev = torch.device("cuda:0")
+    g1, g2 = mb.Tiling(64, 128, order, 16, 40), mb.Tiling(256, 256, 2 - order, 0, 0, 32)
+    for T, k, E, bad in ((0, 2, 8, 0), (1, 6, 64, 0), (170, 6, 100, 3), (171, 6, 64, 0), (2500, 4, 1000, 0), (8192, 3, 8, 7)):
+        rng = np.random.default_rng(T + E)
+        ids = rng.integers(0, E, (T, k)).astype(np.int32)
+        ids.reshape(-1)[:bad] = -1
+        ids = torch.from_numpy(ids).to(dev)
+        R, N1, N2 = T * k, 896, 512
+        maps = [mb.alloc_task_map(max(T, 1), k, E, 64, 128, N1, dev).fill_(7) for _ in range(2)]
+        maps += [mb.alloc_task_map(max(R, 1), 1, E, 256, 256, N2, dev).fill_(7) for _ in range(2)]
+        mb.moe_build_task_map_ex(ids, T, k, E, N1, g1, maps[0])
+        mb.moe_build_task_map_ex(ids.reshape(R, 1), R, 1, E, N2, g2, maps[2])
+        mb.moe_build_task_map_pair(ids, T, k, E, N1, g1, maps[1], N2, g2, maps[3])
+        used = mb.moe_map_offsets(E)["sorted_rows"] + R - bad
+        for a, b in ((0, 1), (2, 3)):
+            assert torch.equal(maps[a][:used], maps[b][:used]), (T, k, E, a)
+    assert mb.moe_build_task_map_pair(ids, T, k, E, N1, g1, maps[1], N2, g2, maps[1], check=False) == mb.MOE_ERR_INVALID_ARG
