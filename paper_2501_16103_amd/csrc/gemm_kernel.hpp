@@ -56,6 +56,7 @@ struct GemmArgs {
     // tail-split launches (cus_per_xcd > 0): the tiles of an XCD's last, partly filled round are left to the
     // workgroups of the tail launch whenever those can split them (see tail_parts)
     int cus_per_xcd;
+    int halve_last;                    // 1: short last rounds run as half tiles (see moe_gemm_halves_kernel)
     // heterogeneous launches: a reduction task batched with the GEMM tasks (Alg. 3 with two task types), else red_tiles = 0
     const void* red_Y;                 // [red_T][red_k][red_N] bf16, finished products of an earlier launch
     const float* red_w;                // [red_T][red_k] or nullptr
@@ -1213,6 +1214,61 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
         run_tile<C, Tails...>(b, a.map, L, tc, smem);
     } else {
         run_tile<C, Tails...>(a, a.map, L, tc, smem);
+    }
+}
+
+// A task function and the narrower ones that share its launch, narrowest first.
+template <class C, class... Tails>
+struct TileFns {
+    using Full = C;
+    static __device__ __forceinline__ void run(const GemmArgs& a, const int32_t* __restrict__ map, const MapLayout& L,
+                                               const TileCoord& tc, char* smem) {
+        run_tile<C, Tails...>(a, map, L, tc, smem);
+    }
+};
+
+// One tiling strategy, and the tiles of an XCD's last round as two half tiles each (of BN / 2 columns, Half) when that round
+// would fill at most half of the XCD's 32 CUs: it then takes about half as long.  Nothing is added up afterwards -- a half
+// tile is a tile, with the same k order for every output, so the results are the same bits -- and the map is untouched:
+// block 2 j (+ 1) behind the last full round runs the left (right) half of tile j of the rest.
+// Measured, one workgroup per tile against this: 8 experts, 14336 -> 4096, 666 rows on 128 x 256 tiles (16 per XCD, all
+// halved) 205 -> 169 us, 8192 rows 890 -> 865; 4096 -> 28672, 666 rows (112 per XCD) 371 -> 356; 128 x 128 tiles, 14336 -> 4096,
+// skewed routing of 666 rows 263 -> 237, 64 experts, 1408 -> 2048, 6 rows 12.9 -> 9.5.  A rest of more than half a round gains
+// nothing from halving (its halves need two rounds of half the length), hence the line.
+constexpr int kXcdCus = 32;
+template <class Fns, class Half>
+__global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs a) {
+    using C = typename Fns::Full;
+    using H = typename Half::Full;
+    static_assert(H::NT == C::NT && 2 * H::BN == C::BN && H::LDS_BYTES <= C::LDS_BYTES && H::BMC >= C::BMC && !C::SPLITK, "half tiles");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int32_t* __restrict__ map = a.map;
+    const MapLayout L = map_layout(a.E);
+    const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
+    const int total = map[MOE_HDR_TOTAL_TILES];
+    if (!map_matches<C::BM, C::BN, 0, C::SLACK>(a, map)) return;
+    const int xcd = blockIdx.x & 7;
+    int slot = blockIdx.x >> 3, half = -1;
+    const int n = slots_of_xcd(map, total, xcd);
+    if (a.cus_per_xcd > 0) {
+        const TailSplit ts = tail_split(map, total, xcd, a.cus_per_xcd, a.K / 64);
+        if (ts.parts > 1 && slot >= ts.full) return;   // the tail launch runs this tile
+    } else if (a.halve_last) {
+        const int rest = n % kXcdCus, full = n - rest;
+        if (rest <= kXcdCus / 2 && slot >= full) {
+            half = (slot - full) & 1;
+            slot = full + ((slot - full) >> 1);
+        }
+    }
+    int B;
+    if (slot >= n || !slot_to_block(map, total, xcd, slot, B)) return;
+    const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
+    TileCoord tc = decode_block(map, L, g, B, first_record);
+    if (half < 0) {
+        Fns::run(a, map, L, tc, smem);
+    } else {
+        tc.n_tile = 2 * tc.n_tile + half;
+        Half::run(a, map, L, tc, smem);
     }
 }
 

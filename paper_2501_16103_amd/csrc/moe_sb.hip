@@ -61,6 +61,20 @@ int launch_pipe(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+// One workgroup per tile, two for the tiles of a short last round (Half; not in MOE_LAUNCH_PER_TILE).
+template <class Fns, class Half>
+int launch_halves(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    using C = typename Fns::Full;
+    static unsigned long long attr_done = 0;
+    if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_halves_kernel<Fns, Half>), C::LDS_BYTES, &attr_done) != MOE_OK)
+        return MOE_ERR_HIP;
+    GemmArgs b = a;
+    b.halve_last = mode != MOE_LAUNCH_PER_TILE && a.cus_per_xcd == 0;
+    if (b.halve_last) grid += 8 * (kXcdCus / 2);   // at most 16 more workgroups per XCD
+    moe_gemm_halves_kernel<Fns, Half><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(b);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 // Split-k launch: `parts` workgroups per tile (grid.y), fp32 partial sums into a.partial.
 template <class C, class... Tails>
 int launch_splitk(const GemmArgs& a, int64_t grid, int parts, hipStream_t s) {
@@ -203,6 +217,18 @@ using P8s_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
 using P8s_128x256 = PipeCfg<128, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
 using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true, 3, 0, false, 32>;
 
+// The launches that halve the tiles of a short last round, and the half tiles (room for 64 slack rows serves both 256-row maps)
+using Ph_256x128 = PipeCfg<256, 128, 64, 4, 2, 2, false, 3, 64, false, 16>;
+using Ph_64x128 = PipeCfg<64, 128, 64, 2, 4, 4>;
+using Ph_128x64 = PipeCfg<128, 64, 64, 4, 2, 4>;
+using F_256x256 = TileFns<Pb_256x256, Ps_64x256, Ps_128x256>;
+using F_256x256s32 = TileFns<Pb_256x256s32, Ps_64x256, Ps_128x256>;
+using F_128x256 = TileFns<Pb_128x256, Ps_64x256>;
+using H_256x128 = TileFns<Ph_256x128, Ph_64x128, Pb_128x128>;
+using H_128x128 = TileFns<Pb_128x128, Ph_64x128>;
+using F_128x128 = TileFns<Pb_128x128>;
+using H_128x64 = TileFns<Ph_128x64>;
+
 // The pre-packed weight layout [E][N][K] (K contiguous): the shapes the benchmark uses
 using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
 using Pk_256x256s = PipeCfg<256, 256, 64, 2, 4, 2, false, 2, 64, true>;
@@ -220,13 +246,13 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<Pk_16x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x128, P8k_16x256>},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256, Ps_64x256, Ps_128x256>, 0, 0, MOE_W_LAYOUT_KN, nullptr,
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256, H_256x128>, 0, 0, MOE_W_LAYOUT_KN, nullptr,
      &launch_batched<Pb_256x256, Ps_64x256, Ps_128x256>},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s, Ps_64x256, Ps_128x256>, 0, 64},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s32, Ps_64x256, Ps_128x256>, 0, 32, MOE_W_LAYOUT_KN, nullptr,
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256s32, H_256x128>, 0, 32, MOE_W_LAYOUT_KN, nullptr,
      &launch_batched<Pb_256x256s32, Ps_64x256, Ps_128x256>},
-    {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pb_128x256, Ps_64x256>},
-    {MOE_DTYPE_BF16, 128, 128, 64, &launch_pipe<Pb_128x128>},
+    {MOE_DTYPE_BF16, 128, 256, 64, &launch_halves<F_128x256, H_128x128>},
+    {MOE_DTYPE_BF16, 128, 128, 64, &launch_halves<F_128x128, H_128x64>},
     {MOE_DTYPE_BF16, 64, 256, 64, &launch_pipe<Pb_64x256>},
     {MOE_DTYPE_BF16, 64, 128, 64, &launch_pipe<Pb_64x128>},
     {MOE_DTYPE_BF16, 32, 256, 64, &launch_pipe<Pb_32x256>},
@@ -420,8 +446,8 @@ size_t tail_workspace_bytes(int tile_m, int tile_n) {   // (256-row blocks with 
 
 // The three launches of a tail-split product: whole tiles, the parts of the tail tiles, their sums.
 template <class C, class... Tails>
-int launch_tail_split(const GemmArgs& a, int64_t grid, hipStream_t s) {
-    const int r1 = launch_pipe<C, Tails...>(a, grid, 0, s);
+int launch_tail_split(const GemmArgs& a, int64_t grid, gemm_launch_fn whole, hipStream_t s) {
+    const int r1 = whole(a, grid, MOE_LAUNCH_AUTO, s);
     if (r1 != MOE_OK) return r1;
     using TailC = SplitK<C>;
     static unsigned long long attr_done = 0;
@@ -732,10 +758,10 @@ int moe_grouped_gemm_tail_split(const void* X, const void* W, const void* task_m
     if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     switch (d->tile_m) {
-        case 256: return d->tile_m_slack == 32 ? launch_tail_split<Pb_256x256s32, Ps_64x256, Ps_128x256>(a, grid, s)
-                                               : launch_tail_split<Pb_256x256, Ps_64x256, Ps_128x256>(a, grid, s);
-        case 128: return launch_tail_split<Pb_128x256, Ps_64x256>(a, grid, s);
-        default: return launch_tail_split<Pb_64x256>(a, grid, s);
+        case 256: return d->tile_m_slack == 32 ? launch_tail_split<Pb_256x256s32, Ps_64x256, Ps_128x256>(a, grid, &launch_halves<F_256x256s32, H_256x128>, s)
+                                               : launch_tail_split<Pb_256x256, Ps_64x256, Ps_128x256>(a, grid, &launch_halves<F_256x256, H_256x128>, s);
+        case 128: return launch_tail_split<Pb_128x256, Ps_64x256>(a, grid, &launch_halves<F_128x256, H_128x128>, s);
+        default: return launch_tail_split<Pb_64x256>(a, grid, &launch_pipe<Pb_64x256>, s);
     }
 }
 
