@@ -189,9 +189,11 @@ __device__ __forceinline__ int pswz_w(int krow) {
     int s;
     if constexpr (C::F8W) {
         // a half-wavefront of a transposing read covers 16 k-rows (8 and the 8 sixteen further on) of one 16-column
-        // chunk (16-row MFMA blocks), or 8 k-rows of two adjacent chunks (32-row blocks)
-        static_assert(!C::F8W || C::CPRW == 16, "deep fp8 tiles are 256 columns wide");
-        s = C::MF == 32 ? (krow & 7) << 1 : ((krow & 7) | ((krow >> 1) & 8));
+        // chunk (16-row MFMA blocks), or 8 k-rows of two adjacent chunks (32-row blocks); rows of 128 bytes already
+        // alternate between the two halves of the banks
+        static_assert(!C::F8W || C::CPRW == 16 || C::CPRW == 8, "deep fp8 tiles are 256 or 128 columns wide");
+        if constexpr (C::CPRW == 8) s = C::MF == 32 ? (krow & 6) : (((krow >> 1) & 3) | ((krow >> 2) & 4));
+        else s = C::MF == 32 ? (krow & 7) << 1 : ((krow & 7) | ((krow >> 1) & 8));
     } else if constexpr (C::FP8) s = C::CPRW >= 16 ? (krow & 15) : ((krow >> 1) & 7);
     else if constexpr (C::MF == 32) s = (krow & 3) << 2;
     else s = ((krow & 3) | ((krow >> 1) & 4)) << 1;

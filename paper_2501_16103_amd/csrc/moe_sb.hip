@@ -228,6 +228,11 @@ using H_256x128 = TileFns<Ph_256x128, Ph_64x128, Pb_128x128>;
 using H_128x128 = TileFns<Pb_128x128, Ph_64x128>;
 using F_128x128 = TileFns<Pb_128x128>;
 using H_128x64 = TileFns<Ph_128x64>;
+using P8h_256x128 = PipeCfg<256, 128, 128, 4, 2, 2, true, 3, 0, false, 16>;
+using P8h_128x128 = PipeCfg<128, 128, 128, 2, 4, 3, true, 3, 0, false, 32>;
+using P8h_64x128 = PipeCfg<64, 128, 128, 2, 4, 4, true, 4, 0, false, 32>;
+using F8_256x256 = TileFns<P8_256x256, P8s_64x256, P8s_128x256>;
+using H8_256x128 = TileFns<P8h_256x128, P8h_64x128, P8h_128x128>;
 
 // The pre-packed weight layout [E][N][K] (K contiguous): the shapes the benchmark uses
 using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
@@ -263,7 +268,7 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8_16x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x64>},
     {MOE_DTYPE_FP8_E4M3, 32, 128, 128, &launch_pipe<P8_32x128>},
-    {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_pipe<P8_256x256, P8s_64x256, P8s_128x256>},
+    {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_halves<F8_256x256, H8_256x128>},
     {MOE_DTYPE_FP8_E4M3, 64, 256, 128, &launch_pipe<P8_64x256>},
 };
 

@@ -15,24 +15,30 @@ pytestmark = pytest.mark.gpu
 COUNTS = {256: [256, 288, 1, 64, 65, 128, 129, 0, 200, 260, 513, 17, 270], 128: [128, 1, 64, 65, 129, 100, 0, 33, 300]}
 
 
-@pytest.mark.parametrize("tile_m,tile_n,slack", [(256, 256, 0), (256, 256, 32), (128, 256, 0), (128, 128, 0)])
-def test_half_tiles(tile_m, tile_n, slack):
+@pytest.mark.parametrize("dtype,tile_m,tile_n,slack", [("bf16", 256, 256, 0), ("bf16", 256, 256, 32), ("bf16", 128, 256, 0),
+                                                       ("bf16", 128, 128, 0), ("fp8", 256, 256, 0)])
+def test_half_tiles(dtype, tile_m, tile_n, slack):
     dev = torch.device("cuda:0")
     counts = COUNTS[tile_m]
     E, T = len(counts), sum(counts)
     ids = _ids_from_counts(counts, 9).to(dev)
     for K, nt, order, swiglu in ((64, 1, 0, False), (192, 1, 0, True), (64, 8, 0, False), (128, 9, 0, True), (128, 13, 0, False),
                                  (64, 17, 2, False), (320, 19, 0, False), (64, 23, 1, True), (64, 31, 0, False)):
-        N = nt * tile_n
-        wl = wk.Workload("half_tiles", T, E, 1, K, N)
-        X, W = wk.make_x(wl, dev), wk.make_w(wl, dev)
+        N, xs, ws = nt * tile_n, None, None
+        if dtype == "fp8":
+            K *= 2
+            wl = wk.Workload("half_tiles", T, E, 1, K, N, "fp8")
+            (X, xs), (W, ws) = wk.make_x(wl, dev), wk.make_w(wl, dev)
+        else:
+            wl = wk.Workload("half_tiles", T, E, 1, K, N)
+            X, W = wk.make_x(wl, dev), wk.make_w(wl, dev)
         tmap = mb.alloc_task_map(T, 1, E, tile_m, tile_n, N)
         mb.moe_build_task_map_ex(ids, T, 1, E, N, mb.Tiling(tile_m, tile_n, order, 0, 0, slack), tmap)
         out = []
         for mode in (mb.MOE_LAUNCH_PER_TILE, mb.MOE_LAUNCH_AUTO):
             Y = torch.full((T, N // 2 if swiglu else N), float("nan"), dtype=torch.bfloat16, device=dev)
             mb.moe_grouped_gemm(X, W, None, tmap, Y, mb.GemmDesc(
-                mb.MOE_DTYPE_BF16, T, 1, E, K, N, tile_m, tile_n, tile_m_slack=slack, launch_mode=mode,
+                mb.MOE_DTYPE_FP8_E4M3 if dtype == "fp8" else mb.MOE_DTYPE_BF16, T, 1, E, K, N, tile_m, tile_n, xs, ws, tile_m_slack=slack, launch_mode=mode,
                 epilogue=mb.MOE_EPILOGUE_SWIGLU if swiglu else mb.MOE_EPILOGUE_NONE))
             torch.cuda.synchronize()
             out.append(H.y_bits(Y))
