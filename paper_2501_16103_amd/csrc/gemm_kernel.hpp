@@ -112,6 +112,7 @@ template <int BM_, int BN_, int BK_, int WM_, int WN_, int NS_, bool FP8_ = fals
           bool WKC_ = false, int MFO_ = 0, int NSWH_ = 0>
 struct PipeCfg {
     static constexpr bool SPLITK = false;
+    static constexpr bool ALONE = false;
     static constexpr bool WKC = WKC_;
     // NSWH_ > 0: the weight ring is NSWH_ stages of HALF a k-tile (when whole stages do not divide the LDS left
     // beside the token ring): k-tile kt lives in half-stages (2 kt) % NSWH_ and (2 kt + 1) % NSWH_, and the loop's
@@ -178,6 +179,12 @@ struct PipeCfg {
 template <class C>
 struct SplitK : C {
     static constexpr bool SPLITK = true;
+};
+
+// A task function for tiles whose expert has no other m-tile (see run_tile).
+template <class C>
+struct Alone : C {
+    static constexpr bool ALONE = true;
 };
 
 template <class C>
@@ -1197,7 +1204,7 @@ __device__ __forceinline__ void run_tile(const GemmArgs& a, const int32_t* __res
                                          const TileCoord& tc, char* smem) {
     static_assert(T0::BM < C::BM && T0::NT == C::NT && T0::BN == C::BN && T0::FP8 == C::FP8 && T0::LDS_BYTES <= C::LDS_BYTES,
                   "a tail function shares the launch shape of the full one");
-    if (tc.rows <= T0::BM) pipe_tile<T0>(a, map, L, tc, smem);
+    if (tc.rows <= T0::BM && (!T0::ALONE || tc.m_tiles == 1)) pipe_tile<T0>(a, map, L, tc, smem);
     else run_tile<C, Ts...>(a, map, L, tc, smem);
 }
 

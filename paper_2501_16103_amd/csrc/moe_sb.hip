@@ -198,9 +198,12 @@ using Pb_32x128 = PipeCfg<32, 128, 64, 1, 4, 6>;
 // Narrow task functions that share the launch shape (512 threads, 256-wide n-tiles) of Pb_256x256: used for its
 // partly filled tiles and as the small-expert strategy of a two-strategy launch
 using Ps_64x256 = PipeCfg<64, 256, 64, 1, 8, 3>;
-// (three stages, as the 128-row launch has them: with two, one stage of weights was in flight; 64 experts, 2048 -> 2816, 73 rows
-// each: 156 -> 138 us, 8 experts, 4096 -> 28672, 83 rows each: 420 -> 367 us, now the same as the 128-row launch)
-using Ps_128x256 = PipeCfg<128, 256, 64, 1, 8, 3>;
+// Three stages, as the 128-row launch has them, where the tile is its expert's only one: with two, one stage of weights is in
+// flight (64 experts, 2048 -> 2816, 73 rows each: 156 -> 138 us, 8 experts, 4096 -> 28672, 83 rows each: 420 -> 367 us).  Two where a
+// full tile shares the weight panel: the narrow tile must not run ahead of it out of L2 (8 experts, 4096 -> 28672, 349 rows
+// each: 666 us against 697 with three).
+using Ps_128x256 = Alone<PipeCfg<128, 256, 64, 1, 8, 3>>;
+using Pt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2>;
 // 16-row tiles and fp8: the weight stream starts before the token rows are known.  One workgroup per CU with enough
 // wavefronts to issue a stage's DMA instructions side by side (4 each per stage: a wavefront's own 16 took longer than the
 // stage's share of the HBM rate) streams faster than two workgroups of two wavefronts: 8 experts, 4096 -> 28672,
@@ -214,6 +217,7 @@ using P8_32x128 = PipeCfg<32, 128, 128, 1, 2, 4, true>;
 // fp8 at prefill sizes: the 256 x 256 launch shape with its two narrow task functions, and a 64-row tile
 using P8_256x256 = PipeCfg<256, 256, 128, 2, 4, 2, true, 3, 0, false, 16>;
 using P8s_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
+// (fp8 panels are half as large and stay in L2: three stages for every such tile; 2048 -> 2816, 4096 tokens 182 us, 187 with two)
 using P8s_128x256 = PipeCfg<128, 256, 128, 1, 8, 3, true, 3, 0, false, 32>;
 using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true, 3, 0, false, 32>;
 
@@ -221,8 +225,8 @@ using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true, 3, 0, false, 32>;
 using Ph_256x128 = PipeCfg<256, 128, 64, 4, 2, 2, false, 3, 64, false, 16>;
 using Ph_64x128 = PipeCfg<64, 128, 64, 2, 4, 4>;
 using Ph_128x64 = PipeCfg<128, 64, 64, 4, 2, 4>;
-using F_256x256 = TileFns<Pb_256x256, Ps_64x256, Ps_128x256>;
-using F_256x256s32 = TileFns<Pb_256x256s32, Ps_64x256, Ps_128x256>;
+using F_256x256 = TileFns<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>;
+using F_256x256s32 = TileFns<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>;
 using F_128x256 = TileFns<Pb_128x256, Ps_64x256>;
 using H_256x128 = TileFns<Ph_256x128, Ph_64x128, Pb_128x128>;
 using H_128x128 = TileFns<Pb_128x128, Ph_64x128>;
@@ -238,24 +242,25 @@ using H8_256x128 = TileFns<P8h_256x128, P8h_64x128, P8h_128x128>;
 using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
 using Pk_256x256s = PipeCfg<256, 256, 64, 2, 4, 2, false, 2, 64, true>;
 using Pks_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, true>;
-using Pks_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
+using Pks_128x256 = Alone<PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>>;
+using Pkt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2, false, 2, 0, true>;
 using Pk_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pk_16x256 = PipeCfg<16, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using P8k_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true, 3, 0, true>;
 using P8k_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true, 6, 0, true>;
 
 const GemmVariant kVariants[] = {
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256, Pks_64x256, Pks_128x256>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256s, Pks_64x256, Pks_128x256>, 0, 64, MOE_W_LAYOUT_NK},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 0, MOE_W_LAYOUT_NK},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256s, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 64, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pk_128x256, Pks_64x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<Pk_16x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x128, P8k_16x256>},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256, H_256x128>, 0, 0, MOE_W_LAYOUT_KN, nullptr,
-     &launch_batched<Pb_256x256, Ps_64x256, Ps_128x256>},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s, Ps_64x256, Ps_128x256>, 0, 64},
+     &launch_batched<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s, Ps_64x256, Ps_128x256, Pt_128x256>, 0, 64},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256s32, H_256x128>, 0, 32, MOE_W_LAYOUT_KN, nullptr,
-     &launch_batched<Pb_256x256s32, Ps_64x256, Ps_128x256>},
+     &launch_batched<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_halves<F_128x256, H_128x128>},
     {MOE_DTYPE_BF16, 128, 128, 64, &launch_halves<F_128x128, H_128x64>},
     {MOE_DTYPE_BF16, 64, 256, 64, &launch_pipe<Pb_64x256>},
@@ -273,8 +278,8 @@ const GemmVariant kVariants[] = {
 };
 
 const GemmVariant kPairVariants[] = {
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe2<Pb_256x256, Ps_64x256, Ps_64x256, Ps_128x256>, 64},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe2<Pb_256x256, Ps_128x256, Ps_64x256, Ps_128x256>, 128},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe2<Pb_256x256, Ps_64x256, Ps_64x256, Ps_128x256, Pt_128x256>, 64},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe2<Pb_256x256, Ps_128x256, Ps_64x256, Ps_128x256, Pt_128x256>, 128},
 };
 
 const GemmVariant* find_variant(int dtype, int tile_m, int tile_n, int tile_m_small = 0, int tile_m_slack = 0,
@@ -429,7 +434,7 @@ int run_splitk(const void* X, const void* W, const void* task_map, void* Y, cons
     if (grid == 0) return MOE_OK;
     grid = (grid + 7) / 8 * 8 + 8;
     if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
-    const int rc = launch_splitk<Pb_256x256, Ps_64x256, Ps_128x256>(a, grid, k_parts, s);
+    const int rc = launch_splitk<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>(a, grid, k_parts, s);
     if (rc != MOE_OK) return rc;
     const int64_t R = (int64_t)d->T * d->k;
     const long long chunks = (long long)R * (d->N / 8);
@@ -763,8 +768,8 @@ int moe_grouped_gemm_tail_split(const void* X, const void* W, const void* task_m
     if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     switch (d->tile_m) {
-        case 256: return d->tile_m_slack == 32 ? launch_tail_split<Pb_256x256s32, Ps_64x256, Ps_128x256>(a, grid, &launch_halves<F_256x256s32, H_256x128>, s)
-                                               : launch_tail_split<Pb_256x256, Ps_64x256, Ps_128x256>(a, grid, &launch_halves<F_256x256, H_256x128>, s);
+        case 256: return d->tile_m_slack == 32 ? launch_tail_split<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>(a, grid, &launch_halves<F_256x256s32, H_256x128>, s)
+                                               : launch_tail_split<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>(a, grid, &launch_halves<F_256x256, H_256x128>, s);
         case 128: return launch_tail_split<Pb_128x256, Ps_64x256>(a, grid, &launch_halves<F_128x256, H_128x128>, s);
         default: return launch_tail_split<Pb_64x256>(a, grid, &launch_pipe<Pb_64x256>, s);
     }
