@@ -269,7 +269,7 @@ typedef struct moe_gemm_desc {
  *                        tiles over [E][K][N] weights two for the tiles of an XCD's last round that fills at most half of its CUs
  *   MOE_LAUNCH_PER_TILE  always one workgroup per tile
  *   MOE_LAUNCH_RESIDENT  resident workgroups (each runs a contiguous share of its XCD's tiles back to back) wherever
- *                        a kernel for that exists: 16-row tiles with E <= 256 (fp8: T + E <= 2048); elsewhere the
+ *                        a kernel for that exists: 16-row tiles over [E][K][N] weights with E <= 256 (fp8: T + E <= 2048); elsewhere the
  *                        same as MOE_LAUNCH_AUTO
  *   a value >= 8         MOE_LAUNCH_RESIDENT with at most that many workgroups (rounded down to a multiple of 8)
  */

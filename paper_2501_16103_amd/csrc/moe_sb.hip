@@ -245,17 +245,20 @@ using Pks_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pks_128x256 = Alone<PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>>;
 using Pkt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2, false, 2, 0, true>;
 using Pk_128x256 = PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>;
-using Pk_16x256 = PipeCfg<16, 256, 64, 1, 8, 3, false, 3, 0, true>;
-using P8k_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true, 3, 0, true>;
-using P8k_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true, 6, 0, true>;
+// (16-row tiles over this layout: two workgroups of two wavefronts per CU, one tile each.  The wide resident form of the other
+// layout was faster at 4 tokens, 64 experts, 2048 -> 2816 fp8 (20.7 us against 22.5), but slower at 16 (47.0 / 42.5) and 256
+// (105 / 89): a DMA instruction touches eight 128-byte pieces of weight rows here.)
+using Pk_16x256 = PipeCfg<16, 256, 64, 1, 2, 2, false, 2, 0, true>;
+using P8k_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true, 2, 0, true>;
+using P8k_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true, 4, 0, true>;
 
 const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256s, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 64, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pk_128x256, Pks_64x256>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<Pk_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK, &launch_stream<P8k_16x128, P8k_16x256>},
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256, H_256x128>, 0, 0, MOE_W_LAYOUT_KN, nullptr,
      &launch_batched<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s, Ps_64x256, Ps_128x256, Pt_128x256>, 0, 64},

@@ -1,6 +1,6 @@
 """Resident 16-row launches against one workgroup per tile, bit for bit: shares of less than one, one to two and many tiles
 per workgroup, 128-wide tiles run in pairs (an even number of n-tiles) and singly (an odd one, or K too short for the pair's
-ring), both weight layouts."""
+ring); [E][N][K] weights, whose launches stay one workgroup per tile in every mode."""
 import pytest
 import torch
 
