@@ -75,7 +75,67 @@ def check_no_spill_in_k_loops(asm_text: str) -> None:
                 raise RuntimeError(f"{name}: register spill inside a k loop (it would drain the DMA ring every iteration)")
 
 
-def _compile(src: str, lib: str, check_spills: bool, verbose: bool) -> str:
+# MFMAs of the alternating-role loops are written out, so the compiler does not know them and keeps no distance between an
+# ordinary vector instruction and an MFMA that reads its result (two wait states on gfx950; it does so around its own).
+# The build refuses a GEMM kernel where such an MFMA follows the write of one of its operands too closely on any path.
+MFMA_READ_WAIT_STATES = 2
+
+
+def _registers(operand: str) -> set:
+    m = re.fullmatch(r"([va])(?:(\d+)|\[(\d+):(\d+)\])", operand.strip())
+    if not m:
+        return set()
+    lo, hi = (m.group(2), m.group(2)) if m.group(2) else (m.group(3), m.group(4))
+    return {(m.group(1), r) for r in range(int(lo), int(hi) + 1)}
+
+
+def check_mfma_operand_distance(asm_text: str) -> None:
+    for m in re.finditer(r"^(_ZN3moe\S*gemm\S*):\s*(?:;.*)?$", asm_text, re.M):
+        name = m.group(1)
+        code = []   # (is a label, text, written out by hand)
+        in_asm = False
+        for ln in asm_text[m.end():asm_text.find(".Lfunc_end", m.end())].splitlines():
+            if "#ASMSTART" in ln or "#ASMEND" in ln:
+                in_asm = "#ASMSTART" in ln
+                continue
+            text = ln.split(";")[0].strip()
+            label = re.match(r"(\.LBB\S+):", text)
+            if label:
+                code.append((True, label.group(1), False))
+            elif re.match(r"[a-z]+_", text):
+                code.append((False, text, in_asm))
+        branches_to = {}
+        for k, (is_label, text, _) in enumerate(code):
+            b = re.match(r"s_c?branch\S*\s+(\.LBB\S+)", text)
+            if b and not is_label:
+                branches_to.setdefault(b.group(1), []).append(k)
+
+        def before(k):   # the lines that can run just before line k
+            prev = [k - 1] if k > 0 and not re.match(r"s_(branch|endpgm|setpc_b64)\b", code[k - 1][1]) else []
+            return prev + (branches_to.get(code[k][1], []) if code[k][0] else [])
+
+        for k, (is_label, text, by_hand) in enumerate(code):
+            if is_label or not by_hand or not text.startswith("v_mfma"):
+                continue
+            reads = set().union(*(_registers(op) for op in text.split(None, 1)[1].split(",")[1:4]))
+            todo, seen = [(p, 0) for p in before(k)], set()
+            while todo:
+                p, waited = todo.pop()
+                if waited >= MFMA_READ_WAIT_STATES or (p, waited) in seen:
+                    continue
+                seen.add((p, waited))
+                p_label, p_text, _ = code[p]
+                if not p_label:
+                    operands = p_text.split(None, 1)[1].split(",") if " " in p_text else []
+                    written = set().union(*(_registers(op) for op in operands[:2 if p_text.startswith("v_swap") else 1]))
+                    if p_text.startswith("v_") and not p_text.startswith("v_mfma") and written & reads:
+                        raise RuntimeError(f"{name}: '{text}' {waited} wait states behind '{p_text}'")
+                    nop = re.match(r"s_nop\s+(\d+)", p_text)
+                    waited += int(nop.group(1)) + 1 if nop else 1
+                todo += [(q, waited) for q in before(p)]
+
+
+def _compile(src: str, lib: str, check_asm: bool, verbose: bool) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     with tempfile.TemporaryDirectory() as tmp:
         out = os.path.join(tmp, os.path.basename(lib))
@@ -83,12 +143,14 @@ def _compile(src: str, lib: str, check_spills: bool, verbose: bool) -> str:
         res = subprocess.run(cmd, cwd=tmp, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
-        if check_spills:
+        if check_asm:
             asm = [f for f in os.listdir(tmp) if f.endswith(".s") and "amdgcn" in f]
             if not asm:
                 raise RuntimeError("no device assembly found next to the built library")
             with open(os.path.join(tmp, asm[0])) as f:
-                check_no_spill_in_k_loops(f.read())
+                asm_text = f.read()
+            check_no_spill_in_k_loops(asm_text)
+            check_mfma_operand_distance(asm_text)
         shutil.copyfile(out, lib)
         os.chmod(lib, 0o755)
     if verbose:

@@ -852,6 +852,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             cur = nxt;
             curw = nxtw;
         };
+        // In front of the loop: the writes of the accumulators end here, two wait states before the first MFMA that reads
+        // them (left alone, the compiler puts the zeroing of the last one directly before the loop; the build checks this).
+#pragma unroll
+        for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+            for (int mb = 0; mb < NMB; ++mb) asm volatile("" : "+v"(acc[nb][mb]));
+        asm volatile("s_nop 1");
         int kt = 0;
         for (; kt + 2 < KT; ++kt) iteration(kt, std::true_type{});
         for (; kt < KT; ++kt) iteration(kt, std::false_type{});
