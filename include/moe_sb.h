@@ -263,10 +263,11 @@ typedef struct moe_gemm_desc {
 
 /* How moe_grouped_gemm maps workgroups to tiles (moe_gemm_desc.launch_mode).  The task map and the results are the
  * same in every mode; tests and measurements use the explicit modes.
- *   MOE_LAUNCH_AUTO      resident workgroups where a kernel for that exists and the grid bound is at least two
- *                        tiles per resident workgroup (or, for 128-wide tiles that can be run in pairs, one pair per
- *                        CU), else one workgroup per tile -- for 256 x 256, 128 x 256 and 128 x 128 bf16 and 256 x 256 fp8
- *                        tiles over [E][K][N] weights two for the tiles of an XCD's last round that fills at most half of its CUs
+ *   MOE_LAUNCH_AUTO      resident workgroups where a kernel for that exists and the tiles are many: 256-wide ones where the
+ *                        grid bound is at least two per CU, 128-wide ones where a uniform routing would give more than two
+ *                        per CU (or, if they can be run in pairs, more than one); else one workgroup per tile -- for
+ *                        256 x 256, 128 x 256 and 128 x 128 bf16 and 256 x 256 fp8 tiles over [E][K][N] weights two for the
+ *                        tiles of an XCD's last round that fills at most half of its CUs
  *   MOE_LAUNCH_PER_TILE  always one workgroup per tile
  *   MOE_LAUNCH_RESIDENT  resident workgroups (each runs a contiguous share of its XCD's tiles back to back) wherever
  *                        a kernel for that exists: 16-row tiles over [E][K][N] weights with E <= 256 (fp8: T + E <= 2048); elsewhere the

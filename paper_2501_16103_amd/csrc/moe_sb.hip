@@ -119,40 +119,86 @@ inline int resident_workgroups(const void* fn, int threads, int lds, ResidentCac
 constexpr int kCus = 256;
 constexpr int kSpareSlots = 16;   // workgroups a launch's grid holds beyond the bound on its tiles (see grouped_gemm_impl)
 
-// Resident workgroups for at most `tiles` tiles of C, PAIR of the map's tiles each.  *launched stays false where one
-// workgroup per tile is asked for, where K is too short to fill the ring, or where single tiles are fewer than two per
-// resident workgroup: there is nothing to stream across then.
+// Tiles of 16 rows that a uniform routing gives: one for each expert it hits; from half a tile of rows per expert on, rows
+// fill a tile half on average.
+double expected_tiles16(int64_t R, int E, int64_t nt) {
+    const double hit = E * (1.0 - pow(1.0 - 1.0 / E, (double)R)), filled = R / 16.0 + E / 2.0;
+    return (R >= 8 * (int64_t)E && filled > hit ? filled : hit) * (double)nt;
+}
+
+// 16-row tiles, one workgroup per tile: C fills a CU by itself, C2 is the same tile with two wavefronts and a shallower
+// ring, two workgroups per CU.  Up to one tile per CU the deep form streams faster (64 experts, 2048 -> 2816, fp8, 132 tiles of
+// 128 columns: 13.6 us with C2, 10.8 with C).  Beyond that a tile's start and store leave the CU idle unless a second
+// workgroup covers them: 341 tiles of 1408 columns 19.5 us with C2, 21.7 with C; 512 experts, 1024 -> 2048, fp8, 5024 tiles
+// 116 / 146; 256 experts, K = 128, 4466 tiles 35 / 49.  Only 256-wide tiles with at least 32 k-tiles make up for it, once
+// there are more of them than two per CU (384 experts, 2048 -> 2816, bf16, 4213 tiles 701 / 678).
+template <class C, class C2>
+int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    const double tiles = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
+    const bool deep = tiles <= kCus || (tiles > 2 * kCus && C::BN == 256 && a.K / C::BK >= 32);
+    if (deep && grid * C::NT <= 0xffffffffll) return launch_pipe<C>(a, grid, mode, s);   // (a launch holds 2^32 work items)
+    return launch_pipe<C2>(a, grid, mode, s);
+}
+
+// Resident workgroups for at most `tiles` tiles of C, PAIR of the map's tiles each, where `wanted` or asked for by the
+// launch mode.  *launched stays false where neither holds, or where K is too short to fill the ring.
 template <class C, int PAIR>
-int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t s, bool* launched) {
+int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t s, bool wanted, bool* launched) {
     const int lds = C::LDS_BYTES + (C::FP8 ? 4 * (a.T + a.E) : 0);
     static ResidentCache cache;
     int resident = 0;
-    *launched = false;
-    if (a.K / C::BK < C::NS) return MOE_OK;
+    *launched = (wanted || mode >= MOE_LAUNCH_RESIDENT) && a.K / C::BK >= C::NS;
+    if (!*launched) return MOE_OK;
     if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C, PAIR>), C::NT, lds, &cache, &resident) != MOE_OK)
         return MOE_ERR_HIP;
-    *launched = !(mode == MOE_LAUNCH_PER_TILE || (mode == MOE_LAUNCH_AUTO && PAIR == 1 && tiles < 2 * (int64_t)resident));
-    if (!*launched) return MOE_OK;
     int64_t g = tiles < resident ? tiles : resident;
     if (mode >= 8 && g > mode) g = mode / 8 * 8;
     moe_gemm_stream_kernel<C, PAIR><<<dim3((unsigned)g), dim3(C::NT), lds, s>>>(a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-// Streaming launch: as many workgroups as stay resident at once (grid is only an upper bound here).  CW: the same tile
-// twice as wide, for maps of 128-wide tiles whose N holds a whole number of 256-wide ones: the map's n-tiles are then run
-// in pairs wherever the pairs still give every CU one (fp8, 64 experts, 2048 -> 2816, 32 tokens: 56 -> 52 us).
-template <class C, class CW = C>
+// Streaming launch (not called in MOE_LAUNCH_PER_TILE): as many workgroups as stay resident at once, grid is only an upper
+// bound here.  256-wide tiles: from two
+// tiles per workgroup on, counted by the bound.  128-wide ones: once more are expected than the CUs hold in the two-workgroup form
+// of launch_rows16, for up to there no tile waits for a second round (64 experts, 2048 -> 1408, fp8: 363 tiles 19.7 us per tile,
+// 22.2 streaming; 572 tiles 32.4 / 28.6).  CW: the same tile twice as wide, for maps of 128-wide tiles whose N holds a whole
+// number of 256-wide ones: the map's n-tiles are then run in pairs once more of them are expected than CUs (fp8, 64 experts,
+// 2048 -> 2816: 3 tokens, 330 tiles, 22.5 -> 18.0 us, 20.5 with C2; 32 tokens 56 -> 52).  A K too short for the deep ring
+// streams in the two-workgroup form, from two tiles per workgroup on (256 experts, K = 128, 2233 tiles: 30 us, 34 per tile).
+// (Between one and two 256-wide tiles per CU the deep form is kept: a uniform routing of 5 tokens, 297 tiles, takes 62 us with
+// it and 55 with two workgroups per CU, but a skewed one of the same size, 176 tiles, 29 and 38.)
+template <class C, class C2, class CW = C>
 int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    const double expected = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
     bool launched = false;
     if constexpr (CW::BN == 2 * C::BN) {
-        const int64_t pairs = (grid - kSpareSlots) / 2;
-        if (mode != MOE_LAUNCH_PER_TILE && a.N % CW::BN == 0 && (pairs >= kCus || mode >= MOE_LAUNCH_RESIDENT)) {
-            const int rc = launch_stream_kernel<CW, 2>(a, (pairs + 7) / 8 * 8, mode, s, &launched);
+        if (a.N % CW::BN == 0) {
+            const int64_t pairs = (grid - kSpareSlots) / 2;
+            const int rc = launch_stream_kernel<CW, 2>(a, (pairs + 7) / 8 * 8, mode, s, expected > kCus, &launched);
             if (rc != MOE_OK || launched) return rc;
         }
     }
-    const int rc = launch_stream_kernel<C, 1>(a, grid, mode, s, &launched);
+    const bool many = C::BN == 256 ? grid >= 2 * kCus : expected > 2 * kCus;
+    const int rc = launch_stream_kernel<C, 1>(a, grid, mode, s, many, &launched);
+    if (rc != MOE_OK || launched) return rc;
+    if (a.K / C::BK < C::NS) {
+        const int rc2 = launch_stream_kernel<C2, 1>(a, grid, mode, s, grid >= 4 * kCus, &launched);
+        if (rc2 != MOE_OK || launched) return rc2;
+    }
+    if (C::BN == 256 && a.K / C::BK >= C::NS) return launch_pipe<C>(a, grid, mode, s);
+    return launch_rows16<C, C2>(a, grid, mode, s);
+}
+
+// The same for the 64-wide tile, four workgroups per CU either way: resident from two tiles per workgroup on.
+template <class C>
+int launch_stream_narrow(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    const int lds = C::LDS_BYTES + 4 * (a.T + a.E);
+    static ResidentCache cache;
+    int resident = 0;
+    bool launched = false;
+    if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C, 1>), C::NT, lds, &cache, &resident) != MOE_OK)
+        return MOE_ERR_HIP;
+    const int rc = launch_stream_kernel<C, 1>(a, grid, mode, s, grid >= 2 * (int64_t)resident, &launched);
     if (rc != MOE_OK || launched) return rc;
     return launch_pipe<C>(a, grid, mode, s);
 }
@@ -206,12 +252,17 @@ using Ps_128x256 = Alone<PipeCfg<128, 256, 64, 1, 8, 3>>;
 using Pt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2>;
 // 16-row tiles and fp8: the weight stream starts before the token rows are known.  One workgroup per CU with enough
 // wavefronts to issue a stage's DMA instructions side by side (4 each per stage: a wavefront's own 16 took longer than the
-// stage's share of the HBM rate) streams faster than two workgroups of two wavefronts: 8 experts, 4096 -> 28672,
+// stage's share of the HBM rate) streams faster than two workgroups of two wavefronts (the Pd forms): 8 experts, 4096 -> 28672,
 // 16 tokens 280 -> 267 us (7.0 TB/s), 64 experts, 2048 -> 2816, 32 tokens 121 -> 98 us, one token (128-wide) 18.8 -> 14.5 us.
+// launch_rows16 says which of the two runs one workgroup per tile.
 using Pb_16x256 = PipeCfg<16, 256, 64, 1, 8, 3>;
 using Pb_16x128 = PipeCfg<16, 128, 64, 1, 4, 6>;
+using Pd_16x256 = PipeCfg<16, 256, 64, 1, 2, 2>;
+using Pd_16x128 = PipeCfg<16, 128, 64, 1, 2, 4>;
 using P8_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true>;
 using P8_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true>;
+using P8d_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true>;
+using P8d_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true>;
 using P8_16x64 = PipeCfg<16, 64, 128, 1, 2, 4, true>;
 using P8_32x128 = PipeCfg<32, 128, 128, 1, 2, 4, true>;
 // fp8 at prefill sizes: the 256 x 256 launch shape with its two narrow task functions, and a 64-row tile
@@ -270,11 +321,11 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 64, 128, 64, &launch_pipe<Pb_64x128>},
     {MOE_DTYPE_BF16, 32, 256, 64, &launch_pipe<Pb_32x256>},
     {MOE_DTYPE_BF16, 32, 128, 64, &launch_pipe<Pb_32x128>},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pb_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256>},
-    {MOE_DTYPE_BF16, 16, 128, 64, &launch_pipe<Pb_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pb_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x64>},
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256, Pd_16x256>},
+    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pd_16x128, Pb_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256, P8d_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8d_16x128, P8_16x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream_narrow<P8_16x64>},
     {MOE_DTYPE_FP8_E4M3, 32, 128, 128, &launch_pipe<P8_32x128>},
     {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_halves<F8_256x256, H8_256x128>},
     {MOE_DTYPE_FP8_E4M3, 64, 256, 128, &launch_pipe<P8_64x256>},

@@ -23,6 +23,18 @@ CASES = [
     ("fp8", "nk", 128, 32, 64, 6, 512, 512, "uniform_topk", True, (8, 128, 2)),
     ("fp8", "nk", 256, 50, 16, 2, 896, 512, "zipf", False, (8, 40, 2)),
     ("fp8", "kn", 256, 50, 200, 2, 128, 512, "zipf", False, (8, 2)),         # one k-tile, four groups of task records
+    # K too short for the deep ring: resident in the two-wavefront form
+    ("bf16", "kn", 256, 60, 32, 2, 128, 512, "gauss_topk", True, (8, 32, 2)),
+    ("bf16", "kn", 128, 60, 32, 2, 320, 384, "zipf", False, (8, 32, 2)),
+    ("fp8", "kn", 256, 60, 32, 2, 256, 512, "zipf", False, (8, 32, 2)),
+    ("fp8", "kn", 128, 60, 32, 2, 512, 640, "gauss_topk", True, (8, 32, 2)),
+    # more tiles than CUs, one workgroup per tile in the two-wavefront form (more than 256 experts, or T + E > 2048)
+    ("bf16", "kn", 256, 100, 300, 4, 192, 512, "gauss_topk", False, (2,)),
+    ("bf16", "kn", 128, 100, 300, 4, 384, 256, "zipf", True, (2,)),
+    ("fp8", "kn", 256, 100, 300, 4, 128, 512, "zipf", True, (2,)),
+    ("fp8", "kn", 128, 2000, 64, 1, 256, 256, "gauss_topk", False, (2,)),
+    # the same with 32 k-tiles and more than two 256-wide tiles per CU: the deep form
+    ("bf16", "kn", 256, 100, 300, 4, 2048, 768, "gauss_topk", False, (2,)),
 ]
 
 
@@ -64,3 +76,21 @@ def test_stream_shares(oracle_mod, dtype, layout, tile_n, T, E, k, K, N, routing
         _check_swiglu(oracle_mod, want, res, Xf, Wf, ids.numpy(), k, K, *sc)
     else:
         _check_y(want, res, Xf, Wf, ids.numpy(), k, K, H.tol_fp8(K) if fp8 else H.tol_bf16(K), *sc)
+
+
+def test_more_tiles_than_work_items_of_the_deep_form():
+    """2^23 + 4096 tiles of 256 columns: more than a launch of 512 threads per tile can hold, not more than one of 128."""
+    dev, T, E, K, N = torch.device("cuda:0"), 32768, 512, 64, 2048
+    g = torch.Generator(device=dev).manual_seed(5)
+    X = torch.randn(T, K, generator=g, device=dev).to(torch.bfloat16)
+    W = (torch.randn(E, K, N, generator=g, device=dev) / 8).to(torch.bfloat16)
+    ids = torch.arange(E, dtype=torch.int32, device=dev).expand(T, E).contiguous()      # every token to every expert
+    tmap = mb.alloc_task_map(T, E, E, 16, 256, N)
+    mb.moe_build_task_map(ids, T, E, E, 16, 256, N, tmap)
+    Y = torch.empty(T, E, N // 2, dtype=torch.bfloat16, device=dev)
+    mb.moe_grouped_gemm(X, W, ids, tmap, Y, mb.GemmDesc(mb.MOE_DTYPE_BF16, T, E, E, K, N, 16, 256, epilogue=mb.MOE_EPILOGUE_SWIGLU))
+    for e in (0, 1, 255, 256, 510, 511):
+        gate, up = (X.double() @ W[e].double()).split(N // 2, dim=1)
+        want = (torch.nn.functional.silu(gate) * up).to(torch.bfloat16).double()
+        # one bf16 rounding each, and K * 2^-24 of sums of at most about 4 * |x||w| in front of it
+        assert ((Y[:, e].double() - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4).all(), f"expert {e}"
