@@ -217,8 +217,8 @@ int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N,
  *   fp8: up to 24 rows per expert (the decode regime) 16-row tiles, 256 wide when that gives between one and two
  *   workgroups per CU, else 128; above that 256 x 256 (64 x 256 up to 96 rows per expert where one tile per expert
  *   and 256 columns would leave CUs without one);
- *   bf16: up to half a row per expert (a token or two) 16-row tiles, 256 wide when that covers half of the CUs, else
- *   128; up to 48 rows per expert 128 x 128 when 256-wide tiles would leave CUs without one; else up to
+ *   bf16: up to half a row per expert (a token or two) 16-row tiles, 128 wide while those cover at most three quarters
+ *   of the CUs, 256 wide once they are more than the CUs (128 x 128 between the two); up to 48 rows per expert 128 x 128 when 256-wide tiles would leave CUs without one; else up to
  *   8 rows 16 x 256; from 48 to 96 rows 128 x 256; otherwise 256 x 256 (its launch handles tiles of at most 64 and
  *   128 rows with narrower task functions), with 32 slack rows above 192 rows per expert.  Where that choice
  *   would give fewer than three quarters of the CUs a tile under a balanced routing (few experts and a narrow N:

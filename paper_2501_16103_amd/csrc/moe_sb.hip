@@ -618,10 +618,14 @@ int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling*
         g.tile_m = 16;
         g.tile_n = (N % 256 == 0 && t256 >= cus && t256 <= 2 * cus) ? 256 : 128;
     } else if (mean_rows <= 0.5 && active * ((N + 255) / 256) < cus && N % 128 == 0) {
-        // a token or two: one row per expert that is hit.  The 16-row tiles move no padding rows; 128 wide while 256-wide
-        // ones would leave more than half of the CUs without one (64 experts, top-6, one token: 2048 -> 2816 14.5 us
-        // against 17.2 for 128 x 128, 1408 -> 2048 10.3 against 12.9; at 4 tokens the latter 19.4 us 256 wide, 27 128 wide)
-        g.tile_m = 16; g.tile_n = active * ((N + 255) / 256) >= cus / 2 ? 256 : 128;
+        // a token or two: one row per expert that is hit.  The 16-row tiles move no padding rows; 128 wide while they cover
+        // at most 3/4 of the CUs, 256 wide once there are more narrow ones than CUs (64 experts, top-6, one token: 2048 -> 2816
+        // 14.5 us against 17.2 for 128 x 128, 1408 -> 2048 10.3 against 12.9; at 4 tokens the latter 19.4 us 256 wide, 27
+        // 128 wide).  Between the two, 128 x 128 (256 experts, top-8, 7168 -> 4096, one token, 256 narrow tiles: 76 us
+        // against 81 for 16 x 128 and 90 for 16 x 256; 32 experts, 2048 -> 2048, 16 tokens: 21 against 21 and 26).
+        const int64_t narrow = active * (N / 128);
+        if (narrow > 3 * cus / 4 && narrow <= cus) { g.tile_m = 128; g.tile_n = 128; }
+        else { g.tile_m = 16; g.tile_n = narrow > cus ? 256 : 128; }
     } else if (mean_rows <= 48 && active * ((N + 255) / 256) < cus && N % 128 == 0) {
         // too few 256-wide tiles to give every CU one: halve the tile width; 128 rows also hold a skewed
         // routing's busiest expert in one tile

@@ -157,6 +157,12 @@ def test_default_tiling_is_supported_and_matches_the_benchmark_choices():
                             (512, 2048, 2048, (64, 128)), (32, 14336, 4096, (128, 128))):
         g = mb.moe_default_tiling(mb.MOE_DTYPE_BF16, R, 1, 8, K, N)
         assert (g.tile_m, g.tile_n) == want and mb.moe_tiling_supported(mb.MOE_DTYPE_BF16, g), (R, K, N, g)
+    # a token or two: narrow 16-row tiles up to three quarters of a tile per CU, wide ones above one, between them 128 x 128
+    for (T, E, k, K, N, want) in ((1, 64, 6, 2048, 2816, (16, 128)), (2, 64, 6, 2048, 2816, (16, 256)), (4, 64, 6, 1408, 2048, (16, 256)),
+                                  (1, 8, 2, 14336, 4096, (16, 128)), (2, 64, 6, 1408, 2048, (16, 128)), (1, 256, 8, 7168, 4096, (128, 128)), (2, 256, 8, 7168, 4096, (16, 256)),
+                                  (16, 32, 1, 2048, 2048, (128, 128)), (4, 256, 8, 2048, 1408, (16, 128))):
+        g = mb.moe_default_tiling(mb.MOE_DTYPE_BF16, T, k, E, K, N)
+        assert (g.tile_m, g.tile_n) == want and mb.moe_tiling_supported(mb.MOE_DTYPE_BF16, g), (T, E, K, N, g)
     # N that only 64-wide tiles divide, and one nothing divides
     g = mb.moe_default_tiling(mb.MOE_DTYPE_FP8_E4M3, 8, 2, 16, 256, 192)
     assert (g.tile_m, g.tile_n) == (16, 64) and mb.moe_tiling_supported(mb.MOE_DTYPE_FP8_E4M3, g)
