@@ -218,9 +218,10 @@ int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N,
  *   workgroups per CU, else 128; above that 256 x 256 (64 x 256 up to 96 rows per expert where one tile per expert
  *   and 256 columns would leave CUs without one);
  *   bf16: up to half a row per expert (a token or two) 16-row tiles, 128 wide while those cover at most three quarters
- *   of the CUs, 256 wide once they are more than the CUs (128 x 128 between the two); up to 48 rows per expert 128 x 128 when 256-wide tiles would leave CUs without one; else up to
- *   8 rows 16 x 256; from 48 to 96 rows 128 x 256; otherwise 256 x 256 (its launch handles tiles of at most 64 and
- *   128 rows with narrower task functions), with 32 slack rows above 192 rows per expert.  Where that choice
+ *   of the CUs, 256 wide once they are more than the CUs (128 x 128 between the two); up to 48 rows per expert
+ *   128 x 128 when 256-wide tiles would leave CUs without one; else up to 8 rows 16 x 256; from 48 to 96 rows
+ *   128 x 256 (up to 52 rows 64 x 128 where 256 does not divide N); otherwise 256 x 256 (its launch handles tiles of at
+ *   most 64 and 128 rows with narrower task functions), with 32 slack rows above 192 rows per expert.  Where that choice
  *   would give fewer than three quarters of the CUs a tile under a balanced routing (few experts and a narrow N:
  *   a down projection at a few hundred tokens), the largest of 128 x 256, 128 x 128, 64 x 128 that does.
  * Always ascending order, one strategy.  The result satisfies moe_tiling_supported when N % tile_n == 0 allows

@@ -643,8 +643,10 @@ int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling*
         bool short_grid;
         if (mean_rows > 48 && mean_rows <= 96) {
             // counts straddle 64: the 64- and 128-row functions of the 128-row launch, which read every weight panel once
-            // (64 experts, 73 rows each: 2048 -> 2816 137 us against 180 for 64-row tiles, 1408 -> 2048 75 against 91)
-            g.tile_m = 128;
+            // (64 experts, 73 rows each: 2048 -> 2816 137 us against 180 for 64-row tiles, 1408 -> 2048 75 against 91).
+            // Where N takes 128-wide tiles the 128-row launch has one function only, which pays once most counts are above
+            // 64 (64 experts, 2048 -> 1408: 49 rows each 68 us on 64 x 128 tiles, 74 on 128 x 128; 56 rows 76 / 73, 64 rows 83 / 75).
+            g.tile_m = N % 256 != 0 && mean_rows <= 52 && active * ((N + 255) / 256) < 3 * cus ? 64 : 128;
             g.tile_n = 256;
             short_grid = active * ((N + 255) / 256) < cus;
         } else {

@@ -163,6 +163,11 @@ def test_default_tiling_is_supported_and_matches_the_benchmark_choices():
                                   (16, 32, 1, 2048, 2048, (128, 128)), (4, 256, 8, 2048, 1408, (16, 128))):
         g = mb.moe_default_tiling(mb.MOE_DTYPE_BF16, T, k, E, K, N)
         assert (g.tile_m, g.tile_n) == want and mb.moe_tiling_supported(mb.MOE_DTYPE_BF16, g), (T, E, K, N, g)
+    # 48 to 96 rows: 128-row tiles, but 64 x 128 up to 52 rows where N takes no 256-wide tile and the grid is short
+    for (T, N, want) in ((533, 1408, (64, 128)), (554, 1408, (64, 128)), (560, 1408, (128, 128)), (1000, 1408, (128, 128)), (533, 2048, (128, 256)),
+                         (533, 2944, (128, 128))):
+        g = mb.moe_default_tiling(mb.MOE_DTYPE_BF16, T, 6, 64, 2048, N)
+        assert (g.tile_m, g.tile_n) == want and mb.moe_tiling_supported(mb.MOE_DTYPE_BF16, g), (T, N, g)
     # N that only 64-wide tiles divide, and one nothing divides
     g = mb.moe_default_tiling(mb.MOE_DTYPE_FP8_E4M3, 8, 2, 16, 256, 192)
     assert (g.tile_m, g.tile_n) == (16, 64) and mb.moe_tiling_supported(mb.MOE_DTYPE_FP8_E4M3, g)
