@@ -127,7 +127,8 @@ int64_t moe_grid_upper_bound(int T, int k, int E, int tile_m, int tile_n, int N)
  *   topk_ids  DEVICE int32 [T, k] row-major: expert chosen for token t, slot j.
  *   T >= 0 tokens (0 gives a valid empty map), 1 <= k <= E, 1 <= E <= 1024,
  *   T*k <= 2^24, tile_m in {16,32,64,128,256}, tile_n in {64,128,256}, N >= 1.
- *   task_map  DEVICE, >= moe_task_map_bytes(T,...) bytes, written entirely (but for the scratch part).  The allocation must really be
+ *   task_map  DEVICE, >= moe_task_map_bytes(T,...) bytes, written entirely up to sorted_rows; beyond T*k = 1024 the scratch
+ *             part holds the histogram of every 1024 rows, below that it is left alone.  The allocation must really be
  *             that large: the kernels read a few words past sorted_rows (into the scratch part).
  * Deterministic: the same input gives the same bytes.  Ids outside [0,E) are
  * counted in header[MOE_HDR_STATUS] and force total_tiles = 0.
@@ -206,7 +207,7 @@ int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, c
  * Both maps of a feed-forward layer in one build: task_map as moe_build_task_map_ex(topk_ids, T, k, E, N, tiling) gives it,
  * and task_map2 as moe_build_task_map_ex(topk_ids, T * k, 1, E, N2, tiling2) does -- the second product sees the T * k
  * activated rows as tokens of their own with one expert each, so its rows, counts and offsets are the first map's.  Same
- * bytes (the scratch parts aside) and errors as those two calls; the two maps must be different buffers.
+ * bytes and errors as those two calls; the two maps must be different buffers.
  */
 int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map,
                             int N2, const moe_tiling* tiling2, void* task_map2, void* stream);

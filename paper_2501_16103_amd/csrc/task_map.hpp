@@ -402,6 +402,7 @@ __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* _
                                                                 int T, int k, int E, int N, moe_tiling g, TwinMap twin) {
     extern __shared__ int s_mem[];
     __shared__ int s_tmp[kTmpInts];
+    __shared__ int s_bad[kWaves];
     const MapLayout L = map_layout(E);
     const int hs = hist_stride(L.E64);
     int* s_wave = s_mem;                  // [kWaves][E64]
@@ -420,6 +421,8 @@ __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* _
     int rank, size;
     wave_match(e, valid, key_bits(E), rank, size);
     if (valid && rank == 0) s_wave[w * L.E64 + e] = size;
+    const int wave_bad = __popcll(__ballot(in_range && !valid));
+    if (__lane_id() == 0) s_bad[w] = wave_bad;
     if (chunk_hist) {
         // thread (column, part): the parts share out the chunks
         const int cols = L.E64 + 1, parts = kMapThreads / L.E64;
@@ -458,7 +461,7 @@ __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* _
     const int bad = s_hist[L.E64] + s_hist[hs + L.E64];
     const int before = tid < L.E64 ? s_hist[tid] : 0;
     const int cnt = tid < L.E64 ? before + s_hist[hs + tid] : 0;
-    if (tid < L.E64) scan_waves(s_wave, L.E64, kWaves, tid);
+    const int own = tid < L.E64 ? scan_waves(s_wave, L.E64, kWaves, tid) : 0;
     __syncthreads();   // (the ordering work below reuses s_hist)
     const int off = finish_map(map, L, cnt, bad, T, k, E, N, g, s_tmp, s_hist, chunk == 0);
     if (twin.map && chunk == 0) {
@@ -471,6 +474,17 @@ __global__ __launch_bounds__(kMapThreads) void map_scan_scatter(const int32_t* _
         const size_t at = L.off_rows + s_off[e] + s_wave[w * L.E64 + e] + rank;
         map[at] = r;
         if (twin.map) twin.map[at] = r;
+    }
+    // The scratch parts hold the histogram of every chunk either way.
+    const size_t hist_at = L.off_rows + round_up64((size_t)R) + (size_t)chunk * hs;
+    if (!chunk_hist || twin.map) {
+        for (int i = tid; i < hs; i += kMapThreads) {
+            int v = i < L.E64 ? own : 0;   // (i == tid there)
+            if (i == L.E64)
+                for (int j = 0; j < kWaves; ++j) v += s_bad[j];
+            if (!chunk_hist) map[hist_at + i] = v;
+            if (twin.map) twin.map[hist_at + i] = v;
+        }
     }
 }
 

@@ -47,6 +47,13 @@ def test_map_build_chunk_edges(order, bad):
         rec = got[o["task_records"]: o["task_records"] + 4 * ((E + 63) // 64 * 64)].reshape(-1, 4)
         np.testing.assert_array_equal(rec[:M], np.stack([np.cumsum(tiles[sigma]), sigma, counts[sigma], offsets[sigma]], axis=1))
         np.testing.assert_array_equal(rec[M:], np.tile([2 ** 31 - 1, -1, 0, 0], (len(rec) - M, 1)))
+        if R > CHUNK:   # scratch: one histogram per chunk (experts, bad ids, spare columns), the same from one launch or two
+            E64, at = (E + 63) // 64 * 64, o["sorted_rows"] + (R + 63) // 64 * 64
+            for c in range((R + CHUNK - 1) // CHUNK):
+                part, line = ids[c * CHUNK: (c + 1) * CHUNK], got[at + c * (E64 + 64): at + (c + 1) * (E64 + 64)]
+                good = (part >= 0) & (part < E)
+                want = np.concatenate([np.bincount(part[good], minlength=E64), [(~good).sum()], np.zeros(63, int)])
+                np.testing.assert_array_equal(line, want, err_msg=f"R={R} E={E} chunk {c}")
         assert np.all(got[o["sigma"] + M: o["tile_prefix"]] == -1) and np.all(got[o["tile_prefix"] + M: o["task_records"]] == 2 ** 31 - 1)
 
 
@@ -69,4 +76,6 @@ def test_map_pair_equals_two_builds(order):
         used = mb.moe_map_offsets(E)["sorted_rows"] + R - bad
         for a, b in ((0, 1), (2, 3)):
             assert torch.equal(maps[a][:used], maps[b][:used]), (T, k, E, a)
+            if bad == 0:
+                assert torch.equal(maps[a], maps[b]), (T, k, E, a, "scratch")
     assert mb.moe_build_task_map_pair(ids, T, k, E, N1, g1, maps[1], N2, g2, maps[1], check=False) == mb.MOE_ERR_INVALID_ARG
