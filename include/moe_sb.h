@@ -207,7 +207,7 @@ int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, c
  * Both maps of a feed-forward layer in one build: task_map as moe_build_task_map_ex(topk_ids, T, k, E, N, tiling) gives it,
  * and task_map2 as moe_build_task_map_ex(topk_ids, T * k, 1, E, N2, tiling2) does -- the second product sees the T * k
  * activated rows as tokens of their own with one expert each, so its rows, counts and offsets are the first map's.  Same
- * bytes and errors as those two calls; the two maps must be different buffers.
+ * bytes and errors as those two calls; the two maps must not overlap (MOE_ERR_INVALID_ARG).
  */
 int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map,
                             int N2, const moe_tiling* tiling2, void* task_map2, void* stream);

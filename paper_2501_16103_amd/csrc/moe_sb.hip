@@ -717,8 +717,11 @@ int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N,
                             int N2, const moe_tiling* tiling2, void* task_map2, void* stream) {
     int rc = check_build_args(topk_ids, T, k, E, N, tiling, task_map);
     if (rc == MOE_OK) rc = check_build_args(topk_ids, T * k, 1, E, N2, tiling2, task_map2);
-    if (rc == MOE_OK && task_map == task_map2) rc = MOE_ERR_INVALID_ARG;
     if (rc != MOE_OK) return rc;
+    const uintptr_t at = (uintptr_t)task_map, at2 = (uintptr_t)task_map2;
+    if (at < at2 + moe_task_map_bytes(T * k, 1, E, tiling2->tile_m, tiling2->tile_n, N2) &&
+        at2 < at + moe_task_map_bytes(T, k, E, tiling->tile_m, tiling->tile_n, N))
+        return MOE_ERR_INVALID_ARG;
     const TwinMap twin = {static_cast<int32_t*>(task_map2), N2, *tiling2};
     return build_maps(topk_ids, T, k, E, N, *tiling, task_map, twin, static_cast<hipStream_t>(stream));
 }

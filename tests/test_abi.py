@@ -94,6 +94,17 @@ def test_null_arguments_rejected_on_host():
     assert lib.moe_task_map_expand(None, 8, None, 0, None) == mb.MOE_ERR_INVALID_ARG
 
 
+def test_map_pair_refuses_overlapping_buffers_on_host():
+    """Any overlap of the two maps, not only equal pointers (addresses only: nothing is launched before the check)."""
+    lib, T, k, E, N, N2 = mb.lib(), 300, 6, 64, 512, 256
+    g = mb.Tiling(64, 128).c_struct()
+    n1, n2 = mb.moe_task_map_bytes(T, k, E, 64, 128, N), mb.moe_task_map_bytes(T * k, 1, E, 64, 128, N2)
+    base = 1 << 30
+    for first, second in ((base, base), (base, base + 16), (base, base + (n1 - 4) // 16 * 16), (base + (n2 - 4) // 16 * 16, base)):
+        assert lib.moe_build_task_map_pair(16, T, k, E, N, ctypes.byref(g), first, N2, ctypes.byref(g), second,
+                                           None) == mb.MOE_ERR_INVALID_ARG, (first, second)
+
+
 def test_mfma_probe_rejects_bad_arguments_before_any_launch():
     from paper_2501_16103_amd import probe
     lib = probe.lib()
