@@ -192,7 +192,7 @@ __device__ __forceinline__ int pswz_x(int row) {
     return C::CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 template <class C>
-__device__ __forceinline__ int pswz_w(int krow) {
+__host__ __device__ constexpr int pswz_w(int krow) {
     int s;
     if constexpr (C::F8W) {
         // a half-wavefront of a transposing read covers 16 k-rows (8 and the 8 sixteen further on) of one 16-column
@@ -205,6 +205,18 @@ __device__ __forceinline__ int pswz_w(int krow) {
     else if constexpr (C::MF == 32) s = (krow & 3) << 2;
     else s = ((krow & 3) | ((krow >> 1) & 4)) << 1;
     return s & (C::CPRW - 1);
+}
+// k-rows after which pswz_w repeats.  The deep fp8 swizzle of 16-row blocks looks at bit 4 of the k-row too, the others at bits
+// 0 to 3 only.
+template <class C>
+constexpr int swz_w_period() {
+    return C::F8W && C::MF == 16 ? 32 : 16;
+}
+template <class C>
+constexpr bool swz_w_repeats() {
+    for (int r = 0; r < 128; ++r)
+        if (pswz_w<C>(r) != pswz_w<C>(r + swz_w_period<C>())) return false;
+    return true;
 }
 
 // A workgroup's run of consecutive tiles for the streaming kernel: the task records stay in registers, so the
@@ -307,10 +319,11 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     constexpr bool ROWS16 = C::BM == 16 && MF == 16 && MBW == 1 && XI == 1 && NS == NSW && C::SLACK == 0 && !C::SPLITK;
     static_assert(!STREAM || (ROWS16 && KSTEPS % 2 == 0), "the streaming loop is written for 16-row tiles");
     // per-lane source offsets inside a tile; everything that depends on the tile (expert, n-tile) is in the base pointer
-    // When a wavefront's weight instructions lie a multiple of 16 k-rows apart they share swizzle and lane
+    // When a wavefront's weight instructions lie a multiple of the swizzle's period apart they share swizzle and lane
     // pattern: one offset register serves them all and the distance goes into the scalar base.
     // ([E][N][K]: a multiple of 32 tile rows apart, which the swizzle and the gate/up units of 16 rows both repeat on.)
-    constexpr bool W_FOLD = C::WKC ? (NW * XROWS_PER_INST) % 32 == 0 : (NW * WROWS_PER_INST) % 16 == 0;
+    static_assert(C::WKC || swz_w_repeats<C>(), "weight swizzle period");
+    constexpr bool W_FOLD = C::WKC ? (NW * XROWS_PER_INST) % 32 == 0 : (NW * WROWS_PER_INST) % swz_w_period<C>() == 0;
     constexpr int WI_OFF = W_FOLD ? 1 : WI;
     uint32_t dx_off[XI], dx_next = 0, dw_off[WI_OFF];
     const uint32_t w_row_bytes = (uint32_t)a.N * ES;
