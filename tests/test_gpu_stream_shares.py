@@ -1,6 +1,6 @@
 """Resident 16-row launches against one workgroup per tile, bit for bit: shares of less than one, one to two and many tiles
 per workgroup, 128-wide tiles run in pairs (an even number of n-tiles) and singly (an odd one, or K too short for the pair's
-ring); [E][N][K] weights, whose launches stay one workgroup per tile in every mode."""
+ring).  [E][N][K] weights have one launch, one workgroup per tile, in every mode: those rows are checked against the oracle only."""
 import pytest
 import torch
 
@@ -18,10 +18,10 @@ CASES = [
     ("bf16", "kn", 128, 40, 16, 2, 448, 640, "gauss_topk", True, (8, 64, 2)),
     ("bf16", "kn", 128, 33, 8, 2, 128, 512, "zipf", False, (8, 2)),          # two k-tiles: no ring is filled
     ("bf16", "kn", 256, 90, 8, 2, 192, 768, "zipf", True, (8, 24, 64, 2)),   # several m-tiles per expert
-    ("bf16", "nk", 256, 90, 8, 2, 256, 768, "zipf", False, (8, 24, 2)),
+    ("bf16", "nk", 256, 90, 8, 2, 256, 768, "zipf", False, ()),
     ("fp8", "kn", 128, 32, 64, 6, 384, 512, "uniform_topk", False, (8, 128, 2)),
-    ("fp8", "nk", 128, 32, 64, 6, 512, 512, "uniform_topk", True, (8, 128, 2)),
-    ("fp8", "nk", 256, 50, 16, 2, 896, 512, "zipf", False, (8, 40, 2)),
+    ("fp8", "nk", 128, 32, 64, 6, 512, 512, "uniform_topk", True, ()),
+    ("fp8", "nk", 256, 50, 16, 2, 896, 512, "zipf", False, ()),
     ("fp8", "kn", 256, 50, 200, 2, 128, 512, "zipf", False, (8, 2)),         # one k-tile, four groups of task records
     # K too short for the deep ring: resident in the two-wavefront form
     ("bf16", "kn", 256, 60, 32, 2, 128, 512, "gauss_topk", True, (8, 32, 2)),
@@ -63,7 +63,7 @@ def test_stream_shares(oracle_mod, dtype, layout, tile_n, T, E, k, K, N, routing
         return H.y_bits(Y)
 
     want = run(mb.MOE_LAUNCH_PER_TILE)
-    for mode in modes + (mb.MOE_LAUNCH_AUTO,):
+    for mode in modes + ((mb.MOE_LAUNCH_AUTO,) if layout == "kn" else ()):
         assert (run(mode) == want).all(), f"launch mode {mode}"
     if fp8:
         res = oracle_mod.grouped_gemm_fp8(wk.bits(X), wk.bits(W), xs.numpy(), ws.numpy(), ids.numpy())
