@@ -198,7 +198,17 @@ class Point:
                     frac_mfma=round(tf_gemm / peak_t, 4), gbs_gemm=round(gbs, 1),
                     frac_hbm=round(gbs / PEAK_HBM_GBS, 4), bound=bound, alg_bytes=abytes, flops=wl.flops,
                     launch_mode=self.launch_mode, tail_split=self.tail_ws is not None,
-                    kernel="moe_gemm_pipe_kernel")
+                    kernel=self.kernel_name())
+
+    def kernel_name(self) -> str:
+        """The kernel moe_grouped_gemm runs this point with (16-row tiles: resident or one workgroup per tile, by size)."""
+        wl = self.wl
+        if self.small[0]:
+            return "moe_gemm_pipe2_kernel"
+        tile = (wl.dtype, wl.tile_m, wl.tile_n)
+        if not self.w_nk and self.slack in (0, 32) and tile in (("bf16", 256, 256), ("bf16", 128, 256), ("bf16", 128, 128), ("fp8", 256, 256)):
+            return "moe_gemm_halves_kernel"
+        return "moe_gemm_stream_kernel / moe_gemm_pipe_kernel" if wl.tile_m == 16 and not self.w_nk else "moe_gemm_pipe_kernel"
 
 
 def cpu_baseline(pt: Point, target_s: float = 30.0) -> dict:

@@ -36,6 +36,8 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
 #define MOE_LDS(T) __attribute__((address_space(3))) T
 
+constexpr int kXcdCus = 32;   // CUs of each of the 8 XCDs
+
 struct GemmArgs {
     const void* X;
     const void* W;
@@ -1277,7 +1279,6 @@ struct TileFns {
 // halved) 205 -> 169 us, 8192 rows 890 -> 865; 4096 -> 28672, 666 rows (112 per XCD) 371 -> 356; 128 x 128 tiles, 14336 -> 4096,
 // skewed routing of 666 rows 263 -> 237, 64 experts, 1408 -> 2048, 6 rows 12.9 -> 9.5.  A rest of more than half a round gains
 // nothing from halving (its halves need two rounds of half the length), hence the line.
-constexpr int kXcdCus = 32;
 template <class Fns, class Half>
 __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs a) {
     using C = typename Fns::Full;

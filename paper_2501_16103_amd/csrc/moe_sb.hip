@@ -136,7 +136,7 @@ inline int resident_workgroups(const void* fn, int threads, int lds, ResidentCac
     return MOE_OK;
 }
 
-constexpr int kCus = 256;
+constexpr int kCus = 8 * kXcdCus;
 constexpr int kSpareSlots = 16;   // workgroups a launch's grid holds beyond the bound on its tiles (see grouped_gemm_impl)
 
 // Tiles of 16 rows that a uniform routing gives: one for each expert it hits; from half a tile of rows per expert on, rows
@@ -521,8 +521,7 @@ int run_splitk(const void* X, const void* W, const void* task_map, void* Y, cons
 }
 
 // ---- tail split (see tail_parts in gemm_kernel.hpp); MI355X: 8 XCDs of 32 CUs
-constexpr int kCusPerXcd = 32;
-static_assert(kTailBlocksPerXcd >= 4 * (kCusPerXcd - 1), "workspace blocks per XCD");
+static_assert(kTailBlocksPerXcd >= 4 * (kXcdCus - 1), "workspace blocks per XCD");
 
 size_t tail_workspace_bytes(int tile_m, int tile_n) {   // (256-row blocks with room for 32 slack rows)
     return size_t(8) * kTailBlocksPerXcd * (tile_m == 256 ? 288 : tile_m) * tile_n * sizeof(float);
@@ -539,7 +538,7 @@ int launch_tail_split(const GemmArgs& a, int64_t grid, gemm_launch_fn whole, hip
     if (ensure_lds_attr(fn, TailC::LDS_BYTES, &attr_done) != MOE_OK) return MOE_ERR_HIP;
     moe_gemm_tail_kernel<TailC, SplitK<Tails>...><<<dim3(8 * kTailBlocksPerXcd), dim3(TailC::NT), TailC::LDS_BYTES, s>>>(a);
     if (hipGetLastError() != hipSuccess) return MOE_ERR_HIP;
-    moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK><<<dim3(8 * kCusPerXcd * kTailReduceSlices), dim3(256), 0, s>>>(a);
+    moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK><<<dim3(8 * kXcdCus * kTailReduceSlices), dim3(256), 0, s>>>(a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -623,7 +622,7 @@ int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling*
     const int64_t R = (int64_t)T * k;
     const double mean_rows = (double)R / E;
     const int64_t active = R < E ? R : E;   // experts that can have rows at all
-    const int cus = 256;
+    const int cus = kCus;
     moe_tiling g = {16, 128, MOE_ORDER_ASCENDING, 0, 0, 0};
     if (dtype == MOE_DTYPE_FP8_E4M3 && mean_rows > 24) {
         // prefill sizes.  The 256-row launch runs its partly filled tiles with narrower functions, so below 96 rows per
@@ -791,7 +790,7 @@ int moe_default_k_parts(int T, int k, int E, int K, int N) {
     const int64_t active = R < E ? R : E;
     const double mt = mean_rows / 256 + 0.5;
     const double tiles = (double)active * (mt < 1.0 ? 1.0 : mt) * (N / 256);
-    const int cus = 256, kt = K / 64;
+    const int cus = kCus, kt = K / 64;
     // worth it where 256 x 256 tiles would leave CUs idle through a long k loop and the experts are not tiny
     // (measured on 8 experts, N = 4096, K = 14336, us with map build and reduction: 1024 rows 255 -> 198, 1536 rows
     // 294 -> 224; at 768 rows the 128 x 128 tiles of moe_default_tiling are faster, 171 against 190)
@@ -844,7 +843,7 @@ int moe_grouped_gemm_tail_split(const void* X, const void* W, const void* task_m
     a.T = d->T; a.k = d->k; a.E = d->E; a.K = d->K; a.N = d->N;
     a.tile_m_slack = d->tile_m_slack;
     a.partial = static_cast<float*>(workspace);
-    a.cus_per_xcd = kCusPerXcd;
+    a.cus_per_xcd = kXcdCus;
     int64_t grid = moe_grid_upper_bound_tiled(d->T, d->k, d->E, d->tile_m, d->tile_n, d->N, 0, 0);
     if (grid == 0) return MOE_OK;
     grid = (grid + 7) / 8 * 8 + 16;
