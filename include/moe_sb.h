@@ -216,7 +216,8 @@ int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N,
  * A reasonable tiling for a problem shape, from the measurements behind this library (HOST, pure; the routing
  * itself is not known to the host, so the choice goes by the mean rows per expert T*k/E):
  *   fp8: up to 24 rows per expert (the decode regime) 16-row tiles, 256 wide when that gives between one and two
- *   workgroups per CU, else 128; above that 256 x 256 (64 x 256 up to 96 rows per expert where one tile per expert
+ *   workgroups per CU, else 128 (from about 12 rows on 256 x 256 is faster over [E][K][N] weights, up to 1.7 times at 24; the rule
+ *   does not know the layout, and [E][N][K] fp8 weights have 16-row kernels only); above that 256 x 256 (64 x 256 up to 96 rows per expert where one tile per expert
  *   and 256 columns would leave CUs without one);
  *   bf16: up to half a row per expert (a token or two) 16-row tiles, 128 wide while those cover at most three quarters
  *   of the CUs, 256 wide once they are more than the CUs (128 x 128 between the two); up to 48 rows per expert

@@ -6,8 +6,9 @@
 // an LDS pipeline feeding MFMA (the CDNA4 counterpart of the pipeline of
 // Sec. 4.4): a global->LDS DMA ring (no register staging), hand-placed MFMA /
 // LDS-read / DMA interleave, per-wavefront skipping of all-padding row blocks in
-// an expert's last m-tile.  moe_gemm_pipe_kernel runs one tiling strategy,
-// moe_gemm_pipe2_kernel two (Alg. 3 with two task types).  The contraction is computed transposed: the weight
+// an expert's last m-tile.  moe_gemm_pipe_kernel runs one tiling strategy, moe_gemm_halves_kernel
+// the same with half tiles in a short last round, moe_gemm_stream_kernel 16-row tiles on resident workgroups,
+// moe_gemm_pipe2_kernel two strategies (Alg. 3 with two task types).  The contraction is computed transposed: the weight
 // tile is the MFMA "A" operand (accumulator rows = output columns n) and the
 // token tile the "B" operand (accumulator columns = token rows m), so that each
 // lane ends up with runs of 4 consecutive n for one token row.
@@ -1210,7 +1211,7 @@ __device__ __forceinline__ TailSplit tail_split(const int32_t* __restrict__ map,
 // a map that does not belong to this launch (wrong shape, tiling or status): those do nothing.
 template <int BM_BIG, int BN, int BM_SMALL, int SLACK>
 __device__ __forceinline__ bool locate_tile(const GemmArgs& a, const int32_t* __restrict__ map, MapLayout& L, TileCoord& tc) {
-    // the first 64 task records travel together with the header: one memory round trip before the tile is known
+    // the first 64 task records are asked for right behind the header check: no further dependent load before the tile is known
     L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
     const int total = map[MOE_HDR_TOTAL_TILES];
