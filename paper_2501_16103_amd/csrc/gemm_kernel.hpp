@@ -1181,6 +1181,58 @@ __device__ __forceinline__ int slots_of_xcd(const int32_t* __restrict__ map, int
     return left < 0 ? 0 : (left < per_xcd ? left : per_xcd);
 }
 
+// An ascending map with crowded and nearly empty experts side by side (Sec. 5's uneven scenario).  Tiles of at most kLightRows
+// rows only stream a weight panel, so equal numbers of consecutive blocks are very unequal amounts of work: an XCD whose run
+// happens to hold two crowded experts is the last to finish.  Here both kinds are dealt out by themselves, one
+// contiguous run of each per XCD, and every other XCD starts with its light run, so that at any time some XCDs stream while the
+// others compute (no interleaving inside an XCD: the streams would displace the panels that the full tiles share in its L2).
+// Like slot_to_block this is a bijection between a launch's slots and the map's blocks.
+// Measured (64 experts, 3584 -> 2560, eight crowded experts and 56 with one row): 4096 tokens 632-665 -> 599-628 us, 2000 tokens
+// 398 -> 355, 1024 tokens 269 -> 246.  With both kinds in one order on all XCDs 631-646, 381 and 273.
+constexpr int kLightRows = 64;
+struct TwoKinds {
+    bool on = false;
+    int before, upto;        // lane t: blocks in front of task t; light blocks up to and with task t
+    int heavy, light;        // blocks of each kind
+    // Only in launches of three rounds and more with both kinds in numbers: an eighth of the blocks cannot make the XCDs' shares very
+    // unequal, and in a short launch the filling of its last round counts for more (64 experts, 1408 -> 2048, a skewed routing
+    // of 777 x 6 rows, 620 blocks: 73 us in plain order, 76 dealt by kind).
+    static constexpr int kMinBlocks = 3 * 8 * kXcdCus;
+    __device__ __forceinline__ void look(const int4& record, int total, int crowded_rows) {
+        if (total < kMinBlocks) return;
+        const int lane = __lane_id();
+        const bool is_light = record.z > 0 && record.z <= kLightRows;
+        if (!__ballot(is_light) || !__ballot(record.z > crowded_rows)) return;
+        const int prev = __shfl_up(record.x, 1, 64);
+        before = lane == 0 ? 0 : prev;
+        upto = is_light ? record.x - before : 0;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(upto, d, 64);
+            upto += lane >= d ? o : 0;
+        }
+        light = __builtin_amdgcn_readlane(upto, 63);
+        heavy = total - light;
+        on = 8 * light >= total && 8 * heavy >= total;
+    }
+    __device__ __forceinline__ int slots(int xcd) const {
+        return (int)(((long long)heavy * (xcd + 1) >> 3) - ((long long)heavy * xcd >> 3)) +
+               (int)(((long long)light * (xcd + 1) >> 3) - ((long long)light * xcd >> 3));
+    }
+    // slot < slots(xcd)
+    __device__ __forceinline__ int block(const int4& record, int xcd, int slot) const {
+        const int h0 = (int)((long long)heavy * xcd >> 3), nh = (int)((long long)heavy * (xcd + 1) >> 3) - h0;
+        const int l0 = (int)((long long)light * xcd >> 3), nl = (int)((long long)light * (xcd + 1) >> 3) - l0;
+        const bool is_light = (xcd & 1) ? slot < nl : slot >= nh;
+        const int i = is_light ? l0 + ((xcd & 1) ? slot : slot - nh) : h0 + ((xcd & 1) ? slot - nl : slot);
+        // the task that holds the i-th block of its kind: the first whose running count is above i
+        const int mine = is_light ? upto : record.x - upto;
+        const int t = __popcll(__ballot(i >= mine));
+        const int in_front = t > 0 ? __builtin_amdgcn_readlane(mine, (t - 1) & 63) : 0;
+        return __builtin_amdgcn_readlane(before, t & 63) + i - in_front;
+    }
+};
+
 // Tail split.  With one workgroup per tile an XCD's tiles run in rounds of `cus` (its CUs); when the last round is
 // only partly filled, the other CUs idle for a whole tile's duration.  The t tiles of that round can instead be run
 // by P = 2 or 4 workgroups each, every one over a part of K (fp32 partial sums, added afterwards): the t * P parts
@@ -1293,7 +1345,9 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
     if (!map_matches_at_once<C::BM, C::BN, C::SLACK>(a, map)) return;
     const int xcd = blockIdx.x & 7;
     int slot = blockIdx.x >> 3, half = -1;
-    const int n = slots_of_xcd(map, total, xcd);
+    TwoKinds kinds;
+    if (a.halve_last && L.E64 == 64 && map[MOE_HDR_SIGMA_ORDER] == MOE_ORDER_ASCENDING) kinds.look(first_record, total, C::BMC);
+    const int n = kinds.on ? kinds.slots(xcd) : slots_of_xcd(map, total, xcd);
     if (a.cus_per_xcd > 0) {
         const TailSplit ts = tail_split(map, total, xcd, a.cus_per_xcd, a.K / 64);
         if (ts.parts > 1 && slot >= ts.full) return;   // the tail launch runs this tile
@@ -1305,7 +1359,9 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
         }
     }
     int B;
-    if (slot >= n || !slot_to_block(map, total, xcd, slot, B)) return;
+    if (slot >= n) return;
+    if (kinds.on) B = kinds.block(first_record, xcd, slot);
+    else if (!slot_to_block(map, total, xcd, slot, B)) return;
     const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
     TileCoord tc = decode_block(map, L, g, B, first_record);
     if (half < 0) {
