@@ -343,13 +343,12 @@ size_t moe_splitk_static_scratch_bytes(void);
 /*
  * moe_grouped_gemm for launches whose last round of tiles is only partly filled (Sec. 3.1's map is unchanged; this
  * is a property of the launch).  With one workgroup per tile an XCD's tiles run in rounds of its 32 CUs; when the
- * last round holds t < 32 tiles the other CUs idle for a whole tile's duration.  Here those t tiles are run by
- * P workgroups each, every one over a part of K; their fp32 sums go to `workspace` and are added in ascending order
- * of the parts, rounded once to bf16 and scattered to Y.  P is the smallest of 1, 2, 4 that minimises the last
- * round's length ceil(t * P / 32) / P (e.g. t <= 8: 4 parts, a quarter; t = 16: 2 parts, a half; t = 22: 4 parts,
- * three quarters; t = 27: no split), chosen per XCD on the device, and only if every part keeps at least 8 k-tiles.
- * All other tiles run exactly as in moe_grouped_gemm (their results are bit for bit the same); the tail tiles differ
- * from it in summation order only.  Three launches on `stream`.
+ * last round holds t < 32 tiles the other CUs idle for a whole tile's duration.  Here, where t is at most 16, those tiles are run
+ * by P workgroups each, every one over a part of K; their fp32 sums go to `workspace` and are added in ascending order
+ * of the parts, rounded once to bf16 and scattered to Y.  P = floor(32 / t), at most 8, with at least 8 k-tiles of 64 a part, chosen
+ * per XCD on the device, and only where K is long enough for the parts to beat running the round as half tiles (for two parts,
+ * more than 140 k-tiles).  All other tiles run exactly as in moe_grouped_gemm (their results are bit for bit the same); the tail
+ * tiles differ from it in summation order only.  Two launches on `stream`.
  *   workspace  DEVICE, 16-byte aligned, at least moe_tail_split_workspace_bytes(tile_m, tile_n) bytes
  *              (8 * 128 * rows * tile_n * 4 with rows = tile_m, 288 for 256-row tiles: 288 MiB), owned by the caller, contents undefined
  *              afterwards; calls that share it must not overlap.

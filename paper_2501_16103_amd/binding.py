@@ -426,18 +426,35 @@ class MoeLayerPlan:
 
     The second product sees the T*k activated rows as tokens of their own, each routed to exactly one expert
     (the flattened routing with k = 1), so one build writes both maps and the same entry point serves both products (the
-    second one in its split-k form, with a workspace held here, where moe_default_k_parts says so).  Nothing here computes:
+    second one with its last round of tiles in parts along K, see _long_down, or in its split-k form where
+    moe_default_k_parts says so, with a workspace held here).  Nothing here computes:
     the plan holds caller-visible device buffers and issues calls on the current stream."""
+
+    @staticmethod
+    def _long_down(R: int, E: int, inter: int, hidden: int) -> bool:
+        """Whether the down product takes moe_grouped_gemm_tail_split on 256-row tiles.  With a long K and few tiles a partly
+        filled last round costs most of the product; which routing leaves which rest is only known on the device, where that call
+        decides.  8 experts, 14336 -> 4096, us, the tiling or split-k otherwise taken / this: uniform routing of 400 rows 149 / 147,
+        666 157 / 156, 1400 188 / 190, 2000 332 / 228, 8192 719-885 / 715-780; skewed 400 217 / 152, 666 237 / 166, 1400 301 / 289,
+        2000 309 / 276, 4094 498 / 437, 8192 835 / 771.  Between 96 and 120 rows per expert a skewed routing fills more than half a
+        round of 256-row tiles and the narrow tiles stay (800 rows 251 / 273); with fewer than 12 there is nothing to share out."""
+        rows = R / E
+        return inter % 64 == 0 and inter >= 7168 and hidden % 256 == 0 and (12 <= rows <= 96 or rows >= 120)
 
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):
         self.T, self.k, self.E, self.hidden, self.inter = T, k, E, hidden, inter
         R = T * k
         self.g1 = moe_default_tiling(MOE_DTYPE_BF16, T, k, E, hidden, 2 * inter)
         # the down product is the short-grid case (few experts, N = hidden): split along K where that pays
-        self.k_parts = moe_default_k_parts(R, 1, E, inter, hidden) if R > 0 else 1
-        self.g2 = Tiling(256, 256) if self.k_parts > 1 else moe_default_tiling(MOE_DTYPE_BF16, R, 1, E, inter, hidden)
-        self.workspace = (torch.empty(moe_splitk_workspace_bytes(R, 1, hidden, self.k_parts) // 4, dtype=torch.float32, device=device)
-                          if self.k_parts > 1 else None)
+        self.tail_split = self._long_down(R, E, inter, hidden)
+        self.k_parts = moe_default_k_parts(R, 1, E, inter, hidden) if R > 0 and not self.tail_split else 1
+        if self.tail_split:
+            self.g2, nbytes = Tiling(256, 256, tile_m_slack=32), moe_tail_split_workspace_bytes(256, 256)
+        elif self.k_parts > 1:
+            self.g2, nbytes = Tiling(256, 256), moe_splitk_workspace_bytes(R, 1, hidden, self.k_parts)
+        else:
+            self.g2, nbytes = moe_default_tiling(MOE_DTYPE_BF16, R, 1, E, inter, hidden), 0
+        self.workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=device) if nbytes else None
         self.map1 = alloc_task_map(T, k, E, self.g1.tile_m, self.g1.tile_n, 2 * inter, device)
         self.map2 = alloc_task_map(R, 1, E, self.g2.tile_m, self.g2.tile_n, hidden, device)
         self.act = torch.empty((R, inter), dtype=torch.bfloat16, device=device)       # [T, k, inter]
@@ -458,7 +475,9 @@ class MoeLayerPlan:
         flat = topk_ids.reshape(T * k, 1)
         moe_build_task_map_pair(topk_ids, T, k, E, 2 * self.inter, self.g1, self.map1, self.hidden, self.g2, self.map2)
         moe_grouped_gemm(X, W_gate_up, topk_ids, self.map1, self.act, self.d1)
-        if self.k_parts > 1:
+        if self.tail_split:
+            moe_grouped_gemm_tail_split(self.act, W_down, self.map2, self.down, self.d2, self.workspace)
+        elif self.k_parts > 1:
             moe_grouped_gemm_splitk(self.act, W_down, self.map2, self.down, self.d2, self.k_parts, self.workspace)
         else:
             moe_grouped_gemm(self.act, W_down, flat, self.map2, self.down, self.d2)

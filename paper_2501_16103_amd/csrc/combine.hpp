@@ -57,8 +57,8 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const u32x4_t* __restr
                       (long long)gridDim.x * 256);
 }
 
-// Last step of a tail-split product: blocks (x, j, 0 .. kTailReduceSlices-1) add the parts of the x-th XCD's tail tile j
-// (compact blocks [x][j * P + p][BM + SLACK][BN] of the workspace, kTailBlocksPerXcd blocks per XCD, p ascending), round
+// Last step of a tail-split product: blocks (x, j, 0 .. kTailReduceSlices-1) add the parts of the x-th XCD's tail tile j where
+// it ran in parts (blocks of the workspace as moe_gemm_tail_kernel wrote them, in the order of k), round
 // once to bf16 and scatter the tile's rows to Y; each of the slices takes every kTailReduceSlices-th stretch of 256
 // chunks (a tile by one workgroup streamed at a fifth of the rate: 42 us of an 0.8 ms product).
 constexpr int kTailReduceSlices = 8;
@@ -69,25 +69,26 @@ __global__ __launch_bounds__(256) void moe_tail_reduce_kernel(GemmArgs a) {
     const MapLayout L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
     const int total = map[MOE_HDR_TOTAL_TILES];
-    if (!map_matches<BM, BN, 0, SLACK>(a, map)) return;
+    if (!map_matches_at_once<BM, BN, SLACK>(a, map)) return;
     const int xcd = blockIdx.x & 7, j = (int)(blockIdx.x >> 3) / kTailReduceSlices, slice = (int)(blockIdx.x >> 3) % kTailReduceSlices;
-    const TailSplit ts = tail_split(map, total, xcd, a.cus_per_xcd, a.K / 64);
-    if (ts.parts == 1 || j >= ts.tail) return;
+    const int n = slots_of_xcd(map, total, xcd), rest = n % kXcdCus, kt = a.K / 64;
+    const int parts = tail_parts(rest, kt);
+    if (j >= rest || parts == 1) return;
     int B;
-    if (!slot_to_block(map, total, xcd, ts.full + j, B)) return;
+    if (!slot_to_block(map, total, xcd, n - rest + j, B)) return;
     const moe_tiling g = {BM, BN, 0, 0, 0, SLACK};
     const TileCoord tc = decode_block(map, L, g, B, first_record);
-    const float* base = a.partial + ((size_t)(xcd * kTailBlocksPerXcd + j * ts.parts) * BMC) * BN;
+    const float* blocks = a.partial + (size_t)(xcd * kTailBlocksPerXcd + j * parts) * (BMC * BN);
     const int32_t* rows = map + L.off_rows + tc.row_base;
     u32x4_t* Y = static_cast<u32x4_t*>(a.Y);
     constexpr int CPR = BN / 8;   // 8-column chunks per tile row
     for (int c = slice * 256 + threadIdx.x; c < tc.rows * CPR; c += 256 * kTailReduceSlices) {
         const int m = c / CPR, col = c - m * CPR;
-        const float* src = base + (size_t)m * BN + col * 8;
+        const float* src = blocks + (size_t)m * BN + col * 8;
         f32x4_t lo = *reinterpret_cast<const f32x4_t*>(src), hi = *reinterpret_cast<const f32x4_t*>(src + 4);
-        for (int p = 1; p < ts.parts; ++p) {
-            lo += *reinterpret_cast<const f32x4_t*>(src + (size_t)p * BMC * BN);
-            hi += *reinterpret_cast<const f32x4_t*>(src + (size_t)p * BMC * BN + 4);
+        for (int p = 1; p < parts; ++p) {
+            lo += *reinterpret_cast<const f32x4_t*>(src + (size_t)p * (BMC * BN));
+            hi += *reinterpret_cast<const f32x4_t*>(src + (size_t)p * (BMC * BN) + 4);
         }
         u32x4_t o;
         o.x = pack_bf16(lo[0], lo[1]); o.y = pack_bf16(lo[2], lo[3]);

@@ -51,14 +51,11 @@ struct GemmArgs {
     int tile_m_slack;                  // slack rows of the map's last m-tiles
     int swiglu;                        // 1: W = [gate | up] halves of N, Y[r, i] = silu(gate_i) * up_i, Y is [R, N/2]
     float* partial;                    // split-k launches: fp32 partial sums [gridDim.y][R (sorted row position)][N]
-    // split-k task functions: which part of K this workgroup runs, and where its partial sums go (set per workgroup
-    // by the kernel, not by the host): partial_tile != nullptr: row m of the tile at partial_tile + m * BN (a
-    // compact per-tile block); else row position p, column n at partial + (k_part * R + p) * N + n
-    int k_part, k_parts;
+    // split-k task functions: which part of K this workgroup runs (k_tiles k-tiles from k_tile0 on), and where its partial sums
+    // go (set per workgroup by the kernel, not by the host): partial_tile != nullptr: row m of the tile at partial_tile + m * BN (a
+    // compact block); else row position p, column n at partial + (k_part * R + p) * N + n
+    int k_part, k_tile0, k_tiles;
     float* partial_tile;
-    // tail-split launches (cus_per_xcd > 0): the tiles of an XCD's last, partly filled round are left to the
-    // workgroups of the tail launch whenever those can split them (see tail_parts)
-    int cus_per_xcd;
     int halve_last;                    // 1: short last rounds run as half tiles (see moe_gemm_halves_kernel)
     // heterogeneous launches: a reduction task batched with the GEMM tasks (Alg. 3 with two task types), else red_tiles = 0
     const void* red_Y;                 // [red_T][red_k][red_N] bf16, finished products of an earlier launch
@@ -358,9 +355,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
         dw_off[j] = (uint32_t)krow * w_row_bytes + col_bytes;
     }
     // split-k: this workgroup's part of K (the row pitch of X and the k stride of W are those of the whole K)
-    const int k_parts = C::SPLITK ? a.k_parts : 1;
-    const int KT = a.K / BK / k_parts;
-    const int k_first = C::SPLITK ? a.k_part * KT * BK : 0;
+    const int KT = C::SPLITK ? a.k_tiles : a.K / BK;
+    const int k_first = C::SPLITK ? a.k_tile0 * BK : 0;
     const char* Xb = static_cast<const char*>(a.X) + (size_t)k_first * ES;
     // weight base of a tile: expert, and the first column the tile reads (half as far with the fused activation)
     auto w_base = [&](const TileCoord& t) {
@@ -373,8 +369,11 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     const uint32_t lds0 = (uint32_t)(uintptr_t)(MOE_LDS(char)*)smem;
 
     // Weight panels that only this tile reads are fetched non-temporally -- when the grid is large enough to
-    // stream from all CUs (measured: +10 % HBM throughput on the weight-streaming points, -9 % on a 132-tile grid).
-    const bool nt_ok = map[MOE_HDR_TOTAL_TILES] >= 256;
+    // stream from all CUs (measured: +10 % HBM throughput on the weight-streaming points, -9 % on a 132-tile grid).  What
+    // counts is workgroups: a tile that runs as two halves or in parts along K has as many streams.  (8 experts, 14336 -> 4096, 128 tiles
+    // of 256 columns, without the hint / with it: 666 rows as halves 168 / 158 us, in two parts 166 / 156, 200 rows in two parts
+    // 154 / 143.)
+    const bool nt_ok = map[MOE_HDR_TOTAL_TILES] * tc.sharers >= 256;
     bool w_once = nt_ok && tc.m_tiles == 1, w_once_next = false;
     // j-th token-row / weight-row DMA instruction of this wave for k-tile kt, into ring stage `stage`
     auto dma_x = [&](int j, int kt, int stage, bool next) __attribute__((always_inline)) {
@@ -1233,31 +1232,25 @@ struct TwoKinds {
     }
 };
 
-// Tail split.  With one workgroup per tile an XCD's tiles run in rounds of `cus` (its CUs); when the last round is
-// only partly filled, the other CUs idle for a whole tile's duration.  The t tiles of that round can instead be run
-// by P = 2 or 4 workgroups each, every one over a part of K (fp32 partial sums, added afterwards): the t * P parts
-// then take ceil(t * P / cus) sub-rounds of 1 / P of a tile's duration.  P is the smallest of 1, 2, 4 that makes
-// this shortest (parts keep at least 8 k-tiles).  The map is untouched: this is a property of the launch.
-__host__ __device__ inline int tail_parts(int t, int cus, int k_tiles) {
-    if (t <= 0) return 1;
-    int best = 1, best_len = 4;                       // duration of the last round in quarters of a tile
-    for (int P = 2; P <= 4; P *= 2) {
-        if (k_tiles % P != 0 || k_tiles / P < 8) break;
-        const int len = (t * P + cus - 1) / cus * (4 / P);
-        if (len < best_len) { best = P; best_len = len; }
-    }
-    return best;
+// Tail split.  With one workgroup per tile an XCD's tiles run in rounds of its 32 CUs, and while the t tiles of a partly
+// filled last round run, the other CUs idle for a whole tile's duration.  If they fill at most half of the CUs, each can instead be
+// run by P = floor(32 / t) workgroups (8 at most), every one over a part of K of at least 8 k-tiles; their fp32 sums are added
+// afterwards, in the order of k.  That takes 1 / P of a tile's duration and about 14 k-tiles' worth for the second ring fill, the
+// sums' way through memory and their addition; as half tiles (see moe_gemm_halves_kernel) the round takes six tenths.
+// The parts of all tiles begin at the same k, so that tiles of one weight panel go on sharing it: cutting the whole round into 32 equal
+// stretches, which would also serve a round more than half full, was slower than running it whole (8 experts, 14336 -> 4096,
+// a skewed routing of 2000 rows, 26 tiles per XCD: 351 us against 275).
+// The map is untouched: this is a property of the launch.
+constexpr int kPartOverhead = 14, kMaxTailParts = 8;
+__host__ __device__ inline int tail_parts(int t, int kt) {
+    if (t <= 0 || t > kXcdCus / 2) return 1;
+    int P = kXcdCus / t < kMaxTailParts ? kXcdCus / t : kMaxTailParts;
+    if (kt / P < 8) P = kt / 8;
+    return P >= 2 && 10 * (kt / P + kPartOverhead) < 6 * kt ? P : 1;
 }
-constexpr int kTailBlocksPerXcd = 128;   // upper bound on t * P (t < cus <= 32, P <= 4): blocks of the tail workspace per XCD
-struct TailSplit { int full, tail, parts; };   // slots [0, full) run whole tiles, slots [full, full + tail) are split
-__device__ __forceinline__ TailSplit tail_split(const int32_t* __restrict__ map, int total, int xcd, int cus, int k_tiles) {
-    const int n_x = slots_of_xcd(map, total, xcd);
-    TailSplit ts;
-    ts.full = n_x / cus * cus;
-    ts.tail = n_x - ts.full;
-    ts.parts = tail_parts(ts.tail, cus, k_tiles);
-    return ts;
-}
+// First k-tile of part p.
+__host__ __device__ inline int part_begin(int kt, int P, int p) { return (int)((long long)kt * p / P); }
+constexpr int kTailBlocksPerXcd = kXcdCus;   // blocks of partial sums per XCD
 
 // Block index -> tile (Alg. 2 + 4), shared by the kernels below.  Returns false for surplus workgroups and for
 // a map that does not belong to this launch (wrong shape, tiling or status): those do nothing.
@@ -1270,10 +1263,6 @@ __device__ __forceinline__ bool locate_tile(const GemmArgs& a, const int32_t* __
     if (!map_matches<BM_BIG, BN, BM_SMALL, SLACK>(a, map)) return false;
     int B;
     if (!slot_to_block(map, total, blockIdx.x & 7, blockIdx.x >> 3, B)) return false;
-    if (a.cus_per_xcd > 0) {
-        const TailSplit ts = tail_split(map, total, blockIdx.x & 7, a.cus_per_xcd, a.K / 64);
-        if (ts.parts > 1 && (int)(blockIdx.x >> 3) >= ts.full) return false;   // the tail launch runs this tile
-    }
     const moe_tiling g = {BM_BIG, BN, 0, BM_SMALL, a.small_max_rows, SLACK};
     tc = decode_block(map, L, g, B, first_record);
     return true;
@@ -1307,7 +1296,9 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
         // one of gridDim.y workgroups that share the tile
         GemmArgs b = a;
         b.k_part = (int)blockIdx.y;
-        b.k_parts = (int)gridDim.y;
+        b.k_tiles = a.K / C::BK / (int)gridDim.y;
+        b.k_tile0 = b.k_part * b.k_tiles;
+        tc.sharers = (int)gridDim.y;
         run_tile<C, Tails...>(b, a.map, L, tc, smem);
     } else {
         run_tile<C, Tails...>(a, a.map, L, tc, smem);
@@ -1348,10 +1339,7 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
     TwoKinds kinds;
     if (a.halve_last && L.E64 == 64 && map[MOE_HDR_SIGMA_ORDER] == MOE_ORDER_ASCENDING) kinds.look(first_record, total, C::BMC);
     const int n = kinds.on ? kinds.slots(xcd) : slots_of_xcd(map, total, xcd);
-    if (a.cus_per_xcd > 0) {
-        const TailSplit ts = tail_split(map, total, xcd, a.cus_per_xcd, a.K / 64);
-        if (ts.parts > 1 && slot >= ts.full) return;   // the tail launch runs this tile
-    } else if (a.halve_last) {
+    if (a.halve_last) {
         const int rest = n % kXcdCus, full = n - rest;
         if (rest <= kXcdCus / 2 && slot >= full) {
             half = (slot - full) & 1;
@@ -1368,34 +1356,59 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
         Fns::run(a, map, L, tc, smem);
     } else {
         tc.n_tile = 2 * tc.n_tile + half;
+        tc.sharers = 2;
         Half::run(a, map, L, tc, smem);
     }
 }
 
-// The tail launch of a tail-split product: workgroup i of XCD x runs part i % P of the x-th XCD's tail tile i / P
-// (P = that XCD's number of parts) and leaves its fp32 sums in its own compact block of the workspace,
-// [x][i][BM + SLACK][BN].  C and Tails are split-k task functions.
-template <class C, class... Tails>
-__global__ __launch_bounds__(C::NT) void moe_gemm_tail_kernel(GemmArgs a) {
-    static_assert(C::SPLITK, "split-k task functions");
+// A tail-split product: whole tiles in the full rounds of every XCD, and the tiles of its last round in parts along K where that
+// pays (see tail_parts), else whole or as half tiles.  Part p of tail tile j of XCD x leaves its fp32 sums in
+// block x * 32 + j * P + p of the workspace, [BM + SLACK][BN].  Parts: the split-k task functions.
+// (One launch: the parts start as the CUs come free from the last full round, without a gap between two launches.)
+template <class Fns, class Half, class Parts>
+__global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a) {
+    using C = typename Fns::Full;
+    static_assert(Parts::Full::SPLITK && Parts::Full::BMC == C::BMC && Parts::Full::NT == C::NT, "split-k task functions");
+    constexpr bool HALVES = Half::Full::BN < C::BN;   // (no half tiles for this shape: Half = Fns)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int32_t* __restrict__ map = a.map;
     const MapLayout L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
     const int total = map[MOE_HDR_TOTAL_TILES];
-    if (!map_matches<C::BM, C::BN, 0, C::SLACK>(a, map)) return;
-    const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
-    const TailSplit ts = tail_split(map, total, xcd, a.cus_per_xcd, a.K / 64);
-    if (ts.parts == 1 || i >= ts.tail * ts.parts) return;
+    if (!map_matches_at_once<C::BM, C::BN, C::SLACK>(a, map)) return;
+    const int xcd = blockIdx.x & 7;
+    int slot = blockIdx.x >> 3, half = -1;
+    const int n = slots_of_xcd(map, total, xcd), rest = n % kXcdCus, full = n - rest, kt = a.K / C::BK;
+    const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
+    const int parts = slot >= full ? tail_parts(rest, kt) : 1;
     int B;
-    if (!slot_to_block(map, total, xcd, ts.full + i / ts.parts, B)) return;
-    const moe_tiling g = {C::BM, C::BN, 0, 0, 0, C::SLACK};
-    const TileCoord tc = decode_block(map, L, g, B, first_record);
-    GemmArgs b = a;
-    b.k_part = i % ts.parts;
-    b.k_parts = ts.parts;
-    b.partial_tile = a.partial + ((size_t)(xcd * kTailBlocksPerXcd + i) * C::BMC) * C::BN;
-    run_tile<C, Tails...>(b, map, L, tc, smem);
+    if (parts > 1) {
+        const int i = slot - full, p = i % parts;
+        if (i >= rest * parts || !slot_to_block(map, total, xcd, full + i / parts, B)) return;
+        TileCoord tc = decode_block(map, L, g, B, first_record);
+        tc.sharers = full > 0 ? 1 : parts;
+        GemmArgs b = a;
+        b.k_tile0 = part_begin(kt, parts, p);
+        b.k_tiles = part_begin(kt, parts, p + 1) - b.k_tile0;
+        b.partial_tile = a.partial + (size_t)(xcd * kTailBlocksPerXcd + i) * (C::BMC * C::BN);
+        Parts::run(b, map, L, tc, smem);
+        return;
+    }
+    if (HALVES && rest <= kXcdCus / 2 && slot >= full) {
+        half = (slot - full) & 1;
+        slot = full + ((slot - full) >> 1);
+    }
+    if (slot >= n || !slot_to_block(map, total, xcd, slot, B)) return;
+    TileCoord tc = decode_block(map, L, g, B, first_record);
+    if constexpr (HALVES) {
+        if (half >= 0) {
+            tc.n_tile = 2 * tc.n_tile + half;
+            tc.sharers = 2;
+            Half::run(a, map, L, tc, smem);
+            return;
+        }
+    }
+    Fns::run(a, map, L, tc, smem);
 }
 
 // Two tiling strategies in one launch (Alg. 3 with K = 2 task types): the expert's row count picks the task

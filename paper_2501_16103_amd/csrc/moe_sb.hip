@@ -90,7 +90,7 @@ int launch_halves(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
     if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_halves_kernel<Fns, Half>), C::LDS_BYTES, &attr_done) != MOE_OK)
         return MOE_ERR_HIP;
     GemmArgs b = a;
-    b.halve_last = mode != MOE_LAUNCH_PER_TILE && a.cus_per_xcd == 0;
+    b.halve_last = mode != MOE_LAUNCH_PER_TILE;
     if (b.halve_last) grid = 8 * halved_slots(grid / 8);
     moe_gemm_halves_kernel<Fns, Half><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(b);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
@@ -304,6 +304,10 @@ using H_256x128 = TileFns<Ph_256x128, Ph_64x128, Pb_128x128>;
 using H_128x128 = TileFns<Pb_128x128, Ph_64x128>;
 using F_128x128 = TileFns<Pb_128x128>;
 using H_128x64 = TileFns<Ph_128x64>;
+// The same in parts along K
+using S_256x256 = TileFns<SplitK<Pb_256x256>, SplitK<Ps_64x256>, SplitK<Ps_128x256>, SplitK<Pt_128x256>>;
+using S_256x256s32 = TileFns<SplitK<Pb_256x256s32>, SplitK<Ps_64x256>, SplitK<Ps_128x256>, SplitK<Pt_128x256>>;
+using S_128x256 = TileFns<SplitK<Pb_128x256>, SplitK<Ps_64x256>>;
 using P8h_256x128 = PipeCfg<256, 128, 128, 4, 2, 2, true, 3, 0, false, 16>;
 using P8h_128x128 = PipeCfg<128, 128, 128, 2, 4, 3, true, 3, 0, false, 32>;
 using P8h_64x128 = PipeCfg<64, 128, 128, 2, 4, 4, true, 4, 0, false, 32>;
@@ -522,24 +526,24 @@ int run_splitk(const void* X, const void* W, const void* task_map, void* Y, cons
 }
 
 // ---- tail split (see tail_parts in gemm_kernel.hpp); MI355X: 8 XCDs of 32 CUs
-static_assert(kTailBlocksPerXcd >= 4 * (kXcdCus - 1), "workspace blocks per XCD");
+constexpr int kTailWorkspaceBlocks = 128;   // blocks per XCD that the workspace is sized for
+static_assert(kTailWorkspaceBlocks >= kTailBlocksPerXcd, "workspace blocks per XCD");
 
 size_t tail_workspace_bytes(int tile_m, int tile_n) {   // (256-row blocks with room for 32 slack rows)
-    return size_t(8) * kTailBlocksPerXcd * (tile_m == 256 ? 288 : tile_m) * tile_n * sizeof(float);
+    return size_t(8) * kTailWorkspaceBlocks * (tile_m == 256 ? 288 : tile_m) * tile_n * sizeof(float);
 }
 
-// The three launches of a tail-split product: whole tiles, the parts of the tail tiles, their sums.
-template <class C, class... Tails>
-int launch_tail_split(const GemmArgs& a, int64_t grid, gemm_launch_fn whole, hipStream_t s) {
-    const int r1 = whole(a, grid, MOE_LAUNCH_AUTO, s);
-    if (r1 != MOE_OK) return r1;
-    using TailC = SplitK<C>;
+// The two launches of a tail-split product: the tiles, those of a short last round in parts; the sums of the parts.
+template <class Fns, class Half, class Parts>
+int launch_tail_split(const GemmArgs& a, int64_t grid, hipStream_t s) {
+    using C = typename Fns::Full;
     static unsigned long long attr_done = 0;
-    const void* fn = reinterpret_cast<const void*>(&moe_gemm_tail_kernel<TailC, SplitK<Tails>...>);
-    if (ensure_lds_attr(fn, TailC::LDS_BYTES, &attr_done) != MOE_OK) return MOE_ERR_HIP;
-    moe_gemm_tail_kernel<TailC, SplitK<Tails>...><<<dim3(8 * kTailBlocksPerXcd), dim3(TailC::NT), TailC::LDS_BYTES, s>>>(a);
+    const void* fn = reinterpret_cast<const void*>(&moe_gemm_tail_kernel<Fns, Half, Parts>);
+    if (ensure_lds_attr(fn, C::LDS_BYTES, &attr_done) != MOE_OK) return MOE_ERR_HIP;
+    grid = 8 * ((grid / 8 + kXcdCus - 1) / kXcdCus * kXcdCus);   // every CU of a last round
+    moe_gemm_tail_kernel<Fns, Half, Parts><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(a);
     if (hipGetLastError() != hipSuccess) return MOE_ERR_HIP;
-    moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK><<<dim3(8 * kXcdCus * kTailReduceSlices), dim3(256), 0, s>>>(a);
+    moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK><<<dim3(8 * (kXcdCus / 2) * kTailReduceSlices), dim3(256), 0, s>>>(a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -844,17 +848,16 @@ int moe_grouped_gemm_tail_split(const void* X, const void* W, const void* task_m
     a.T = d->T; a.k = d->k; a.E = d->E; a.K = d->K; a.N = d->N;
     a.tile_m_slack = d->tile_m_slack;
     a.partial = static_cast<float*>(workspace);
-    a.cus_per_xcd = kXcdCus;
     int64_t grid = moe_grid_upper_bound_tiled(d->T, d->k, d->E, d->tile_m, d->tile_n, d->N, 0, 0);
     if (grid == 0) return MOE_OK;
     grid = (grid + 7) / 8 * 8 + 16;
     if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     switch (d->tile_m) {
-        case 256: return d->tile_m_slack == 32 ? launch_tail_split<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>(a, grid, &launch_halves<F_256x256s32, H_256x128>, s)
-                                               : launch_tail_split<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>(a, grid, &launch_halves<F_256x256, H_256x128>, s);
-        case 128: return launch_tail_split<Pb_128x256, Ps_64x256>(a, grid, &launch_halves<F_128x256, H_128x128>, s);
-        default: return launch_tail_split<Pb_64x256>(a, grid, &launch_pipe<Pb_64x256>, s);
+        case 256: return d->tile_m_slack == 32 ? launch_tail_split<F_256x256s32, H_256x128, S_256x256s32>(a, grid, s)
+                                               : launch_tail_split<F_256x256, H_256x128, S_256x256>(a, grid, s);
+        case 128: return launch_tail_split<F_128x256, H_128x128, S_128x256>(a, grid, s);
+        default: return launch_tail_split<TileFns<Pb_64x256>, TileFns<Pb_64x256>, TileFns<SplitK<Pb_64x256>>>(a, grid, s);
     }
 }
 

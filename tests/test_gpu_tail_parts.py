@@ -1,0 +1,114 @@
+"""The tail split at the long K it is made for: every number of parts that a last round of 1 to 17 tiles per XCD gets, with and
+without full rounds in front, ragged parts (a K that the parts do not divide) and every task function, against 64-bit products; tiles
+that do not run in parts are bit for bit what moe_grouped_gemm gives.  And the layer plan that takes it."""
+import pytest
+import torch
+
+from paper_2501_16103_amd import binding as mb
+from tests import helpers as H
+from tests.test_gpu_parity import _ids_from_counts
+
+pytestmark = pytest.mark.gpu
+
+
+def _parts(t, kt):
+    """Workgroups per tile of a last round of t tiles, written down from the rule's description."""
+    if not 1 <= t <= 16:
+        return 1
+    p = min(32 // t, 8, kt // 8)
+    return p if p >= 2 and kt // p + 14 < 0.6 * kt else 1
+
+
+CASES = [
+    # tile_m (negative: 32 slack rows), rows per expert, n-tiles, K        tiles per XCD (the last XCDs may hold fewer)
+    (256, [300, 1, 64], 2, 14336),                 # 1: 8 parts of 28 k-tiles
+    (256, [129, 256, 0, 513, 65], 3, 14336),       # 3: 8 parts
+    (-256, [288, 129, 200, 256, 31], 8, 9280),     # 5: 6 parts of 145 k-tiles
+    (256, [70, 128, 250, 3, 1], 16, 7168),         # 10: 3 parts of 112 k-tiles
+    (256, [90, 128, 64, 250], 32, 9152),           # 16: 2 parts of 143 k-tiles
+    (256, [90, 128, 64, 250], 32, 7168),           # 16, K too short for two parts: half tiles
+    (-256, [288, 100, 257, 40], 34, 14336),        # 17: whole
+    (128, [128, 64, 129, 1], 7, 14336),            # 128-row tiles, 5: 6 parts
+    (64, [64, 33, 70], 2, 7168),                   # 64-row tiles, 1: 8 parts
+    (-256, [9000, 280], 8, 7168),                  # 36: a full round and 4, 8 parts
+]
+
+
+@pytest.mark.parametrize("tile_m,counts,nt,K", CASES)
+def test_tail_parts(tile_m, counts, nt, K):
+    dev = torch.device("cuda:0")
+    slack, tile_m = (32, 256) if tile_m < 0 else (0, tile_m)
+    E, T, N = len(counts), sum(counts), nt * 256
+    ids = _ids_from_counts(counts, 5).to(dev)
+    g = torch.Generator(device=dev).manual_seed(K + nt)
+    X = torch.randn((T, K), generator=g, device=dev).to(torch.bfloat16)
+    W = (torch.randn((E, K, N), generator=g, device=dev) * K ** -0.5).to(torch.bfloat16)
+    tmap = mb.alloc_task_map(T, 1, E, tile_m, 256, N)
+    mb.moe_build_task_map_ex(ids, T, 1, E, N, mb.Tiling(tile_m, 256, tile_m_slack=slack), tmap)
+    desc = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, 1, E, K, N, tile_m, 256, tile_m_slack=slack)
+    words = mb.moe_tail_split_workspace_bytes(tile_m, 256) // 4
+    ws = torch.full((words,), float("nan"), dtype=torch.float32, device=dev)
+    Y, plain = (torch.full((T, N), float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    mb.moe_grouped_gemm_tail_split(X, W, tmap, Y, desc, ws)
+    mb.moe_grouped_gemm(X, W, None, tmap, plain, desc)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(Y.float()).all()), "an output was never written"
+    # one rounding to bf16 and fp32 sums in some order, against 64 bits
+    for e in range(E):
+        r = torch.nonzero(ids[:, 0] == e).flatten()
+        for r in r.split(1024):
+            want = X[r].double() @ W[e].double()
+            bound = 2.0 ** -8 * want.abs() * 1.001 + H.sum_err_coeff(K, False) * (X[r].abs().double() @ W[e].abs().double()) + 1e-30
+            assert bool(((Y[r].double() - want).abs() <= bound).all()), f"expert {e}"
+    # which tiles ran in parts
+    total = int(tmap[mb.HDR["TOTAL_TILES"]])
+    share = -(-total // 8)
+    in_parts, expected = set(), set()
+    for x in range(8):
+        n = max(0, min(share, total - x * share))
+        p = _parts(n % 32, K // 64)
+        if p > 1:
+            in_parts |= set(range(x * share + n // 32 * 32, x * share + n))
+            expected.add(p)
+    written = int(torch.isfinite(ws).any().item())
+    assert bool(written) == bool(expected)
+    rows, B = [torch.nonzero(ids[:, 0] == e).flatten().tolist() for e in range(E)], 0
+    for e in range(E):
+        if not counts[e]:
+            continue
+        mt = max(1, -(-(counts[e] - slack) // tile_m))
+        for n in range(nt):
+            for m in range(mt):
+                if B not in in_parts:
+                    r = torch.tensor(rows[e][m * tile_m:] if m == mt - 1 else rows[e][m * tile_m:(m + 1) * tile_m], device=dev)
+                    cols = slice(n * 256, (n + 1) * 256)
+                    assert torch.equal(Y[r, cols].view(torch.int16), plain[r, cols].view(torch.int16)), f"tile {B}"
+                B += 1
+    assert B == total
+
+
+def test_layer_with_a_long_down_product():
+    """A layer whose down product takes the tail split: its output is the weighted sum of the products of its own activations."""
+    dev = torch.device("cuda:0")
+    T, k, E, hidden, inter = 150, 2, 4, 256, 7168
+    plan = mb.MoeLayerPlan(T, k, E, hidden, inter, dev)
+    assert plan.tail_split and plan.k_parts == 1
+    g = torch.Generator(device=dev).manual_seed(3)
+    X = torch.randn((T, hidden), generator=g, device=dev).to(torch.bfloat16)
+    W1 = (torch.randn((E, hidden, 2 * inter), generator=g, device=dev) * hidden ** -0.5).to(torch.bfloat16)
+    W2 = (torch.randn((E, inter, hidden), generator=g, device=dev) * inter ** -0.5).to(torch.bfloat16)
+    ids = torch.stack([torch.randperm(E, generator=g, device=dev)[:k] for _ in range(T)]).to(torch.int32)
+    wts = torch.rand((T, k), generator=g, device=dev, dtype=torch.float32)
+    plan.workspace.fill_(float("nan"))
+    out = plan.forward(X, W1, W2, ids, wts)
+    torch.cuda.synchronize()
+    flat, act = ids.reshape(-1).long(), plan.act
+    for e in range(E):
+        r = torch.nonzero(flat == e).flatten()
+        want = act[r].double() @ W2[e].double()
+        bound = 2.0 ** -8 * want.abs() * 1.001 + H.sum_err_coeff(inter, False) * (act[r].abs().double() @ W2[e].abs().double()) + 1e-30
+        assert bool(((plan.down[r].double() - want).abs() <= bound).all())
+    terms = plan.down.double().view(T, k, hidden) * wts.double()[:, :, None]
+    want = terms.sum(dim=1)
+    bound = 2.0 ** -8 * want.abs() * 1.001 + (k + 1) * 2.0 ** -24 * terms.abs().sum(dim=1) + 1e-30
+    assert bool(((out.double() - want).abs() <= bound).all())
