@@ -109,7 +109,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 // (K contiguous, a pre-packed layout) instead of [E][K][N]: the weight tile then has the token tile's geometry
 // and needs no transposing LDS reads.
 template <int BM_, int BN_, int BK_, int WM_, int WN_, int NS_, bool FP8_ = false, int NSW_ = NS_, int SLACK_ = 0,
-          bool WKC_ = false, int MFO_ = 0, int NSWH_ = 0>
+          bool WKC_ = false, int MFO_ = 0, int NSWH_ = 0, int NSWQ_ = 0>
 struct PipeCfg {
     static constexpr bool SPLITK = false;
     static constexpr bool ALONE = false;
@@ -119,6 +119,11 @@ struct PipeCfg {
     // reach ahead is that of ceil(NSWH_ / 2) whole stages.
     static constexpr bool WHALF = NSWH_ > 0;
     static constexpr int NSWH = NSWH_;
+    // NSWQ_ > 0 ([E][N][K], alternating roles): the weight ring is NSWQ_ quarters of a stage, of BN / 4 columns and the whole depth of
+    // a k-tile each, which is what one DMA instruction per wavefront fills and one wavefront column reads: quarter j of k-tile kt lives in
+    // quarter (4 kt + j) % NSWQ_ of the ring.
+    static constexpr bool WQUART = NSWQ_ > 0;
+    static constexpr int NSWQ = NSWQ_;
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, NS = NS_, SLACK = SLACK_;
     static constexpr int NSW = WHALF ? (NSWH_ + 1) / 2 : NSW_;
     static constexpr int BMC = BM + SLACK;                     // row capacity of the tile in LDS and registers
@@ -152,11 +157,13 @@ struct PipeCfg {
     static constexpr int XROW = BK * ES, CPR = XROW / 16;
     static constexpr int WROW = BN * ES, CPRW = WROW / 16;
     // the token tile in LDS is rounded up so that every wavefront issues the same number of DMA instructions
-    static constexpr int XS_BYTES = (BMC * XROW + 16 * NT - 1) / (16 * NT) * (16 * NT);
+    // (with quarters the loop does not issue the instructions that would fill nothing but the rounding, and LDS has no room for it)
+    static constexpr int XS_BYTES = WQUART ? BMC * XROW : (BMC * XROW + 16 * NT - 1) / (16 * NT) * (16 * NT);
     static constexpr int WS_BYTES = BK * WROW;                 // (BN rows of XROW bytes when WKC: same size)
     static constexpr int W_RING = NS * XS_BYTES;               // byte offset of the weight ring
-    static constexpr int WH_BYTES = WS_BYTES / 2;
-    static constexpr int LDS_BYTES = NS * XS_BYTES + (WHALF ? NSWH * WH_BYTES : NSW * WS_BYTES);
+    static constexpr int WH_BYTES = WS_BYTES / 2, WQ_BYTES = WS_BYTES / 4;
+    static constexpr int LDS_BYTES = NS * XS_BYTES + (WHALF ? NSWH * WH_BYTES : WQUART ? NSWQ * WQ_BYTES : NSW * WS_BYTES);
+    static_assert(!WQUART || (PP && WKC_ && !FP8_ && KSTEPS == 2 && WN_ == 4 && NT == 512 && NSWQ_ == 11), "quarter-stage weight ring");
     static_assert(!WHALF || (NS_ == 2 && !FP8_ && !WKC_ && BK_ / (MFO_ == 16 ? 32 : 16) == 2 && NSWH_ % 2 == 1),
                   "half-stage weight ring: two k-steps per k-tile, two token stages, an odd number of half-stages");
     // weight-fragment LDS reads per k-step and block (two 4-k halves for bf16, 8-k pieces for fp8: one, or four for
@@ -309,8 +316,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
 
     // ---- DMA geometry: one wave instruction moves 64 x 16 B = 1 KiB, linear in LDS
     constexpr int XI_TOT = C::XS_BYTES / 1024, WI_TOT = C::WS_BYTES / 1024;
-    static_assert(XI_TOT % NW == 0 && WI_TOT % NW == 0, "every wave issues the same number of DMA instructions");
-    constexpr int XI = XI_TOT / NW, WI = WI_TOT / NW;
+    static_assert((XI_TOT % NW == 0 || C::WQUART) && WI_TOT % NW == 0, "every wave issues the same number of DMA instructions");
+    constexpr int XI = (XI_TOT + NW - 1) / NW, WI = WI_TOT / NW;
     constexpr int XI_BODY = C::SLACK == 0 ? XI : C::BM * C::XROW / 1024 / NW;   // instructions that cover rows < BM
     static_assert(C::SLACK == 0 || (C::BM * C::XROW) % (1024 * NW) == 0, "slack rows start at a DMA instruction boundary");
     constexpr int XROWS_PER_INST = 1024 / C::XROW, WROWS_PER_INST = 1024 / C::WROW;
@@ -399,8 +406,18 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
         dma16(dw_off[0], src, lds0 + C::W_RING + hs * C::WH_BYTES + (jj * NW + wave) * 1024);
     };
 
+    // quarter-stage weight ring: this wave's instruction for quarter j of k-tile kt, into quarter q of the ring
+    auto dma_wq = [&](int j, int kt, int q) __attribute__((always_inline)) {
+        dma16(dw_off[W_FOLD ? 0 : j], Wt + (size_t)kt * w_kt_stride + (W_FOLD ? (size_t)j * w_fold : (size_t)0),
+              lds0 + C::W_RING + q * C::WQ_BYTES + wave * 1024);
+    };
+
     if (C::EARLY_W) {
-        if constexpr (C::WHALF) {
+        if constexpr (C::WQUART) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (q / 4 < KT) dma_wq(q % 4, q / 4, q);
+        } else if constexpr (C::WHALF) {
             // (alternating roles: the loop's first iteration fetches the ring's last stage like every other one)
 #pragma unroll
             for (int q = 0; q < (C::PP ? 4 : C::NSWH); ++q)
@@ -516,7 +533,9 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             if constexpr (C::WKC) {
                 const int nb = r - 1;
                 const int row = wn * C::WTN + nb * MF + lrow;
-                const char* wrow = ws + C::W_RING + row * C::XROW;
+                // (quarters: sw is the ring's quarter that holds this wavefront's columns)
+                const char* wrow = C::WQUART ? smem + C::W_RING + sw * C::WQ_BYTES + (nb * MF + lrow) * C::XROW
+                                             : ws + C::W_RING + row * C::XROW;
                 if constexpr (C::FP8) {
                     const int c = kk * 2 + (g >> 1);
                     wq[wbuf(buf, nb)][nb][0] = *reinterpret_cast<const u32x2_t*>(wrow + ((c ^ pswz_x<C>(row)) << 4) + (g & 1) * 8);
@@ -775,14 +794,20 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             wait_vmcnt<0>();
             __syncthreads();
             if (ROLE == 0) {
-                reads(0, 0, 0);
+                reads(0, C::WQUART ? wn : 0, 0);
                 lgkm0();
             }
         }
         auto iteration = [&](int kt, auto steady_tag) __attribute__((always_inline)) {
             constexpr bool STEADY = decltype(steady_tag)::value;   // kt + 2 < KT: the refills have a target (else there are none)
             const int nxt = cur ^ 1;
-            const int nxtw = C::WHALF ? (curw + 2 >= C::NSWH ? curw + 2 - C::NSWH : curw + 2) : (curw + 1 == NSW ? 0 : curw + 1);
+            const int nxtw = C::WQUART ? (curw + 4 >= C::NSWQ ? curw + 4 - C::NSWQ : curw + 4)
+                             : C::WHALF ? (curw + 2 >= C::NSWH ? curw + 2 - C::NSWH : curw + 2) : (curw + 1 == NSW ? 0 : curw + 1);
+            // quarters: the one of tile kt (of tile kt+1) that this wavefront reads; quarter j of tile kt+2 goes where q2 + j says
+            const int rdw = C::WQUART ? (curw + wn >= C::NSWQ ? curw + wn - C::NSWQ : curw + wn) : curw;
+            const int rdn = C::WQUART ? (nxtw + wn >= C::NSWQ ? nxtw + wn - C::NSWQ : nxtw + wn) : nxtw;
+            const int q2 = nxtw + 4 >= C::NSWQ ? nxtw + 4 - C::NSWQ : nxtw + 4;
+            auto quarter = [&](int j) __attribute__((always_inline)) { return q2 + j >= C::NSWQ ? q2 + j - C::NSWQ : q2 + j; };
             const int prevw = C::WHALF ? (curw == 0 ? C::NSWH - 1 : curw - 1) : (curw == 0 ? NSW - 1 : curw - 1);
             // weight instructions into the stage that the barrier after slot 3 of tile kt-1 freed (whole stages: tile
             // kt+2, first half of its instructions; half-stages: half-k-tile 2 kt + 4), then the second half (half-stages:
@@ -790,18 +815,25 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             // stage that the prologue left empty
             auto wa = [&](int j) __attribute__((always_inline)) {
                 if constexpr (STEADY) {
-                    if constexpr (C::WHALF) dma_wh(j, 2 * kt + 4, prevw);
+                    if constexpr (C::WQUART) dma_wq(j, kt + 2, quarter(j));
+                    else if constexpr (C::WHALF) dma_wh(j, 2 * kt + 4, prevw);
                     else dma_w(j, kt + 2, prevw, false, 0);
                 }
             };
             auto wb = [&](int j) __attribute__((always_inline)) {
                 if constexpr (STEADY) {
-                    if constexpr (C::WHALF) dma_wh(j, 2 * kt + 5, curw);
+                    if constexpr (C::WQUART) dma_wq(WH + j, kt + 2, quarter(WH + j));
+                    else if constexpr (C::WHALF) dma_wh(j, 2 * kt + 5, curw);
                     else dma_w(WH + j, kt + 2, prevw, false, 0);
                 }
             };
+            // (quarters: slot 2 issues one weight instruction, and the last one, whose quarter slot 3 frees, follows the token rows)
+            constexpr int WB = C::WQUART ? 1 : WH, XWL = C::WQUART ? XIL + 1 : XIL, WAIT = C::WQUART ? 3 : WI;
             auto xr = [&](int j) __attribute__((always_inline)) {
-                if constexpr (STEADY) dma_x(j, kt + 2, cur, false);
+                if constexpr (STEADY) {
+                    if (C::WQUART && j == XIL) dma_wq(3, kt + 2, quarter(3));
+                    else dma_x(j, kt + 2, cur, false);
+                }
             };
             auto none = [](int) __attribute__((always_inline)) {};
             using std::integral_constant;
@@ -837,32 +869,32 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             } else if constexpr (ROLE == 0) {
                 mma(integral_constant<int, WH>{}, wa);
                 bar();
-                reads(cur, curw, 1);
+                reads(cur, rdw, 1);
 #pragma unroll
-                for (int j = 0; j < WH; ++j) wb(j);
+                for (int j = 0; j < WB; ++j) wb(j);
                 lgkm0();
                 bar();
                 mma(integral_constant<int, 0>{}, none);
-                if (STEADY) wait_vmcnt<WI>(); else wait_vmcnt<0>();
+                if (STEADY) wait_vmcnt<WAIT>(); else wait_vmcnt<0>();
                 bar();
-                if (STEADY || kt + 1 < KT) reads(nxt, nxtw, 0);
+                if (STEADY || kt + 1 < KT) reads(nxt, rdn, 0);
 #pragma unroll
-                for (int j = 0; j < XIL; ++j) xr(j);
+                for (int j = 0; j < XWL; ++j) xr(j);
                 lgkm0();
                 bar();
             } else {
-                reads(cur, curw, 0);
+                reads(cur, rdw, 0);
 #pragma unroll
                 for (int j = 0; j < WH; ++j) wa(j);
                 lgkm0();
                 bar();
-                mma(integral_constant<int, WH>{}, wb);
+                mma(integral_constant<int, WB>{}, wb);
                 bar();
-                reads(cur, curw, 1);
+                reads(cur, rdw, 1);
                 lgkm0();
-                if (STEADY) wait_vmcnt<WI>(); else wait_vmcnt<0>();
+                if (STEADY) wait_vmcnt<WAIT>(); else wait_vmcnt<0>();
                 bar();
-                mma(integral_constant<int, XIL>{}, xr);
+                mma(integral_constant<int, XWL>{}, xr);
                 bar();
             }
             cur = nxt;
@@ -1303,6 +1335,50 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
     } else {
         run_tile<C, Tails...>(a, a.map, L, tc, smem);
     }
+}
+
+// One tiling strategy without slack rows in the map, run as if the map had OVER::SLACK of them: an expert's last tile of so few rows
+// would move a whole weight panel for them (and takes three quarters of a full tile's time), so the tile before takes
+// them along (OVER: the full task function with room for them).  Each wavefront works out the TilePrefix of that tiling from
+// the task records in its lanes, so the XCDs share the tiles that are left evenly (with the absorbed tiles as workgroups without work
+// instead, an XCD that held many of them ended early and nothing was gained: 3000 tokens 1060 -> 1145 us).
+// Where no expert has such a tile, all tiles fit one round, the launch is longer than eight rounds, there are more than 64 experts
+// or the map orders tiles by kind, it runs the map's own tiles.  8 experts, 4096 -> 28672, us, without / with (tiles
+// left per XCD): 1000 tokens (112) 540 / 476, 2047 tokens (224) 912 / 807, a skewed routing of 1023 tokens 555 / 505; but 3000 tokens (336)
+// 1069 / 1114, 4096 tokens (448) 1516 / 1524: there the small tiles run beside the full ones, at the chip's power limit, at no cost.
+constexpr int kAbsorbMaxBlocks = 8 * 8 * kXcdCus;
+template <class OVER, class C, class... Tails>
+__global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
+    static_assert(OVER::BM == C::BM && OVER::BN == C::BN && OVER::NT == C::NT && OVER::SLACK > 0 && C::SLACK == 0, "task functions must be launch-compatible");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int32_t* __restrict__ map = a.map;
+    const MapLayout L = map_layout(a.E);
+    const int lane = __lane_id();
+    int4 record = reinterpret_cast<const int4*>(map + L.off_records)[lane];
+    int total = map[MOE_HDR_TOTAL_TILES];
+    if (!map_matches_at_once<C::BM, C::BN, 0>(a, map)) return;
+    moe_tiling g = {C::BM, C::BN, 0, 0, 0, 0};
+    const bool small_last = record.z > C::BM && (record.z - 1) % C::BM < OVER::SLACK;
+    if (L.E64 == 64 && total > 8 * kXcdCus && map[MOE_HDR_SIGMA_ORDER] != MOE_ORDER_INTERLEAVE && __ballot(small_last)) {
+        const moe_tiling over = {C::BM, C::BN, 0, 0, 0, OVER::SLACK};
+        int upto = record.z > 0 ? expert_m_tiles(record.z, over) * (a.N / C::BN) : 0;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(upto, d, 64);
+            upto += lane >= d ? o : 0;
+        }
+        const int left = __builtin_amdgcn_readlane(upto, 63);
+        if (left <= kAbsorbMaxBlocks) {
+            g = over;
+            total = left;
+            record.x = record.z > 0 ? upto : 0x7fffffff;
+        }
+    }
+    int B;
+    if (!slot_to_block(map, total, blockIdx.x & 7, blockIdx.x >> 3, B)) return;
+    const TileCoord tc = decode_block(map, L, g, B, record);
+    if (tc.rows > C::BM) pipe_tile<OVER>(a, map, L, tc, smem);
+    else run_tile<C, Tails...>(a, map, L, tc, smem);
 }
 
 // A task function and the narrower ones that share its launch, narrowest first.

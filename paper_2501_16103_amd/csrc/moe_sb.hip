@@ -62,6 +62,17 @@ int launch_pipe(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+// One workgroup per tile, with the few rows of an expert's last tile run by the one before it (not in MOE_LAUNCH_PER_TILE).
+template <class OVER, class C, class... Tails>
+int launch_absorb(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    if (mode == MOE_LAUNCH_PER_TILE) return launch_pipe<C, Tails...>(a, grid, mode, s);
+    static unsigned long long attr_done = 0;
+    constexpr int lds = OVER::LDS_BYTES > C::LDS_BYTES ? OVER::LDS_BYTES : C::LDS_BYTES;
+    if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_absorb_kernel<OVER, C, Tails...>), lds, &attr_done) != MOE_OK) return MOE_ERR_HIP;
+    moe_gemm_absorb_kernel<OVER, C, Tails...><<<dim3((unsigned)grid), dim3(C::NT), lds, s>>>(a);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 // Workgroups an XCD needs for at most `most` tiles when the rest behind its last full round runs as half tiles (see
 // moe_gemm_halves_kernel): the most that any count up to `most` takes.  A workgroup too many is not free: it waits for the LDS
 // of a whole CU to find out that it has no tile (16 more per XCD on every launch cost 0.3 to 1 us: 16 experts, 512 -> 4096,
@@ -316,6 +327,8 @@ using H8_256x128 = TileFns<P8h_256x128, P8h_64x128, P8h_128x128>;
 
 // The pre-packed weight layout [E][N][K] (K contiguous): the shapes the benchmark uses
 using Pk_256x256 = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 0, true, 16>;
+// (room for 32 more rows: two token stages of 36 KB and eleven quarters of a weight stage)
+using Pk_256x256o = PipeCfg<256, 256, 64, 2, 4, 2, false, 3, 32, true, 16, 0, 11>;
 using Pk_256x256s = PipeCfg<256, 256, 64, 2, 4, 2, false, 2, 64, true>;
 using Pks_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, true>;
 using Pks_128x256 = Alone<PipeCfg<128, 256, 64, 1, 8, 3, false, 3, 0, true>>;
@@ -329,7 +342,7 @@ using P8k_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true, 2, 0, true>;
 using P8k_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true, 4, 0, true>;
 
 const GemmVariant kVariants[] = {
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 0, MOE_W_LAYOUT_NK},
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_absorb<Pk_256x256o, Pk_256x256, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pk_256x256s, Pks_64x256, Pks_128x256, Pkt_128x256>, 0, 64, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_pipe<Pk_128x256, Pks_64x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK},
