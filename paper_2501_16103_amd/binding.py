@@ -436,10 +436,19 @@ class MoeLayerPlan:
         filled last round costs most of the product; which routing leaves which rest is only known on the device, where that call
         decides.  8 experts, 14336 -> 4096, us, the tiling or split-k otherwise taken / this: uniform routing of 400 rows 149 / 147,
         666 157 / 156, 1400 188 / 190, 2000 332 / 228, 8192 719-885 / 715-780; skewed 400 217 / 152, 666 237 / 166, 1400 301 / 289,
-        2000 309 / 276, 4094 498 / 437, 8192 835 / 771.  Between 96 and 120 rows per expert a skewed routing fills more than half a
-        round of 256-row tiles and the narrow tiles stay (800 rows 251 / 273); with fewer than 12 there is nothing to share out."""
+        2000 309 / 276, 4094 498 / 437, 8192 835 / 771; 2 rows 59 / 41, 4 rows 76 / 75, 8 rows 109 / 98.  Between 96 and 120 rows per
+        expert a skewed routing fills more than half a round of 256-row tiles and the narrow tiles stay (800 rows 251 / 273); from
+        2 to 12 rows every expert has one tile and both take the same time."""
         rows = R / E
-        return inter % 64 == 0 and inter >= 7168 and hidden % 256 == 0 and (12 <= rows <= 96 or rows >= 120)
+        return R > 0 and inter % 64 == 0 and inter >= 7168 and hidden % 256 == 0 and (rows <= 2 or 12 <= rows <= 96 or rows >= 120)
+
+    @staticmethod
+    def _few_tiles(g: Tiling, R: int, E: int, hidden: int) -> Tiling:
+        """A token's down product on at most three quarters as many 128-wide 16-row tiles as there are CUs runs on 128 x 128 tiles
+        instead, which the launch halves: twice the workgroups, of eight wavefronts (64 experts, 1408 -> 2048, us: 6 rows 11.3 / 9.8,
+        12 rows 14.6 / 13.9; 16 experts, 1024 -> 4096, 2 rows 10.0 / 9.2; 8 experts, 2048 -> 8192, 1 row 15.2 / 13.6)."""
+        narrow = (g.tile_m, g.tile_n) == (16, 128) and min(R, E) * (hidden // 128) <= 192
+        return Tiling(128, 128) if narrow else g
 
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):
         self.T, self.k, self.E, self.hidden, self.inter = T, k, E, hidden, inter
@@ -453,7 +462,7 @@ class MoeLayerPlan:
         elif self.k_parts > 1:
             self.g2, nbytes = Tiling(256, 256), moe_splitk_workspace_bytes(R, 1, hidden, self.k_parts)
         else:
-            self.g2, nbytes = moe_default_tiling(MOE_DTYPE_BF16, R, 1, E, inter, hidden), 0
+            self.g2, nbytes = self._few_tiles(moe_default_tiling(MOE_DTYPE_BF16, R, 1, E, inter, hidden), R, E, hidden), 0
         self.workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=device) if nbytes else None
         self.map1 = alloc_task_map(T, k, E, self.g1.tile_m, self.g1.tile_n, 2 * inter, device)
         self.map2 = alloc_task_map(R, 1, E, self.g2.tile_m, self.g2.tile_n, hidden, device)

@@ -375,12 +375,13 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     const size_t w_kt_stride = C::WKC ? (size_t)BK * ES : (size_t)BK * w_row_bytes;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(MOE_LDS(char)*)smem;
 
-    // Weight panels that only this tile reads are fetched non-temporally -- when the grid is large enough to
-    // stream from all CUs (measured: +10 % HBM throughput on the weight-streaming points, -9 % on a 132-tile grid).  What
-    // counts is workgroups: a tile that runs as two halves or in parts along K has as many streams.  (8 experts, 14336 -> 4096, 128 tiles
-    // of 256 columns, without the hint / with it: 666 rows as halves 168 / 158 us, in two parts 166 / 156, 200 rows in two parts
-    // 154 / 143.)
-    const bool nt_ok = map[MOE_HDR_TOTAL_TILES] * tc.sharers >= 256;
+    // Weight panels that only this tile reads are fetched non-temporally -- when the launch streams from nearly all CUs (measured:
+    // +10 % HBM throughput on the weight-streaming points, -9 % on 132 tiles of 128 columns).  What counts is workgroups: a tile that
+    // runs as two halves or in parts along K has as many streams.  Without the hint / with it, us: 8 experts, 14336 -> 4096, 128
+    // tiles, 666 rows as halves 168 / 158, in two parts 166 / 156; 256-wide 16-row tiles, 224 of 64 k-tiles 85.5 / 77.5, 231 of 32
+    // 43.9 / 38.3, but 168 of 22 19.3 / 20.9 and 128 of 32 23.0 / 26.7.
+    const int streams = map[MOE_HDR_TOTAL_TILES] * tc.sharers;
+    const bool nt_ok = streams >= 256 || (C::BN == 256 && streams >= 192);
     bool w_once = nt_ok && tc.m_tiles == 1, w_once_next = false;
     // j-th token-row / weight-row DMA instruction of this wave for k-tile kt, into ring stage `stage`
     auto dma_x = [&](int j, int kt, int stage, bool next) __attribute__((always_inline)) {
@@ -1236,12 +1237,7 @@ struct TwoKinds {
         if (!__ballot(is_light) || !__ballot(record.z > crowded_rows)) return;
         const int prev = __shfl_up(record.x, 1, 64);
         before = lane == 0 ? 0 : prev;
-        upto = is_light ? record.x - before : 0;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int o = __shfl_up(upto, d, 64);
-            upto += lane >= d ? o : 0;
-        }
+        upto = wave_incl_scan(is_light ? record.x - before : 0);
         light = __builtin_amdgcn_readlane(upto, 63);
         heavy = total - light;
         on = 8 * light >= total && 8 * heavy >= total;
@@ -1361,12 +1357,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
     const bool small_last = record.z > C::BM && (record.z - 1) % C::BM < OVER::SLACK;
     if (L.E64 == 64 && total > 8 * kXcdCus && map[MOE_HDR_SIGMA_ORDER] != MOE_ORDER_INTERLEAVE && __ballot(small_last)) {
         const moe_tiling over = {C::BM, C::BN, 0, 0, 0, OVER::SLACK};
-        int upto = record.z > 0 ? expert_m_tiles(record.z, over) * (a.N / C::BN) : 0;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int o = __shfl_up(upto, d, 64);
-            upto += lane >= d ? o : 0;
-        }
+        const int upto = wave_incl_scan(record.z > 0 ? expert_m_tiles(record.z, over) * (a.N / C::BN) : 0);
         const int left = __builtin_amdgcn_readlane(upto, 63);
         if (left <= kAbsorbMaxBlocks) {
             g = over;

@@ -40,6 +40,19 @@ __host__ __device__ inline size_t round_up64(size_t v) { return (v + 63) / 64 * 
 // per-chunk histogram row: E64 expert columns + 64 spare (column E64 counts bad ids)
 __host__ __device__ inline int hist_stride(int E64) { return E64 + 64; }
 
+// Inclusive scan over the lanes of a wavefront, all of them active.  In the lanes' own registers (DPP: shifts by 1, 2, 4 and 8
+// inside each row of 16, then the last lane of a row to the rows behind it): the same with __shfl_up is six round trips through
+// the LDS crossbar, one after the other, and a small build has two to four such scans in its chain.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // ---------------------------------------------------------------- decode
 
 // Alg. 2 on one wavefront: lane t tests p = (B >= TilePrefix[t]); the ballot is the
@@ -128,16 +141,6 @@ __device__ __forceinline__ void wave_match(int key, bool valid, int nbits, int& 
     const unsigned long long below = (1ull << __lane_id()) - 1ull;
     rank = __popcll(peers & below);
     size = __popcll(peers);
-}
-
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    const int lane = __lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(v, d, 64);
-        if (lane >= d) v += o;
-    }
-    return v;
 }
 
 // Inclusive scan across the threads of the block (at most kMapThreads; s_tmp: >= kWaves ints of LDS).

@@ -87,19 +87,23 @@ def test_tail_parts(tile_m, counts, nt, K):
     assert B == total
 
 
-def test_layer_with_a_long_down_product():
-    """A layer whose down product takes the tail split: its output is the weighted sum of the products of its own activations."""
+@pytest.mark.parametrize("T,k,E,hidden,inter,tail", [(150, 2, 4, 256, 7168, True), (1, 2, 8, 512, 7168, True), (3, 2, 8, 256, 14336, True),
+                                                     (1, 6, 64, 256, 384, False), (2, 2, 16, 512, 256, False)])
+def test_layer_whose_down_product_leaves_the_default_tiling(T, k, E, hidden, inter, tail):
+    """Layers whose down product takes the tail split (long K) or 128 x 128 tiles (a token or two): the down product is that of the
+    layer's own activations, and its output their weighted sum."""
     dev = torch.device("cuda:0")
-    T, k, E, hidden, inter = 150, 2, 4, 256, 7168
     plan = mb.MoeLayerPlan(T, k, E, hidden, inter, dev)
-    assert plan.tail_split and plan.k_parts == 1
+    assert plan.tail_split == tail and plan.k_parts == 1
+    assert tail or (plan.g2.tile_m, plan.g2.tile_n) == (128, 128)
     g = torch.Generator(device=dev).manual_seed(3)
     X = torch.randn((T, hidden), generator=g, device=dev).to(torch.bfloat16)
     W1 = (torch.randn((E, hidden, 2 * inter), generator=g, device=dev) * hidden ** -0.5).to(torch.bfloat16)
     W2 = (torch.randn((E, inter, hidden), generator=g, device=dev) * inter ** -0.5).to(torch.bfloat16)
     ids = torch.stack([torch.randperm(E, generator=g, device=dev)[:k] for _ in range(T)]).to(torch.int32)
     wts = torch.rand((T, k), generator=g, device=dev, dtype=torch.float32)
-    plan.workspace.fill_(float("nan"))
+    if tail:
+        plan.workspace.fill_(float("nan"))
     out = plan.forward(X, W1, W2, ids, wts)
     torch.cuda.synchronize()
     flat, act = ids.reshape(-1).long(), plan.act
