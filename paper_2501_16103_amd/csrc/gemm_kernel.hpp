@@ -138,7 +138,8 @@ struct PipeCfg {
     // tests on seven kinds of input, K = 128 ... 8192, mixed magnitudes and cancellation among them), and on the fp8 layer
     // (64 experts, top-6, 2048 -> 2816) the outputs are the same bits.  There the product went from 283 to 176 us at
     // 4096 tokens and from 473 to 303 us at 8192; with the fused activation from 263 to 177 us at 4096.
-    static constexpr bool F8W = FP8_ && !WKC_ && BM_ >= 64;
+    // (streamed tiles, one wavefront row of 16-row blocks, are bound by memory and keep 16x16x32)
+    static constexpr bool F8W = FP8_ && !WKC_ && BM_ >= 64 && !(MFO_ == 16 && WM_ == 1);
     static constexpr int KS = F8W ? (MF == 32 ? 64 : 128) : (MF == 32 ? 16 : 32);   // k elements per MFMA
     static constexpr int KSTEPS = BK / KS;
     static constexpr int NBW = WTN / MF, MBW = WTM / MF;
@@ -148,7 +149,7 @@ struct PipeCfg {
     // single-buffered, each reloaded for the next k-step as soon as the MFMAs of its row block are issued (XROLL).
     // Tiles of several 16-row blocks per wavefront: every wavefront runs the loop copy compiled for its own
     // number of live blocks (a run-time test around every MFMA defeats the software pipelining there).
-    static constexpr bool PERWAVE = MF == 16 && MBW_BODY >= 4;
+    static constexpr bool PERWAVE = MF == 16 && MBW_BODY >= 4 && WM_ > 1;
     // ... and with at least four weight blocks per wavefront the fragments are reloaded in place (see reads_after)
     static constexpr bool XROLL = PERWAVE && WTN / MF >= 4;
     // ... and they run their k loop in two alternating roles (see run_pp in pipe_tile).  [E][N][K] weights, 4096 -> 28672,
@@ -324,7 +325,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     static_assert((NS - 1) * XI + (NSW - 1) * WI < 64, "vmcnt range");
     // 16-row tiles get their row ids through the scalar path: their wait (lgkmcnt) leaves the weight stream in flight, and
     // the ids stay in a register for the epilogue.
-    constexpr bool ROWS16 = C::BM == 16 && MF == 16 && MBW == 1 && XI == 1 && NS == NSW && C::SLACK == 0 && !C::SPLITK;
+    // (Streamed tiles hold as many rows as the wavefronts' one DMA instruction each covers: 32 or 64.)
+    constexpr bool ROWS16 = MF == 16 && C::WM == 1 && C::BM <= 64 && XI == 1 && NS == NSW && C::SLACK == 0 && !C::SPLITK && (C::BM == 16 || STREAM);
     static_assert(!STREAM || (ROWS16 && KSTEPS % 2 == 0), "the streaming loop is written for 16-row tiles");
     // per-lane source offsets inside a tile; everything that depends on the tile (expert, n-tile) is in the base pointer
     // When a wavefront's weight instructions lie a multiple of the swizzle's period apart they share swizzle and lane
@@ -438,19 +440,24 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
 
     // ---- per-tile row information
     const int32_t* rows_of_tile = map + L.off_rows + tc.row_base;
-    // 16-row tiles: lane j < 16 holds the flat row id of tile row j (row 0's for j past the tile's rows).  Streaming: the
+    // 16-row (streamed: up to 64-row) tiles: lane j holds the flat row id of tile row j (row 0's for j past the tile's rows).  Streaming: the
     // token's scale comes from LDS, so that no vector-memory wait is ever generated
     int rows_v = 0, rows_v_next = 0;
     auto stream_rows = [&](const TileCoord& t, int& rv, uint32_t& dxo) {
-        i32x8_t lo, hi;
-        scalar_load16(map + L.off_rows + t.row_base, lo, hi);
-        int v = lo[0];
+        int v = 0;
 #pragma unroll
-        for (int j = 1; j < 16; ++j) v = (lane == j && j < t.rows) ? (j < 8 ? lo[j] : hi[j - 8]) : v;
+        for (int q = 0; q < MBW; ++q) {
+            if (q > 0 && 16 * q >= t.rows) continue;
+            i32x8_t lo, hi;
+            scalar_load16(map + L.off_rows + t.row_base + 16 * q, lo, hi);
+            if (q == 0) v = lo[0];
+#pragma unroll
+            for (int j = q == 0 ? 1 : 0; j < 16; ++j) v = (lane == 16 * q + j && 16 * q + j < t.rows) ? (j < 8 ? lo[j] : hi[j - 8]) : v;
+        }
         rv = v;
-        const int tok = v / a.k;                                       // lanes 0..15
+        const int tok = v / a.k;                                       // one per tile row (row 0's past the tile's rows)
         const int row = wave * XROWS_PER_INST + lane / C::CPR, pos = lane % C::CPR;
-        const int tok_of_row = __shfl(tok, row);
+        const int tok_of_row = __shfl(tok, row & 63);
         dxo = (uint32_t)tok_of_row * (uint32_t)(a.K * ES) + ((pos ^ pswz_x<C>(row)) << 4);
     };
     if constexpr (ROWS16) {
@@ -1004,7 +1011,26 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             // every wavefront moves its share of the slack rows; only those whose slack block holds a real row compute it
             if (mb_live == MBW) run_nt(integral_constant<int, MBW>{}, integral_constant<int, XI>{}, std::false_type{});
             else run_nt(integral_constant<int, C::MBW_BODY>{}, integral_constant<int, XI>{}, std::false_type{});
-        } else if (STREAM || mb_live == C::MBW_BODY) {
+        } else if constexpr (STREAM) {
+            // 16 rows at a time: a copy of the loop for one, two or all row blocks.  (The tile before fetched the first fragments
+            // of row block 0 only.)
+            auto more_blocks = [&](int nmb) __attribute__((always_inline)) {
+                if (!first) {
+#pragma unroll
+                    for (int mb = 1; mb < MBW; ++mb)
+                        if (mb < nmb) read_one(WREADS + mb, cur, curw, 0, 0, false);
+                }
+            };
+            if (MBW == 1 || tc.rows <= 16) {
+                run_nt(integral_constant<int, 1>{}, integral_constant<int, XI_BODY>{}, std::false_type{});
+            } else if (MBW > 2 && tc.rows <= 32) {
+                more_blocks(2);
+                run_nt(integral_constant<int, MBW < 2 ? MBW : 2>{}, integral_constant<int, XI_BODY>{}, std::false_type{});
+            } else {
+                more_blocks(MBW);
+                run_nt(integral_constant<int, MBW>{}, integral_constant<int, XI_BODY>{}, std::false_type{});
+            }
+        } else if (mb_live == C::MBW_BODY) {
             run_nt(integral_constant<int, C::MBW_BODY>{}, integral_constant<int, XI_BODY>{}, std::false_type{});
         } else {
             run_nt(integral_constant<int, C::MBW_BODY>{}, integral_constant<int, XI_BODY>{}, std::true_type{});
@@ -1496,6 +1522,11 @@ __global__ __launch_bounds__(CBIG::NT) void moe_gemm_pipe2_kernel(GemmArgs a) {
 // workgroup does not stop at tile boundaries.  Requires E <= 256, K / BK >= ring depth, one tiling strategy;
 // fp8 scales are staged in LDS behind the rings (T + E floats).  PAIR = 2: C is twice as wide as the map's tiles and runs
 // two neighbouring n-tiles as one (the map has an even number of them).
+// C::BM > 16: up to C::BM rows of an expert, whole 16-row tiles of the map, run as one tile and read the weight panel once -- the token
+// stages have room for them anyway, because every wavefront issues a DMA instruction.  The TilePrefix of those tiles is worked out
+// from the task records in the lanes.  64 experts, 2048 -> 2816,
+// fp8, us, 16-row tiles one by one / this: 128 tokens 62 / 62, 160 75 / 64, 256 109 / 68, skewed routing 107 tokens 71 / 64, 128 73 / 67,
+// 256 97 / 79; 16 experts, 4096 -> 4096, 128 tokens 61 / 49, 190 84 / 50.
 template <class C, int PAIR = 1>
 __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1507,13 +1538,26 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
 #pragma unroll
     for (int gi = 0; gi < TileStream::MAX_GROUPS; ++gi)
         ts.rec[gi] = 64 * gi < L.E64 ? recs[64 * gi + lane] : make_int4(0x7fffffff, -1, 0, 0);
-    const int total = map[MOE_HDR_TOTAL_TILES] / PAIR;
+    int total = map[MOE_HDR_TOTAL_TILES] / PAIR;
     const bool hdr_ok = map[MOE_HDR_MAGIC] == MOE_MAP_MAGIC && map[MOE_HDR_T] == a.T && map[MOE_HDR_K_TOP] == a.k &&
-                        map[MOE_HDR_E] == a.E && map[MOE_HDR_N] == a.N && map[MOE_HDR_TILE_M] == C::BM &&
+                        map[MOE_HDR_E] == a.E && map[MOE_HDR_N] == a.N && map[MOE_HDR_TILE_M] == 16 &&
                         map[MOE_HDR_TILE_N] * PAIR == C::BN && map[MOE_HDR_STATUS] == 0 && map[MOE_HDR_TILE_M_SMALL] == 0 &&
                         map[MOE_HDR_SMALL_MAX_ROWS] == 0 && a.tile_m_small == 0 && a.small_max_rows == 0 &&
                         map[MOE_HDR_TILE_M_SLACK] == 0 && a.tile_m_slack == 0;
     if (!hdr_ok) return;
+    ts.tiling = moe_tiling{C::BM, C::BN, 0, 0, 0, 0};
+    ts.pair = PAIR;
+    if constexpr (C::BM > 16) {
+        ts.pair = 1;
+        total = 0;
+#pragma unroll
+        for (int gi = 0; gi < TileStream::MAX_GROUPS; ++gi) {
+            if (64 * gi >= L.E64) continue;
+            const int cnt = ts.rec[gi].z, upto = total + wave_incl_scan(cnt > 0 ? (cnt + C::BM - 1) / C::BM * (a.N / C::BN) : 0);
+            total = __builtin_amdgcn_readlane(upto, 63);
+            ts.rec[gi].x = cnt > 0 ? upto : 0x7fffffff;
+        }
+    }
     // each XCD owns one contiguous run of block indices (see locate_tile); its resident workgroups split it evenly
     const int per_xcd = (total + 7) >> 3;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
@@ -1539,8 +1583,6 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     }
     ts.xs_lds = xs_lds;
     ts.ws_lds = ws_lds;
-    ts.tiling = moe_tiling{C::BM, C::BN, 0, 0, 0, 0};
-    ts.pair = PAIR;
     ts.next_B = t0 + 1;
     ts.end_B = t1;
     const TileCoord tc = decode_from_registers(ts, t0);

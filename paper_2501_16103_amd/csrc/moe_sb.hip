@@ -199,19 +199,29 @@ int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t
 // streams in the two-workgroup form, from two tiles per workgroup on (256 experts, K = 128, 2233 tiles: 30 us, 34 per tile).
 // (Between one and two 256-wide tiles per CU the deep form is kept: a uniform routing of 5 tokens, 297 tiles, takes 62 us with
 // it and 55 with two workgroups per CU, but a skewed one of the same size, 176 tiles, 29 and 38.)
-template <class C, class C2, class CW = C>
+// CS, CW: with room for the rows of several of the map's tiles (see moe_gemm_stream_kernel), from 8 to 32 rows per expert on average
+// and 16 k-tiles on.  Below, nearly every expert has one tile, and the larger task function costs 1 to 3 % (64 experts, 2048 ->
+// 2816, fp8, 32 tokens); beyond, few experts are left with too few workgroups (8 experts, K = 256, 75 rows each: 7.4 -> 11.5 us), and
+// such maps are not the default; with a short K the rows of a full tile take longer than its panel (64 experts, 1024 -> 2048, fp8, a
+// skewed routing of 200 tokens 28.6 -> 35.0).
+template <class C, class C2, class CW1, class CS, class CW>
 int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
     const double expected = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
     bool launched = false;
+    const int64_t R = (int64_t)a.T * a.k;
+    const bool several = R >= 8 * (int64_t)a.E && R <= 32 * (int64_t)a.E && a.K / C::BK >= 16;
+    static_assert(CS::BN == C::BN && CS::LDS_BYTES == C::LDS_BYTES && CS::NT == C::NT, "the streamed tile is the same but for its rows");
     if constexpr (CW::BN == 2 * C::BN) {
         if (a.N % CW::BN == 0) {
-            const int64_t pairs = (grid - kSpareSlots) / 2;
-            const int rc = launch_stream_kernel<CW, 2>(a, (pairs + 7) / 8 * 8, mode, s, expected > kCus, &launched);
+            const int64_t pairs = ((grid - kSpareSlots) / 2 + 7) / 8 * 8;
+            const int rc = several ? launch_stream_kernel<CW, 2>(a, pairs, mode, s, expected > kCus, &launched)
+                                    : launch_stream_kernel<CW1, 2>(a, pairs, mode, s, expected > kCus, &launched);
             if (rc != MOE_OK || launched) return rc;
         }
     }
     const bool many = C::BN == 256 ? grid >= 2 * kCus : expected > 2 * kCus;
-    const int rc = launch_stream_kernel<C, 1>(a, grid, mode, s, many, &launched);
+    const int rc = several ? launch_stream_kernel<CS, 1>(a, grid, mode, s, many, &launched)
+                            : launch_stream_kernel<C, 1>(a, grid, mode, s, many, &launched);
     if (rc != MOE_OK || launched) return rc;
     if (a.K / C::BK < C::NS) {
         const int rc2 = launch_stream_kernel<C2, 1>(a, grid, mode, s, grid >= 4 * kCus, &launched);
@@ -289,10 +299,15 @@ using Pt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2>;
 // launch_rows16 says which of the two runs one workgroup per tile.
 using Pb_16x256 = PipeCfg<16, 256, 64, 1, 8, 3>;
 using Pb_16x128 = PipeCfg<16, 128, 64, 1, 4, 6>;
+// (streamed: as many rows as the token stages hold)
+using Pq_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, false, 16>;
+using Pq_32x128 = PipeCfg<32, 128, 64, 1, 4, 6, false, 6, 0, false, 16>;
 using Pd_16x256 = PipeCfg<16, 256, 64, 1, 2, 2>;
 using Pd_16x128 = PipeCfg<16, 128, 64, 1, 2, 4>;
 using P8_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true>;
 using P8_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true>;
+using P8q_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true, 3, 0, false, 16>;
+using P8q_32x128 = PipeCfg<32, 128, 128, 1, 4, 6, true, 6, 0, false, 16>;
 using P8d_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true>;
 using P8d_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true>;
 using P8_16x64 = PipeCfg<16, 64, 128, 1, 2, 4, true>;
@@ -359,10 +374,10 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 64, 128, 64, &launch_pipe<Pb_64x128>},
     {MOE_DTYPE_BF16, 32, 256, 64, &launch_pipe<Pb_32x256>},
     {MOE_DTYPE_BF16, 32, 128, 64, &launch_pipe<Pb_32x128>},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256, Pd_16x256>},
-    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pd_16x128, Pb_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256, P8d_16x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8d_16x128, P8_16x256>},
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256, Pd_16x256, Pb_16x256, Pq_64x256, Pq_64x256>},
+    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pd_16x128, Pb_16x256, Pq_32x128, Pq_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256, P8d_16x256, P8_16x256, P8q_64x256, P8q_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8d_16x128, P8_16x256, P8q_32x128, P8q_64x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream_narrow<P8_16x64>},
     {MOE_DTYPE_FP8_E4M3, 32, 128, 128, &launch_pipe<P8_32x128>},
     {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_halves<F8_256x256, H8_256x128>},
