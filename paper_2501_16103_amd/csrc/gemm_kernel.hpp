@@ -1245,8 +1245,10 @@ __device__ __forceinline__ int slots_of_xcd(const int32_t* __restrict__ map, int
 // contiguous run of each per XCD, and every other XCD starts with its light run, so that at any time some XCDs stream while the
 // others compute (no interleaving inside an XCD: the streams would displace the panels that the full tiles share in its L2).
 // Like slot_to_block this is a bijection between a launch's slots and the map's blocks.
-// Measured (64 experts, 3584 -> 2560, eight crowded experts and 56 with one row): 4096 tokens 632-665 -> 599-628 us, 2000 tokens
-// 398 -> 355, 1024 tokens 269 -> 246.  With both kinds in one order on all XCDs 631-646, 381 and 273.
+// Measured (64 experts, 3584 -> 2560, eight crowded experts and 56 with one row; all of six routings, twice, clocks settled, in
+// turn with plain order): 4096 tokens 602-625 -> 588-598 us, 2000 tokens 360-372 -> 347-352, 1024 tokens 251-265 -> 243-247.  Both
+// kinds in one order on all XCDs gave less than every other XCD starting with its light run (one run of each, 2000 tokens: plain
+// 377-399, one order 378-400, this 357-374; the first routing left out, clocks still settling).
 constexpr int kLightRows = 64;
 struct TwoKinds {
     bool on = false;
