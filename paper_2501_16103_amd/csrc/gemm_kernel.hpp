@@ -1366,11 +1366,27 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
 // them along (OVER: the full task function with room for them).  Each wavefront works out the TilePrefix of that tiling from
 // the task records in its lanes, so the XCDs share the tiles that are left evenly (with the absorbed tiles as workgroups without work
 // instead, an XCD that held many of them ended early and nothing was gained: 3000 tokens 1060 -> 1145 us).
-// Where no expert has such a tile, all tiles fit one round, the launch is longer than eight rounds, there are more than 64 experts
-// or the map orders tiles by kind, it runs the map's own tiles.  8 experts, 4096 -> 28672, us, without / with (tiles
-// left per XCD): 1000 tokens (112) 540 / 476, 2047 tokens (224) 912 / 807, a skewed routing of 1023 tokens 555 / 505; but 3000 tokens (336)
-// 1069 / 1114, 4096 tokens (448) 1516 / 1524: there the small tiles run beside the full ones, at the chip's power limit, at no cost.
+// Where that leaves the number of rounds as it was, it only makes tiles longer (see absorb_pays); there, where all tiles fit one round,
+// where the launch is longer than eight rounds, for more than 64 experts and for maps that order tiles by kind, it runs the map's own
+// tiles.  8 experts, 4096 -> 28672, us, without / with (tiles left per XCD): 1000 tokens (112) 540 / 476, 2047 tokens (224) 912 / 807, a
+// skewed routing of 1023 tokens 555 / 505; but 3000 tokens (336) 1069 / 1114, 4096 tokens (448) 1516 / 1524: there the small tiles run
+// beside the full ones, at the chip's power limit, at no cost.
 constexpr int kAbsorbMaxBlocks = 8 * 8 * kXcdCus;
+// total: tiles of the map; left: those after absorbing; few: the map's tiles of at most 128 rows, which take about half as long as a
+// full one.  Absorbed or not, an expert's rows are the same work; what is saved is a round, and only where the short tiles' places
+// are not what fills the rounds as they are: with the rest of a round left over, the map's mixture of long and short tiles ends
+// half a round beyond its work, equal tiles at the end of a whole round.  Without / with, us (tiles -> left, few): 4096 -> 4096, 514
+// rows each of 8 experts (336 -> 256, 80) 165 / 110; 4096 -> 8192, 257 rows (352 -> 256, 96) 188 / 155, 270 rows (512 -> 288, 256)
+// 197 / 217, 545 rows (768 -> 672, 256) 272 / 313; 4096 -> 28672, 4 experts, a skewed routing of 257 rows each (672 -> 560, 224)
+// 266 / 319.  Of 171 such launches (4 to 64 experts, K 1024 to 14336, even and skewed routings) this rule makes 3 slower, by at
+// most 4 %, and 58 faster, by up to a third; taken always, 68 were slower, by up to a fifth.
+__host__ __device__ constexpr bool absorb_pays(int total, int left, int few) {
+    constexpr int cus = 8 * kXcdCus;
+    const int rounds = (left + cus - 1) / cus;
+    return rounds < (total + cus - 1) / cus && 2 * cus * rounds < 2 * total - few + cus;
+}
+static_assert(absorb_pays(336, 256, 80) && absorb_pays(352, 256, 96) && absorb_pays(2352, 1792, 560), "a round less");
+static_assert(!absorb_pays(512, 288, 256) && !absorb_pays(768, 672, 256) && !absorb_pays(672, 560, 224) && !absorb_pays(1792, 1568, 896), "no round less");
 template <class OVER, class C, class... Tails>
 __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
     static_assert(OVER::BM == C::BM && OVER::BN == C::BN && OVER::NT == C::NT && OVER::SLACK > 0 && C::SLACK == 0, "task functions must be launch-compatible");
@@ -1387,7 +1403,9 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
         const moe_tiling over = {C::BM, C::BN, 0, 0, 0, OVER::SLACK};
         const int upto = wave_incl_scan(record.z > 0 ? expert_m_tiles(record.z, over) * (a.N / C::BN) : 0);
         const int left = __builtin_amdgcn_readlane(upto, 63);
-        if (left <= kAbsorbMaxBlocks) {
+        const bool few_last = record.z > 0 && (record.z - 1) % C::BM < 128;
+        const int few = __popcll(__ballot(few_last)) * (a.N / C::BN);
+        if (left <= kAbsorbMaxBlocks && absorb_pays(total, left, few)) {
             g = over;
             total = left;
             record.x = record.z > 0 ? upto : 0x7fffffff;
