@@ -68,14 +68,14 @@ __global__ __launch_bounds__(256) void moe_tail_reduce_kernel(GemmArgs a) {
     const int32_t* __restrict__ map = a.map;
     const MapLayout L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
-    const int total = map[MOE_HDR_TOTAL_TILES];
-    if (!map_matches_at_once<BM, BN, SLACK>(a, map)) return;
+    int total, order;
+    if (!map_matches_at_once<BM, BN, SLACK>(a, map, total, order)) return;
     const int xcd = blockIdx.x & 7, j = (int)(blockIdx.x >> 3) / kTailReduceSlices, slice = (int)(blockIdx.x >> 3) % kTailReduceSlices;
-    const int n = slots_of_xcd(map, total, xcd), rest = n % kXcdCus, kt = a.K / 64;
+    const int n = slots_of_xcd(map, order, total, xcd), rest = n % kXcdCus, kt = a.K / 64;
     const int parts = tail_parts(rest, kt);
     if (j >= rest || parts == 1) return;
     int B;
-    if (!slot_to_block(map, total, xcd, n - rest + j, B)) return;
+    if (!slot_to_block(map, order, total, xcd, n - rest + j, B)) return;
     const moe_tiling g = {BM, BN, 0, 0, 0, SLACK};
     const TileCoord tc = decode_block(map, L, g, B, first_record);
     const float* blocks = a.partial + (size_t)(xcd * kTailBlocksPerXcd + j * parts) * (BMC * BN);
@@ -130,10 +130,10 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_batched_kernel(GemmArgs a) {
     const int32_t* __restrict__ map = a.map;
     MapLayout L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
-    const int total = map[MOE_HDR_TOTAL_TILES];
+    const int total = map[MOE_HDR_TOTAL_TILES], order = map[MOE_HDR_SIGMA_ORDER];
     if (!map_matches<C::BM, C::BN, 0, C::SLACK>(a, map)) return;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int ng = slots_of_xcd(map, total, xcd);
+    const int ng = slots_of_xcd(map, order, total, xcd);
     const int r0 = (int)((long long)a.red_tiles * xcd >> 3), r1 = (int)((long long)a.red_tiles * (xcd + 1) >> 3);
     const int nr = r1 - r0, n = ng + nr;
     if (slot >= n) return;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_batched_kernel(GemmArgs a) {
         return;
     }
     int B;
-    if (!slot_to_block(map, total, xcd, slot - before, B)) return;
+    if (!slot_to_block(map, order, total, xcd, slot - before, B)) return;
     const moe_tiling g = {C::BM, C::BN, 0, 0, 0, C::SLACK};
     const TileCoord tc = decode_block(map, L, g, B, first_record);
     run_tile<C, Tails...>(a, map, L, tc, smem);

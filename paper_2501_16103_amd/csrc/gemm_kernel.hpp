@@ -1193,22 +1193,30 @@ __device__ __forceinline__ bool map_matches(const GemmArgs& a, const int32_t* __
 
 // The same with all words read before the first is looked at, instead of one after the other, each with its own wait: the
 // launches whose workgroups also work out their half tiles make up for that here (16 experts, 512 -> 4096, 300 rows: 14.3 us
-// without half tiles, 15.3 with them, 14.4 with this).  (The 16-row launches keep the other form: with this one their k loop
+// without half tiles, 15.3 with them, 14.4 with this).  The count of tiles and their order are among them, and the callers take them
+// from here: read where they are used, behind branches, the order alone was fetched three times, each with its own wait
+// (fp8, 64
+// experts, 2048 -> 2816, 8192 tokens: 306.3 -> 303.9 us).  (The 16-row launches keep the other form: with this one their k loop
 // comes out 5 % slower, 8 experts, 14336 -> 4096, one token 61 -> 64 us.)
 template <int BM, int BN, int SLACK>
-__device__ __forceinline__ bool map_matches_at_once(const GemmArgs& a, const int32_t* __restrict__ map) {
-    return (map[MOE_HDR_MAGIC] == MOE_MAP_MAGIC) & (map[MOE_HDR_T] == a.T) & (map[MOE_HDR_K_TOP] == a.k) & (map[MOE_HDR_E] == a.E) &
-           (map[MOE_HDR_N] == a.N) & (map[MOE_HDR_TILE_M] == BM) & (map[MOE_HDR_TILE_N] == BN) & (map[MOE_HDR_STATUS] == 0) &
-           (map[MOE_HDR_TILE_M_SMALL] == 0) & (map[MOE_HDR_SMALL_MAX_ROWS] == a.small_max_rows) & (a.tile_m_small == 0) &
-           (map[MOE_HDR_TILE_M_SLACK] == SLACK) & (a.tile_m_slack == SLACK);
+__device__ __forceinline__ bool map_matches_at_once(const GemmArgs& a, const int32_t* __restrict__ map, int& total, int& order) {
+    total = map[MOE_HDR_TOTAL_TILES];
+    order = map[MOE_HDR_SIGMA_ORDER];
+    // (as one word of differing bits: a chain of comparisons goes through the vector unit and back, once per word.  total, order and
+    // the launch's own switch take part, or the compiler would fetch them behind the test.)
+    const int differ = (map[MOE_HDR_MAGIC] ^ MOE_MAP_MAGIC) | (map[MOE_HDR_T] ^ a.T) | (map[MOE_HDR_K_TOP] ^ a.k) | (map[MOE_HDR_E] ^ a.E) |
+                       (map[MOE_HDR_N] ^ a.N) | (map[MOE_HDR_TILE_M] ^ BM) | (map[MOE_HDR_TILE_N] ^ BN) | map[MOE_HDR_STATUS] |
+                       map[MOE_HDR_TILE_M_SMALL] | (map[MOE_HDR_SMALL_MAX_ROWS] ^ a.small_max_rows) | a.tile_m_small |
+                       (map[MOE_HDR_TILE_M_SLACK] ^ SLACK) | (a.tile_m_slack ^ SLACK) | (total >> 31) | (order & ~3) | (a.halve_last & ~1);
+    return differ == 0;
 }
 
 // Which block index slot `slot` of XCD `xcd` runs (the XCD-aware remap in front of Alg. 2 / 4: a bijection between
 // a launch's slots and the map's blocks, not part of the map).  Workgroup ids are dealt round-robin to the 8 XCDs;
 // every XCD gets one contiguous run of block indices so that neighbours in the map share an L2.  Returns false
 // for slots beyond the XCD's share (and then for every larger slot as well).
-__device__ __forceinline__ bool slot_to_block(const int32_t* __restrict__ map, int total, int xcd, int slot, int& B) {
-    if (map[MOE_HDR_SIGMA_ORDER] == MOE_ORDER_INTERLEAVE) {
+__device__ __forceinline__ bool slot_to_block(const int32_t* __restrict__ map, int order, int total, int xcd, int slot, int& B) {
+    if (order == MOE_ORDER_INTERLEAVE) {
         // Sec. 4.2: blocks [0, heavy) are compute-bound, [heavy, total) only stream weights.  Every XCD gets a
         // contiguous share of each part and walks the two shares interleaved in proportion (slot s takes the
         // next light block whenever floor((s+1) * nl / n) exceeds floor(s * nl / n)), so that the light tiles'
@@ -1228,8 +1236,8 @@ __device__ __forceinline__ bool slot_to_block(const int32_t* __restrict__ map, i
     return B < total;
 }
 // Slots of XCD `xcd` for which slot_to_block returns true.
-__device__ __forceinline__ int slots_of_xcd(const int32_t* __restrict__ map, int total, int xcd) {
-    if (map[MOE_HDR_SIGMA_ORDER] == MOE_ORDER_INTERLEAVE) {
+__device__ __forceinline__ int slots_of_xcd(const int32_t* __restrict__ map, int order, int total, int xcd) {
+    if (order == MOE_ORDER_INTERLEAVE) {
         const int heavy = map[MOE_HDR_HEAVY_TILES], light = total - heavy;
         return (int)(((long long)heavy * (xcd + 1) >> 3) - ((long long)heavy * xcd >> 3)) +
                (int)(((long long)light * (xcd + 1) >> 3) - ((long long)light * xcd >> 3));
@@ -1318,7 +1326,7 @@ __device__ __forceinline__ bool locate_tile(const GemmArgs& a, const int32_t* __
     const int total = map[MOE_HDR_TOTAL_TILES];
     if (!map_matches<BM_BIG, BN, BM_SMALL, SLACK>(a, map)) return false;
     int B;
-    if (!slot_to_block(map, total, blockIdx.x & 7, blockIdx.x >> 3, B)) return false;
+    if (!slot_to_block(map, map[MOE_HDR_SIGMA_ORDER], total, blockIdx.x & 7, blockIdx.x >> 3, B)) return false;
     const moe_tiling g = {BM_BIG, BN, 0, BM_SMALL, a.small_max_rows, SLACK};
     tc = decode_block(map, L, g, B, first_record);
     return true;
@@ -1395,11 +1403,11 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
     const MapLayout L = map_layout(a.E);
     const int lane = __lane_id();
     int4 record = reinterpret_cast<const int4*>(map + L.off_records)[lane];
-    int total = map[MOE_HDR_TOTAL_TILES];
-    if (!map_matches_at_once<C::BM, C::BN, 0>(a, map)) return;
+    int total, order;
+    if (!map_matches_at_once<C::BM, C::BN, 0>(a, map, total, order)) return;
     moe_tiling g = {C::BM, C::BN, 0, 0, 0, 0};
     const bool small_last = record.z > C::BM && (record.z - 1) % C::BM < OVER::SLACK;
-    if (L.E64 == 64 && total > 8 * kXcdCus && map[MOE_HDR_SIGMA_ORDER] != MOE_ORDER_INTERLEAVE && __ballot(small_last)) {
+    if (L.E64 == 64 && total > 8 * kXcdCus && order != MOE_ORDER_INTERLEAVE && __ballot(small_last)) {
         const moe_tiling over = {C::BM, C::BN, 0, 0, 0, OVER::SLACK};
         const int upto = wave_incl_scan(record.z > 0 ? expert_m_tiles(record.z, over) * (a.N / C::BN) : 0);
         const int left = __builtin_amdgcn_readlane(upto, 63);
@@ -1412,7 +1420,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
         }
     }
     int B;
-    if (!slot_to_block(map, total, blockIdx.x & 7, blockIdx.x >> 3, B)) return;
+    if (!slot_to_block(map, order, total, blockIdx.x & 7, blockIdx.x >> 3, B)) return;
     const TileCoord tc = decode_block(map, L, g, B, record);
     if (tc.rows > C::BM) pipe_tile<OVER>(a, map, L, tc, smem);
     else run_tile<C, Tails...>(a, map, L, tc, smem);
@@ -1445,13 +1453,15 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
     const int32_t* __restrict__ map = a.map;
     const MapLayout L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
-    const int total = map[MOE_HDR_TOTAL_TILES];
-    if (!map_matches_at_once<C::BM, C::BN, C::SLACK>(a, map)) return;
+    int total, order;
+    if (!map_matches_at_once<C::BM, C::BN, C::SLACK>(a, map, total, order)) return;
     const int xcd = blockIdx.x & 7;
     int slot = blockIdx.x >> 3, half = -1;
+    // (not for tiles of 128 columns: 64 experts, 2048 -> 1408, eight of them crowded, 400 to 2000 tokens, 0.99 to 1.01 of the time in plain
+    // order, and the code alone costs 2 to 4 % of a short launch: 4 experts, 1024 -> 2048, 64 tiles 9.2 -> 9.5 us)
     TwoKinds kinds;
-    if (a.halve_last && L.E64 == 64 && map[MOE_HDR_SIGMA_ORDER] == MOE_ORDER_ASCENDING) kinds.look(first_record, total, C::BMC);
-    const int n = kinds.on ? kinds.slots(xcd) : slots_of_xcd(map, total, xcd);
+    if (C::BN == 256 && a.halve_last && L.E64 == 64 && order == MOE_ORDER_ASCENDING) kinds.look(first_record, total, C::BMC);
+    const int n = kinds.on ? kinds.slots(xcd) : slots_of_xcd(map, order, total, xcd);
     if (a.halve_last) {
         const int rest = n % kXcdCus, full = n - rest;
         if (rest <= kXcdCus / 2 && slot >= full) {
@@ -1462,7 +1472,7 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
     int B;
     if (slot >= n) return;
     if (kinds.on) B = kinds.block(first_record, xcd, slot);
-    else if (!slot_to_block(map, total, xcd, slot, B)) return;
+    else if (!slot_to_block(map, order, total, xcd, slot, B)) return;
     const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
     TileCoord tc = decode_block(map, L, g, B, first_record);
     if (half < 0) {
@@ -1487,17 +1497,17 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a
     const int32_t* __restrict__ map = a.map;
     const MapLayout L = map_layout(a.E);
     const int4 first_record = reinterpret_cast<const int4*>(map + L.off_records)[__lane_id()];
-    const int total = map[MOE_HDR_TOTAL_TILES];
-    if (!map_matches_at_once<C::BM, C::BN, C::SLACK>(a, map)) return;
+    int total, order;
+    if (!map_matches_at_once<C::BM, C::BN, C::SLACK>(a, map, total, order)) return;
     const int xcd = blockIdx.x & 7;
     int slot = blockIdx.x >> 3, half = -1;
-    const int n = slots_of_xcd(map, total, xcd), rest = n % kXcdCus, full = n - rest, kt = a.K / C::BK;
+    const int n = slots_of_xcd(map, order, total, xcd), rest = n % kXcdCus, full = n - rest, kt = a.K / C::BK;
     const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
     const int parts = slot >= full ? tail_parts(rest, kt) : 1;
     int B;
     if (parts > 1) {
         const int i = slot - full, p = i % parts;
-        if (i >= rest * parts || !slot_to_block(map, total, xcd, full + i / parts, B)) return;
+        if (i >= rest * parts || !slot_to_block(map, order, total, xcd, full + i / parts, B)) return;
         TileCoord tc = decode_block(map, L, g, B, first_record);
         tc.sharers = full > 0 ? 1 : parts;
         GemmArgs b = a;
@@ -1511,7 +1521,7 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a
         half = (slot - full) & 1;
         slot = full + ((slot - full) >> 1);
     }
-    if (slot >= n || !slot_to_block(map, total, xcd, slot, B)) return;
+    if (slot >= n || !slot_to_block(map, order, total, xcd, slot, B)) return;
     TileCoord tc = decode_block(map, L, g, B, first_record);
     if constexpr (HALVES) {
         if (half >= 0) {
