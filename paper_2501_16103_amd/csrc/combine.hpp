@@ -145,7 +145,8 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_batched_kernel(GemmArgs a) {
     int B;
     if (!slot_to_block(map, order, total, xcd, slot - before, B)) return;
     const moe_tiling g = {C::BM, C::BN, 0, 0, 0, C::SLACK};
-    const TileCoord tc = decode_block(map, L, g, B, first_record);
+    TileCoord tc = decode_block(map, L, g, B, first_record);
+    tc.streams = total;
     run_tile<C, Tails...>(a, map, L, tc, smem);
 }
 

@@ -378,12 +378,14 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     const uint32_t lds0 = (uint32_t)(uintptr_t)(MOE_LDS(char)*)smem;
 
     // Weight panels that only this tile reads are fetched non-temporally -- when the launch streams from nearly all CUs (measured:
-    // +10 % HBM throughput on the weight-streaming points, -9 % on 132 tiles of 128 columns).  What counts is workgroups: a tile that
-    // runs as two halves or in parts along K has as many streams.  Without the hint / with it, us: 8 experts, 14336 -> 4096, 128
-    // tiles, 666 rows as halves 168 / 158, in two parts 166 / 156; 256-wide 16-row tiles, 224 of 64 k-tiles 85.5 / 77.5, 231 of 32
-    // 43.9 / 38.3, but 168 of 22 19.3 / 20.9 and 128 of 32 23.0 / 26.7.
-    const int streams = map[MOE_HDR_TOTAL_TILES] * tc.sharers;
-    const bool nt_ok = streams >= 256 || (C::BN == 256 && streams >= 192);
+    // +10 % HBM throughput on the weight-streaming points, -9 % on 132 tiles of 128 columns).  What counts is workgroups: the launch's own
+    // tiles, which may hold several of the map's, times those that share one (as two halves or in parts along K).  Without the hint /
+    // with it, us: 8 experts, 14336 -> 4096, 128 tiles, 666 rows as halves 168 / 158, in two parts 166 / 156; 256-wide 16-row tiles,
+    // 224 of 64 k-tiles 85.5 / 77.5, 231 of 32 43.9 / 38.3, but 168 of 22 19.3 / 20.9 and 128 of 32 23.0 / 26.7.
+    // Resident workgroups that stream one tile after the other always gain from it (tiles of 256 columns, weights at another place in
+    // each launch; without / with, fp8): 32 experts, 4096 -> 4096, 112 tiles 31.8 / 29.8, 128 tiles 32.5 / 30.7; 64 experts, 2048 -> 2816,
+    // 132 tiles 18.0 / 16.5, 187 tiles 20.8 / 18.3; 8 experts, 88 tiles 19.7 / 18.2.
+    const bool nt_ok = STREAM || tc.streams >= 256 || (C::BN == 256 && tc.streams >= 192);
     bool w_once = nt_ok && tc.m_tiles == 1, w_once_next = false;
     // j-th token-row / weight-row DMA instruction of this wave for k-tile kt, into ring stage `stage`
     auto dma_x = [&](int j, int kt, int stage, bool next) __attribute__((always_inline)) {
@@ -1329,6 +1331,7 @@ __device__ __forceinline__ bool locate_tile(const GemmArgs& a, const int32_t* __
     if (!slot_to_block(map, map[MOE_HDR_SIGMA_ORDER], total, blockIdx.x & 7, blockIdx.x >> 3, B)) return false;
     const moe_tiling g = {BM_BIG, BN, 0, BM_SMALL, a.small_max_rows, SLACK};
     tc = decode_block(map, L, g, B, first_record);
+    tc.streams = total;
     return true;
 }
 
@@ -1362,7 +1365,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
         b.k_part = (int)blockIdx.y;
         b.k_tiles = a.K / C::BK / (int)gridDim.y;
         b.k_tile0 = b.k_part * b.k_tiles;
-        tc.sharers = (int)gridDim.y;
+        tc.streams *= (int)gridDim.y;
         run_tile<C, Tails...>(b, a.map, L, tc, smem);
     } else {
         run_tile<C, Tails...>(a, a.map, L, tc, smem);
@@ -1421,7 +1424,8 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
     }
     int B;
     if (!slot_to_block(map, order, total, blockIdx.x & 7, blockIdx.x >> 3, B)) return;
-    const TileCoord tc = decode_block(map, L, g, B, record);
+    TileCoord tc = decode_block(map, L, g, B, record);
+    tc.streams = total;
     if (tc.rows > C::BM) pipe_tile<OVER>(a, map, L, tc, smem);
     else run_tile<C, Tails...>(a, map, L, tc, smem);
 }
@@ -1475,11 +1479,11 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
     else if (!slot_to_block(map, order, total, xcd, slot, B)) return;
     const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
     TileCoord tc = decode_block(map, L, g, B, first_record);
+    tc.streams = half < 0 ? total : 2 * total;
     if (half < 0) {
         Fns::run(a, map, L, tc, smem);
     } else {
         tc.n_tile = 2 * tc.n_tile + half;
-        tc.sharers = 2;
         Half::run(a, map, L, tc, smem);
     }
 }
@@ -1509,7 +1513,7 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a
         const int i = slot - full, p = i % parts;
         if (i >= rest * parts || !slot_to_block(map, order, total, xcd, full + i / parts, B)) return;
         TileCoord tc = decode_block(map, L, g, B, first_record);
-        tc.sharers = full > 0 ? 1 : parts;
+        tc.streams = full > 0 ? total : parts * total;
         GemmArgs b = a;
         b.k_tile0 = part_begin(kt, parts, p);
         b.k_tiles = part_begin(kt, parts, p + 1) - b.k_tile0;
@@ -1523,10 +1527,10 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a
     }
     if (slot >= n || !slot_to_block(map, order, total, xcd, slot, B)) return;
     TileCoord tc = decode_block(map, L, g, B, first_record);
+    tc.streams = half < 0 ? total : 2 * total;
     if constexpr (HALVES) {
         if (half >= 0) {
             tc.n_tile = 2 * tc.n_tile + half;
-            tc.sharers = 2;
             Half::run(a, map, L, tc, smem);
             return;
         }
@@ -1615,7 +1619,8 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     ts.ws_lds = ws_lds;
     ts.next_B = t0 + 1;
     ts.end_B = t1;
-    const TileCoord tc = decode_from_registers(ts, t0);
+    TileCoord tc = decode_from_registers(ts, t0);
+    tc.streams = total;
     pipe_tile<C, true>(a, map, L, tc, smem, &ts);
 }
 

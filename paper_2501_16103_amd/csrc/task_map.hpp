@@ -90,7 +90,7 @@ struct TileCoord {
     int e, m_tile, n_tile, rows, row_base;  // row_base: index into sorted_rows of the tile's first row
     int small;                              // task type (Alg. 3): 1 = the expert uses the small tiling strategy
     int m_tiles;                            // m-tiles of the expert: 1 = no other tile reads this tile's weight panel
-    int sharers = 1;                        // workgroups that run the tile between them (halves, parts along K)
+    int streams = 0;                        // tiles of the launch, as it runs them, times the workgroups that share one (halves, parts along K)
 };
 
 // Tiling strategy of an expert with cnt rows: tile_m_small when cnt <= small_max_rows (0 = one strategy).
