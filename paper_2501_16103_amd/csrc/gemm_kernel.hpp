@@ -1302,17 +1302,20 @@ struct TwoKinds {
 // filled last round run, the other CUs idle for a whole tile's duration.  If they fill at most half of the CUs, each can instead be
 // run by P = floor(32 / t) workgroups (8 at most), every one over a part of K of at least 8 k-tiles; their fp32 sums are added
 // afterwards, in the order of k.  That takes 1 / P of a tile's duration and about 14 k-tiles' worth for the second ring fill, the
-// sums' way through memory and their addition; as half tiles (see moe_gemm_halves_kernel) the round takes six tenths.
+// sums' way through memory and their addition; as half tiles (see moe_gemm_halves_kernel) the round takes six tenths.  Tiles of 64 rows
+// have no halves: there the parts have to beat the whole round, with a tenth to spare (8 experts, 64-row tiles, last round of t tiles,
+// us, whole / in parts: K = 2048, t = 4 32.0 / 17.9, behind a full round 72.8 / 59.6; K = 7168, t = 16 102.7 / 81.1, behind a full round 259.9 / 233.7;
+// K = 2048, t = 16 stays whole: in two parts it takes as long).
 // The parts of all tiles begin at the same k, so that tiles of one weight panel go on sharing it: cutting the whole round into 32 equal
 // stretches, which would also serve a round more than half full, was slower than running it whole (8 experts, 14336 -> 4096,
 // a skewed routing of 2000 rows, 26 tiles per XCD: 351 us against 275).
 // The map is untouched: this is a property of the launch.
 constexpr int kPartOverhead = 14, kMaxTailParts = 8;
-__host__ __device__ inline int tail_parts(int t, int kt) {
+__host__ __device__ inline int tail_parts(int t, int kt, bool halves) {
     if (t <= 0 || t > kXcdCus / 2) return 1;
     int P = kXcdCus / t < kMaxTailParts ? kXcdCus / t : kMaxTailParts;
     if (kt / P < 8) P = kt / 8;
-    return P >= 2 && 10 * (kt / P + kPartOverhead) < 6 * kt ? P : 1;
+    return P >= 2 && 10 * (kt / P + kPartOverhead) < (halves ? 6 : 9) * kt ? P : 1;
 }
 // First k-tile of part p.
 __host__ __device__ inline int part_begin(int kt, int P, int p) { return (int)((long long)kt * p / P); }
@@ -1489,7 +1492,7 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_halves_kernel(GemmArgs
 }
 
 // A tail-split product: whole tiles in the full rounds of every XCD, and the tiles of its last round in parts along K where that
-// pays (see tail_parts), else whole or as half tiles.  Part p of tail tile j of XCD x leaves its fp32 sums in
+// pays (see tail_parts), else as half tiles where the shape has them, or whole.  Part p of tail tile j of XCD x leaves its fp32 sums in
 // block x * 32 + j * P + p of the workspace, [BM + SLACK][BN].  Parts: the split-k task functions.
 // (One launch: the parts start as the CUs come free from the last full round, without a gap between two launches.)
 template <class Fns, class Half, class Parts>
@@ -1507,7 +1510,7 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a
     int slot = blockIdx.x >> 3, half = -1;
     const int n = slots_of_xcd(map, order, total, xcd), rest = n % kXcdCus, full = n - rest, kt = a.K / C::BK;
     const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
-    const int parts = slot >= full ? tail_parts(rest, kt) : 1;
+    const int parts = slot >= full ? tail_parts(rest, kt, HALVES) : 1;
     int B;
     if (parts > 1) {
         const int i = slot - full, p = i % parts;

@@ -11,12 +11,12 @@ from tests.test_gpu_parity import _ids_from_counts
 pytestmark = pytest.mark.gpu
 
 
-def _parts(t, kt):
+def _parts(t, kt, tile_m):
     """Workgroups per tile of a last round of t tiles, written down from the rule's description."""
     if not 1 <= t <= 16:
         return 1
     p = min(32 // t, 8, kt // 8)
-    return p if p >= 2 and kt // p + 14 < 0.6 * kt else 1
+    return p if p >= 2 and 10 * (kt // p + 14) < (9 if tile_m == 64 else 6) * kt else 1
 
 
 CASES = [
@@ -30,6 +30,9 @@ CASES = [
     (-256, [288, 100, 257, 40], 34, 14336),        # 17: whole
     (128, [128, 64, 129, 1], 7, 14336),            # 128-row tiles, 5: 6 parts
     (64, [64, 33, 70], 2, 7168),                   # 64-row tiles, 1: 8 parts
+    (64, [64, 33, 70], 8, 2048),                   # 64-row tiles have no halves: 4, 4 parts of 8 k-tiles
+    (64, [64, 33, 64, 1], 32, 2304),               # 16: 2 parts of 18 k-tiles
+    (64, [64, 33, 64, 1], 32, 2176),               # 16, K too short for two parts: whole
     (-256, [9000, 280], 8, 7168),                  # 36: a full round and 4, 8 parts
 ]
 
@@ -63,15 +66,17 @@ def test_tail_parts(tile_m, counts, nt, K):
     # which tiles ran in parts
     total = int(tmap[mb.HDR["TOTAL_TILES"]])
     share = -(-total // 8)
-    in_parts, expected = set(), set()
+    in_parts, blocks = set(), set()
     for x in range(8):
         n = max(0, min(share, total - x * share))
-        p = _parts(n % 32, K // 64)
+        t = n % 32
+        p = _parts(t, K // 64, tile_m)
         if p > 1:
-            in_parts |= set(range(x * share + n // 32 * 32, x * share + n))
-            expected.add(p)
-    written = int(torch.isfinite(ws).any().item())
-    assert bool(written) == bool(expected)
+            in_parts |= set(range(x * share + n - t, x * share + n))
+            blocks |= set(range(x * 32, x * 32 + t * p))
+    # each part left its sums in the workspace, and nothing else was written there
+    written = torch.isfinite(ws.view(-1, (tile_m + slack) * 256)[:256]).any(dim=1).nonzero().flatten().tolist()
+    assert set(written) == blocks and not bool(torch.isfinite(ws[256 * (tile_m + slack) * 256:]).any())
     rows, B = [torch.nonzero(ids[:, 0] == e).flatten().tolist() for e in range(E)], 0
     for e in range(E):
         if not counts[e]:
