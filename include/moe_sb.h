@@ -346,8 +346,8 @@ size_t moe_splitk_static_scratch_bytes(void);
  * last round holds t < 32 tiles the other CUs idle for a whole tile's duration.  Here, where t is at most 16, those tiles are run
  * by P workgroups each, every one over a part of K; their fp32 sums go to `workspace` and are added in ascending order
  * of the parts, rounded once to bf16 and scattered to Y.  P = floor(32 / t), at most 8, with at least 8 k-tiles of 64 a part, chosen
- * per XCD on the device, and only where K is long enough for the parts to beat running the round as half tiles (for two parts,
- * more than 140 k-tiles) or, on 64-row tiles, whole (for two parts, 35 k-tiles).  All other tiles run exactly as in moe_grouped_gemm (their results are bit for bit the same); the tail
+ * per XCD on the device, and only where K is long enough for the parts to beat what they replace, the round as half tiles or, on
+ * 64-row tiles, whole (for two parts: more than 93 k-tiles on 256-row tiles, 140 on 128-row ones, 35 on 64-row ones).  All other tiles run exactly as in moe_grouped_gemm (their results are bit for bit the same); the tail
  * tiles differ from it in summation order only.  Two launches on `stream`.
  *   workspace  DEVICE, 16-byte aligned, at least moe_tail_split_workspace_bytes(tile_m, tile_n) bytes
  *              (8 * 128 * rows * tile_n * 4 with rows = tile_m, 288 for 256-row tiles: 288 MiB), owned by the caller, contents undefined

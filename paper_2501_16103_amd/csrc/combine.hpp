@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void moe_combine_kernel(const u32x4_t* __restr
 // once to bf16 and scatter the tile's rows to Y; each of the slices takes every kTailReduceSlices-th stretch of 256
 // chunks (a tile by one workgroup streamed at a fifth of the rate: 42 us of an 0.8 ms product).
 constexpr int kTailReduceSlices = 8;
-template <int BM, int BN, int SLACK, bool HALVES>
+template <int BM, int BN, int SLACK>
 __global__ __launch_bounds__(256) void moe_tail_reduce_kernel(GemmArgs a) {
     constexpr int BMC = BM + SLACK;   // rows of a workspace block
     const int32_t* __restrict__ map = a.map;
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void moe_tail_reduce_kernel(GemmArgs a) {
     if (!map_matches_at_once<BM, BN, SLACK>(a, map, total, order)) return;
     const int xcd = blockIdx.x & 7, j = (int)(blockIdx.x >> 3) / kTailReduceSlices, slice = (int)(blockIdx.x >> 3) % kTailReduceSlices;
     const int n = slots_of_xcd(map, order, total, xcd), rest = n % kXcdCus, kt = a.K / 64;
-    const int parts = tail_parts(rest, kt, HALVES);
+    const int parts = tail_parts(rest, kt, BM);
     if (j >= rest || parts == 1) return;
     int B;
     if (!slot_to_block(map, order, total, xcd, n - rest + j, B)) return;

@@ -1302,23 +1302,27 @@ struct TwoKinds {
 // filled last round run, the other CUs idle for a whole tile's duration.  If they fill at most half of the CUs, each can instead be
 // run by P = floor(32 / t) workgroups (8 at most), every one over a part of K of at least 8 k-tiles; their fp32 sums are added
 // afterwards, in the order of k.  That takes 1 / P of a tile's duration and about 14 k-tiles' worth for the second ring fill, the
-// sums' way through memory and their addition; as half tiles (see moe_gemm_halves_kernel) the round takes six tenths.  Tiles of 64 rows
-// have no halves: there the parts have to beat the whole round, with a tenth to spare (8 experts, 64-row tiles, last round of t tiles,
-// us, whole / in parts: K = 2048, t = 4 32.0 / 17.9, behind a full round 72.8 / 59.6; K = 7168, t = 16 102.7 / 81.1, behind a full round 259.9 / 233.7;
-// K = 2048, t = 16 stays whole: in two parts it takes as long).
+// sums' way through memory and their addition.  What it replaces is the round as half tiles (see moe_gemm_halves_kernel), six tenths and
+// a half of a whole one on 256-row tiles, six tenths on 128-row ones, whose sums weigh more beside their shorter loop; 64-row tiles have
+// no halves, there the parts have to beat the whole round, with a tenth to spare.  8 experts, a last round of t tiles per XCD by
+// itself / behind a full round, us, halves (64 rows: whole) and in two parts: 256 rows, K = 8192, t = 11 130 111 / 370 356, t = 16
+// 154 140 / 380 370; K = 7168, t = 12 118 107 / 317 308, t = 16 133 127 / 332 331; K = 6144, t = 16 115 113 / 293 295.  128 rows,
+// K = 8192, t = 16 100 104 / 289 288.  64 rows, K = 2048, t = 4 (four parts) 32 18 / 73 60, K = 7168, t = 16 103 81 / 260 234.
 // The parts of all tiles begin at the same k, so that tiles of one weight panel go on sharing it: cutting the whole round into 32 equal
 // stretches, which would also serve a round more than half full, was slower than running it whole (8 experts, 14336 -> 4096,
 // a skewed routing of 2000 rows, 26 tiles per XCD: 351 us against 275).
 // The map is untouched: this is a property of the launch.
 constexpr int kPartOverhead = 14, kMaxTailParts = 8;
-__host__ __device__ inline int tail_parts(int t, int kt, bool halves) {
+// Twentieths of a whole round that the parts have to stay below.
+__host__ __device__ constexpr int tail_worth(int tile_m) { return tile_m >= 256 ? 13 : tile_m >= 128 ? 12 : 18; }
+__host__ __device__ constexpr int tail_parts(int t, int kt, int tile_m) {
     if (t <= 0 || t > kXcdCus / 2) return 1;
     int P = kXcdCus / t < kMaxTailParts ? kXcdCus / t : kMaxTailParts;
     if (kt / P < 8) P = kt / 8;
-    return P >= 2 && 10 * (kt / P + kPartOverhead) < (halves ? 6 : 9) * kt ? P : 1;
+    return P >= 2 && 20 * (kt / P + kPartOverhead) < tail_worth(tile_m) * kt ? P : 1;
 }
 // First k-tile of part p.
-__host__ __device__ inline int part_begin(int kt, int P, int p) { return (int)((long long)kt * p / P); }
+__host__ __device__ inline int part_begin(int kt, int P, int p) { return kt * p / P; }   // (K below 2^31: kt * p stays far below it)
 constexpr int kTailBlocksPerXcd = kXcdCus;   // blocks of partial sums per XCD
 
 // Block index -> tile (Alg. 2 + 4), shared by the kernels below.  Returns false for surplus workgroups and for
@@ -1510,16 +1514,17 @@ __global__ __launch_bounds__(Fns::Full::NT) void moe_gemm_tail_kernel(GemmArgs a
     int slot = blockIdx.x >> 3, half = -1;
     const int n = slots_of_xcd(map, order, total, xcd), rest = n % kXcdCus, full = n - rest, kt = a.K / C::BK;
     const moe_tiling g = {C::BM, C::BN, 0, 0, a.small_max_rows, C::SLACK};
-    const int parts = slot >= full ? tail_parts(rest, kt, HALVES) : 1;
+    const int parts = slot >= full ? tail_parts(rest, kt, C::BM) : 1;
     int B;
     if (parts > 1) {
-        const int i = slot - full, p = i % parts;
-        if (i >= rest * parts || !slot_to_block(map, order, total, xcd, full + i / parts, B)) return;
+        // (the divisions run in the vector unit: back to scalars, which the addresses of the DMA instructions are made of)
+        const int i = slot - full, j = __builtin_amdgcn_readfirstlane(i / parts), p = i - j * parts;
+        if (j >= rest || !slot_to_block(map, order, total, xcd, full + j, B)) return;
         TileCoord tc = decode_block(map, L, g, B, first_record);
         tc.streams = full > 0 ? total : parts * total;
         GemmArgs b = a;
-        b.k_tile0 = part_begin(kt, parts, p);
-        b.k_tiles = part_begin(kt, parts, p + 1) - b.k_tile0;
+        b.k_tile0 = __builtin_amdgcn_readfirstlane(part_begin(kt, parts, p));
+        b.k_tiles = __builtin_amdgcn_readfirstlane(part_begin(kt, parts, p + 1)) - b.k_tile0;
         b.partial_tile = a.partial + (size_t)(xcd * kTailBlocksPerXcd + i) * (C::BMC * C::BN);
         Parts::run(b, map, L, tc, smem);
         return;

@@ -571,7 +571,7 @@ int launch_tail_split(const GemmArgs& a, int64_t grid, hipStream_t s) {
     grid = 8 * ((grid / 8 + kXcdCus - 1) / kXcdCus * kXcdCus);   // every CU of a last round
     moe_gemm_tail_kernel<Fns, Half, Parts><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(a);
     if (hipGetLastError() != hipSuccess) return MOE_ERR_HIP;
-    moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK, (Half::Full::BN < C::BN)><<<dim3(8 * (kXcdCus / 2) * kTailReduceSlices), dim3(256), 0, s>>>(a);
+    moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK><<<dim3(8 * (kXcdCus / 2) * kTailReduceSlices), dim3(256), 0, s>>>(a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 

@@ -16,7 +16,7 @@ def _parts(t, kt, tile_m):
     if not 1 <= t <= 16:
         return 1
     p = min(32 // t, 8, kt // 8)
-    return p if p >= 2 and 10 * (kt // p + 14) < (9 if tile_m == 64 else 6) * kt else 1
+    return p if p >= 2 and 20 * (kt // p + 14) < {256: 13, 128: 12, 64: 18}[tile_m] * kt else 1
 
 
 CASES = [
@@ -25,10 +25,12 @@ CASES = [
     (256, [129, 256, 0, 513, 65], 3, 14336),       # 3: 8 parts
     (-256, [288, 129, 200, 256, 31], 8, 9280),     # 5: 6 parts of 145 k-tiles
     (256, [70, 128, 250, 3, 1], 16, 7168),         # 10: 3 parts of 112 k-tiles
-    (256, [90, 128, 64, 250], 32, 9152),           # 16: 2 parts of 143 k-tiles
-    (256, [90, 128, 64, 250], 32, 7168),           # 16, K too short for two parts: half tiles
+    (256, [90, 128, 64, 250], 32, 6080),           # 16: 2 parts of 47 and 48 k-tiles
+    (256, [90, 128, 64, 250], 32, 5888),           # 16, K too short for two parts: half tiles
     (-256, [288, 100, 257, 40], 34, 14336),        # 17: whole
     (128, [128, 64, 129, 1], 7, 14336),            # 128-row tiles, 5: 6 parts
+    (128, [128, 64, 90, 1], 32, 9088),             # 16: 2 parts of 71 k-tiles
+    (128, [128, 64, 90, 1], 32, 8960),             # 16, K too short for two parts: half tiles
     (64, [64, 33, 70], 2, 7168),                   # 64-row tiles, 1: 8 parts
     (64, [64, 33, 70], 8, 2048),                   # 64-row tiles have no halves: 4, 4 parts of 8 k-tiles
     (64, [64, 33, 64, 1], 32, 2304),               # 16: 2 parts of 18 k-tiles
