@@ -96,7 +96,7 @@ class Point:
                                 mb.MOE_EPILOGUE_SWIGLU if swiglu else mb.MOE_EPILOGUE_NONE,
                                 mb.MOE_W_LAYOUT_NK if w_nk else mb.MOE_W_LAYOUT_KN, launch_mode)
         self.launch_mode = launch_mode
-        # the tiles of a partly filled last round split along K (moe_grouped_gemm_tail_split; 288 MiB workspace at 256-row tiles)
+        # the tiles of a partly filled last round split along K (moe_grouped_gemm_tail_split; 72 MiB workspace at 256-row tiles)
         self.tail_ws = (torch.empty(mb.moe_tail_split_workspace_bytes(wl.tile_m, wl.tile_n) // 4, dtype=torch.float32, device=dev)
                         if tail_split else None)
         self.tiling = mb.Tiling(wl.tile_m, wl.tile_n, order, small[0], small[1], self.slack)

@@ -554,11 +554,15 @@ int run_splitk(const void* X, const void* W, const void* task_map, void* Y, cons
 }
 
 // ---- tail split (see tail_parts in gemm_kernel.hpp); MI355X: 8 XCDs of 32 CUs
-constexpr int kTailWorkspaceBlocks = 128;   // blocks per XCD that the workspace is sized for
-static_assert(kTailWorkspaceBlocks >= kTailBlocksPerXcd, "workspace blocks per XCD");
+constexpr bool tail_blocks_fit() {   // (a long K: a shorter one never has more parts)
+    for (int t = 0; t < kXcdCus; ++t)
+        if (tail_parts(t, 1 << 20, 256) > 1 && t * tail_parts(t, 1 << 20, 256) > kTailBlocksPerXcd) return false;
+    return true;
+}
+static_assert(tail_blocks_fit(), "every part has a block of the workspace");
 
 size_t tail_workspace_bytes(int tile_m, int tile_n) {   // (256-row blocks with room for 32 slack rows)
-    return size_t(8) * kTailWorkspaceBlocks * (tile_m == 256 ? 288 : tile_m) * tile_n * sizeof(float);
+    return size_t(8) * kTailBlocksPerXcd * (tile_m == 256 ? 288 : tile_m) * tile_n * sizeof(float);
 }
 
 // The two launches of a tail-split product: the tiles, those of a short last round in parts; the sums of the parts.

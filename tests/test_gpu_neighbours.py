@@ -732,8 +732,8 @@ def test_tail_split_argument_errors(dev):
     mb.moe_build_task_map(ids, T, 1, E, 256, 256, N, tmap)
     ws = torch.empty(mb.moe_tail_split_workspace_bytes(256, 256) // 4, dtype=torch.float32, device=dev)
     d = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, 1, E, K, N, 256, 256)
-    assert mb.moe_tail_split_workspace_bytes(256, 256) == 8 * 128 * 288 * 256 * 4
-    assert mb.moe_tail_split_workspace_bytes(64, 256) == 8 * 128 * 64 * 256 * 4
+    assert mb.moe_tail_split_workspace_bytes(256, 256) == 8 * 32 * 288 * 256 * 4
+    assert mb.moe_tail_split_workspace_bytes(64, 256) == 8 * 32 * 64 * 256 * 4
     assert mb.moe_tail_split_workspace_bytes(32, 256) == 0 and mb.moe_tail_split_workspace_bytes(256, 128) == 0
     assert mb.moe_grouped_gemm_tail_split(X, W, tmap, Y, d, ws, check=False) == mb.MOE_OK
     assert mb.moe_grouped_gemm_tail_split(X, W, tmap, Y, d, ws[:1000], check=False) == mb.MOE_ERR_INVALID_ARG

@@ -52,7 +52,9 @@ def test_tail_parts(tile_m, counts, nt, K):
     mb.moe_build_task_map_ex(ids, T, 1, E, N, mb.Tiling(tile_m, 256, tile_m_slack=slack), tmap)
     desc = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, 1, E, K, N, tile_m, 256, tile_m_slack=slack)
     words = mb.moe_tail_split_workspace_bytes(tile_m, 256) // 4
-    ws = torch.full((words,), float("nan"), dtype=torch.float32, device=dev)
+    guard = 1024
+    buf = torch.full((words + 2 * guard,), float("nan"), dtype=torch.float32, device=dev)
+    ws = buf[guard: guard + words]
     Y, plain = (torch.full((T, N), float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(2))
     mb.moe_grouped_gemm_tail_split(X, W, tmap, Y, desc, ws)
     mb.moe_grouped_gemm(X, W, None, tmap, plain, desc)
@@ -77,8 +79,11 @@ def test_tail_parts(tile_m, counts, nt, K):
             in_parts |= set(range(x * share + n - t, x * share + n))
             blocks |= set(range(x * 32, x * 32 + t * p))
     # each part left its sums in the workspace, and nothing else was written there
-    written = torch.isfinite(ws.view(-1, (tile_m + slack) * 256)[:256]).any(dim=1).nonzero().flatten().tolist()
-    assert set(written) == blocks and not bool(torch.isfinite(ws[256 * (tile_m + slack) * 256:]).any())
+    used = 256 * (tile_m + slack) * 256
+    written = torch.isfinite(ws[:used].view(256, -1)).any(dim=1).nonzero().flatten().tolist()
+    assert set(written) == blocks and not bool(torch.isfinite(ws[used:]).any()), "wrote to another block"
+    assert bool(torch.isnan(buf[:guard]).all()) and bool(torch.isnan(buf[-guard:]).all()), "wrote outside the workspace"
+    assert words == 256 * (288 if tile_m == 256 else tile_m) * 256, "32 blocks per XCD: the most that the parts of a round take"
     rows, B = [torch.nonzero(ids[:, 0] == e).flatten().tolist() for e in range(E)], 0
     for e in range(E):
         if not counts[e]:
