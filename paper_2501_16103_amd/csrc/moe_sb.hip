@@ -189,6 +189,25 @@ int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+// Whether the streaming launch runs the rows of several 16-row tiles as one tile (see moe_gemm_stream_kernel): nt n-tiles as it runs
+// them.  From 8 to 32 rows per expert on average and from 16 k-tiles on.  At 8 to 10 rows an even routing gives nearly every expert
+// one tile, and the larger task function costs 1 to 2 % (bf16, 256 experts, 2048 -> 2048, 6 %: 317 -> 339 us), but skewed ones gain ten
+// times that (the same 332 -> 281; 64 experts, 2048 -> 2816, 122 -> 110); below 8 rows the cost stays (fp8, 32 tokens, 1 to 3 %).  Beyond 32, few
+// experts are left with too few workgroups (8 experts, K = 256, 75 rows each: 7.4 -> 11.5 us), and such maps are not the default; with a
+// short K the rows of a full tile take longer than its panel (64 experts, 1024 -> 2048, fp8, a skewed routing of 200 tokens 28.6 -> 35.0).
+// Tiles that all start at once gain nothing from being fewer, the longest of them only gets longer: below two tiles per CU, it takes
+// a round less under a uniform routing (tiles expected one by one / merged; fp8, us: 8 experts, 2048 -> 2816, 20 rows, 154 / 88, 17.2
+// -> 18.1 and, skewed, 16.7 -> 20.9; 32 experts, 10 rows, 396 / 352, 35.3 -> 36.4, skewed 36.2 -> 40.4, but 16 rows, 528 / 352, 41.5 -> 37.6;
+// 16 experts, 4096 -> 4096, 16 rows, 384 / 256, 61.5 -> 47.3).  A launch of a given number of workgroups merges by rows and K alone.
+constexpr bool merges16(int64_t R, int E, int64_t nt, int k_tiles, int mode) {
+    if (R < 8 * (int64_t)E || R > 32 * (int64_t)E || k_tiles < 16) return false;
+    const int64_t merged = E * nt, single = R * nt / 16 + merged / 2;
+    return mode >= MOE_LAUNCH_RESIDENT || merged >= 2 * kCus || (single + kCus - 1) / kCus > (merged + kCus - 1) / kCus;
+}
+static_assert(merges16(64 * 8, 64, 11, 16, MOE_LAUNCH_AUTO) && !merges16(64 * 8 - 1, 64, 11, 16, MOE_LAUNCH_AUTO), "many tiles");
+static_assert(!merges16(8 * 20, 8, 11, 16, MOE_LAUNCH_AUTO) && !merges16(32 * 10, 32, 11, 16, MOE_LAUNCH_AUTO), "few tiles, no round less");
+static_assert(merges16(32 * 16, 32, 11, 16, MOE_LAUNCH_AUTO) && merges16(16 * 16, 16, 16, 32, MOE_LAUNCH_AUTO), "a round less");
+
 // Streaming launch (not called in MOE_LAUNCH_PER_TILE): as many workgroups as stay resident at once, grid is only an upper
 // bound here.  256-wide tiles: from two
 // tiles per workgroup on, counted by the bound.  128-wide ones: once more are expected than the CUs hold in the two-workgroup form
@@ -199,29 +218,24 @@ int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t
 // streams in the two-workgroup form, from two tiles per workgroup on (256 experts, K = 128, 2233 tiles: 30 us, 34 per tile).
 // (Between one and two 256-wide tiles per CU the deep form is kept: a uniform routing of 5 tokens, 297 tiles, takes 62 us with
 // it and 55 with two workgroups per CU, but a skewed one of the same size, 176 tiles, 29 and 38.)
-// CS, CW: with room for the rows of several of the map's tiles (see moe_gemm_stream_kernel), from 8 to 32 rows per expert on average
-// and 16 k-tiles on.  Below, nearly every expert has one tile, and the larger task function costs 1 to 3 % (64 experts, 2048 ->
-// 2816, fp8, 32 tokens); beyond, few experts are left with too few workgroups (8 experts, K = 256, 75 rows each: 7.4 -> 11.5 us), and
-// such maps are not the default; with a short K the rows of a full tile take longer than its panel (64 experts, 1024 -> 2048, fp8, a
-// skewed routing of 200 tokens 28.6 -> 35.0).
+// CS, CW: with room for the rows of several of the map's tiles, see merges16.
 template <class C, class C2, class CW1, class CS, class CW>
 int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
     const double expected = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
     bool launched = false;
-    const int64_t R = (int64_t)a.T * a.k;
-    const bool several = R >= 8 * (int64_t)a.E && R <= 32 * (int64_t)a.E && a.K / C::BK >= 16;
+    auto several = [&](int bn) { return merges16((int64_t)a.T * a.k, a.E, a.N / bn, a.K / C::BK, mode); };
     static_assert(CS::BN == C::BN && CS::LDS_BYTES == C::LDS_BYTES && CS::NT == C::NT, "the streamed tile is the same but for its rows");
     if constexpr (CW::BN == 2 * C::BN) {
         if (a.N % CW::BN == 0) {
             const int64_t pairs = ((grid - kSpareSlots) / 2 + 7) / 8 * 8;
-            const int rc = several ? launch_stream_kernel<CW, 2>(a, pairs, mode, s, expected > kCus, &launched)
-                                    : launch_stream_kernel<CW1, 2>(a, pairs, mode, s, expected > kCus, &launched);
+            const int rc = several(CW::BN) ? launch_stream_kernel<CW, 2>(a, pairs, mode, s, expected > kCus, &launched)
+                                            : launch_stream_kernel<CW1, 2>(a, pairs, mode, s, expected > kCus, &launched);
             if (rc != MOE_OK || launched) return rc;
         }
     }
     const bool many = C::BN == 256 ? grid >= 2 * kCus : expected > 2 * kCus;
-    const int rc = several ? launch_stream_kernel<CS, 1>(a, grid, mode, s, many, &launched)
-                            : launch_stream_kernel<C, 1>(a, grid, mode, s, many, &launched);
+    const int rc = several(C::BN) ? launch_stream_kernel<CS, 1>(a, grid, mode, s, many, &launched)
+                                  : launch_stream_kernel<C, 1>(a, grid, mode, s, many, &launched);
     if (rc != MOE_OK || launched) return rc;
     if (a.K / C::BK < C::NS) {
         const int rc2 = launch_stream_kernel<C2, 1>(a, grid, mode, s, grid >= 4 * kCus, &launched);
