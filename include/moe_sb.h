@@ -359,6 +359,11 @@ int moe_grouped_gemm_tail_split(const void* X, const void* W, const void* task_m
                                 void* workspace, size_t workspace_bytes, void* stream);
 /* HOST, pure; 0 for a tile shape without a tail-split launch. */
 size_t moe_tail_split_workspace_bytes(int tile_m, int tile_n);
+/* Whether to take moe_grouped_gemm_tail_split, on 256 x 256 tiles with 32 slack rows, for a bf16 product of these sizes (HOST, pure):
+ * 1 where, under a uniform routing, the last round of such tiles splits into parts that beat the other forms (moe_default_tiling,
+ * moe_default_k_parts), or an uneven one gains by it and a uniform one loses at most a few percent; else 0.  Only from 112 k-tiles
+ * of 64 on.  MOE_ERR_INVALID_ARG (negative) on bad arguments. */
+int moe_default_tail_split(int T, int k, int E, int K, int N);
 
 /* Bytes of workspace moe_grouped_gemm_splitk needs (0 for k_parts < 2 or bad sizes).  HOST, pure. */
 size_t moe_splitk_workspace_bytes(int T, int k, int N, int k_parts);

@@ -50,7 +50,7 @@ EXPORTS = [
     "moe_task_map_status", "moe_task_map_expand", "moe_grouped_gemm", "moe_tile_supported", "moe_combine",
     "moe_grouped_gemm_splitk", "moe_splitk_workspace_bytes", "moe_default_k_parts",
     "moe_grouped_gemm_splitk_static", "moe_splitk_static_scratch_bytes",
-    "moe_grouped_gemm_batched", "moe_reduce_task_tiles", "moe_grouped_gemm_tail_split", "moe_tail_split_workspace_bytes",
+    "moe_grouped_gemm_batched", "moe_reduce_task_tiles", "moe_grouped_gemm_tail_split", "moe_tail_split_workspace_bytes", "moe_default_tail_split",
     "moe_strerror",
 ]
 
@@ -149,6 +149,8 @@ def lib() -> ctypes.CDLL:
         L.moe_grouped_gemm_tail_split.restype = ctypes.c_int
         L.moe_grouped_gemm_tail_split.argtypes = [ctypes.c_void_p] * 4 + [ctypes.POINTER(moe_gemm_desc), ctypes.c_void_p,
                                                                           ctypes.c_size_t, ctypes.c_void_p]
+        L.moe_default_tail_split.restype = ctypes.c_int
+        L.moe_default_tail_split.argtypes = [ctypes.c_int] * 5
         L.moe_tail_split_workspace_bytes.restype = ctypes.c_size_t
         L.moe_tail_split_workspace_bytes.argtypes = [ctypes.c_int, ctypes.c_int]
         L.moe_splitk_workspace_bytes.restype = ctypes.c_size_t
@@ -374,6 +376,14 @@ def moe_tail_split_workspace_bytes(tile_m: int = 256, tile_n: int = 256) -> int:
     return int(lib().moe_tail_split_workspace_bytes(tile_m, tile_n))
 
 
+def moe_default_tail_split(T: int, k: int, E: int, K: int, N: int) -> bool:
+    """Whether moe_grouped_gemm_tail_split on 256 x 256 tiles with 32 slack rows is the form to take for a product of these sizes."""
+    rc = int(lib().moe_default_tail_split(T, k, E, K, N))
+    if rc < 0:
+        raise MoeError(rc, "moe_default_tail_split")
+    return rc == 1
+
+
 def moe_grouped_gemm_tail_split(X: torch.Tensor, W: torch.Tensor, task_map: torch.Tensor, Y: torch.Tensor, desc: "GemmDesc",
                                 workspace: Optional[torch.Tensor], check: bool = True) -> int:
     """moe_grouped_gemm with the tiles of a partly filled last round split along K; `workspace`: device tensor of
@@ -426,21 +436,9 @@ class MoeLayerPlan:
 
     The second product sees the T*k activated rows as tokens of their own, each routed to exactly one expert
     (the flattened routing with k = 1), so one build writes both maps and the same entry point serves both products (the
-    second one with its last round of tiles in parts along K, see _long_down, or in its split-k form where
+    second one with its last round of tiles in parts along K, where moe_default_tail_split says so, or in its split-k form where
     moe_default_k_parts says so, with a workspace held here).  Nothing here computes:
     the plan holds caller-visible device buffers and issues calls on the current stream."""
-
-    @staticmethod
-    def _long_down(R: int, E: int, inter: int, hidden: int) -> bool:
-        """Whether the down product takes moe_grouped_gemm_tail_split on 256-row tiles.  With a long K and few tiles a partly
-        filled last round costs most of the product; which routing leaves which rest is only known on the device, where that call
-        decides.  8 experts, 14336 -> 4096, us, the tiling or split-k otherwise taken / this: uniform routing of 400 rows 149 / 147,
-        666 157 / 156, 1400 188 / 190, 2000 332 / 228, 8192 719-885 / 715-780; skewed 400 217 / 152, 666 237 / 166, 1400 301 / 289,
-        2000 309 / 276, 4094 498 / 437, 8192 835 / 771; 2 rows 59 / 41, 4 rows 76 / 75, 8 rows 109 / 98.  Between 96 and 120 rows per
-        expert a skewed routing fills more than half a round of 256-row tiles and the narrow tiles stay (800 rows 251 / 273); from
-        2 to 12 rows every expert has one tile and both take the same time."""
-        rows = R / E
-        return R > 0 and inter % 64 == 0 and inter >= 7168 and hidden % 256 == 0 and (rows <= 2 or 12 <= rows <= 96 or rows >= 120)
 
     @staticmethod
     def _few_tiles(g: Tiling, R: int, E: int, hidden: int) -> Tiling:
@@ -455,7 +453,7 @@ class MoeLayerPlan:
         R = T * k
         self.g1 = moe_default_tiling(MOE_DTYPE_BF16, T, k, E, hidden, 2 * inter)
         # the down product is the short-grid case (few experts, N = hidden): split along K where that pays
-        self.tail_split = self._long_down(R, E, inter, hidden)
+        self.tail_split = R > 0 and moe_default_tail_split(R, 1, E, inter, hidden)
         self.k_parts = moe_default_k_parts(R, 1, E, inter, hidden) if R > 0 and not self.tail_split else 1
         if self.tail_split:
             self.g2, nbytes = Tiling(256, 256, tile_m_slack=32), moe_tail_split_workspace_bytes(256, 256)

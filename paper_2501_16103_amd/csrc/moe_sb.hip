@@ -593,6 +593,15 @@ int launch_tail_split(const GemmArgs& a, int64_t grid, hipStream_t s) {
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+// Tiles of 256 rows, with 32 slack rows on an expert's last one, that a uniform routing gives each XCD.  An expert that is hit has a
+// tile, and one more for every 256 rows from the 33rd beyond its first tile on; its count of rows is taken as normal around the mean.
+double expected_tiles_per_xcd(int64_t R, int E, int64_t nt) {
+    const double hit = E * (1.0 - pow(1.0 - 1.0 / E, (double)R)), rows = R / hit, spread = sqrt(2.0 * rows);
+    double m_tiles = 1.0;
+    for (double more = 288.0; more < rows + 4.0 * spread; more += 256.0) m_tiles += 0.5 * erfc((more - rows) / spread);
+    return hit * m_tiles * (double)nt / 8.0;
+}
+
 // This device's address of the static scratch array, looked up once per device (with that device current) and
 // kept: every GPU the library runs on holds its own copy of the array at its own address.  In host code the
 // array's name is only a handle for this lookup, never a device address.
@@ -864,6 +873,34 @@ int moe_grouped_gemm_splitk(const void* X, const void* W, const void* task_map, 
     if (!workspace || ((uintptr_t)workspace & 15)) return MOE_ERR_INVALID_ARG;
     if (workspace_bytes < moe_splitk_workspace_bytes(d->T, d->k, d->N, k_parts)) return MOE_ERR_INVALID_ARG;
     return run_splitk(X, W, task_map, Y, d, k_parts, static_cast<float*>(workspace), static_cast<hipStream_t>(stream));
+}
+
+int moe_default_tail_split(int T, int k, int E, int K, int N) {
+    if (T < 0 || k < 1 || E < 1 || k > E || K < 1 || N < 1) return MOE_ERR_INVALID_ARG;
+    const int64_t R = (int64_t)T * k;
+    const int kt = K / 64;
+    if (R == 0 || R > (1 << 24) || K % 64 != 0 || N % 256 != 0 || kt < 112) return 0;   // (more rows than a map holds)
+    const double rows = (double)R / E, t = expected_tiles_per_xcd(R, E, N / 256);
+    // Which routing leaves which rest of a round is only known on the device, where the call decides; what decides here is the rest that
+    // a uniform one leaves.  Down products, weights at another place in each call, us, the tiling or split-k otherwise taken / the tail
+    // split, for a uniform and a skewed routing:
+    // A last round that splits into parts by itself.  14336 -> 5120, 4 experts, 8 rows each 117 / 94 and 118 / 94; 8192 -> 4096, 6 experts,
+    // 32 rows 76 / 68 and 82 / 73; 7168 -> 2048, 8 experts, 48 rows 52 / 46 and 72 / 58; 32 experts, 8 rows in all 49 / 32 and 49 / 32.
+    if (t <= 13) return tail_parts(t < 1.5 ? 1 : (int)(t + 0.5), kt, 256) > 1;
+    // More tiles run in two parts, where 128 x 128 tiles fill the chip as well: with a uniform routing that is as long or up to
+    // 5 % longer, but a skewed one gains.  From K = 10240 on, unless every expert has a handful of rows: 14336 -> 4096, 8 experts, 12 rows
+    // 142 / 143 and 145 / 143, 64 rows 150 / 151 and 226 / 169, but 4 rows 141 / 142 and 140 / 142; 7168 -> 2048, 16 experts, 64 rows 80 / 85 and
+    // 110 / 140.  Beyond 96 rows a skewed one fills more than half a round (14336 -> 4096, 8 experts, 110 rows 0.98 and 1.05 to 1.11 of the
+    // time).  Where split-k is the other form (120 rows and more) at any K: 7168 -> 4096, 8 experts, 160 rows 110 / 111 and 165 / 140.
+    if (t <= 16.5) return tail_parts(16, kt, 256) > 1 && (rows >= 120 || (rows >= 12 && rows <= 96 && kt >= 160));
+    // One full round, where rows can differ enough for the rest to be open: the second launch costs 1 to 2 % if there is none.
+    // 14336 -> 4096, 16 experts, 160 rows 320 / 324 and 528 / 407; 8192 -> 8192, 8 experts, 64 rows 169 / 171 and 215 / 181, but 24 rows 164 / 166
+    // and 163 / 166 (7168 -> 2048, 32 experts, 2 rows 139 / 126 and 96 / 98: mostly empty tiles are left to the 16-row launch).
+    if (t <= 40) return rows >= 32;
+    // Up to three rounds of 256-row tiles, whose last one is the same, four where experts have several tiles: 14336 -> 4096, 8 experts, 1024
+    // rows 704 / 707 and 864 / 741, 16 experts 1590 / 1451 and 1623 / 1516; 7168 -> 2048, 64 experts, 256 rows 494 / 458 and 590 / 565, but 96 rows
+    // (128-row tiles otherwise) 300 / 302 and 368 / 388.  7168 -> 4096, 64 experts (128 tiles per XCD), 64 to 400 rows: 0.98 to 1.08 of the time.
+    return (t <= 100 && rows >= 120) || (t <= 140 && rows >= 512);
 }
 
 size_t moe_splitk_static_scratch_bytes(void) { return kStaticScratchBytes; }

@@ -150,6 +150,33 @@ def test_splitk_host_functions():
     assert lib.moe_grouped_gemm_splitk(16, 16, 16, 16, None, 2, 16, 1 << 30, None) == mb.MOE_ERR_INVALID_ARG
 
 
+def test_default_tail_split():
+    """Host-only: the rest of a round that a uniform routing leaves decides, for any number of experts."""
+    cases = {  # R, E, K, N
+        True: [(2, 8, 14336, 4096), (8, 8, 14336, 4096), (96, 8, 14336, 4096), (666, 8, 14336, 4096), (8192, 8, 14336, 4096),   # the Mixtral sizes
+               (64, 8, 7168, 2048), (384, 8, 7168, 2048), (16, 4, 14336, 5120), (192, 6, 8192, 4096), (1280, 8, 7168, 4096),     # a rest that splits
+               (2560, 16, 14336, 4096), (512, 8, 8192, 8192), (64 * 256, 64, 7168, 2048), (16384, 16, 14336, 4096)],                                       # full rounds before it
+        False: [(16, 8, 14336, 4096), (32, 8, 14336, 4096),                       # 14 and 16 tiles per XCD, a handful of rows
+                (880, 8, 14336, 4096),                                            # a skewed routing fills more than half a round
+                (512, 8, 7168, 4096), (1024, 16, 7168, 2048), (8, 8, 7168, 8192),  # 16, 16 and 21 tiles, K too short for two parts to pay
+                (64, 64, 7168, 2048), (256, 128, 7168, 2048), (32, 32, 7168, 7168), (64, 32, 7168, 2048),   # rounds of nearly empty tiles
+                (96 * 64, 64, 7168, 2048), (300 * 64, 64, 7168, 4096),             # several rounds
+                (666, 8, 7104, 4096), (666, 8, 14336, 4000), (666, 8, 14340, 4096), (0, 8, 14336, 4096)],
+    }
+    for want, sizes in cases.items():
+        for R, E, K, N in sizes:
+            assert mb.moe_default_tail_split(R, 1, E, K, N) == want, (R, E, K, N)
+            assert mb.moe_default_tail_split(R // 2, 2, E, K, N) == want or R % 2 or E < 2
+    with pytest.raises(mb.MoeError):
+        mb.moe_default_tail_split(8, 20, 16, 14336, 4096)
+    # a layer plan follows it, and holds a workspace only then
+    for T, k, E, hidden, inter, tail in ((1, 2, 8, 4096, 14336, True), (8, 2, 8, 4096, 14336, False), (333, 2, 8, 4096, 14336, True),
+                                         (64, 2, 64, 2048, 7168, False)):
+        plan = mb.MoeLayerPlan(T, k, E, hidden, inter, "cpu")
+        assert plan.tail_split == tail and (plan.workspace is not None) == tail
+        assert not tail or plan.workspace.numel() * 4 == mb.moe_tail_split_workspace_bytes(256, 256) == 8 * 32 * 288 * 256 * 4
+
+
 def test_default_tiling_is_supported_and_matches_the_benchmark_choices():
     """Host-only: the heuristic returns a tiling a kernel exists for, and reproduces the tilings the benchmark
     points were tuned to (slack rows aside, where the heuristic always enables them for 256-row tiles)."""
