@@ -442,10 +442,12 @@ class MoeLayerPlan:
 
     @staticmethod
     def _few_tiles(g: Tiling, R: int, E: int, hidden: int) -> Tiling:
-        """A token's down product on at most three quarters as many 128-wide 16-row tiles as there are CUs runs on 128 x 128 tiles
-        instead, which the launch halves: twice the workgroups, of eight wavefronts (64 experts, 1408 -> 2048, us: 6 rows 11.3 / 9.8,
-        12 rows 14.6 / 13.9; 16 experts, 1024 -> 4096, 2 rows 10.0 / 9.2; 8 experts, 2048 -> 8192, 1 row 15.2 / 13.6)."""
-        narrow = (g.tile_m, g.tile_n) == (16, 128) and min(R, E) * (hidden // 128) <= 192
+        """A token's down product on at most half as many 128-wide 16-row tiles as there are CUs runs on 128 x 128 tiles instead, which
+        the launch halves then: twice the workgroups, of eight wavefronts (us: 64 experts, 1408 -> 2048, 6 rows 13.0 / 11.2; 4096 -> 1024,
+        16 rows 32.6 / 25.7; 16 experts, 1024 -> 4096, 4 rows 11.5 / 9.5; 8 experts, 2048 -> 8192, 2 rows 17.7 / 15.0).  Beyond half, they
+        would not be halved (64 experts, 1408 -> 2048, 12 rows 15.7 / 15.6; 384 -> 2048, 12 rows 7.0 / 7.5; 32 experts, 512 -> 2048, 12
+        rows 7.7 / 8.3)."""
+        narrow = (g.tile_m, g.tile_n) == (16, 128) and min(R, E) * (hidden // 128) <= 128
         return Tiling(128, 128) if narrow else g
 
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):

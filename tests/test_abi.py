@@ -177,6 +177,14 @@ def test_default_tail_split():
         assert not tail or plan.workspace.numel() * 4 == mb.moe_tail_split_workspace_bytes(256, 256) == 8 * 32 * 288 * 256 * 4
 
 
+def test_layer_plan_takes_wide_tiles_only_where_they_are_halved():
+    """Host-only: 128 x 128 tiles for a token's down product, up to 16 per XCD -- the rests that the launch runs as half tiles."""
+    for T, k, E, hidden, inter, want in ((1, 6, 64, 2048, 1408, (128, 128)), (2, 6, 64, 2048, 1408, (16, 128)), (4, 4, 64, 1024, 4096, (128, 128)),
+                                         (6, 4, 64, 1024, 4096, (16, 128)), (2, 6, 64, 2048, 384, (16, 128)), (3, 4, 32, 2048, 512, (16, 128))):
+        plan = mb.MoeLayerPlan(T, k, E, hidden, inter, "cpu")
+        assert (plan.g2.tile_m, plan.g2.tile_n) == want, (T, k, E, hidden, inter)
+
+
 def test_default_tiling_is_supported_and_matches_the_benchmark_choices():
     """Host-only: the heuristic returns a tiling a kernel exists for, and reproduces the tilings the benchmark
     points were tuned to (slack rows aside, where the heuristic always enables them for 256-row tiles)."""
