@@ -618,48 +618,42 @@ def test_heterogeneous_batch_argument_errors(dev):
     assert bool((out == 7.0).all()) and bool((Y == 7.0).all())
 
 
-def _tail_blocks(total, k_tiles, cus=32):
+def _tail_blocks(total, k_tiles, tile_m):
     """Block indices that a tail-split launch runs in parts, and the number of parts, per the rule in moe_sb.h
-    (ascending sigma order: XCD x owns blocks [x * ceil(total / 8), ...))."""
+    (ascending sigma order: XCD x owns blocks [x * ceil(total / 8), ...)); and the blocks of the workspace they fill."""
     per_xcd = (total + 7) // 8
-    out = {}
+    out, work = {}, set()
     for x in range(8):
         n_x = max(0, min(per_xcd, total - x * per_xcd))
-        full = n_x // cus * cus
-        t = n_x - full
-        parts, best = 1, 4     # length of the last round in quarters of a tile
-        for P in (2, 4):
-            if t == 0 or k_tiles % P or k_tiles // P < 8:
-                break
-            length = -(-t * P // cus) * (4 // P)
-            if length < best:
-                parts, best = P, length
+        t = n_x % 32
+        parts = H.tail_parts(t, k_tiles, tile_m)
         if parts > 1:
-            for B in range(x * per_xcd + full, x * per_xcd + n_x):
+            work |= set(range(x * 32, x * 32 + t * parts))
+            for B in range(x * per_xcd + n_x - t, x * per_xcd + n_x):
                 out[B] = parts
-    return out
+    return out, work
 
 
 TAIL_CASES = [
     # tile_m, per-expert row counts (k = 1), K, N  (tile_n = 256)                    tiles -> tail of each XCD
-    (256, [300, 0, 513, 129, 255, 700], 2048, 1024),        # 40 tiles: 5 per XCD, all of them tail, 4 parts
-    (256, [257, 320, 321, 256, 1, 64, 65, 0, 576], 1024, 512),   # 26 tiles, 4 per XCD (the last XCD fewer), K = 1024: 2 parts at most
-    (256, [9000, 6000, 4100], 2048, 1024),                  # 77 m-tiles x 4: 308 tiles, 39 per XCD: 32 whole + 7 tail tiles, 4 parts
-    (256, [5000, 5200, 3000], 2048, 1024),                  # 212 tiles, 27 per XCD: no split shortens the round
-    (256, [4000, 5200, 2000], 2048, 1024),                  # 180 tiles, 23 per XCD: 4 parts in three sub-rounds
-    (256, [300, 200], 512, 256),                            # K too short to split: everything runs whole
-    (128, [70, 3, 140, 129, 300], 2048, 1024),              # 128-row tiles (and the 64-row task function for the small ones)
-    (128, [2000, 2100, 900], 1024, 2048),                   # 41 m-tiles x 8 = 328 tiles: 32 whole + 9 tail per XCD, 2 parts
-    (64, [172, 107, 61, 39, 52, 23, 32, 26], 2048, 1024),   # 64-row tiles, the row counts of a skewed routing
-    (-256, [1025, 1040, 991, 1055, 280, 300], 2048, 512),   # (negative: 32 slack rows) tail tiles of 257 .. 287 rows
-    (-256, [9000, 6000, 4113], 2048, 1024),                 # slack rows, whole rounds and a tail
+    (256, [300, 0, 513, 129, 255, 700], 2560, 1024),        # 40 tiles: 5 per XCD, all of them tail, 5 parts
+    (256, [257, 320, 321, 256, 1, 64, 65, 0, 576], 2304, 512),   # 26 tiles, 4 per XCD (the last XCDs fewer): 4 parts at most
+    (256, [9000, 6000, 4100], 2560, 1024),                  # 77 m-tiles x 4: 308 tiles, 39 per XCD: 32 whole + 7 tail tiles, 4 parts
+    (256, [5000, 5200, 3000], 2048, 1024),                  # 212 tiles, 27 per XCD: more than half a round, whole
+    (256, [4000, 5200, 2000], 2048, 1024),                  # 180 tiles, 23 per XCD: whole
+    (256, [300, 200], 512, 256),                            # K too short to split: everything runs whole or as halves
+    (128, [70, 3, 140, 129, 300], 2560, 1024),              # 128-row tiles (and the 64-row task function for the small ones), 5 parts
+    (128, [2000, 2100, 900], 4096, 2048),                   # 41 m-tiles x 8 = 328 tiles: 32 whole + 9 tail per XCD, 3 parts
+    (64, [172, 107, 61, 39, 52, 23, 32, 26], 2048, 1024),   # 64-row tiles, the row counts of a skewed routing: 6 per XCD, 4 parts
+    (-256, [1025, 1040, 991, 1055, 280, 300], 2560, 512),   # (negative: 32 slack rows) tail tiles of 257 .. 287 rows, 5 parts
+    (-256, [9000, 6000, 4113], 2560, 1024),                 # slack rows, whole rounds and a tail
 ]
 
 
 @pytest.mark.parametrize("tile_m,counts,K,N", TAIL_CASES)
 def test_tail_split_parity(dev, oracle_mod, tile_m, counts, K, N):
-    """The tiles of a partly filled last round run in 2 or 4 parts along K: Y == oracle, nothing outside Y, every
-    element written; every tile outside the tails bit for bit what moe_grouped_gemm gives."""
+    """The tiles of a partly filled last round run in parts along K: Y == oracle, nothing outside Y, every
+    element written; every tile outside the tails bit for bit what moe_grouped_gemm gives; the workspace shows which parts ran."""
     from tests.test_gpu_parity import _build_map, _check_y, _ids_from_counts
     slack = 32 if tile_m < 0 else 0
     tile_m = abs(tile_m)
@@ -685,7 +679,11 @@ def test_tail_split_parity(dev, oracle_mod, tile_m, counts, K, N):
     assert not np.any(got == POISON), "an output was never written"
     tm = oracle_mod.build_task_map(ids.numpy(), T, 1, E, tile_m, 256, N, tile_m_slack=slack)
     table = oracle_mod.full_table(tm.counts, tile_m, 256, N, tile_m_slack=slack)
-    tails = _tail_blocks(tm.total_tiles, K // 64)
+    tails, work = _tail_blocks(tm.total_tiles, K // 64, tile_m)
+    used = 256 * (tile_m + slack) * 256
+    blocks = torch.isfinite(ws[guard: guard + used].view(256, -1)).any(dim=1).nonzero().flatten().tolist()
+    assert set(blocks) == work, "other parts ran than the rule says"
+    assert bool(tails) == (K > 2048 or tile_m == 64), "the cases with a long K must exercise the split"
     if T <= 3000:
         res = oracle_mod.grouped_gemm_bf16(wk.bits(X), wk.bits(W), ids.numpy())
         _check_y(got, res, X.double().numpy(), W.double().numpy(), ids.numpy(), 1, K, H.tol_bf16(K))
@@ -716,8 +714,6 @@ def test_tail_split_parity(dev, oracle_mod, tile_m, counts, K, N):
         np.testing.assert_array_equal(got[rr, n_tile * 256:(n_tile + 1) * 256], plain[rr, n_tile * 256:(n_tile + 1) * 256])
         whole += 1
     assert whole + len(tails) == tm.total_tiles
-    if K >= 1024 and tm.total_tiles not in (212,):
-        assert len(tails) > 0, "the case must exercise the split"
     if not tails:
         np.testing.assert_array_equal(got, plain)
 
