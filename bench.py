@@ -201,11 +201,15 @@ class Point:
                     kernel=self.kernel_name())
 
     def kernel_name(self) -> str:
-        """The kernel moe_grouped_gemm runs this point with (16-row tiles: resident or one workgroup per tile, by size)."""
+        """The kernel that runs this point's product (16-row tiles: resident or one workgroup per tile, by size)."""
         wl = self.wl
+        if self.tail_ws is not None:
+            return "moe_gemm_tail_kernel"
         if self.small[0]:
             return "moe_gemm_pipe2_kernel"
         tile = (wl.dtype, wl.tile_m, wl.tile_n)
+        if self.w_nk and tile == ("bf16", 256, 256) and self.slack == 0 and self.launch_mode != mb.MOE_LAUNCH_PER_TILE:
+            return "moe_gemm_absorb_kernel"
         if not self.w_nk and self.slack in (0, 32) and tile in (("bf16", 256, 256), ("bf16", 128, 256), ("bf16", 128, 128), ("fp8", 256, 256)):
             return "moe_gemm_halves_kernel"
         return "moe_gemm_stream_kernel / moe_gemm_pipe_kernel" if wl.tile_m == 16 and not self.w_nk else "moe_gemm_pipe_kernel"

@@ -1380,7 +1380,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
 }
 
 // One tiling strategy without slack rows in the map, run as if the map had OVER::SLACK of them: an expert's last tile of so few rows
-// would move a whole weight panel for them (and takes three quarters of a full tile's time), so the tile before takes
+// would move a whole weight panel for them (and takes half to three quarters of a full tile's time), so the tile before takes
 // them along (OVER: the full task function with room for them).  Each wavefront works out the TilePrefix of that tiling from
 // the task records in its lanes, so the XCDs share the tiles that are left evenly (with the absorbed tiles as workgroups without work
 // instead, an XCD that held many of them ended early and nothing was gained: 3000 tokens 1060 -> 1145 us).
