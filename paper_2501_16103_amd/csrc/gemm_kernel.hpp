@@ -1155,7 +1155,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             }
         }
         if constexpr (STAGED) {
-            // read the corner back row by row: cu 16-byte chunks per row, 64 / cu rows per instruction
+            // read the corner back row by row: cu 16-byte chunks per row, 64 / cu rows per instruction.  The stores are whole 128-byte lines
+            // that this launch does not read again, and go out non-temporally: kept in L2 they push out the weight panels and token rows that
+            // the workgroups share (a round of 256 tiles writes as much as all L2s hold), and what is still there at the end of the
+            // launch is written back then.  64 experts, 2048 -> 3072, plain / non-temporal, us: bf16 32 rows each 136 / 127, 128 rows 160 / 145,
+            // 256 rows 208 / 198, 512 rows 350 / 346; fp8 78 / 73, 97 / 91, 128 / 115, 205 / 201.  (Write-through without the hint is as good
+            // up to 128 rows and no better than plain stores beyond.)
             wait_vmcnt<0>();   // the row ids, long since there; told here so that no wait lands between the stores
             const int cu = cu_;
             const int rpi = 64 / cu;
@@ -1167,7 +1172,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 const int r = r_pass[pass];
                 if (r >= 0) {
                     const u32x4_t v = *reinterpret_cast<const u32x4_t*>(stage + lr * RBMAX + ((c ^ (lr & (CPROF - 1))) << 4));
-                    *reinterpret_cast<u32x4_t*>(Yb + (size_t)r * y_row_bytes + col_bytes) = v;
+                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(Yb + (size_t)r * y_row_bytes + col_bytes));
                 }
             }
         }
