@@ -38,6 +38,7 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 #define MOE_LDS(T) __attribute__((address_space(3))) T
 
 constexpr int kXcdCus = 32;   // CUs of each of the 8 XCDs
+constexpr int kOnceTiles = 192;   // 256-wide tiles of a launch from which on weights that one tile reads are fetched non-temporally (see pipe_tile)
 
 struct GemmArgs {
     const void* X;
@@ -385,7 +386,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // Resident workgroups that stream one tile after the other always gain from it (tiles of 256 columns, weights at another place in
     // each launch; without / with, fp8): 32 experts, 4096 -> 4096, 112 tiles 31.8 / 29.8, 128 tiles 32.5 / 30.7; 64 experts, 2048 -> 2816,
     // 132 tiles 18.0 / 16.5, 187 tiles 20.8 / 18.3; 8 experts, 88 tiles 19.7 / 18.2.
-    const bool nt_ok = STREAM || tc.streams >= 256 || (C::BN == 256 && tc.streams >= 192);
+    const bool nt_ok = STREAM || tc.streams >= 256 || (C::BN == 256 && tc.streams >= kOnceTiles);
     bool w_once = nt_ok && tc.m_tiles == 1, w_once_next = false;
     // j-th token-row / weight-row DMA instruction of this wave for k-tile kt, into ring stage `stage`
     auto dma_x = [&](int j, int kt, int stage, bool next) __attribute__((always_inline)) {
@@ -408,13 +409,17 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     static_assert(!C::WHALF || (W_FOLD && C::EARLY_W && WI % 2 == 0 && !STREAM), "half-stage weight ring");
     auto dma_wh = [&](int jj, int q, int hs) __attribute__((always_inline)) {
         const char* src = Wt + (size_t)q * (w_kt_stride / 2) + (size_t)(jj * NW * WROWS_PER_INST) * w_row_bytes;
-        dma16(dw_off[0], src, lds0 + C::W_RING + hs * C::WH_BYTES + (jj * NW + wave) * 1024);
+        const uint32_t dst = lds0 + C::W_RING + hs * C::WH_BYTES + (jj * NW + wave) * 1024;
+        if constexpr (C::ALONE) dma16_nt(dw_off[0], src, dst);
+        else dma16(dw_off[0], src, dst);
     };
 
     // quarter-stage weight ring: this wave's instruction for quarter j of k-tile kt, into quarter q of the ring
     auto dma_wq = [&](int j, int kt, int q) __attribute__((always_inline)) {
-        dma16(dw_off[W_FOLD ? 0 : j], Wt + (size_t)kt * w_kt_stride + (W_FOLD ? (size_t)j * w_fold : (size_t)0),
-              lds0 + C::W_RING + q * C::WQ_BYTES + wave * 1024);
+        const char* src = Wt + (size_t)kt * w_kt_stride + (W_FOLD ? (size_t)j * w_fold : (size_t)0);
+        const uint32_t dst = lds0 + C::W_RING + q * C::WQ_BYTES + wave * 1024;
+        if constexpr (C::ALONE) dma16_nt(dw_off[W_FOLD ? 0 : j], src, dst);
+        else dma16(dw_off[W_FOLD ? 0 : j], src, dst);
     };
 
     if (C::EARLY_W) {
@@ -827,14 +832,14 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 if constexpr (STEADY) {
                     if constexpr (C::WQUART) dma_wq(j, kt + 2, quarter(j));
                     else if constexpr (C::WHALF) dma_wh(j, 2 * kt + 4, prevw);
-                    else dma_w(j, kt + 2, prevw, false, 0);
+                    else dma_w(j, kt + 2, prevw, false, C::ALONE);
                 }
             };
             auto wb = [&](int j) __attribute__((always_inline)) {
                 if constexpr (STEADY) {
                     if constexpr (C::WQUART) dma_wq(WH + j, kt + 2, quarter(WH + j));
                     else if constexpr (C::WHALF) dma_wh(j, 2 * kt + 5, curw);
-                    else dma_w(WH + j, kt + 2, prevw, false, 0);
+                    else dma_w(WH + j, kt + 2, prevw, false, C::ALONE);
                 }
             };
             // (quarters: slot 2 issues one weight instruction, and the last one, whose quarter slot 3 frees, follows the token rows)
@@ -855,7 +860,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 // After slot 1 nobody reads tile kt any more.  Slot 1 refills the weight stage freed one k-tile earlier,
                 // slot 2 the token stage just freed; at the wait only slot 1's weight instructions may be in flight.
                 auto wt = [&](int j) __attribute__((always_inline)) {
-                    if constexpr (STEADY) dma_w(j, kt + 2, prevw, false, 0);
+                    if constexpr (STEADY) dma_w(j, kt + 2, prevw, false, C::ALONE);
                 };
                 if constexpr (ROLE == 0) {
                     mma(integral_constant<int, WI>{}, wt);
@@ -1384,6 +1389,31 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_pipe_kernel(GemmArgs a) {
     }
 }
 
+// A task function and the narrower ones that share its launch, narrowest first.
+template <class C, class... Tails>
+struct TileFns {
+    using Full = C;
+    static __device__ __forceinline__ void run(const GemmArgs& a, const int32_t* __restrict__ map, const MapLayout& L,
+                                               const TileCoord& tc, char* smem) {
+        run_tile<C, Tails...>(a, map, L, tc, smem);
+    }
+};
+
+// The same with a copy of the full task function for tiles whose expert has no other m-tile: nobody else reads their weights, which are
+// fetched non-temporally there (the hint is part of the instruction; a branch at each of them costs the alternating-role loop 2 to 5 %).
+// Where two m-tiles read a panel it has to stay in L2 until the slower one has it: hinted there too, equal tiles gain (64 experts,
+// 3584 -> 2560, 512 rows each 509 -> 473 us) but unequal ones lose (8 experts, 4096 -> 28672, 375 rows each 689 -> 710, 1024 rows 1497 -> 1562).
+// One tile each, plain / hinted, us: 64 experts, 2048 -> 3072, bf16 140 rows 162 / 151, 192 rows 172 / 166, 256 rows 203 / 194, 280 rows (32 slack)
+// 222 / 205; fp8 256 rows 117 / 114; 8 experts, 4096 -> 28672, 150 rows 399 / 387.
+template <class C, class... Tails>
+struct TileFnsOnce : TileFns<C, Tails...> {
+    static __device__ __forceinline__ void run(const GemmArgs& a, const int32_t* __restrict__ map, const MapLayout& L,
+                                               const TileCoord& tc, char* smem) {
+        if (tc.m_tiles == 1 && tc.rows > C::BM / 2 && tc.streams >= kOnceTiles) pipe_tile<Alone<C>>(a, map, L, tc, smem);
+        else run_tile<C, Tails...>(a, map, L, tc, smem);
+    }
+};
+
 // One tiling strategy without slack rows in the map, run as if the map had OVER::SLACK of them: an expert's last tile of so few rows
 // would move a whole weight panel for them (and takes half to three quarters of a full tile's time), so the tile before takes
 // them along (OVER: the full task function with room for them).  Each wavefront works out the TilePrefix of that tiling from
@@ -1439,18 +1469,8 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_absorb_kernel(GemmArgs a) {
     TileCoord tc = decode_block(map, L, g, B, record);
     tc.streams = total;
     if (tc.rows > C::BM) pipe_tile<OVER>(a, map, L, tc, smem);
-    else run_tile<C, Tails...>(a, map, L, tc, smem);
+    else TileFnsOnce<C, Tails...>::run(a, map, L, tc, smem);
 }
-
-// A task function and the narrower ones that share its launch, narrowest first.
-template <class C, class... Tails>
-struct TileFns {
-    using Full = C;
-    static __device__ __forceinline__ void run(const GemmArgs& a, const int32_t* __restrict__ map, const MapLayout& L,
-                                               const TileCoord& tc, char* smem) {
-        run_tile<C, Tails...>(a, map, L, tc, smem);
-    }
-};
 
 // One tiling strategy, and the tiles of an XCD's last round as two half tiles each (of BN / 2 columns, Half) when that round
 // would fill at most half of the XCD's 32 CUs: it then takes about half as long.  Nothing is added up afterwards -- a half

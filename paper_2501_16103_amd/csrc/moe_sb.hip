@@ -337,8 +337,8 @@ using P8_64x256 = PipeCfg<64, 256, 128, 1, 4, 3, true, 3, 0, false, 32>;
 using Ph_256x128 = PipeCfg<256, 128, 64, 4, 2, 2, false, 3, 64, false, 16>;
 using Ph_64x128 = PipeCfg<64, 128, 64, 2, 4, 4>;
 using Ph_128x64 = PipeCfg<128, 64, 64, 4, 2, 4>;
-using F_256x256 = TileFns<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>;
-using F_256x256s32 = TileFns<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>;
+using F_256x256 = TileFnsOnce<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>;
+using F_256x256s32 = TileFnsOnce<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>;
 using F_128x256 = TileFns<Pb_128x256, Ps_64x256>;
 using H_256x128 = TileFns<Ph_256x128, Ph_64x128, Pb_128x128>;
 using H_128x128 = TileFns<Pb_128x128, Ph_64x128>;
@@ -351,7 +351,7 @@ using S_128x256 = TileFns<SplitK<Pb_128x256>, SplitK<Ps_64x256>>;
 using P8h_256x128 = PipeCfg<256, 128, 128, 4, 2, 2, true, 3, 0, false, 16>;
 using P8h_128x128 = PipeCfg<128, 128, 128, 2, 4, 3, true, 3, 0, false, 32>;
 using P8h_64x128 = PipeCfg<64, 128, 128, 2, 4, 4, true, 4, 0, false, 32>;
-using F8_256x256 = TileFns<P8_256x256, P8s_64x256, P8s_128x256>;
+using F8_256x256 = TileFnsOnce<P8_256x256, P8s_64x256, P8s_128x256>;
 using H8_256x128 = TileFns<P8h_256x128, P8h_64x128, P8h_128x128>;
 
 // The pre-packed weight layout [E][N][K] (K contiguous): the shapes the benchmark uses
