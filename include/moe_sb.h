@@ -306,6 +306,17 @@ int moe_grouped_gemm(const void* X, const void* W, const int32_t* topk_ids, cons
                      const moe_gemm_desc* desc, void* stream);
 
 /*
+ * moe_build_task_map_pair(topk_ids, T, k, E, N, tiling, task_map, N2, tiling2, task_map2, stream), then
+ * moe_grouped_gemm(X, W, topk_ids, task_map, Y, desc, stream): same maps, same product, same errors in the same order (the builds'
+ * first).  A step of a few rows on 16-row tiles takes one launch for both, a 3 us map build less in front of it; everything else
+ * takes the launches of the two calls.  `desc` as for moe_grouped_gemm.
+ */
+int moe_build_task_map_pair_gemm(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map,
+                                 int N2, const moe_tiling* tiling2, void* task_map2, const void* X, const void* W, void* Y,
+                                 const moe_gemm_desc* desc, void* stream);
+
+
+/*
  * The same product for launches too short to give every CU a tile (few experts, a narrow N and a long K: a down
  * projection at several hundred tokens), split along K: every tile of the map (Sec. 3.1: the map is unchanged, a
  * workgroup finds its tile as always) is run by k_parts workgroups, each over one k_parts-th of K; their fp32 sums

@@ -46,7 +46,7 @@ EXPORTS = [
     "moe_map_off_counts", "moe_map_off_offsets", "moe_map_off_sigma", "moe_map_off_tile_prefix",
     "moe_map_off_task_records", "moe_map_off_sorted_rows", "moe_task_map_bytes", "moe_grid_upper_bound", "moe_build_task_map",
     "moe_build_task_map_ordered", "moe_build_task_map_tiled", "moe_grid_upper_bound_tiled", "moe_tile_pair_supported",
-    "moe_build_task_map_ex", "moe_build_task_map_pair", "moe_tiling_supported", "moe_w_layout_supported", "moe_default_tiling",
+    "moe_build_task_map_ex", "moe_build_task_map_pair", "moe_build_task_map_pair_gemm", "moe_tiling_supported", "moe_w_layout_supported", "moe_default_tiling",
     "moe_task_map_status", "moe_task_map_expand", "moe_grouped_gemm", "moe_tile_supported", "moe_combine",
     "moe_grouped_gemm_splitk", "moe_splitk_workspace_bytes", "moe_default_k_parts",
     "moe_grouped_gemm_splitk_static", "moe_splitk_static_scratch_bytes",
@@ -115,6 +115,9 @@ def lib() -> ctypes.CDLL:
         L.moe_build_task_map_pair.restype = ctypes.c_int
         L.moe_build_task_map_pair.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 4 + [
             ctypes.POINTER(moe_tiling), ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(moe_tiling), ctypes.c_void_p, ctypes.c_void_p]
+        L.moe_build_task_map_pair_gemm.restype = ctypes.c_int
+        L.moe_build_task_map_pair_gemm.argtypes = L.moe_build_task_map_pair.argtypes[:-1] + [ctypes.c_void_p] * 3 + [
+            ctypes.POINTER(moe_gemm_desc), ctypes.c_void_p]
         L.moe_tiling_supported.restype = ctypes.c_int
         L.moe_tiling_supported.argtypes = [ctypes.c_int, ctypes.POINTER(moe_tiling)]
         L.moe_default_tiling.restype = ctypes.c_int
@@ -341,6 +344,17 @@ def moe_grouped_gemm(X: torch.Tensor, W: torch.Tensor, topk_ids: Optional[torch.
     return rc
 
 
+def moe_build_task_map_pair_gemm(topk_ids: torch.Tensor, T: int, k: int, E: int, N: int, tiling: Tiling, task_map: torch.Tensor,
+                                 N2: int, tiling2: Tiling, task_map2: torch.Tensor, X: torch.Tensor, W: torch.Tensor, Y: torch.Tensor,
+                                 desc: GemmDesc, check: bool = True) -> int:
+    g, g2, d = tiling.c_struct(), tiling2.c_struct(), desc.c_struct()
+    rc = lib().moe_build_task_map_pair_gemm(_ptr(topk_ids), T, k, E, N, ctypes.byref(g), _ptr(task_map), N2, ctypes.byref(g2), _ptr(task_map2),
+                                            _ptr(X), _ptr(W), _ptr(Y), ctypes.byref(d), _stream())
+    if check and rc != MOE_OK:
+        raise MoeError(rc, "moe_build_task_map_pair_gemm")
+    return rc
+
+
 def moe_combine(Y: torch.Tensor, topk_weights: Optional[torch.Tensor], T: int, k: int, N: int, out: torch.Tensor,
                 check: bool = True) -> int:
     rc = lib().moe_combine(_ptr(Y), _ptr(topk_weights), T, k, N, _ptr(out), _stream())
@@ -435,8 +449,8 @@ class MoeLayerPlan:
         maps of both products -> gate+up product with the fused gated activation -> down product -> weighted sum.
 
     The second product sees the T*k activated rows as tokens of their own, each routed to exactly one expert
-    (the flattened routing with k = 1), so one build writes both maps and the same entry point serves both products (the
-    second one with its last round of tiles in parts along K, where moe_default_tail_split says so, or in its split-k form where
+    (the flattened routing with k = 1), so one build writes both maps (together with the first product) and the same entry point serves
+    both products (the second one with its last round of tiles in parts along K, where moe_default_tail_split says so, or in its split-k form where
     moe_default_k_parts says so, with a workspace held here).  Nothing here computes:
     the plan holds caller-visible device buffers and issues calls on the current stream."""
 
@@ -482,8 +496,8 @@ class MoeLayerPlan:
         topk_ids int32 [T, k]; topk_weights fp32 [T, k] or None.  Returns out [T, hidden] (the plan's buffer)."""
         T, k, E = self.T, self.k, self.E
         flat = topk_ids.reshape(T * k, 1)
-        moe_build_task_map_pair(topk_ids, T, k, E, 2 * self.inter, self.g1, self.map1, self.hidden, self.g2, self.map2)
-        moe_grouped_gemm(X, W_gate_up, topk_ids, self.map1, self.act, self.d1)
+        moe_build_task_map_pair_gemm(topk_ids, T, k, E, 2 * self.inter, self.g1, self.map1, self.hidden, self.g2, self.map2,
+                                     X, W_gate_up, self.act, self.d1)
         if self.tail_split:
             moe_grouped_gemm_tail_split(self.act, W_down, self.map2, self.down, self.d2, self.workspace)
         elif self.k_parts > 1:

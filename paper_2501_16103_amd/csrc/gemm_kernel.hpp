@@ -240,6 +240,7 @@ struct TileStream {
     moe_tiling tiling;
     const float* xs_lds;                  // LDS copies of x_scale[T] and w_scale[E] (fp8)
     const float* ws_lds;
+    int sorted;                           // routing in registers (see RoutingInLanes): lane p: sorted_rows[p]
 };
 
 // Alg. 2 + 4 on registers (see decode_block): B must be below the total tile count.  With pair = 2 (an even number of
@@ -305,7 +306,8 @@ __device__ __forceinline__ void scalar_load16(const int32_t* p, i32x8_t& lo, i32
 // spreads its live blocks evenly over the wavefront rows.  The loop exists in copies for a compile-time number of
 // blocks per wavefront and in one copy that tests each block at run time; tiles of many 16-row blocks (PERWAVE)
 // have a copy for every live-block count and each wavefront runs its own.
-template <class C, bool STREAM = false>
+// LANES: there is no map; the row ids are those of ts->sorted.
+template <class C, bool STREAM = false, bool LANES = false>
 __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __restrict__ map, const MapLayout& L,
                                           TileCoord tc, char* smem, TileStream* ts = nullptr) {
     constexpr int BN = C::BN, BK = C::BK, ES = C::ES, NT = C::NT, NW = NT / 64, NS = C::NS, NSW = C::NSW, MF = C::MF;
@@ -450,10 +452,12 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     // 16-row (streamed: up to 64-row) tiles: lane j holds the flat row id of tile row j (row 0's for j past the tile's rows).  Streaming: the
     // token's scale comes from LDS, so that no vector-memory wait is ever generated
     int rows_v = 0, rows_v_next = 0;
+    static_assert(!LANES || (ROWS16 && C::BM == 16), "routing in registers: 16-row tiles");
     auto stream_rows = [&](const TileCoord& t, int& rv, uint32_t& dxo) {
         int v = 0;
+        if constexpr (LANES) v = __shfl(ts->sorted, t.row_base + (lane < t.rows ? lane : 0));
 #pragma unroll
-        for (int q = 0; q < MBW; ++q) {
+        for (int q = 0; q < (LANES ? 0 : MBW); ++q) {
             if (q > 0 && 16 * q >= t.rows) continue;
             i32x8_t lo, hi;
             scalar_load16(map + L.off_rows + t.row_base + 16 * q, lo, hi);
@@ -1584,6 +1588,26 @@ __global__ __launch_bounds__(CBIG::NT) void moe_gemm_pipe2_kernel(GemmArgs a) {
     else run_tile<CBIG, Tails...>(a, a.map, L, tc, smem);
 }
 
+// Share [t0, t1) of a launch's tiles that resident workgroup `block` of `blocks` runs; false: none.
+__device__ __forceinline__ bool stream_share(int total, int block, int blocks, int& t0, int& t1) {
+    // each XCD owns one contiguous run of block indices (see locate_tile); its resident workgroups split it evenly
+    const int per_xcd = (total + 7) >> 3;
+    const int xcd = block & 7, slot = block >> 3, slots = blocks >> 3;
+    const int x0 = xcd * per_xcd;
+    const int n_x = total - x0 < per_xcd ? total - x0 : per_xcd;
+    if (n_x <= 0) return false;
+    // Shares: the fewest workgroups that end in the same number of rounds, all with full shares -- the others would only
+    // take HBM bandwidth from the longest ones (8 experts, 4096 -> 28672, 16 tokens, 3.5 tiles per workgroup: 267 us against
+    // 279 with shares of 3 and 4; 64 experts, 2048 -> 2816, 8 tokens, 1.5 each: 62 against 65) -- unless that left close to
+    // half of them idle: below 1.5 tiles each, one for everybody and a second for some.
+    const int per_wg = (n_x + slots - 1) / slots;
+    const bool even = 2 * n_x < 3 * slots;
+    t0 = x0 + (even ? (int)((long long)n_x * slot / slots) : slot * per_wg);
+    t1 = even ? x0 + (int)((long long)n_x * (slot + 1) / slots) : t0 + per_wg;
+    if (t1 > x0 + n_x) t1 = x0 + n_x;
+    return t0 < t1;
+}
+
 // Streaming launch for 16-row tiles (the weight-streaming regime): a fixed number of resident workgroups, each
 // running a contiguous share of its XCD's tiles through pipe_tile<C, true>, so that the weight stream of a
 // workgroup does not stop at tile boundaries.  Requires E <= 256, K / BK >= ring depth, one tiling strategy;
@@ -1625,22 +1649,8 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
             ts.rec[gi].x = cnt > 0 ? upto : 0x7fffffff;
         }
     }
-    // each XCD owns one contiguous run of block indices (see locate_tile); its resident workgroups split it evenly
-    const int per_xcd = (total + 7) >> 3;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
-    const int x0 = xcd * per_xcd;
-    const int n_x = total - x0 < per_xcd ? total - x0 : per_xcd;
-    if (n_x <= 0) return;
-    // Shares: the fewest workgroups that end in the same number of rounds, all with full shares -- the others would only
-    // take HBM bandwidth from the longest ones (8 experts, 4096 -> 28672, 16 tokens, 3.5 tiles per workgroup: 267 us against
-    // 279 with shares of 3 and 4; 64 experts, 2048 -> 2816, 8 tokens, 1.5 each: 62 against 65) -- unless that left close to
-    // half of them idle: below 1.5 tiles each, one for everybody and a second for some.
-    const int per_wg = (n_x + slots - 1) / slots;
-    const bool even = 2 * n_x < 3 * slots;
-    const int t0 = x0 + (even ? (int)((long long)n_x * slot / slots) : slot * per_wg);
-    int t1 = even ? x0 + (int)((long long)n_x * (slot + 1) / slots) : t0 + per_wg;
-    if (t1 > x0 + n_x) t1 = x0 + n_x;
-    if (t0 >= t1) return;
+    int t0, t1;
+    if (!stream_share(total, (int)blockIdx.x, (int)gridDim.x, t0, t1)) return;
     float* xs_lds = reinterpret_cast<float*>(smem + C::LDS_BYTES);
     float* ws_lds = xs_lds + a.T;
     if constexpr (C::FP8) {
@@ -1655,6 +1665,77 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
     TileCoord tc = decode_from_registers(ts, t0);
     tc.streams = total;
     pipe_tile<C, true>(a, map, L, tc, smem, &ts);
+}
+
+// The routing of at most 64 rows over at most 64 experts, worked out by every wavefront from the ids themselves: lane r holds row r's id.
+// The experts are tasks in the order of their first row (nothing depends on the order).  Two ballots per key bit, two scans and six
+// lane exchanges behind one load, about what fetching the header and the records of a finished map takes.  Returns the number of tiles, 0
+// also where an id is outside [0, E).
+__device__ __forceinline__ int routing_in_lanes(const int32_t* __restrict__ ids, int R, int E, int nt, TileStream& ts) {
+    const int lane = __lane_id();
+    const bool in_range = lane < R;
+    const int e = in_range ? ids[lane] : 0;
+    const bool valid = in_range && e >= 0 && e < E;
+    if (__ballot(in_range && !valid)) return 0;
+    int rank, size;
+    const unsigned long long peers = wave_match(e, valid, key_bits(E), rank, size);
+    const bool leader = valid && rank == 0;
+    const int rows_upto = wave_incl_scan(leader ? size : 0);
+    const int tiles_upto = wave_incl_scan(leader ? (size + 15) / 16 * nt : 0);
+    const int offset = rows_upto - size;
+    const int first = valid ? __ffsll((unsigned long long)peers) - 1 : lane;   // the lane that holds my expert's first row
+    const int offset_of_mine = __shfl(offset, first);
+    // lanes beyond R keep their own place, so that every lane is sent to a place of its own
+    ts.sorted = __builtin_amdgcn_ds_permute((valid ? offset_of_mine + rank : lane) << 2, lane);
+    const unsigned long long leaders = __ballot(leader), below = (1ull << lane) - 1ull;
+    const int task = (leader ? __popcll(leaders & below) : __popcll(leaders) + __popcll(~leaders & below)) << 2;
+    ts.rec[0] = make_int4(__builtin_amdgcn_ds_permute(task, leader ? tiles_upto : 0x7fffffff), __builtin_amdgcn_ds_permute(task, leader ? e : -1),
+                          __builtin_amdgcn_ds_permute(task, leader ? size : 0), __builtin_amdgcn_ds_permute(task, leader ? offset : 0));
+#pragma unroll
+    for (int gi = 1; gi < TileStream::MAX_GROUPS; ++gi) ts.rec[gi] = make_int4(0x7fffffff, -1, 0, 0);
+    return __builtin_amdgcn_readlane(tiles_upto, 63);
+}
+
+// What the map of a launch that does without one is built from; the launch builds it all the same, for the calls behind it.
+struct MapToBuild {
+    const int32_t* ids;
+    int32_t* map;
+    moe_tiling tiling;
+    TwinMap twin;
+};
+constexpr int kMapBlocks = 8;   // workgroups in front of the tiles' (a multiple of 8, so that these keep their XCDs); the first builds the map
+
+// The 16-row product of a step of a few rows together with its task map: a map build of six rows is 3 us of latency and a launch of its
+// own in front of a product of 15, so here every wavefront works the routing out for itself and one more workgroup writes the map.
+// Whole layers, map in a launch of its own / in this one, us: 64 experts, top-6, 2048 / 1408, 1 token 34.9 / 30.5, 4 tokens 66.2 / 62.1; 8 experts,
+// top-2, 4096 / 14336, 16 tokens 416 / 412.  (The map's workgroup comes first: where the tiles fill every CU it delays one of them.)
+// RESIDENT: the streaming launch, else one workgroup per tile.
+template <class C, int PAIR, bool RESIDENT>
+__global__ __launch_bounds__(C::NT) void moe_gemm_with_map_kernel(GemmArgs a, MapToBuild m) {
+    static_assert(C::BM == 16 && !C::FP8, "16-row bf16 tiles");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if (blockIdx.x < kMapBlocks) {
+        if (blockIdx.x == 0) build_small(m.ids, m.map, a.T, a.k, a.E, a.N, m.tiling, m.twin, reinterpret_cast<int*>(smem));
+        return;
+    }
+    const int block = (int)blockIdx.x - kMapBlocks, blocks = (int)gridDim.x - kMapBlocks;
+    TileStream ts;
+    const int total = routing_in_lanes(m.ids, a.T * a.k, a.E, a.N / (C::BN / PAIR), ts) / PAIR;
+    ts.tiling = moe_tiling{16, C::BN, 0, 0, 0, 0};
+    ts.pair = PAIR;
+    ts.xs_lds = ts.ws_lds = nullptr;
+    const MapLayout L = map_layout(a.E);
+    int t0, t1;
+    if constexpr (RESIDENT) {
+        if (!stream_share(total, block, blocks, t0, t1)) return;
+        ts.next_B = t0 + 1;
+        ts.end_B = t1;
+    } else {
+        if (!slot_to_block(nullptr, MOE_ORDER_ASCENDING, total, block & 7, block >> 3, t0)) return;
+    }
+    TileCoord tc = decode_from_registers(ts, t0);
+    tc.streams = total;
+    pipe_tile<C, RESIDENT, true>(a, nullptr, L, tc, smem, &ts);
 }
 
 }  // namespace moe

@@ -259,6 +259,19 @@ int launch_stream_narrow(const GemmArgs& a, int64_t grid, int mode, hipStream_t 
     return launch_pipe<C>(a, grid, mode, s);
 }
 
+// The launch that builds the maps as well (see moe_gemm_with_map_kernel), `tiles`: bound on its tiles.
+template <class C, int PAIR, bool RESIDENT>
+int launch_with_map(const GemmArgs& a, const MapToBuild& m, int64_t tiles, hipStream_t s) {
+    static ResidentCache cache;
+    int resident = 0;
+    const void* fn = reinterpret_cast<const void*>(&moe_gemm_with_map_kernel<C, PAIR, RESIDENT>);
+    if (resident_workgroups(fn, C::NT, C::LDS_BYTES, &cache, &resident) != MOE_OK) return MOE_ERR_HIP;
+    int64_t g = (tiles + 7) / 8 * 8;
+    if (RESIDENT && g > resident) g = resident;
+    moe_gemm_with_map_kernel<C, PAIR, RESIDENT><<<dim3((unsigned)(g + kMapBlocks)), dim3(C::NT), C::LDS_BYTES, s>>>(a, m);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 template <class CBIG, class CSMALL, class... Tails>
 int launch_pipe2(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
     constexpr int lds = CBIG::LDS_BYTES > CSMALL::LDS_BYTES ? CBIG::LDS_BYTES : CSMALL::LDS_BYTES;
@@ -495,6 +508,18 @@ int check_build_args(const int32_t* topk_ids, int T, int k, int E, int N, const 
     if (order != MOE_ORDER_ASCENDING && order != MOE_ORDER_SPREAD && order != MOE_ORDER_INTERLEAVE) return MOE_ERR_INVALID_ARG;
     if (((uintptr_t)task_map & 15) || ((uintptr_t)topk_ids & 3)) return MOE_ERR_INVALID_ARG;
     return check_map_args(T, k, E, tile_m, tile_n, N);
+}
+
+int check_pair_args(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, const void* task_map, int N2,
+                    const moe_tiling* tiling2, const void* task_map2) {
+    int rc = check_build_args(topk_ids, T, k, E, N, tiling, task_map);
+    if (rc == MOE_OK) rc = check_build_args(topk_ids, T * k, 1, E, N2, tiling2, task_map2);
+    if (rc != MOE_OK) return rc;
+    const uintptr_t at = (uintptr_t)task_map, at2 = (uintptr_t)task_map2;
+    if (at < at2 + moe_task_map_bytes(T * k, 1, E, tiling2->tile_m, tiling2->tile_n, N2) &&
+        at2 < at + moe_task_map_bytes(T, k, E, tiling->tile_m, tiling->tile_n, N))
+        return MOE_ERR_INVALID_ARG;
+    return MOE_OK;
 }
 
 // The launches of a build (arguments already checked).
@@ -774,15 +799,46 @@ int moe_build_task_map_ex(const int32_t* topk_ids, int T, int k, int E, int N, c
 
 int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map,
                             int N2, const moe_tiling* tiling2, void* task_map2, void* stream) {
-    int rc = check_build_args(topk_ids, T, k, E, N, tiling, task_map);
-    if (rc == MOE_OK) rc = check_build_args(topk_ids, T * k, 1, E, N2, tiling2, task_map2);
+    const int rc = check_pair_args(topk_ids, T, k, E, N, tiling, task_map, N2, tiling2, task_map2);
     if (rc != MOE_OK) return rc;
-    const uintptr_t at = (uintptr_t)task_map, at2 = (uintptr_t)task_map2;
-    if (at < at2 + moe_task_map_bytes(T * k, 1, E, tiling2->tile_m, tiling2->tile_n, N2) &&
-        at2 < at + moe_task_map_bytes(T, k, E, tiling->tile_m, tiling->tile_n, N))
-        return MOE_ERR_INVALID_ARG;
     const TwinMap twin = {static_cast<int32_t*>(task_map2), N2, *tiling2};
     return build_maps(topk_ids, T, k, E, N, *tiling, task_map, twin, static_cast<hipStream_t>(stream));
+}
+
+int moe_build_task_map_pair_gemm(const int32_t* topk_ids, int T, int k, int E, int N, const moe_tiling* tiling, void* task_map, int N2,
+                                 const moe_tiling* tiling2, void* task_map2, const void* X, const void* W, void* Y,
+                                 const moe_gemm_desc* d, void* stream) {
+    int rc = check_pair_args(topk_ids, T, k, E, N, tiling, task_map, N2, tiling2, task_map2);
+    if (rc != MOE_OK) return rc;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const int64_t R = (int64_t)T * k;
+    const moe_tiling g = *tiling;
+    // One launch for up to 64 rows and experts (a wavefront's lanes) on 16-row bf16 tiles, in the form that moe_grouped_gemm takes for
+    // them (launch_stream, launch_rows16).
+    if (d && R > 0 && R <= 64 && E <= 64 && g.tile_m == 16 && (g.tile_n == 128 || g.tile_n == 256) && g.order == MOE_ORDER_ASCENDING &&
+        g.tile_m_small == 0 && g.tile_m_slack == 0 && d->dtype == MOE_DTYPE_BF16 && d->w_layout == MOE_W_LAYOUT_KN &&
+        d->launch_mode == MOE_LAUNCH_AUTO && d->T == T && d->k == k && d->E == E && d->N == N && d->tile_m == 16 && d->tile_n == g.tile_n &&
+        d->tile_m_small == 0 && d->small_max_rows == 0 && d->tile_m_slack == 0 &&
+        (d->epilogue == MOE_EPILOGUE_NONE || d->epilogue == MOE_EPILOGUE_SWIGLU) && d->K >= 64 * 3 && d->K % 64 == 0 && N % g.tile_n == 0 &&
+        (int64_t)T * d->K * 2 < (int64_t)1 << 32 && X && W && Y && !(((uintptr_t)X | (uintptr_t)W | (uintptr_t)Y) & 15) &&
+        !merges16(R, E, N / 256, d->K / 64, MOE_LAUNCH_AUTO) && !merges16(R, E, N / 128, d->K / 64, MOE_LAUNCH_AUTO)) {
+        GemmArgs a{};
+        a.X = X; a.W = W; a.Y = Y;
+        a.T = T; a.k = k; a.E = E; a.K = d->K; a.N = N;
+        a.swiglu = d->epilogue == MOE_EPILOGUE_SWIGLU;
+        const MapToBuild m = {topk_ids, static_cast<int32_t*>(task_map), g, {static_cast<int32_t*>(task_map2), N2, *tiling2}};
+        const int64_t tiles = moe_grid_upper_bound(T, k, E, 16, g.tile_n, N);
+        const double expected = expected_tiles16(R, E, N / g.tile_n);
+        if (g.tile_n == 256) {
+            return (tiles + 7) / 8 * 8 + kSpareSlots >= 2 * kCus ? launch_with_map<Pb_16x256, 1, true>(a, m, tiles, s)
+                                                                   : launch_with_map<Pb_16x256, 1, false>(a, m, tiles, s);
+        }
+        if (N % 256 == 0 && expected > kCus) return launch_with_map<Pb_16x256, 2, true>(a, m, tiles / 2, s);
+        if (expected <= kCus) return launch_with_map<Pb_16x128, 1, false>(a, m, tiles, s);
+    }
+    const TwinMap twin = {static_cast<int32_t*>(task_map2), N2, *tiling2};
+    rc = build_maps(topk_ids, T, k, E, N, g, task_map, twin, s);
+    return rc != MOE_OK ? rc : grouped_gemm_impl(X, W, task_map, Y, d, nullptr, stream);
 }
 
 int moe_task_map_status(const void* task_map, void* stream) {

@@ -130,8 +130,8 @@ __device__ __forceinline__ TileCoord decode_block(const int32_t* __restrict__ ma
 // ---------------------------------------------------------------- build
 
 // Among the lanes of a wavefront holding the same key: my rank (lanes below me with
-// my key) and the group size.  Invalid lanes take no part.
-__device__ __forceinline__ void wave_match(int key, bool valid, int nbits, int& rank, int& size) {
+// my key), the group size and the lanes themselves.  Invalid lanes take no part.
+__device__ __forceinline__ unsigned long long wave_match(int key, bool valid, int nbits, int& rank, int& size) {
     unsigned long long peers = __ballot(valid);
     for (int b = 0; b < nbits; ++b) {
         const int bit = (key >> b) & 1;
@@ -141,6 +141,7 @@ __device__ __forceinline__ void wave_match(int key, bool valid, int nbits, int& 
     const unsigned long long below = (1ull << __lane_id()) - 1ull;
     rank = __popcll(peers & below);
     size = __popcll(peers);
+    return peers;
 }
 
 // Inclusive scan across the threads of the block (at most kMapThreads; s_tmp: >= kWaves ints of LDS).
@@ -336,9 +337,8 @@ __host__ __device__ inline int small_build_threads(int64_t R, int E64) { return 
 __host__ __device__ inline size_t small_build_lds(int threads, int E64) {
     return ((size_t)(threads / 64 + 3) * E64 + kTmpInts + 1) * sizeof(int);
 }
-__global__ __launch_bounds__(kMapThreads) void map_build_small(const int32_t* __restrict__ ids, int32_t* __restrict__ map,
-                                                                int T, int k, int E, int N, moe_tiling g, TwinMap twin) {
-    extern __shared__ int s_mem[];
+__device__ __forceinline__ void build_small(const int32_t* __restrict__ ids, int32_t* __restrict__ map, int T, int k, int E, int N,
+                                            const moe_tiling& g, const TwinMap& twin, int* s_mem) {
     const MapLayout L = map_layout(E);
     const int nwaves = blockDim.x >> 6;
     int* s_wave = s_mem;                   // [nwaves][E64]
@@ -373,6 +373,12 @@ __global__ __launch_bounds__(kMapThreads) void map_build_small(const int32_t* __
         map[at] = tid;
         if (twin.map) twin.map[at] = tid;
     }
+}
+
+__global__ __launch_bounds__(kMapThreads) void map_build_small(const int32_t* __restrict__ ids, int32_t* __restrict__ map,
+                                                                int T, int k, int E, int N, moe_tiling g, TwinMap twin) {
+    extern __shared__ int s_mem[];
+    build_small(ids, map, T, k, E, N, g, twin, s_mem);
 }
 
 // Larger builds: one workgroup per chunk of kChunkRows rows.  Every workgroup needs the counts of all experts over all

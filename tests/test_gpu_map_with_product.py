@@ -1,0 +1,94 @@
+"""A step of a few rows: the maps of a layer and its first product in one launch, against the two calls."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2501_16103_amd import binding as mb
+
+pytestmark = pytest.mark.gpu
+
+
+def _routing(kind, T, k, E, g):
+    if kind == "one":          # every row on one expert: several 16-row tiles, rows beyond the first in the same lane order
+        return torch.full((T, k), E - 1, dtype=torch.int32)
+    if kind == "repeat":       # ids drawn with repetition, also within a token
+        return torch.randint(0, E, (T, k), generator=g, dtype=torch.int32)
+    if kind == "bad":
+        ids = torch.randint(0, E, (T, k), generator=g, dtype=torch.int32)
+        ids[T // 2, k - 1] = E
+        return ids
+    return torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).to(torch.int32)
+
+
+@pytest.mark.parametrize("T,k,E,K,N,kind,swiglu", [
+    (1, 6, 64, 256, 384, "topk", True),        # 128-wide tiles, one workgroup each
+    (1, 1, 1, 192, 256, "topk", False),        # the smallest K and one expert
+    (7, 2, 8, 512, 640, "topk", False),        # N with an odd number of 128-wide tiles
+    (64, 1, 64, 256, 2816, "topk", True),      # as many rows and experts as a wavefront has lanes
+    (10, 6, 64, 320, 2816, "repeat", True),    # 256-wide tiles or pairs, resident
+    (32, 2, 5, 256, 512, "repeat", False),
+    (33, 1, 3, 256, 256, "one", False),        # three tiles of one expert, the last with one row
+    (64, 1, 64, 256, 128, "one", True),
+    (4, 6, 64, 2048, 2816, "topk", True),      # 256-wide tiles, one workgroup each
+    (9, 7, 60, 256, 8192, "topk", False),      # 63 rows, E below a multiple of 64
+    (12, 5, 64, 256, 512, "bad", False),       # an id outside [0, E): maps with a status, no product
+    (13, 5, 64, 256, 512, "topk", False),      # 65 rows: the two calls
+    (6, 4, 65, 256, 512, "topk", False),       # 65 experts: the two calls
+])
+def test_product_with_its_maps(T, k, E, K, N, kind, swiglu):
+    dev = torch.device("cuda:0")
+    g = torch.Generator().manual_seed(100 * T + E)
+    ids = _routing(kind, T, k, E, g).to(dev)
+    X = torch.randn((T, K), generator=g).to(torch.bfloat16).to(dev)
+    W = (torch.randn((E, K, N), generator=g) * K ** -0.5).to(torch.bfloat16).to(dev)
+    out = N // 2 if swiglu else N
+    for tile_n in (128, 256):
+        if N % tile_n:
+            continue
+        g1, g2, N2 = mb.Tiling(16, tile_n), mb.Tiling(128, 128), 256
+        d = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, K, N, 16, tile_n, epilogue=int(swiglu))
+        got = []
+        for together in (False, True):
+            m1, m2 = mb.alloc_task_map(T, k, E, 16, tile_n, N, dev), mb.alloc_task_map(T * k, 1, E, 128, 128, N2, dev)
+            m1.fill_(-7), m2.fill_(-7)
+            Y = torch.full((T * k, out), 9.0, dtype=torch.bfloat16, device=dev)
+            if together:
+                mb.moe_build_task_map_pair_gemm(ids, T, k, E, N, g1, m1, N2, g2, m2, X, W, Y, d)
+            else:
+                mb.moe_build_task_map_pair(ids, T, k, E, N, g1, m1, N2, g2, m2)
+                mb.moe_grouped_gemm(X, W, ids, m1, Y, d)
+            torch.cuda.synchronize()
+            got.append((m1.cpu(), m2.cpu(), Y.view(torch.int16).cpu()))
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
+        assert mb.moe_task_map_status(m1) == (mb.MOE_ERR_ROUTING if kind == "bad" else mb.MOE_OK)
+        if kind == "bad":
+            assert bool((Y == 9.0).all())
+        else:
+            want = torch.einsum("rk,rkn->rn", X.float().repeat_interleave(k, 0), W[ids.flatten().long()].float()) if T * k * K * N < 1 << 27 else None
+            if want is not None and not swiglu:
+                err = (Y.float() - want).abs()
+                assert float(err.max()) < 2.0 ** -7 * float(want.abs().max()) + 1e-3
+                assert np.isfinite(float(err.max()))
+
+
+def test_product_with_its_maps_refuses_what_the_calls_refuse():
+    dev = torch.device("cuda:0")
+    T, k, E, K, N = 2, 2, 8, 256, 256
+    ids = torch.zeros((T, k), dtype=torch.int32, device=dev)
+    X = torch.zeros((T, K), dtype=torch.bfloat16, device=dev)
+    W = torch.zeros((E, K, N), dtype=torch.bfloat16, device=dev)
+    Y = torch.zeros((T * k, N), dtype=torch.bfloat16, device=dev)
+    g1, g2 = mb.Tiling(16, 128), mb.Tiling(128, 128)
+    m1, m2 = mb.alloc_task_map(T, k, E, 16, 128, N, dev), mb.alloc_task_map(T * k, 1, E, 128, 128, N, dev)
+    d = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, K, N, 16, 128)
+
+    def call(maps=(m1, m2), X=X, Y=Y, d=d):
+        return mb.moe_build_task_map_pair_gemm(ids, T, k, E, N, g1, maps[0], N, g2, maps[1], X, W, Y, d, check=False)
+    assert call() == mb.MOE_OK
+    assert call(maps=(m1, m1)) == mb.MOE_ERR_INVALID_ARG                       # maps that overlap
+    assert call(X=None) == mb.MOE_ERR_INVALID_ARG
+    assert call(Y=Y.flatten()[1:]) == mb.MOE_ERR_INVALID_ARG                   # two bytes off a 16-byte boundary
+    assert call(d=mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, 200, N, 16, 128)) == mb.MOE_ERR_UNSUPPORTED
+    assert call(d=mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, K, N, 16, 128, launch_mode=-1)) == mb.MOE_ERR_INVALID_ARG
+    torch.cuda.synchronize()
