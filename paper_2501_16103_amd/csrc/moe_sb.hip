@@ -158,18 +158,19 @@ double expected_tiles16(int64_t R, int E, int64_t nt) {
     return (R >= 8 * (int64_t)E && filled > hit ? filled : hit) * (double)nt;
 }
 
-// 16-row tiles, one workgroup per tile: C fills a CU by itself, C2 is the same tile with two wavefronts and a shallower
-// ring, two workgroups per CU.  Up to one tile per CU the deep form streams faster (64 experts, 2048 -> 2816, fp8, 132 tiles of
-// 128 columns: 13.6 us with C2, 10.8 with C).  Beyond that a tile's start and store leave the CU idle unless a second
-// workgroup covers them: 341 tiles of 1408 columns 19.5 us with C2, 21.7 with C; 512 experts, 1024 -> 2048, fp8, 5024 tiles
-// 116 / 146; 256 experts, K = 128, 4466 tiles 35 / 49.  Only 256-wide tiles with at least 32 k-tiles make up for it, once
-// there are more of them than two per CU (384 experts, 2048 -> 2816, bf16, 4213 tiles 701 / 678).
-template <class C, class C2>
+// 16-row tiles, one workgroup per tile: C fills a CU by itself, C2 is the same tile with a shallower ring, two workgroups per CU, so that
+// one's start and store do not leave the CU idle.  128-wide tiles always take C2 (64 experts, 2048 -> 2816, C / C2, us: fp8, 127 tiles
+// expected 10.9 / 10.3, 243 17.8 / 15.8, 559 32.2 / 27.9; bf16 243 29.4 / 28.0, 559 55.1 / 51.4).  256-wide ones up to one per CU take C, which
+// keeps more of a stream in flight (bf16 121 tiles 29.2 / 42.3, 179 33.4 / 45.2), and beyond two per CU with at least 32 k-tiles (384 experts,
+// 2048 -> 2816, bf16, 4213 tiles 678 / 701); else C2 (280 tiles 57.6 / 53.6, 450 67.9 / 67.3).
+// C3: two wavefronts, for launches of more work items than their count holds (2^32) in the other forms.
+template <class C, class C2, class C3 = C2>
 int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
     const double tiles = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
-    const bool deep = tiles <= kCus || (tiles > 2 * kCus && C::BN == 256 && a.K / C::BK >= 32);
-    if (deep && grid * C::NT <= 0xffffffffll) return launch_pipe<C>(a, grid, mode, s);   // (a launch holds 2^32 work items)
-    return launch_pipe<C2>(a, grid, mode, s);
+    const bool deep = C::BN == 256 && (tiles <= kCus || (tiles > 2 * kCus && a.K / C::BK >= 32));
+    if (deep && grid * C::NT <= 0xffffffffll) return launch_pipe<C>(a, grid, mode, s);
+    if (grid * C2::NT <= 0xffffffffll) return launch_pipe<C2>(a, grid, mode, s);
+    return launch_pipe<C3>(a, grid, mode, s);
 }
 
 // Resident workgroups for at most `tiles` tiles of C, PAIR of the map's tiles each, where `wanted` or asked for by the
@@ -216,8 +217,8 @@ static_assert(merges16(32 * 16, 32, 11, 16, MOE_LAUNCH_AUTO) && merges16(16 * 16
 // number of 256-wide ones: the map's n-tiles are then run in pairs once more of them are expected than CUs (fp8, 64 experts,
 // 2048 -> 2816: 3 tokens, 330 tiles, 22.5 -> 18.0 us, 20.5 with C2; 32 tokens 56 -> 52).  A K too short for the deep ring
 // streams in the two-workgroup form, from two tiles per workgroup on (256 experts, K = 128, 2233 tiles: 30 us, 34 per tile).
-// (Between one and two 256-wide tiles per CU the deep form is kept: a uniform routing of 5 tokens, 297 tiles, takes 62 us with
-// it and 55 with two workgroups per CU, but a skewed one of the same size, 176 tiles, 29 and 38.)
+// (Between one and two 256-wide tiles per CU the deep form is kept: where a uniform routing is expected to give 280 tiles, it takes 57 us
+// against 54 with two workgroups per CU, but a skewed one of the same size, with less than one per CU, 34 against 45.)
 // CS, CW: with room for the rows of several of the map's tiles, see merges16.
 template <class C, class C2, class CW1, class CS, class CW>
 int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
@@ -321,7 +322,7 @@ using Ps_128x256 = Alone<PipeCfg<128, 256, 64, 1, 8, 3>>;
 using Pt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2>;
 // 16-row tiles and fp8: the weight stream starts before the token rows are known.  One workgroup per CU with enough
 // wavefronts to issue a stage's DMA instructions side by side (4 each per stage: a wavefront's own 16 took longer than the
-// stage's share of the HBM rate) streams faster than two workgroups of two wavefronts (the Pd forms): 8 experts, 4096 -> 28672,
+// stage's share of the HBM rate) streams faster than two workgroups of two wavefronts (the Pe forms): 8 experts, 4096 -> 28672,
 // 16 tokens 280 -> 267 us (7.0 TB/s), 64 experts, 2048 -> 2816, 32 tokens 121 -> 98 us, one token (128-wide) 18.8 -> 14.5 us.
 // launch_rows16 says which of the two runs one workgroup per tile.
 using Pb_16x256 = PipeCfg<16, 256, 64, 1, 8, 3>;
@@ -329,14 +330,18 @@ using Pb_16x128 = PipeCfg<16, 128, 64, 1, 4, 6>;
 // (streamed: as many rows as the token stages hold)
 using Pq_64x256 = PipeCfg<64, 256, 64, 1, 8, 3, false, 3, 0, false, 16>;
 using Pq_32x128 = PipeCfg<32, 128, 64, 1, 4, 6, false, 6, 0, false, 16>;
-using Pd_16x256 = PipeCfg<16, 256, 64, 1, 2, 2>;
-using Pd_16x128 = PipeCfg<16, 128, 64, 1, 2, 4>;
+using Pd_16x256 = PipeCfg<16, 256, 64, 1, 8, 2>;
+using Pd_16x128 = PipeCfg<16, 128, 64, 1, 4, 4>;
+using Pe_16x256 = PipeCfg<16, 256, 64, 1, 2, 2>;
+using Pe_16x128 = PipeCfg<16, 128, 64, 1, 2, 4>;
 using P8_16x256 = PipeCfg<16, 256, 128, 1, 8, 3, true>;
 using P8_16x128 = PipeCfg<16, 128, 128, 1, 4, 6, true>;
 using P8q_64x256 = PipeCfg<64, 256, 128, 1, 8, 3, true, 3, 0, false, 16>;
 using P8q_32x128 = PipeCfg<32, 128, 128, 1, 4, 6, true, 6, 0, false, 16>;
-using P8d_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true>;
-using P8d_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true>;
+using P8d_16x256 = PipeCfg<16, 256, 128, 1, 8, 2, true>;
+using P8d_16x128 = PipeCfg<16, 128, 128, 1, 4, 4, true>;
+using P8e_16x256 = PipeCfg<16, 256, 128, 1, 2, 2, true>;
+using P8e_16x128 = PipeCfg<16, 128, 128, 1, 2, 4, true>;
 using P8_16x64 = PipeCfg<16, 64, 128, 1, 2, 4, true>;
 using P8_32x128 = PipeCfg<32, 128, 128, 1, 2, 4, true>;
 // fp8 at prefill sizes: the 256 x 256 launch shape with its two narrow task functions, and a 64-row tile
@@ -401,10 +406,10 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 64, 128, 64, &launch_pipe<Pb_64x128>},
     {MOE_DTYPE_BF16, 32, 256, 64, &launch_pipe<Pb_32x256>},
     {MOE_DTYPE_BF16, 32, 128, 64, &launch_pipe<Pb_32x128>},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256, Pd_16x256, Pb_16x256, Pq_64x256, Pq_64x256>},
-    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pd_16x128, Pb_16x256, Pq_32x128, Pq_64x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256, P8d_16x256, P8_16x256, P8q_64x256, P8q_64x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8d_16x128, P8_16x256, P8q_32x128, P8q_64x256>},
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256, Pe_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256, Pd_16x256, Pb_16x256, Pq_64x256, Pq_64x256>},
+    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128, Pe_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pd_16x128, Pb_16x256, Pq_32x128, Pq_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256, P8e_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256, P8d_16x256, P8_16x256, P8q_64x256, P8q_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128, P8e_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8d_16x128, P8_16x256, P8q_32x128, P8q_64x256>},
     {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream_narrow<P8_16x64>},
     {MOE_DTYPE_FP8_E4M3, 32, 128, 128, &launch_pipe<P8_32x128>},
     {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_halves<F8_256x256, H8_256x128>},
@@ -834,7 +839,7 @@ int moe_build_task_map_pair_gemm(const int32_t* topk_ids, int T, int k, int E, i
                                                                    : launch_with_map<Pb_16x256, 1, false>(a, m, tiles, s);
         }
         if (N % 256 == 0 && expected > kCus) return launch_with_map<Pb_16x256, 2, true>(a, m, tiles / 2, s);
-        if (expected <= kCus) return launch_with_map<Pb_16x128, 1, false>(a, m, tiles, s);
+        if (expected <= kCus) return launch_with_map<Pd_16x128, 1, false>(a, m, tiles, s);
     }
     const TwinMap twin = {static_cast<int32_t*>(task_map2), N2, *tiling2};
     rc = build_maps(topk_ids, T, k, E, N, g, task_map, twin, s);
