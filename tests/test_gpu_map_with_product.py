@@ -92,3 +92,35 @@ def test_product_with_its_maps_refuses_what_the_calls_refuse():
     assert call(d=mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, 200, N, 16, 128)) == mb.MOE_ERR_UNSUPPORTED
     assert call(d=mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, K, N, 16, 128, launch_mode=-1)) == mb.MOE_ERR_INVALID_ARG
     torch.cuda.synchronize()
+
+
+def test_layer_of_a_few_rows_replays_from_a_graph():
+    """The launch takes the ids of each replay, not those of the capture, and its maps are rewritten each time."""
+    dev = torch.device("cuda:0")
+    T, k, E, hidden, inter = 3, 2, 32, 256, 256
+    g = torch.Generator(device=dev).manual_seed(8)
+    X = torch.randn((T, hidden), generator=g, device=dev).to(torch.bfloat16)
+    W1 = (torch.randn((E, hidden, 2 * inter), generator=g, device=dev) * hidden ** -0.5).to(torch.bfloat16)
+    W2 = (torch.randn((E, inter, hidden), generator=g, device=dev) * inter ** -0.5).to(torch.bfloat16)
+    wts = torch.rand((T, k), generator=g, device=dev, dtype=torch.float32)
+    plan, eager = mb.MoeLayerPlan(T, k, E, hidden, inter, dev), mb.MoeLayerPlan(T, k, E, hidden, inter, dev)
+    assert plan.g1.tile_m == 16
+    ids = torch.zeros((T, k), dtype=torch.int32, device=dev)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        plan.forward(X, W1, W2, ids, wts)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            plan.forward(X, W1, W2, ids, wts)
+    for it in range(4):
+        ids.copy_(torch.stack([torch.randperm(E, generator=g, device=dev)[:k] for _ in range(T)]))
+        X.normal_(generator=g)
+        want = eager.forward(X, W1, W2, ids, wts).clone()
+        plan.out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(plan.out.view(torch.int16), want.view(torch.int16)), f"replay {it}"
+        for m, want_m in ((plan.map1, eager.map1), (plan.map2, eager.map2)):
+            written = mb.moe_map_offsets(E)["sorted_rows"] + T * k      # (words: header to the token index arrays)
+            assert torch.equal(m[:written], want_m[:written])
