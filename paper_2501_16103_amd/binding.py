@@ -464,10 +464,23 @@ class MoeLayerPlan:
         narrow = (g.tile_m, g.tile_n) == (16, 128) and min(R, E) * (hidden // 128) <= 128
         return Tiling(128, 128) if narrow else g
 
+    @staticmethod
+    def _streamed(g: Tiling, R: int, E: int, K: int, N: int) -> Tiling:
+        """A gate+up product of 9 to 32 rows per expert whose wide tiles are 1.75 to 4 rounds of the chip, with a long K, is run by the streaming
+        launch of the 16-row tiles (which takes up to 64 rows of an expert as one tile) instead of one workgroup per 256 x 256 tile: the
+        weights of such a launch are all it moves, and a round's start, end and remainder are a tenth of it.  Even / skewed routing,
+        us, 256 x 256 and this: 8 experts, 4096 -> 28672, 9 rows each 311 273 / 312 278, 26 rows 309 283 / 328 313; 4096 -> 14336, 16 rows 162 148 / 165 152;
+        16 experts, 26 rows 318 296 / 334 316; 64 experts, 4096 -> 4096, 16 rows 348 335 / 356 348, but 26 rows 351 341 / 370 383.  At one round
+        (8 experts, 2048 -> 8192, 9 rows 48 46 / 47 69), more than four (256 experts, 7168 -> 4096, 12 rows 2208 / 2284) and with a shorter K (64
+        experts, 2048 -> 2816, 16 rows 115 117 / 122 123) it loses."""
+        tiles, few = E * (N // 256), 8 * E < R <= (32 if E <= 16 else 16) * E
+        streams = few and K >= 4096 and N % 256 == 0 and 448 <= tiles <= 1024 and g.tile_m == 256
+        return Tiling(16, 256) if streams else g
+
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):
         self.T, self.k, self.E, self.hidden, self.inter = T, k, E, hidden, inter
         R = T * k
-        self.g1 = moe_default_tiling(MOE_DTYPE_BF16, T, k, E, hidden, 2 * inter)
+        self.g1 = self._streamed(moe_default_tiling(MOE_DTYPE_BF16, T, k, E, hidden, 2 * inter), R, E, hidden, 2 * inter)
         # the down product is the short-grid case (few experts, N = hidden): split along K where that pays
         self.tail_split = R > 0 and moe_default_tail_split(R, 1, E, inter, hidden)
         self.k_parts = moe_default_k_parts(R, 1, E, inter, hidden) if R > 0 and not self.tail_split else 1

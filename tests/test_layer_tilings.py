@@ -1,0 +1,26 @@
+"""Tilings that a layer plan takes other than the library's default (host only)."""
+import pytest
+
+from paper_2501_16103_amd import binding as mb
+
+
+@pytest.mark.parametrize("T,k,E,hidden,inter,want", [
+    (32, 2, 8, 4096, 14336, (16, 256)),     # 8 rows per expert: the default
+    (33, 2, 8, 4096, 14336, (16, 256)),     # 9 to 32 rows, 896 wide tiles: streamed
+    (128, 2, 8, 4096, 14336, (16, 256)),
+    (129, 2, 8, 4096, 14336, (256, 256)),
+    (64, 2, 8, 4096, 7168, (16, 256)),      # 448 wide tiles
+    (64, 2, 8, 4096, 7040, (256, 256)),     # 440
+    (64, 2, 8, 3840, 14336, (256, 256)),    # a K below 4096
+    (64, 4, 16, 4096, 8192, (16, 256)),     # 1024 wide tiles, 16 experts
+    (128, 4, 16, 4096, 8192, (16, 256)),
+    (64, 4, 17, 4096, 8192, (256, 256)),    # 1088
+    (102, 4, 24, 4096, 4096, (256, 256)),   # 17 rows per expert, more than 16 experts
+    (96, 4, 24, 4096, 4096, (16, 256)),     # 16
+    (777, 6, 64, 2048, 1408, (128, 256)),
+])
+def test_tiling_of_the_first_product(T, k, E, hidden, inter, want):
+    plan = mb.MoeLayerPlan(T, k, E, hidden, inter, "cpu")
+    assert (plan.g1.tile_m, plan.g1.tile_n) == want
+    assert (plan.d1.tile_m, plan.d1.tile_n, plan.d1.tile_m_slack) == (plan.g1.tile_m, plan.g1.tile_n, plan.g1.tile_m_slack)
+    assert mb.moe_tiling_supported(mb.MOE_DTYPE_BF16, plan.g1)
