@@ -1668,7 +1668,7 @@ __global__ __launch_bounds__(C::NT) void moe_gemm_stream_kernel(GemmArgs a) {
 }
 
 // The routing of at most 64 rows over at most 64 experts, worked out by every wavefront from the ids themselves: lane r holds row r's id.
-// The experts are tasks in the order of their first row (nothing depends on the order).  Two ballots per key bit, two scans and six
+// The experts are tasks in the order of their first row (nothing depends on the order).  One ballot per key bit, two scans and six
 // lane exchanges behind one load, about what fetching the header and the records of a finished map takes.  Returns the number of tiles, 0
 // also where an id is outside [0, E).
 __device__ __forceinline__ int routing_in_lanes(const int32_t* __restrict__ ids, int R, int E, int nt, TileStream& ts) {

@@ -166,9 +166,11 @@ double expected_tiles16(int64_t R, int E, int64_t nt) {
 // C3: two wavefronts, for launches of more work items than their count holds (2^32) in the other forms.
 template <class C, class C2, class C3 = C2>
 int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
-    const double tiles = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
-    const bool deep = C::BN == 256 && (tiles <= kCus || (tiles > 2 * kCus && a.K / C::BK >= 32));
-    if (deep && grid * C::NT <= 0xffffffffll) return launch_pipe<C>(a, grid, mode, s);
+    if constexpr (C::BN == 256) {
+        const double tiles = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
+        const bool deep = tiles <= kCus || (tiles > 2 * kCus && a.K / C::BK >= 32);
+        if (deep && grid * C::NT <= 0xffffffffll) return launch_pipe<C>(a, grid, mode, s);
+    }
     if (grid * C2::NT <= 0xffffffffll) return launch_pipe<C2>(a, grid, mode, s);
     return launch_pipe<C3>(a, grid, mode, s);
 }
@@ -242,7 +244,9 @@ int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
         const int rc2 = launch_stream_kernel<C2, 1>(a, grid, mode, s, grid >= 4 * kCus, &launched);
         if (rc2 != MOE_OK || launched) return rc2;
     }
-    if (C::BN == 256 && a.K / C::BK >= C::NS) return launch_pipe<C>(a, grid, mode, s);
+    if constexpr (C::BN == 256) {
+        if (a.K / C::BK >= C::NS) return launch_pipe<C>(a, grid, mode, s);
+    }
     return launch_rows16<C, C2>(a, grid, mode, s);
 }
 
