@@ -232,6 +232,24 @@ int moe_build_task_map_pair(const int32_t* topk_ids, int T, int k, int E, int N,
  */
 int moe_default_tiling(int dtype, int T, int k, int E, int K, int N, moe_tiling* out);
 
+/*
+ * HOST, pure.  The form of launch that moe_grouped_gemm takes for a map of 16-row tiles, tile_n 128 or 256, over [E][K][N] weights, with this
+ * moe_gemm_desc.launch_mode and T > 0: MOE_ROWS16_*, or a negative error code.  The results are the same in every form.
+ *   MOE_ROWS16_PER_TILE_DEEP    one workgroup per tile, a CU by itself
+ *   MOE_ROWS16_PER_TILE         one workgroup per tile, two per CU
+ *   MOE_ROWS16_PER_TILE_SMALL   the same with two wavefronts each, where the other forms need 2^32 work items or more; a launch that needs
+ *                               so many in this form as well is MOE_ERR_UNSUPPORTED
+ *   MOE_ROWS16_STREAM           resident workgroups that run tile after tile
+ *   MOE_ROWS16_STREAM_SHORT_K   the same, two per CU, for a K shorter than the ring
+ *   MOE_ROWS16_PAIRS            resident, two 128-wide n-tiles as one
+ *   MOE_ROWS16_STREAM_MERGED, MOE_ROWS16_PAIRS_MERGED   resident, several 16-row tiles of an expert as one
+ */
+enum {
+    MOE_ROWS16_PER_TILE_DEEP = 1, MOE_ROWS16_PER_TILE = 2, MOE_ROWS16_PER_TILE_SMALL = 3, MOE_ROWS16_STREAM = 4,
+    MOE_ROWS16_STREAM_SHORT_K = 5, MOE_ROWS16_PAIRS = 6, MOE_ROWS16_STREAM_MERGED = 7, MOE_ROWS16_PAIRS_MERGED = 8
+};
+int moe_rows16_launch(int dtype, int tile_n, int T, int k, int E, int K, int N, int launch_mode);
+
 /* 1 if moe_grouped_gemm has a kernel for this dtype and tiling (order is ignored), else 0. HOST, pure. */
 int moe_tiling_supported(int dtype, const moe_tiling* tiling);
 
@@ -290,7 +308,8 @@ enum { MOE_LAUNCH_AUTO = 0, MOE_LAUNCH_PER_TILE = 1, MOE_LAUNCH_RESIDENT = 2 };
  *   fp8: Y = (sum over e4m3 products in fp32) * x_scale[t] * w_scale[e].
  * Accumulation is fp32; the store rounds to bf16 (nearest even).
  * Requires K % 64 == 0 (bf16) / K % 128 == 0 (fp8) and N % tile_n == 0,
- * else MOE_ERR_UNSUPPORTED.  (tile_m, tile_n, dtype) must be a supported
+ * and a launch of less than 2^32 work items (2^23 tiles or more at 512
+ * threads each would be too many), else MOE_ERR_UNSUPPORTED.  (tile_m, tile_n, dtype) must be a supported
  * combination: see moe_tile_supported.  A map whose header does not match
  * `desc`, or whose status is non-zero, makes the kernel a no-op.
  * topk_ids is accepted for symmetry with the problem statement and may be
@@ -315,6 +334,9 @@ int moe_build_task_map_pair_gemm(const int32_t* topk_ids, int T, int k, int E, i
                                  int N2, const moe_tiling* tiling2, void* task_map2, const void* X, const void* W, void* Y,
                                  const moe_gemm_desc* desc, void* stream);
 
+/* HOST, pure.  1 where that call takes one launch for these sizes (moe_rows16_launch says in which form), 2 where it takes the two calls' launches; a
+ * negative error code for bad arguments.  Pointers in `desc` are not looked at. */
+int moe_pair_gemm_launches(int T, int k, int E, int N, const moe_tiling* tiling, const moe_gemm_desc* desc);
 
 /*
  * The same product for launches too short to give every CU a tile (few experts, a narrow N and a long K: a down

@@ -36,6 +36,15 @@ MOE_ORDER_INTERLEAVE = 2
 MOE_LAUNCH_AUTO = 0
 MOE_LAUNCH_PER_TILE = 1
 MOE_LAUNCH_RESIDENT = 2
+# forms of a launch on 16-row tiles (moe_rows16_launch)
+MOE_ROWS16_PER_TILE_DEEP = 1
+MOE_ROWS16_PER_TILE = 2
+MOE_ROWS16_PER_TILE_SMALL = 3
+MOE_ROWS16_STREAM = 4
+MOE_ROWS16_STREAM_SHORT_K = 5
+MOE_ROWS16_PAIRS = 6
+MOE_ROWS16_STREAM_MERGED = 7
+MOE_ROWS16_PAIRS_MERGED = 8
 MOE_MAP_MAGIC = 0x3142534D
 MOE_MAP_HDR_WORDS = 32
 HDR = dict(MAGIC=0, T=1, K_TOP=2, E=3, N=4, TILE_M=5, TILE_N=6, NT=7, M=8, TOTAL_TILES=9, ORDER=10,
@@ -46,7 +55,8 @@ EXPORTS = [
     "moe_map_off_counts", "moe_map_off_offsets", "moe_map_off_sigma", "moe_map_off_tile_prefix",
     "moe_map_off_task_records", "moe_map_off_sorted_rows", "moe_task_map_bytes", "moe_grid_upper_bound", "moe_build_task_map",
     "moe_build_task_map_ordered", "moe_build_task_map_tiled", "moe_grid_upper_bound_tiled", "moe_tile_pair_supported",
-    "moe_build_task_map_ex", "moe_build_task_map_pair", "moe_build_task_map_pair_gemm", "moe_tiling_supported", "moe_w_layout_supported", "moe_default_tiling",
+    "moe_build_task_map_ex", "moe_build_task_map_pair", "moe_build_task_map_pair_gemm", "moe_pair_gemm_launches",
+    "moe_tiling_supported", "moe_w_layout_supported", "moe_default_tiling", "moe_rows16_launch",
     "moe_task_map_status", "moe_task_map_expand", "moe_grouped_gemm", "moe_tile_supported", "moe_combine",
     "moe_grouped_gemm_splitk", "moe_splitk_workspace_bytes", "moe_default_k_parts",
     "moe_grouped_gemm_splitk_static", "moe_splitk_static_scratch_bytes",
@@ -118,6 +128,10 @@ def lib() -> ctypes.CDLL:
         L.moe_build_task_map_pair_gemm.restype = ctypes.c_int
         L.moe_build_task_map_pair_gemm.argtypes = L.moe_build_task_map_pair.argtypes[:-1] + [ctypes.c_void_p] * 3 + [
             ctypes.POINTER(moe_gemm_desc), ctypes.c_void_p]
+        L.moe_pair_gemm_launches.restype = ctypes.c_int
+        L.moe_pair_gemm_launches.argtypes = [ctypes.c_int] * 4 + [ctypes.POINTER(moe_tiling), ctypes.POINTER(moe_gemm_desc)]
+        L.moe_rows16_launch.restype = ctypes.c_int
+        L.moe_rows16_launch.argtypes = [ctypes.c_int] * 8
         L.moe_tiling_supported.restype = ctypes.c_int
         L.moe_tiling_supported.argtypes = [ctypes.c_int, ctypes.POINTER(moe_tiling)]
         L.moe_default_tiling.restype = ctypes.c_int
@@ -353,6 +367,20 @@ def moe_build_task_map_pair_gemm(topk_ids: torch.Tensor, T: int, k: int, E: int,
     if check and rc != MOE_OK:
         raise MoeError(rc, "moe_build_task_map_pair_gemm")
     return rc
+
+
+def moe_pair_gemm_launches(T: int, k: int, E: int, N: int, tiling: Tiling, desc: GemmDesc) -> int:
+    """1 where moe_build_task_map_pair_gemm takes one launch for these sizes, 2 where it takes those of the two calls."""
+    g, d = tiling.c_struct(), desc.c_struct()
+    rc = lib().moe_pair_gemm_launches(T, k, E, N, ctypes.byref(g), ctypes.byref(d))
+    if rc < 0:
+        raise MoeError(rc, "moe_pair_gemm_launches")
+    return rc
+
+
+def moe_rows16_launch(dtype: int, tile_n: int, T: int, k: int, E: int, K: int, N: int, launch_mode: int = MOE_LAUNCH_AUTO) -> int:
+    """Form of the launch that moe_grouped_gemm takes for 16-row tiles (MOE_ROWS16_*), or a negative error code."""
+    return int(lib().moe_rows16_launch(dtype, tile_n, T, k, E, K, N, launch_mode))
 
 
 def moe_combine(Y: torch.Tensor, topk_weights: Optional[torch.Tensor], T: int, k: int, N: int, out: torch.Tensor,

@@ -21,6 +21,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "launch_rules.hpp"
 #include "task_map.hpp"
 
 namespace moe {
@@ -37,7 +38,6 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
 #define MOE_LDS(T) __attribute__((address_space(3))) T
 
-constexpr int kXcdCus = 32;   // CUs of each of the 8 XCDs
 constexpr int kOnceTiles = 192;   // 256-wide tiles of a launch from which on weights that one tile reads are fetched non-temporally (see pipe_tile)
 
 struct GemmArgs {
@@ -233,7 +233,7 @@ constexpr bool swz_w_repeats() {
 // tile after the current one is known without touching memory and its loads can be issued while the current
 // tile still multiplies.
 struct TileStream {
-    static constexpr int MAX_GROUPS = 4;  // E <= 256
+    static constexpr int MAX_GROUPS = kStreamExperts / 64;
     int4 rec[MAX_GROUPS];                 // lane-held task records, group by group
     int next_B, end_B;                    // tiles still to run: [next_B, end_B)
     int pair;                             // tiles of the map per tile here: 2 = two neighbouring n-tiles run as one

@@ -10,6 +10,7 @@
 #include "../../include/moe_sb.h"
 #include "gemm_kernel.hpp"
 #include "combine.hpp"
+#include "launch_rules.hpp"
 #include "task_map.hpp"
 
 using namespace moe;
@@ -55,6 +56,7 @@ inline int ensure_lds_attr(const void* fn, int lds, unsigned long long* done) {
 
 template <class C, class... Tails>
 int launch_pipe(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
+    if (!work_items_fit(grid, C::NT)) return MOE_ERR_UNSUPPORTED;
     static unsigned long long attr_done = 0;
     if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_pipe_kernel<C, Tails...>), C::LDS_BYTES, &attr_done) != MOE_OK)
         return MOE_ERR_HIP;
@@ -66,6 +68,7 @@ int launch_pipe(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
 template <class OVER, class C, class... Tails>
 int launch_absorb(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
     if (mode == MOE_LAUNCH_PER_TILE) return launch_pipe<C, Tails...>(a, grid, mode, s);
+    if (!work_items_fit(grid, C::NT)) return MOE_ERR_UNSUPPORTED;
     static unsigned long long attr_done = 0;
     constexpr int lds = OVER::LDS_BYTES > C::LDS_BYTES ? OVER::LDS_BYTES : C::LDS_BYTES;
     if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_absorb_kernel<OVER, C, Tails...>), lds, &attr_done) != MOE_OK) return MOE_ERR_HIP;
@@ -103,6 +106,7 @@ int launch_halves(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
     GemmArgs b = a;
     b.halve_last = mode != MOE_LAUNCH_PER_TILE;
     if (b.halve_last) grid = 8 * halved_slots(grid / 8);
+    if (!work_items_fit(grid, C::NT)) return MOE_ERR_UNSUPPORTED;
     moe_gemm_halves_kernel<Fns, Half><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(b);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
@@ -110,6 +114,7 @@ int launch_halves(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
 // Split-k launch: `parts` workgroups per tile (grid.y), fp32 partial sums into a.partial.
 template <class C, class... Tails>
 int launch_splitk(const GemmArgs& a, int64_t grid, int parts, hipStream_t s) {
+    if (!work_items_fit(grid, C::NT)) return MOE_ERR_UNSUPPORTED;
     static unsigned long long attr_done = 0;
     if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_pipe_kernel<SplitK<C>, SplitK<Tails>...>), C::LDS_BYTES, &attr_done) != MOE_OK)
         return MOE_ERR_HIP;
@@ -120,6 +125,7 @@ int launch_splitk(const GemmArgs& a, int64_t grid, int parts, hipStream_t s) {
 // Heterogeneous launch: the GEMM tasks' blocks plus a.red_tiles blocks of the reduction task.
 template <class C, class... Tails>
 int launch_batched(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
+    if (!work_items_fit(grid, C::NT)) return MOE_ERR_UNSUPPORTED;
     static unsigned long long attr_done = 0;
     if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_batched_kernel<C, Tails...>), C::LDS_BYTES, &attr_done) != MOE_OK)
         return MOE_ERR_HIP;
@@ -148,42 +154,12 @@ inline int resident_workgroups(const void* fn, int threads, int lds, ResidentCac
     return MOE_OK;
 }
 
-constexpr int kCus = 8 * kXcdCus;
-constexpr int kSpareSlots = 16;   // workgroups a launch's grid holds beyond the bound on its tiles (see grouped_gemm_impl)
-
-// Tiles of 16 rows that a uniform routing gives: one for each expert it hits; from half a tile of rows per expert on, rows
-// fill a tile half on average.
-double expected_tiles16(int64_t R, int E, int64_t nt) {
-    const double hit = E * (1.0 - pow(1.0 - 1.0 / E, (double)R)), filled = R / 16.0 + E / 2.0;
-    return (R >= 8 * (int64_t)E && filled > hit ? filled : hit) * (double)nt;
-}
-
-// 16-row tiles, one workgroup per tile: C fills a CU by itself, C2 is the same tile with a shallower ring, two workgroups per CU, so that
-// one's start and store do not leave the CU idle.  128-wide tiles always take C2 (64 experts, 2048 -> 2816, C / C2, us: fp8, 127 tiles
-// expected 10.9 / 10.3, 243 17.8 / 15.8, 559 32.2 / 27.9; bf16 243 29.4 / 28.0, 559 55.1 / 51.4).  256-wide ones up to one per CU take C, which
-// keeps more of a stream in flight (bf16 121 tiles 29.2 / 42.3, 179 33.4 / 45.2), and beyond two per CU with at least 32 k-tiles (384 experts,
-// 2048 -> 2816, bf16, 4213 tiles 678 / 701); else C2 (280 tiles 57.6 / 53.6, 450 67.9 / 67.3).
-// C3: two wavefronts, for launches of more work items than their count holds (2^32) in the other forms.
-template <class C, class C2, class C3 = C2>
-int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
-    if constexpr (C::BN == 256) {
-        const double tiles = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
-        const bool deep = tiles <= kCus || (tiles > 2 * kCus && a.K / C::BK >= 32);
-        if (deep && grid * C::NT <= 0xffffffffll) return launch_pipe<C>(a, grid, mode, s);
-    }
-    if (grid * C2::NT <= 0xffffffffll) return launch_pipe<C2>(a, grid, mode, s);
-    return launch_pipe<C3>(a, grid, mode, s);
-}
-
-// Resident workgroups for at most `tiles` tiles of C, PAIR of the map's tiles each, where `wanted` or asked for by the
-// launch mode.  *launched stays false where neither holds, or where K is too short to fill the ring.
+// Resident workgroups for at most `tiles` tiles of C, PAIR of the map's tiles each.
 template <class C, int PAIR>
-int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t s, bool wanted, bool* launched) {
+int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t s) {
     const int lds = C::LDS_BYTES + (C::FP8 ? 4 * (a.T + a.E) : 0);
     static ResidentCache cache;
     int resident = 0;
-    *launched = (wanted || mode >= MOE_LAUNCH_RESIDENT) && a.K / C::BK >= C::NS;
-    if (!*launched) return MOE_OK;
     if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C, PAIR>), C::NT, lds, &cache, &resident) != MOE_OK)
         return MOE_ERR_HIP;
     int64_t g = tiles < resident ? tiles : resident;
@@ -192,75 +168,49 @@ int launch_stream_kernel(const GemmArgs& a, int64_t tiles, int mode, hipStream_t
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-// Whether the streaming launch runs the rows of several 16-row tiles as one tile (see moe_gemm_stream_kernel): nt n-tiles as it runs
-// them.  From 8 to 32 rows per expert on average and from 16 k-tiles on.  At 8 to 10 rows an even routing gives nearly every expert
-// one tile, and the larger task function costs 1 to 2 % (bf16, 256 experts, 2048 -> 2048, 6 %: 317 -> 339 us), but skewed ones gain ten
-// times that (the same 332 -> 281; 64 experts, 2048 -> 2816, 122 -> 110); below 8 rows the cost stays (fp8, 32 tokens, 1 to 3 %).  Beyond 32, few
-// experts are left with too few workgroups (8 experts, K = 256, 75 rows each: 7.4 -> 11.5 us), and such maps are not the default; with a
-// short K the rows of a full tile take longer than its panel (64 experts, 1024 -> 2048, fp8, a skewed routing of 200 tokens 28.6 -> 35.0).
-// Tiles that all start at once gain nothing from being fewer, the longest of them only gets longer: below two tiles per CU, it takes
-// a round less under a uniform routing (tiles expected one by one / merged; fp8, us: 8 experts, 2048 -> 2816, 20 rows, 154 / 88, 17.2
-// -> 18.1 and, skewed, 16.7 -> 20.9; 32 experts, 10 rows, 396 / 352, 35.3 -> 36.4, skewed 36.2 -> 40.4, but 16 rows, 528 / 352, 41.5 -> 37.6;
-// 16 experts, 4096 -> 4096, 16 rows, 384 / 256, 61.5 -> 47.3).  A launch of a given number of workgroups merges by rows and K alone.
-constexpr bool merges16(int64_t R, int E, int64_t nt, int k_tiles, int mode) {
-    if (R < 8 * (int64_t)E || R > 32 * (int64_t)E || k_tiles < 16) return false;
-    const int64_t merged = E * nt, single = R * nt / 16 + merged / 2;
-    return mode >= MOE_LAUNCH_RESIDENT || merged >= 2 * kCus || (single + kCus - 1) / kCus > (merged + kCus - 1) / kCus;
-}
-static_assert(merges16(64 * 8, 64, 11, 16, MOE_LAUNCH_AUTO) && !merges16(64 * 8 - 1, 64, 11, 16, MOE_LAUNCH_AUTO), "many tiles");
-static_assert(!merges16(8 * 20, 8, 11, 16, MOE_LAUNCH_AUTO) && !merges16(32 * 10, 32, 11, 16, MOE_LAUNCH_AUTO), "few tiles, no round less");
-static_assert(merges16(32 * 16, 32, 11, 16, MOE_LAUNCH_AUTO) && merges16(16 * 16, 16, 16, 32, MOE_LAUNCH_AUTO), "a round less");
-
-// Streaming launch (not called in MOE_LAUNCH_PER_TILE): as many workgroups as stay resident at once, grid is only an upper
-// bound here.  256-wide tiles: from two
-// tiles per workgroup on, counted by the bound.  128-wide ones: once more are expected than the CUs hold in the two-workgroup form
-// of launch_rows16, for up to there no tile waits for a second round (64 experts, 2048 -> 1408, fp8: 363 tiles 19.7 us per tile,
-// 22.2 streaming; 572 tiles 32.4 / 28.6).  CW: the same tile twice as wide, for maps of 128-wide tiles whose N holds a whole
-// number of 256-wide ones: the map's n-tiles are then run in pairs once more of them are expected than CUs (fp8, 64 experts,
-// 2048 -> 2816: 3 tokens, 330 tiles, 22.5 -> 18.0 us, 20.5 with C2; 32 tokens 56 -> 52).  A K too short for the deep ring
-// streams in the two-workgroup form, from two tiles per workgroup on (256 experts, K = 128, 2233 tiles: 30 us, 34 per tile).
-// (Between one and two 256-wide tiles per CU the deep form is kept: where a uniform routing is expected to give 280 tiles, it takes 57 us
-// against 54 with two workgroups per CU, but a skewed one of the same size, with less than one per CU, 34 against 45.)
-// CS, CW: with room for the rows of several of the map's tiles, see merges16.
-template <class C, class C2, class CW1, class CS, class CW>
-int launch_stream(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
-    const double expected = expected_tiles16((int64_t)a.T * a.k, a.E, a.N / C::BN);
-    bool launched = false;
-    auto several = [&](int bn) { return merges16((int64_t)a.T * a.k, a.E, a.N / bn, a.K / C::BK, mode); };
+// 16-row tiles over [E][K][N] weights in the form that rows16_form says: C the deep one, C2 the shallow one, C3 that with two wavefronts; CS
+// with room for the rows of several of the map's tiles; CW1, CW two of the map's n-tiles as one, without and with that room.
+template <class C, class C2, class C3, class CS, class CW1, class CW>
+int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    constexpr Rows16Forms f = rows16_forms(C::BN);
+    static_assert(C::NT == f.deep.threads && C::NS == f.deep.stages && C2::NT == f.shallow.threads && C2::NS == f.shallow.stages &&
+                  C3::NT == f.small.threads && C3::NS == f.small.stages, "the rules' forms are these");
+    static_assert(C::BK == (C::FP8 ? 128 : 64) && C2::BK == C::BK && C3::BK == C::BK, "k-tiles");
     static_assert(CS::BN == C::BN && CS::LDS_BYTES == C::LDS_BYTES && CS::NT == C::NT, "the streamed tile is the same but for its rows");
-    if constexpr (CW::BN == 2 * C::BN) {
-        if (a.N % CW::BN == 0) {
-            const int64_t pairs = ((grid - kSpareSlots) / 2 + 7) / 8 * 8;
-            const int rc = several(CW::BN) ? launch_stream_kernel<CW, 2>(a, pairs, mode, s, expected > kCus, &launched)
-                                            : launch_stream_kernel<CW1, 2>(a, pairs, mode, s, expected > kCus, &launched);
-            if (rc != MOE_OK || launched) return rc;
-        }
+    const int form = rows16_form(C::FP8, C::BN, a.T, (int64_t)a.T * a.k, a.E, a.K, a.N, grid, mode);
+    switch (form) {
+        case MOE_ROWS16_PER_TILE_DEEP:
+            if constexpr (C::BN == 256) return launch_pipe<C>(a, grid, mode, s);
+            break;
+        case MOE_ROWS16_PER_TILE: return launch_pipe<C2>(a, grid, mode, s);
+        case MOE_ROWS16_PER_TILE_SMALL: return launch_pipe<C3>(a, grid, mode, s);
+        case MOE_ROWS16_STREAM: return launch_stream_kernel<C, 1>(a, grid, mode, s);
+        case MOE_ROWS16_STREAM_MERGED: return launch_stream_kernel<CS, 1>(a, grid, mode, s);
+        case MOE_ROWS16_STREAM_SHORT_K: return launch_stream_kernel<C2, 1>(a, grid, mode, s);
+        case MOE_ROWS16_PAIRS:
+        case MOE_ROWS16_PAIRS_MERGED:
+            if constexpr (CW::BN == 2 * C::BN) {
+                static_assert(CW::NT == f.pairs.threads && CW::NS == f.pairs.stages && CW1::NT == CW::NT && CW1::NS == CW::NS, "pairs");
+                const int64_t pairs = ((grid - kSpareSlots) / 2 + 7) / 8 * 8;
+                return form == MOE_ROWS16_PAIRS ? launch_stream_kernel<CW1, 2>(a, pairs, mode, s) : launch_stream_kernel<CW, 2>(a, pairs, mode, s);
+            }
+            break;
     }
-    const bool many = C::BN == 256 ? grid >= 2 * kCus : expected > 2 * kCus;
-    const int rc = several(C::BN) ? launch_stream_kernel<CS, 1>(a, grid, mode, s, many, &launched)
-                                  : launch_stream_kernel<C, 1>(a, grid, mode, s, many, &launched);
-    if (rc != MOE_OK || launched) return rc;
-    if (a.K / C::BK < C::NS) {
-        const int rc2 = launch_stream_kernel<C2, 1>(a, grid, mode, s, grid >= 4 * kCus, &launched);
-        if (rc2 != MOE_OK || launched) return rc2;
-    }
-    if constexpr (C::BN == 256) {
-        if (a.K / C::BK >= C::NS) return launch_pipe<C>(a, grid, mode, s);
-    }
-    return launch_rows16<C, C2>(a, grid, mode, s);
+    return MOE_ERR_UNSUPPORTED;
 }
 
-// The same for the 64-wide tile, four workgroups per CU either way: resident from two tiles per workgroup on.
+// The 64-wide fp8 tile, four workgroups per CU either way: resident from two tiles per workgroup on.
 template <class C>
-int launch_stream_narrow(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
-    const int lds = C::LDS_BYTES + 4 * (a.T + a.E);
-    static ResidentCache cache;
-    int resident = 0;
-    bool launched = false;
-    if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C, 1>), C::NT, lds, &cache, &resident) != MOE_OK)
-        return MOE_ERR_HIP;
-    const int rc = launch_stream_kernel<C, 1>(a, grid, mode, s, grid >= 2 * (int64_t)resident, &launched);
-    if (rc != MOE_OK || launched) return rc;
+int launch_narrow(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
+    const bool can_stream = mode != MOE_LAUNCH_PER_TILE && a.E <= kStreamExperts && a.T + a.E <= kStreamScales && a.K / C::BK >= C::NS;
+    if (can_stream) {
+        const int lds = C::LDS_BYTES + 4 * (a.T + a.E);
+        static ResidentCache cache;
+        int resident = 0;
+        if (resident_workgroups(reinterpret_cast<const void*>(&moe_gemm_stream_kernel<C, 1>), C::NT, lds, &cache, &resident) != MOE_OK)
+            return MOE_ERR_HIP;
+        if (mode >= MOE_LAUNCH_RESIDENT || grid >= 2 * (int64_t)resident) return launch_stream_kernel<C, 1>(a, grid, mode, s);
+    }
     return launch_pipe<C>(a, grid, mode, s);
 }
 
@@ -279,6 +229,7 @@ int launch_with_map(const GemmArgs& a, const MapToBuild& m, int64_t tiles, hipSt
 
 template <class CBIG, class CSMALL, class... Tails>
 int launch_pipe2(const GemmArgs& a, int64_t grid, int /*mode*/, hipStream_t s) {
+    if (!work_items_fit(grid, CBIG::NT)) return MOE_ERR_UNSUPPORTED;
     constexpr int lds = CBIG::LDS_BYTES > CSMALL::LDS_BYTES ? CBIG::LDS_BYTES : CSMALL::LDS_BYTES;
     static unsigned long long attr_done = 0;
     if (ensure_lds_attr(reinterpret_cast<const void*>(&moe_gemm_pipe2_kernel<CBIG, CSMALL, Tails...>), lds, &attr_done) != MOE_OK)
@@ -293,8 +244,6 @@ struct GemmVariant {
     int tile_m_small = 0;  // second tiling strategy handled by the same launch (0 = none)
     int tile_m_slack = 0;  // rows the last m-tile may hold beyond tile_m
     int w_layout = MOE_W_LAYOUT_KN;
-    // the same tile as a streaming launch (resident workgroups run several tiles back to back), or nullptr
-    gemm_launch_fn fn_stream = nullptr;
     // the same GEMM tasks batched with a reduction task in one launch (moe_grouped_gemm_batched), or nullptr
     gemm_launch_fn fn_batched = nullptr;
 };
@@ -328,7 +277,7 @@ using Pt_128x256 = PipeCfg<128, 256, 64, 1, 8, 2>;
 // wavefronts to issue a stage's DMA instructions side by side (4 each per stage: a wavefront's own 16 took longer than the
 // stage's share of the HBM rate) streams faster than two workgroups of two wavefronts (the Pe forms): 8 experts, 4096 -> 28672,
 // 16 tokens 280 -> 267 us (7.0 TB/s), 64 experts, 2048 -> 2816, 32 tokens 121 -> 98 us, one token (128-wide) 18.8 -> 14.5 us.
-// launch_rows16 says which of the two runs one workgroup per tile.
+// rows16_form says which of them a launch takes.
 using Pb_16x256 = PipeCfg<16, 256, 64, 1, 8, 3>;
 using Pb_16x128 = PipeCfg<16, 128, 64, 1, 4, 6>;
 // (streamed: as many rows as the token stages hold)
@@ -399,10 +348,10 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 16, 256, 64, &launch_pipe<Pk_16x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_pipe<P8k_16x256>, 0, 0, MOE_W_LAYOUT_NK},
     {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_pipe<P8k_16x128>, 0, 0, MOE_W_LAYOUT_NK},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256, H_256x128>, 0, 0, MOE_W_LAYOUT_KN, nullptr,
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256, H_256x128>, 0, 0, MOE_W_LAYOUT_KN,
      &launch_batched<Pb_256x256, Ps_64x256, Ps_128x256, Pt_128x256>},
     {MOE_DTYPE_BF16, 256, 256, 64, &launch_pipe<Pb_256x256s, Ps_64x256, Ps_128x256, Pt_128x256>, 0, 64},
-    {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256s32, H_256x128>, 0, 32, MOE_W_LAYOUT_KN, nullptr,
+    {MOE_DTYPE_BF16, 256, 256, 64, &launch_halves<F_256x256s32, H_256x128>, 0, 32, MOE_W_LAYOUT_KN,
      &launch_batched<Pb_256x256s32, Ps_64x256, Ps_128x256, Pt_128x256>},
     {MOE_DTYPE_BF16, 128, 256, 64, &launch_halves<F_128x256, H_128x128>},
     {MOE_DTYPE_BF16, 128, 128, 64, &launch_halves<F_128x128, H_128x64>},
@@ -410,11 +359,11 @@ const GemmVariant kVariants[] = {
     {MOE_DTYPE_BF16, 64, 128, 64, &launch_pipe<Pb_64x128>},
     {MOE_DTYPE_BF16, 32, 256, 64, &launch_pipe<Pb_32x256>},
     {MOE_DTYPE_BF16, 32, 128, 64, &launch_pipe<Pb_32x128>},
-    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256, Pe_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x256, Pd_16x256, Pb_16x256, Pq_64x256, Pq_64x256>},
-    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128, Pe_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<Pb_16x128, Pd_16x128, Pb_16x256, Pq_32x128, Pq_64x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256, P8e_16x256>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x256, P8d_16x256, P8_16x256, P8q_64x256, P8q_64x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128, P8e_16x128>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream<P8_16x128, P8d_16x128, P8_16x256, P8q_32x128, P8q_64x256>},
-    {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_pipe<P8_16x64>, 0, 0, MOE_W_LAYOUT_KN, &launch_stream_narrow<P8_16x64>},
+    {MOE_DTYPE_BF16, 16, 256, 64, &launch_rows16<Pb_16x256, Pd_16x256, Pe_16x256, Pq_64x256, Pb_16x256, Pq_64x256>},
+    {MOE_DTYPE_BF16, 16, 128, 64, &launch_rows16<Pb_16x128, Pd_16x128, Pe_16x128, Pq_32x128, Pb_16x256, Pq_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 256, 128, &launch_rows16<P8_16x256, P8d_16x256, P8e_16x256, P8q_64x256, P8_16x256, P8q_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 128, 128, &launch_rows16<P8_16x128, P8d_16x128, P8e_16x128, P8q_32x128, P8_16x256, P8q_64x256>},
+    {MOE_DTYPE_FP8_E4M3, 16, 64, 128, &launch_narrow<P8_16x64>},
     {MOE_DTYPE_FP8_E4M3, 32, 128, 128, &launch_pipe<P8_32x128>},
     {MOE_DTYPE_FP8_E4M3, 256, 256, 128, &launch_halves<F8_256x256, H8_256x128>},
     {MOE_DTYPE_FP8_E4M3, 64, 256, 128, &launch_pipe<P8_64x256>},
@@ -496,10 +445,7 @@ int grouped_gemm_impl(const void* X, const void* W, const void* task_map, void* 
     grid = (grid + 7) / 8 * 8 + kSpareSlots;  // spare slots per XCD: the interleaved dealings round their shares up
     if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
     if (red) return v->fn_batched(a, grid, d->launch_mode, static_cast<hipStream_t>(stream));
-    // weight-streaming tiles: keep the workgroups resident and stream tile after tile where the shape allows it
-    const bool can_stream = v->fn_stream && d->E <= 256 && (d->dtype != MOE_DTYPE_FP8_E4M3 || d->T + d->E <= 2048) &&
-                            d->launch_mode != MOE_LAUNCH_PER_TILE;
-    return (can_stream ? v->fn_stream : v->fn)(a, grid, d->launch_mode, static_cast<hipStream_t>(stream));
+    return v->fn(a, grid, d->launch_mode, static_cast<hipStream_t>(stream));
 }
 
 // ---- task maps
@@ -529,6 +475,18 @@ int check_pair_args(const int32_t* topk_ids, int T, int k, int E, int N, const m
         at2 < at + moe_task_map_bytes(T, k, E, tiling->tile_m, tiling->tile_n, N))
         return MOE_ERR_INVALID_ARG;
     return MOE_OK;
+}
+
+// Form (MOE_ROWS16_*) of the one launch that moe_build_task_map_pair_gemm takes for these sizes, 0 where it takes the two calls' launches.
+int pair_gemm_form(int T, int k, int E, int N, const moe_tiling& g, const moe_gemm_desc* d) {
+    const bool plain16 = g.tile_m == 16 && (g.tile_n == 128 || g.tile_n == 256) && g.order == MOE_ORDER_ASCENDING && g.tile_m_small == 0 && g.tile_m_slack == 0;
+    if (!d || !plain16 || d->T != T || d->k != k || d->E != E || d->N != N || d->tile_m != 16 || d->tile_n != g.tile_n || d->tile_m_small != 0 ||
+        d->small_max_rows != 0 || d->tile_m_slack != 0 || d->dtype != MOE_DTYPE_BF16 || d->w_layout != MOE_W_LAYOUT_KN ||
+        d->launch_mode != MOE_LAUNCH_AUTO || (d->epilogue != MOE_EPILOGUE_NONE && d->epilogue != MOE_EPILOGUE_SWIGLU) ||
+        d->K < 1 || d->K % 64 != 0 || N % g.tile_n != 0 || (int64_t)T * d->K * 2 >= (int64_t)1 << 32)
+        return 0;
+    const int64_t grid = (moe_grid_upper_bound(T, k, E, 16, g.tile_n, N) + 7) / 8 * 8 + kSpareSlots;
+    return with_map_form(g.tile_n, T, (int64_t)T * k, E, d->K, N, grid);
 }
 
 // The launches of a build (arguments already checked).
@@ -621,6 +579,7 @@ int launch_tail_split(const GemmArgs& a, int64_t grid, hipStream_t s) {
     const void* fn = reinterpret_cast<const void*>(&moe_gemm_tail_kernel<Fns, Half, Parts>);
     if (ensure_lds_attr(fn, C::LDS_BYTES, &attr_done) != MOE_OK) return MOE_ERR_HIP;
     grid = 8 * ((grid / 8 + kXcdCus - 1) / kXcdCus * kXcdCus);   // every CU of a last round
+    if (!work_items_fit(grid, C::NT)) return MOE_ERR_UNSUPPORTED;
     moe_gemm_tail_kernel<Fns, Half, Parts><<<dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s>>>(a);
     if (hipGetLastError() != hipSuccess) return MOE_ERR_HIP;
     moe_tail_reduce_kernel<C::BM, C::BN, C::SLACK><<<dim3(8 * (kXcdCus / 2) * kTailReduceSlices), dim3(256), 0, s>>>(a);
@@ -820,34 +779,40 @@ int moe_build_task_map_pair_gemm(const int32_t* topk_ids, int T, int k, int E, i
     int rc = check_pair_args(topk_ids, T, k, E, N, tiling, task_map, N2, tiling2, task_map2);
     if (rc != MOE_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t R = (int64_t)T * k;
     const moe_tiling g = *tiling;
-    // One launch for up to 64 rows and experts (a wavefront's lanes) on 16-row bf16 tiles, in the form that moe_grouped_gemm takes for
-    // them (launch_stream, launch_rows16).
-    if (d && R > 0 && R <= 64 && E <= 64 && g.tile_m == 16 && (g.tile_n == 128 || g.tile_n == 256) && g.order == MOE_ORDER_ASCENDING &&
-        g.tile_m_small == 0 && g.tile_m_slack == 0 && d->dtype == MOE_DTYPE_BF16 && d->w_layout == MOE_W_LAYOUT_KN &&
-        d->launch_mode == MOE_LAUNCH_AUTO && d->T == T && d->k == k && d->E == E && d->N == N && d->tile_m == 16 && d->tile_n == g.tile_n &&
-        d->tile_m_small == 0 && d->small_max_rows == 0 && d->tile_m_slack == 0 &&
-        (d->epilogue == MOE_EPILOGUE_NONE || d->epilogue == MOE_EPILOGUE_SWIGLU) && d->K >= 64 * 3 && d->K % 64 == 0 && N % g.tile_n == 0 &&
-        (int64_t)T * d->K * 2 < (int64_t)1 << 32 && X && W && Y && !(((uintptr_t)X | (uintptr_t)W | (uintptr_t)Y) & 15) &&
-        !merges16(R, E, N / 256, d->K / 64, MOE_LAUNCH_AUTO) && !merges16(R, E, N / 128, d->K / 64, MOE_LAUNCH_AUTO)) {
+    if (pair_gemm_form(T, k, E, N, g, d) != 0 && X && W && Y && !(((uintptr_t)X | (uintptr_t)W | (uintptr_t)Y) & 15)) {
         GemmArgs a{};
         a.X = X; a.W = W; a.Y = Y;
         a.T = T; a.k = k; a.E = E; a.K = d->K; a.N = N;
         a.swiglu = d->epilogue == MOE_EPILOGUE_SWIGLU;
         const MapToBuild m = {topk_ids, static_cast<int32_t*>(task_map), g, {static_cast<int32_t*>(task_map2), N2, *tiling2}};
         const int64_t tiles = moe_grid_upper_bound(T, k, E, 16, g.tile_n, N);
-        const double expected = expected_tiles16(R, E, N / g.tile_n);
-        if (g.tile_n == 256) {
-            return (tiles + 7) / 8 * 8 + kSpareSlots >= 2 * kCus ? launch_with_map<Pb_16x256, 1, true>(a, m, tiles, s)
-                                                                   : launch_with_map<Pb_16x256, 1, false>(a, m, tiles, s);
+        switch (pair_gemm_form(T, k, E, N, g, d)) {
+            case MOE_ROWS16_STREAM: return launch_with_map<Pb_16x256, 1, true>(a, m, tiles, s);
+            case MOE_ROWS16_PER_TILE_DEEP: return launch_with_map<Pb_16x256, 1, false>(a, m, tiles, s);
+            case MOE_ROWS16_PAIRS: return launch_with_map<Pb_16x256, 2, true>(a, m, tiles / 2, s);
+            case MOE_ROWS16_PER_TILE: return launch_with_map<Pd_16x128, 1, false>(a, m, tiles, s);
         }
-        if (N % 256 == 0 && expected > kCus) return launch_with_map<Pb_16x256, 2, true>(a, m, tiles / 2, s);
-        if (expected <= kCus) return launch_with_map<Pd_16x128, 1, false>(a, m, tiles, s);
     }
     const TwinMap twin = {static_cast<int32_t*>(task_map2), N2, *tiling2};
     rc = build_maps(topk_ids, T, k, E, N, g, task_map, twin, s);
     return rc != MOE_OK ? rc : grouped_gemm_impl(X, W, task_map, Y, d, nullptr, stream);
+}
+
+int moe_pair_gemm_launches(int T, int k, int E, int N, const moe_tiling* tiling, const moe_gemm_desc* d) {
+    if (!tiling || !d || check_map_args(T, k, E, tiling->tile_m, tiling->tile_n, N) != MOE_OK) return MOE_ERR_INVALID_ARG;
+    return pair_gemm_form(T, k, E, N, *tiling, d) != 0 ? 1 : 2;
+}
+
+int moe_rows16_launch(int dtype, int tile_n, int T, int k, int E, int K, int N, int launch_mode) {
+    if ((dtype != MOE_DTYPE_BF16 && dtype != MOE_DTYPE_FP8_E4M3) || launch_mode < 0 || T < 1 || K < 1) return MOE_ERR_INVALID_ARG;
+    const int rc = check_map_args(T, k, E, 16, tile_n, N);
+    if (rc != MOE_OK) return rc;
+    const int bk = dtype == MOE_DTYPE_BF16 ? 64 : 128;
+    if ((tile_n != 128 && tile_n != 256) || K % bk != 0 || N % tile_n != 0) return MOE_ERR_UNSUPPORTED;
+    const int64_t grid = (moe_grid_upper_bound(T, k, E, 16, tile_n, N) + 7) / 8 * 8 + kSpareSlots;
+    if (grid > 0x7fffffff) return MOE_ERR_UNSUPPORTED;
+    return rows16_form(dtype == MOE_DTYPE_FP8_E4M3, tile_n, T, (int64_t)T * k, E, K, N, grid, launch_mode);
 }
 
 int moe_task_map_status(const void* task_map, void* stream) {

@@ -94,3 +94,23 @@ def test_more_tiles_than_work_items_of_the_deep_form():
         want = (torch.nn.functional.silu(gate) * up).to(torch.bfloat16).double()
         # one bf16 rounding each, and K * 2^-24 of sums of at most about 4 * |x||w| in front of it
         assert ((Y[:, e].double() - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4).all(), f"expert {e}"
+
+
+@pytest.mark.parametrize("tile_n,K", [(256, 64), (128, 128)])
+def test_more_tiles_than_work_items_where_tiles_could_stream(tile_n, K):
+    """The same with 256 experts, which stream but for the short K: 2^23 + 2048 tiles of 256 columns, 2^24 + 4096 of 128."""
+    dev, T, E, N = torch.device("cuda:0"), 65536, 256, 2048
+    assert mb.moe_rows16_launch(mb.MOE_DTYPE_BF16, tile_n, T, E, E, K, N) == mb.MOE_ROWS16_PER_TILE_SMALL
+    g = torch.Generator(device=dev).manual_seed(6)
+    X = torch.randn(T, K, generator=g, device=dev).to(torch.bfloat16)
+    W = (torch.randn(E, K, N, generator=g, device=dev) * K ** -0.5).to(torch.bfloat16)
+    ids = torch.arange(E, dtype=torch.int32, device=dev).expand(T, E).contiguous()
+    tmap = mb.alloc_task_map(T, E, E, 16, tile_n, N)
+    mb.moe_build_task_map(ids, T, E, E, 16, tile_n, N, tmap)
+    Y = torch.empty(T, E, N // 2, dtype=torch.bfloat16, device=dev)
+    mb.moe_grouped_gemm(X, W, ids, tmap, Y, mb.GemmDesc(mb.MOE_DTYPE_BF16, T, E, E, K, N, 16, tile_n, epilogue=mb.MOE_EPILOGUE_SWIGLU))
+    for e in (0, 1, 127, 128, 254, 255):
+        gate, up = (X.double() @ W[e].double()).split(N // 2, dim=1)
+        want = (torch.nn.functional.silu(gate) * up).to(torch.bfloat16).double()
+        # as above: one bf16 rounding each, and K * 2^-24 of sums of at most about 4 * |x||w| (|w| of the order of 1 in all) in front of it
+        assert ((Y[:, e].double() - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4).all(), f"expert {e}"

@@ -1,0 +1,72 @@
+"""Which form of launch a product on 16-row tiles takes (host only)."""
+import pytest
+
+from paper_2501_16103_amd import binding as mb
+
+BF16, FP8 = mb.MOE_DTYPE_BF16, mb.MOE_DTYPE_FP8_E4M3
+THREADS = {  # threads of a workgroup, by tile width: the forms of one workgroup per tile
+    mb.MOE_ROWS16_PER_TILE_DEEP: {256: 512, 128: 256},
+    mb.MOE_ROWS16_PER_TILE: {256: 512, 128: 256},
+    mb.MOE_ROWS16_PER_TILE_SMALL: {256: 128, 128: 128},
+}
+
+
+def _grid(T, k, E, tile_n, N):
+    return (mb.moe_grid_upper_bound(T, k, E, 16, tile_n, N) + 7) // 8 * 8 + 16
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP8])
+@pytest.mark.parametrize("tile_n,E,K,N,T", [
+    (256, 256, 1, 2048, 65536),     # 2^23 + 2048 tiles, streaming refused: one k-tile
+    (256, 512, 1, 2048, 32768),     # ... and more than 256 experts
+    (128, 256, 1, 2048, 65536),     # 2^24 + 4096 narrow ones
+    (128, 512, 2, 2048, 32768),
+    (128, 256, 3, 32768, 4096),     # K below every ring
+])
+def test_a_launch_of_too_many_work_items_takes_two_wavefronts(dtype, tile_n, E, K, N, T):
+    K *= 64 if dtype == BF16 else 128
+    form = mb.moe_rows16_launch(dtype, tile_n, T, E, E, K, N, mb.MOE_LAUNCH_PER_TILE)
+    assert form == mb.MOE_ROWS16_PER_TILE_SMALL
+    assert mb.moe_rows16_launch(dtype, tile_n, T, E, E, K, N) in (form, mb.MOE_ROWS16_STREAM_SHORT_K, mb.MOE_ROWS16_PAIRS_MERGED, mb.MOE_ROWS16_PAIRS)
+    if K == (64 if dtype == BF16 else 128):
+        assert mb.moe_rows16_launch(dtype, tile_n, T, E, E, K, N) == form
+
+
+@pytest.mark.parametrize("dtype", [BF16, FP8])
+@pytest.mark.parametrize("mode", [mb.MOE_LAUNCH_AUTO, mb.MOE_LAUNCH_PER_TILE, mb.MOE_LAUNCH_RESIDENT])
+@pytest.mark.parametrize("tile_n", [256, 128])
+def test_no_form_of_one_workgroup_per_tile_overflows(dtype, mode, tile_n):
+    """Up to the most rows a map holds and beyond the widest product: every launch fits 2^32 - 1 work items or is refused."""
+    bk, seen, refused = 64 if dtype == BF16 else 128, set(), 0
+    for E in (1, 8, 255, 256, 257, 512, 1024):
+        for k in (1, E):
+            for k_tiles in (1, 2, 3, 4, 5, 6, 40):
+                for T in (1, 77, (1 << 20) // k, (1 << 24) // k):
+                    for N in (256, 2048, 4096 + 256, 32768, 65536, 1 << 20):
+                        if T < 1:
+                            continue
+                        form = mb.moe_rows16_launch(dtype, tile_n, T, k, E, k_tiles * bk, N, mode)
+                        grid = _grid(T, k, E, tile_n, N)
+                        seen.add(form)
+                        if form == mb.MOE_ERR_UNSUPPORTED:
+                            refused += 1
+                            assert grid * 128 >= 1 << 32
+                        elif form in THREADS:
+                            assert grid * THREADS[form][tile_n] < 1 << 32, (E, k, k_tiles, T, N)
+                            if form == mb.MOE_ROWS16_PER_TILE_SMALL:
+                                assert grid * THREADS[mb.MOE_ROWS16_PER_TILE][tile_n] >= 1 << 32
+    assert mb.MOE_ROWS16_PER_TILE_SMALL in seen and mb.MOE_ROWS16_PER_TILE in seen and refused
+
+
+@pytest.mark.parametrize("args,want", [
+    ((BF16, 256, 1, 1, 8, 64, 512, -1), mb.MOE_ERR_INVALID_ARG),
+    ((2, 256, 1, 1, 8, 64, 512, 0), mb.MOE_ERR_INVALID_ARG),
+    ((BF16, 256, 1, 9, 8, 64, 512, 0), mb.MOE_ERR_INVALID_ARG),
+    ((BF16, 64, 1, 1, 8, 64, 512, 0), mb.MOE_ERR_UNSUPPORTED),
+    ((BF16, 256, 1, 1, 8, 96, 512, 0), mb.MOE_ERR_UNSUPPORTED),
+    ((FP8, 128, 1, 1, 8, 64, 512, 0), mb.MOE_ERR_UNSUPPORTED),
+    ((BF16, 256, 1, 1, 8, 64, 384, 0), mb.MOE_ERR_UNSUPPORTED),
+    ((BF16, 256, 1, 1, 2000, 64, 512, 0), mb.MOE_ERR_UNSUPPORTED),
+])
+def test_form_of_what_the_product_refuses(args, want):
+    assert mb.moe_rows16_launch(*args) == want
