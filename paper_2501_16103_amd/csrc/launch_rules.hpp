@@ -71,7 +71,12 @@ constexpr Rows16Forms rows16_forms(int tile_n) {
 // 22.2 streaming; 572 tiles 32.4 / 28.6); where N holds a whole number of 256-wide ones, the map's n-tiles are
 // run in pairs once more of them are expected than CUs (fp8, 64 experts,
 // 2048 -> 2816: 3 tokens, 330 tiles, 22.5 -> 18.0 us, 20.5 with two workgroups per CU; 32 tokens 56 -> 52).  A K too short for the deep ring
-// streams in the two-workgroup form, from two tiles per workgroup on (256 experts, K = 128, 2233 tiles: 30 us, 34 per tile).
+// streams in a form of two workgroups per CU.  bf16: from two tiles per workgroup on (per tile / streaming, us: 256 experts, K = 128, 2 rows each,
+// N = 2048 24.4 / 22.3, N = 1024 14.2 / 13.2; skewed 16.7 / 17.5, 10.6 / 12.6).  fp8: the scales behind the rings leave room for two workgroups
+// of two wavefronts only (kStreamScales), which one workgroup per tile, of four, overtakes: 64 experts, 512 -> 1408, 100 tokens, top-6, even 12.4 /
+// 16.3, skewed 13.5 / 16.8; 128 experts, 512 -> 1920, 256 tokens, top-8, 36.1 / 40.7 and 38.1 / 45.6; 256 experts, 512 -> 3968, 600 tokens 158
+// / 162 and 153 / 167.  They lead where tiles are sixteen per CU and nearly empty: 128 experts, 512 -> 8064, 40 tokens 90.9 / 85.6 and
+// 67.3 / 66.6, 150 tokens 114 / 110 and 117 / 120; 256 experts, 512 -> 3968, 150 tokens 98 / 95 and 85 / 88, 256 tokens 108 / 103 and 108 / 111.
 // (Between one and two 256-wide tiles per CU the deep form is kept: where a uniform routing is expected to give 280 tiles, it takes 57 us
 // against 54 with two workgroups per CU, but a skewed one of the same size, with less than one per CU, 34 against 45.)
 inline int rows16_form(bool fp8, int tile_n, int T, int64_t R, int E, int K, int N, int64_t grid, int mode) {
@@ -86,8 +91,9 @@ inline int rows16_form(bool fp8, int tile_n, int T, int64_t R, int E, int K, int
             if (asked || (wide ? grid >= 2 * kCus : expected > 2 * kCus))
                 return merges16(R, E, N / tile_n, k_tiles, mode) ? MOE_ROWS16_STREAM_MERGED : MOE_ROWS16_STREAM;
             if (wide) return MOE_ROWS16_PER_TILE_DEEP;
-        } else if (k_tiles >= f.shallow.stages && (asked || grid >= 4 * kCus)) {
-            return MOE_ROWS16_STREAM_SHORT_K;
+        } else if (k_tiles >= f.shallow.stages) {
+            const bool many = fp8 ? expected >= 16 * kCus && R < 12 * (int64_t)E : grid >= 4 * kCus;
+            if (asked || many) return MOE_ROWS16_STREAM_SHORT_K;
         }
     }
     const bool deep = wide && (expected <= kCus || (expected > 2 * kCus && k_tiles >= 32));

@@ -177,6 +177,9 @@ int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
                   C3::NT == f.small.threads && C3::NS == f.small.stages, "the rules' forms are these");
     static_assert(C::BK == (C::FP8 ? 128 : 64) && C2::BK == C::BK && C3::BK == C::BK, "k-tiles");
     static_assert(CS::BN == C::BN && CS::LDS_BYTES == C::LDS_BYTES && CS::NT == C::NT, "the streamed tile is the same but for its rows");
+    // A short K streams two workgroups per CU: with the scales behind its rings only the smallest fp8 form leaves room for a second one.
+    using CK = std::conditional_t<C::FP8, C3, C2>;
+    static_assert(CK::NS <= f.shallow.stages && 2 * (CK::LDS_BYTES + (C::FP8 ? 4 * kStreamScales : 0)) <= 160 * 1024, "two per CU");
     const int form = rows16_form(C::FP8, C::BN, a.T, (int64_t)a.T * a.k, a.E, a.K, a.N, grid, mode);
     switch (form) {
         case MOE_ROWS16_PER_TILE_DEEP:
@@ -186,7 +189,7 @@ int launch_rows16(const GemmArgs& a, int64_t grid, int mode, hipStream_t s) {
         case MOE_ROWS16_PER_TILE_SMALL: return launch_pipe<C3>(a, grid, mode, s);
         case MOE_ROWS16_STREAM: return launch_stream_kernel<C, 1>(a, grid, mode, s);
         case MOE_ROWS16_STREAM_MERGED: return launch_stream_kernel<CS, 1>(a, grid, mode, s);
-        case MOE_ROWS16_STREAM_SHORT_K: return launch_stream_kernel<C2, 1>(a, grid, mode, s);
+        case MOE_ROWS16_STREAM_SHORT_K: return launch_stream_kernel<CK, 1>(a, grid, mode, s);
         case MOE_ROWS16_PAIRS:
         case MOE_ROWS16_PAIRS_MERGED:
             if constexpr (CW::BN == 2 * C::BN) {

@@ -28,6 +28,8 @@ CASES = [
     ("bf16", "kn", 128, 60, 32, 2, 320, 384, "zipf", False, (8, 32, 2)),
     ("fp8", "kn", 256, 60, 32, 2, 256, 512, "zipf", False, (8, 32, 2)),
     ("fp8", "kn", 128, 60, 32, 2, 512, 640, "gauss_topk", True, (8, 32, 2)),
+    # ... with the most scales that a streaming launch holds (T + E = 2048)
+    ("fp8", "kn", 128, 1984, 64, 1, 512, 384, "zipf", False, (8, 64, 2)),
     # more tiles than CUs, one workgroup per tile in the two-wavefront form (more than 256 experts, or T + E > 2048)
     ("bf16", "kn", 256, 100, 300, 4, 192, 512, "gauss_topk", False, (2,)),
     ("bf16", "kn", 128, 100, 300, 4, 384, 256, "zipf", True, (2,)),

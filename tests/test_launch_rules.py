@@ -70,3 +70,21 @@ def test_no_form_of_one_workgroup_per_tile_overflows(dtype, mode, tile_n):
 ])
 def test_form_of_what_the_product_refuses(args, want):
     assert mb.moe_rows16_launch(*args) == want
+
+
+@pytest.mark.parametrize("dtype,tile_n,E,k,K,N,T,want", [
+    (FP8, 128, 64, 6, 512, 1408, 100, mb.MOE_ROWS16_PER_TILE),            # 1111 tiles at most: two per workgroup of a streaming launch
+    (FP8, 128, 256, 8, 512, 3968, 128, mb.MOE_ROWS16_STREAM_SHORT_K),     # sixteen tiles per CU, 4 rows per expert
+    (FP8, 128, 256, 8, 512, 3968, 383, mb.MOE_ROWS16_STREAM_SHORT_K),
+    (FP8, 128, 256, 8, 512, 3968, 384, mb.MOE_ROWS16_PER_TILE),           # ... 12
+    (FP8, 128, 256, 8, 512, 2176, 45, mb.MOE_ROWS16_PER_TILE),            # 3303 tiles expected
+    (FP8, 128, 256, 8, 384, 3968, 128, mb.MOE_ROWS16_PER_TILE),           # three k-tiles: below this ring too
+    (FP8, 256, 256, 8, 256, 2816, 64, mb.MOE_ROWS16_PER_TILE),
+    (BF16, 256, 256, 8, 128, 2048, 64, mb.MOE_ROWS16_STREAM_SHORT_K),     # no scales: from two tiles per workgroup on
+    (BF16, 128, 128, 8, 320, 1408, 64, mb.MOE_ROWS16_STREAM_SHORT_K),
+    (BF16, 256, 64, 6, 128, 1024, 64, mb.MOE_ROWS16_PER_TILE_DEEP),
+])
+def test_short_k_streams_where_two_workgroups_fit_a_cu_and_lead(dtype, tile_n, E, k, K, N, T, want):
+    assert mb.moe_rows16_launch(dtype, tile_n, T, k, E, K, N) == want
+    if K // (64 if dtype == BF16 else 128) >= (2 if tile_n == 256 else 4):
+        assert mb.moe_rows16_launch(dtype, tile_n, T, k, E, K, N, mb.MOE_LAUNCH_RESIDENT) == mb.MOE_ROWS16_STREAM_SHORT_K
