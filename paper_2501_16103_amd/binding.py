@@ -493,22 +493,40 @@ class MoeLayerPlan:
         return Tiling(128, 128) if narrow else g
 
     @staticmethod
-    def _streamed(g: Tiling, R: int, E: int, K: int, N: int) -> Tiling:
-        """A gate+up product of 9 to 32 rows per expert whose wide tiles are 1.75 to 4 rounds of the chip, with a long K, is run by the streaming
-        launch of the 16-row tiles (which takes up to 64 rows of an expert as one tile) instead of one workgroup per 256 x 256 tile: the
-        weights of such a launch are all it moves, and a round's start, end and remainder are a tenth of it.  Even / skewed routing,
-        us, 256 x 256 and this: 8 experts, 4096 -> 28672, 9 rows each 311 273 / 312 278, 26 rows 309 283 / 328 313; 4096 -> 14336, 16 rows 162 148 / 165 152;
-        16 experts, 26 rows 318 296 / 334 316; 64 experts, 4096 -> 4096, 16 rows 348 335 / 356 348, but 26 rows 351 341 / 370 383.  At one round
-        (8 experts, 2048 -> 8192, 9 rows 48 46 / 47 69), more than four (256 experts, 7168 -> 4096, 12 rows 2208 / 2284) and with a shorter K (64
-        experts, 2048 -> 2816, 16 rows 115 117 / 122 123) it loses."""
-        tiles, few = E * (N // 256), 8 * E < R <= (32 if E <= 16 else 16) * E
-        streams = few and K >= 4096 and N % 256 == 0 and 448 <= tiles <= 1024 and g.tile_m == 256
-        return Tiling(16, 256) if streams else g
+    def _streamed(g: Tiling, T: int, k: int, E: int, K: int, N: int) -> Tiling:
+        """A gate+up product of 9 to 32 rows per expert whose wide tiles are 1.75 to 4 rounds of the chip, and whose 16-row tiles the library would
+        stream with up to 64 rows of an expert as one tile, is run that way instead of with one workgroup per 256 x 256 tile: the weights
+        of such a launch are all it moves, and a round's start, end and remainder are a tenth of it.  What separates gain from loss is N: where
+        the weight rows are a multiple of 2 KB long, the tiles read them at 5.7 to 6.0 TB/s, elsewhere at 6.2 to 6.4, what the
+        stream reads anywhere.  Gain with an even / a skewed routing, weights from HBM (256 x 256 over this):
+          N a multiple of 1024, 9 to 16 rows: 8 experts, K = 1024 to 7168, N = 28672 1.11 to 1.16 / 1.10 to 1.16; 16 experts, K = 2048, N = 14336 1.11 to
+            1.12 / 1.09 to 1.13; 32, 1024 to 4096, 8192 1.04 to 1.07 / 1.00 to 1.04; 64, 2048 to 4096, 3072 1.02 to 1.04 / 1.01 to 1.05; 256, 4096, 1024 1.06 /
+            0.97 to 1.06.  (K does not matter from 1024, where the library merges, on.)
+          a multiple of 512, 9 to 16 rows: up to 48 experts 1.00 to 1.11 / 0.98 to 1.08 (8 experts, 17920 and 22016; 16, 11776; 32, 5632 and 7680; 48,
+            3584), beyond 0.94 to 1.06 / 0.94 to 1.03 (64, 2560 and 3584; 96 and 128, 1536)
+          others, 9 to 16 rows: 0.93 to 1.05 / 0.92 to 1.07 (8, 14592 and 28416; 16, 9984; 64, 2304, 2816 and 3840; 128, 1280; 256, 768)
+          17 to 32 rows, N a multiple of 1024: up to 16 experts 1.00 to 1.15 / 0.94 to 1.12, but with 449 to 512 tiles, two rounds without room for the
+            busy experts' second tiles, 1.03 to 1.11 / 0.86 to 1.06; beyond 16 experts 0.98 to 1.11 / 0.84 to 1.08
+          17 to 32 rows, others: 0.89 to 1.08 / 0.83 to 1.06
+        A few rows more than 8 on 448 to 511 tiles are not merged, as it would not save a round: with 448 still 1.09 to 1.11 / 1.00 to 1.04 (8 experts) and 1.06
+        / 0.97 (16), but 480 1.02 / 0.87 (12) and 32 experts 1.05 / 0.86.  Fewer tiles, 9 rows: 8 experts, 2048 -> 8192 48 / 46 us even, 47 / 69 skewed.
+        Beyond 1024 the gain fades (1280 tiles 1.01 to 1.09 / 0.99 to 1.06; 256 experts, 7168 -> 4096, 12 rows 0.97).  Beyond 256 experts nothing streams:
+        every 16-row tile would read its panel by itself (384 experts, 4096 -> 512, 9 rows 0.90 / 0.96, 24 rows 0.74 / 0.74)."""
+        R, tiles = T * k, E * (N // 256)
+        spare = not 448 < tiles <= 512       # room in the second round for a skewed routing's second tiles
+        if R <= 16 * E:
+            fits = N % (512 if E <= 48 else 1024) == 0
+        else:
+            fits = R <= 32 * E and E <= 16 and N % 1024 == 0 and spare
+        if not (fits and R > 8 * E and 448 <= tiles <= 1024 and g.tile_m == 256):
+            return g
+        form = moe_rows16_launch(MOE_DTYPE_BF16, 256, T, k, E, K, N)
+        return Tiling(16, 256) if form == MOE_ROWS16_STREAM_MERGED or (form == MOE_ROWS16_STREAM and E <= 16 and spare and K >= 1024) else g
 
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):
         self.T, self.k, self.E, self.hidden, self.inter = T, k, E, hidden, inter
         R = T * k
-        self.g1 = self._streamed(moe_default_tiling(MOE_DTYPE_BF16, T, k, E, hidden, 2 * inter), R, E, hidden, 2 * inter)
+        self.g1 = self._streamed(moe_default_tiling(MOE_DTYPE_BF16, T, k, E, hidden, 2 * inter), T, k, E, hidden, 2 * inter)
         # the down product is the short-grid case (few experts, N = hidden): split along K where that pays
         self.tail_split = R > 0 and moe_default_tail_split(R, 1, E, inter, hidden)
         self.k_parts = moe_default_k_parts(R, 1, E, inter, hidden) if R > 0 and not self.tail_split else 1

@@ -11,12 +11,33 @@ from paper_2501_16103_amd import binding as mb
     (129, 2, 8, 4096, 14336, (256, 256)),
     (64, 2, 8, 4096, 7168, (16, 256)),      # 448 wide tiles
     (64, 2, 8, 4096, 7040, (256, 256)),     # 440
-    (64, 2, 8, 3840, 14336, (256, 256)),    # a K below 4096
+    (64, 2, 8, 3840, 14336, (16, 256)),     # any K from which the streamed tiles are merged on
+    (64, 2, 8, 1024, 14336, (16, 256)),
+    (64, 2, 8, 768, 14336, (256, 256)),
     (64, 4, 16, 4096, 8192, (16, 256)),     # 1024 wide tiles, 16 experts
     (128, 4, 16, 4096, 8192, (16, 256)),
     (64, 4, 17, 4096, 8192, (256, 256)),    # 1088
     (102, 4, 24, 4096, 4096, (256, 256)),   # 17 rows per expert, more than 16 experts
     (96, 4, 24, 4096, 4096, (16, 256)),     # 16
+    (36, 2, 8, 4096, 7168, (16, 256)),      # 9 rows: merging the 448 tiles would not save a round, but the second one has room
+    (54, 2, 12, 2048, 5120, (256, 256)),    # ... 480: little room
+    (76, 4, 32, 2048, 1792, (256, 256)),    # ... 448, more experts
+    (36, 2, 8, 768, 7168, (256, 256)),
+    (64, 2, 8, 2048, 11008, (16, 256)),     # N a multiple of 512: up to 48 experts and 16 rows
+    (65, 2, 8, 2048, 11008, (256, 256)),
+    (128, 6, 48, 2048, 1792, (16, 256)),
+    (152, 6, 64, 2048, 1280, (256, 256)),
+    (152, 6, 64, 2048, 1536, (16, 256)),    # ... of 1024
+    (152, 6, 64, 2048, 1408, (256, 256)),
+    (256, 8, 128, 2048, 1024, (16, 256)),
+    (400, 8, 256, 4096, 512, (16, 256)),
+    (65, 4, 16, 2048, 4096, (256, 256)),    # 17 rows, 512 tiles: no room in the last round
+    (64, 4, 16, 2048, 4096, (16, 256)),
+    (65, 4, 16, 2048, 3584, (16, 256)),     # ... 448
+    (400, 8, 257, 4096, 256, (256, 256)),   # more experts than a launch streams
+    (400, 8, 300, 4096, 256, (256, 256)),
+    (600, 8, 384, 4096, 256, (256, 256)),
+    (768, 8, 512, 4096, 256, (256, 256)),
     (777, 6, 64, 2048, 1408, (128, 256)),
 ])
 def test_tiling_of_the_first_product(T, k, E, hidden, inter, want):
