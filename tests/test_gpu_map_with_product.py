@@ -7,6 +7,9 @@ from paper_2501_16103_amd import binding as mb
 
 pytestmark = pytest.mark.gpu
 
+# the forms of the one launch, for 128- and 256-wide tiles (None: the two calls' launches)
+TILE, DEEP, PAIRS, STREAM = mb.MOE_ROWS16_PER_TILE, mb.MOE_ROWS16_PER_TILE_DEEP, mb.MOE_ROWS16_PAIRS, mb.MOE_ROWS16_STREAM
+
 
 def _routing(kind, T, k, E, g):
     if kind == "one":          # every row on one expert: several 16-row tiles, rows beyond the first in the same lane order
@@ -20,33 +23,34 @@ def _routing(kind, T, k, E, g):
     return torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).to(torch.int32)
 
 
-@pytest.mark.parametrize("T,k,E,K,N,kind,swiglu", [
-    (1, 6, 64, 256, 384, "topk", True),        # 128-wide tiles, one workgroup each
-    (1, 1, 1, 192, 256, "topk", False),        # the smallest K and one expert
-    (7, 2, 8, 512, 640, "topk", False),        # N with an odd number of 128-wide tiles
-    (64, 1, 64, 256, 2816, "topk", True),      # as many rows and experts as a wavefront has lanes
-    (10, 6, 64, 320, 2816, "repeat", True),    # 256-wide tiles or pairs, resident
-    (32, 2, 5, 256, 512, "repeat", False),
-    (33, 1, 3, 256, 256, "one", False),        # three tiles of one expert, the last with one row
-    (64, 1, 64, 256, 128, "one", True),
-    (4, 6, 64, 2048, 2816, "topk", True),      # 256-wide tiles, one workgroup each
-    (9, 7, 60, 256, 8192, "topk", False),      # 63 rows, E below a multiple of 64
-    (12, 5, 64, 256, 512, "bad", False),       # an id outside [0, E): maps with a status, no product
-    (13, 5, 64, 256, 512, "topk", False),      # 65 rows: the two calls
-    (6, 4, 65, 256, 512, "topk", False),       # 65 experts: the two calls
+@pytest.mark.parametrize("T,k,E,K,N,kind,swiglu,forms", [
+    (1, 6, 64, 256, 384, "topk", True, (TILE,)),        # 128-wide tiles, one workgroup each
+    (1, 1, 1, 192, 256, "topk", False, (TILE, DEEP)),        # the smallest K and one expert
+    (7, 2, 8, 512, 640, "topk", False, (TILE,)),        # N with an odd number of 128-wide tiles
+    (64, 1, 64, 256, 2816, "topk", True, (PAIRS, STREAM)),      # as many rows and experts as a wavefront has lanes
+    (10, 6, 64, 320, 2816, "repeat", True, (PAIRS, STREAM)),    # 256-wide tiles or pairs, resident
+    (32, 2, 5, 256, 512, "repeat", False, (TILE, DEEP)),
+    (33, 1, 3, 256, 256, "one", False, (TILE, DEEP)),        # three tiles of one expert, the last with one row
+    (64, 1, 64, 256, 128, "one", True, (TILE,)),
+    (4, 6, 64, 2048, 2816, "topk", True, (PAIRS, DEEP)),      # 256-wide tiles, one workgroup each
+    (9, 7, 60, 256, 8192, "topk", False, (PAIRS, STREAM)),      # 63 rows, E below a multiple of 64
+    (12, 5, 64, 256, 512, "bad", False, (TILE, DEEP)),       # an id outside [0, E): maps with a status, no product
+    (13, 5, 64, 256, 512, "topk", False, (None, None)),      # 65 rows: the two calls
+    (6, 4, 65, 256, 512, "topk", False, (None, None)),       # 65 experts: the two calls
 ])
-def test_product_with_its_maps(T, k, E, K, N, kind, swiglu):
+def test_product_with_its_maps(T, k, E, K, N, kind, swiglu, forms):
     dev = torch.device("cuda:0")
     g = torch.Generator().manual_seed(100 * T + E)
     ids = _routing(kind, T, k, E, g).to(dev)
     X = torch.randn((T, K), generator=g).to(torch.bfloat16).to(dev)
     W = (torch.randn((E, K, N), generator=g) * K ** -0.5).to(torch.bfloat16).to(dev)
     out = N // 2 if swiglu else N
-    for tile_n in (128, 256):
-        if N % tile_n:
-            continue
+    assert len(forms) == sum(N % tile_n == 0 for tile_n in (128, 256))
+    for tile_n, form in zip((128, 256), forms):
         g1, g2, N2 = mb.Tiling(16, tile_n), mb.Tiling(128, 128), 256
         d = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, k, E, K, N, 16, tile_n, epilogue=int(swiglu))
+        assert mb.moe_pair_gemm_launches(T, k, E, N, g1, d) == (1 if form else 2)
+        assert form is None or mb.moe_rows16_launch(mb.MOE_DTYPE_BF16, tile_n, T, k, E, K, N) == form
         got = []
         for together in (False, True):
             m1, m2 = mb.alloc_task_map(T, k, E, 16, tile_n, N, dev), mb.alloc_task_map(T * k, 1, E, 128, 128, N2, dev)
@@ -65,11 +69,14 @@ def test_product_with_its_maps(T, k, E, K, N, kind, swiglu):
         if kind == "bad":
             assert bool((Y == 9.0).all())
         else:
-            want = torch.einsum("rk,rkn->rn", X.float().repeat_interleave(k, 0), W[ids.flatten().long()].float()) if T * k * K * N < 1 << 27 else None
-            if want is not None and not swiglu:
-                err = (Y.float() - want).abs()
-                assert float(err.max()) < 2.0 ** -7 * float(want.abs().max()) + 1e-3
-                assert np.isfinite(float(err.max()))
+            if T * k * K * N >= 1 << 28:
+                continue
+            want = torch.einsum("rk,rkn->rn", X.float().repeat_interleave(k, 0), W[ids.flatten().long()].float())
+            if swiglu:
+                want = torch.nn.functional.silu(want[:, :out]) * want[:, out:]
+            err = (Y.float() - want).abs()
+            assert float(err.max()) < 2.0 ** -7 * float(want.abs().max()) + 1e-3
+            assert np.isfinite(float(err.max()))
 
 
 def test_product_with_its_maps_refuses_what_the_calls_refuse():

@@ -88,3 +88,24 @@ def test_short_k_streams_where_two_workgroups_fit_a_cu_and_lead(dtype, tile_n, E
     assert mb.moe_rows16_launch(dtype, tile_n, T, k, E, K, N) == want
     if K // (64 if dtype == BF16 else 128) >= (2 if tile_n == 256 else 4):
         assert mb.moe_rows16_launch(dtype, tile_n, T, k, E, K, N, mb.MOE_LAUNCH_RESIDENT) == mb.MOE_ROWS16_STREAM_SHORT_K
+
+
+@pytest.mark.parametrize("T,k,E,K,N,tile_n,want", [
+    (64, 1, 64, 192, 2816, 256, 1),
+    (65, 1, 64, 192, 2816, 256, 2),     # more rows than a wavefront has lanes
+    (16, 4, 65, 192, 2816, 256, 2),     # ... experts
+    (64, 1, 64, 128, 2816, 256, 2),     # a K shorter than the ring
+    (32, 2, 4, 1024, 32768, 256, 2),    # an expert's rows run as one tile
+    (32, 2, 4, 1024, 32768, 128, 2),
+    (8, 8, 64, 192, 5 * 128, 128, 1),
+    (64, 1, 64, 192, 11 * 128, 128, 2),     # more than one narrow tile per CU, and no pairs
+])
+def test_one_launch_for_maps_and_product(T, k, E, K, N, tile_n, want):
+    d = dict(dtype=BF16, T=T, k=k, E=E, K=K, N=N, tile_m=16, tile_n=tile_n)
+    g = mb.Tiling(16, tile_n)
+    assert mb.moe_pair_gemm_launches(T, k, E, N, g, mb.GemmDesc(**d)) == want
+    for other in (dict(dtype=FP8, K=K * 2), dict(w_layout=mb.MOE_W_LAYOUT_NK), dict(launch_mode=1), dict(launch_mode=2), dict(T=T + 1), dict(tile_m=32),
+                  dict(tile_m_slack=4), dict(tile_m_small=16), dict(K=K + 32), dict(epilogue=7)):
+        assert mb.moe_pair_gemm_launches(T, k, E, N, g, mb.GemmDesc(**{**d, **other})) == 2
+    for tiling in (mb.Tiling(16, tile_n, order=1), mb.Tiling(32, tile_n), mb.Tiling(128, tile_n, tile_m_small=16, small_max_rows=8)):
+        assert mb.moe_pair_gemm_launches(T, k, E, N, tiling, mb.GemmDesc(**d)) == 2
