@@ -113,7 +113,8 @@ template <int BM_, int BN_, int BK_, int WM_, int WN_, int NS_, bool FP8_ = fals
           bool WKC_ = false, int MFO_ = 0, int NSWH_ = 0, int NSWQ_ = 0>
 struct PipeCfg {
     static constexpr bool SPLITK = false;
-    static constexpr bool ALONE = false;
+    static constexpr bool ALONE = false;    // see run_tile
+    static constexpr bool W_ONCE = false;   // weights fetched non-temporally throughout (see TileFnsOnce)
     static constexpr bool WKC = WKC_;
     // NSWH_ > 0: the weight ring is NSWH_ stages of HALF a k-tile (when whole stages do not divide the LDS left
     // beside the token ring): k-tile kt lives in half-stages (2 kt) % NSWH_ and (2 kt + 1) % NSWH_, and the loop's
@@ -191,10 +192,17 @@ struct SplitK : C {
     static constexpr bool SPLITK = true;
 };
 
-// A task function for tiles whose expert has no other m-tile (see run_tile).
+// A narrow task function that run_tile gives only to tiles whose expert has no other m-tile.
 template <class C>
 struct Alone : C {
     static constexpr bool ALONE = true;
+};
+
+// The same task function with the non-temporal hint compiled into the weight loads of its alternating-role loop (see TileFnsOnce).
+template <class C>
+struct WOnce : C {
+    static_assert(C::PP && !C::WQUART, "loops without the run-time hint; the quarter ring's function takes tiles of several m-tiles only");
+    static constexpr bool W_ONCE = true;
 };
 
 template <class C>
@@ -240,7 +248,7 @@ struct TileStream {
     moe_tiling tiling;
     const float* xs_lds;                  // LDS copies of x_scale[T] and w_scale[E] (fp8)
     const float* ws_lds;
-    int sorted;                           // routing in registers (see RoutingInLanes): lane p: sorted_rows[p]
+    int sorted;                           // routing in registers (see routing_in_lanes): lane p: sorted_rows[p]
 };
 
 // Alg. 2 + 4 on registers (see decode_block): B must be below the total tile count.  With pair = 2 (an even number of
@@ -394,9 +402,8 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     auto dma_x = [&](int j, int kt, int stage, bool next) __attribute__((always_inline)) {
         dma16(next ? dx_next : dx_off[j], Xb + (size_t)kt * (BK * ES), lds0 + stage * C::XS_BYTES + (j * NW + wave) * 1024);
     };
-    // ntm: 0 plain, 1 non-temporal, 2 decided at run time.  The 256-row loops are MFMA-bound and always plain:
-    // a branch at each of their DMA instructions measured 2-5 % slower, and a second copy of the loops for the
-    // hinted form made the register allocator spill.
+    // ntm: 0 plain, 1 non-temporal, 2 decided at run time.  The alternating-role loops have no run-time form, as a branch at each of
+    // their DMA instructions measured 2-5 % slower: W_ONCE says it for the whole task function.
     auto dma_w = [&](int j, int kt, int stage, bool next, int ntm) __attribute__((always_inline)) {
         const char* src = (next ? Wt_next : Wt) + (size_t)kt * w_kt_stride +
                           (W_FOLD ? (size_t)j * w_fold : (size_t)0);
@@ -412,16 +419,14 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
     auto dma_wh = [&](int jj, int q, int hs) __attribute__((always_inline)) {
         const char* src = Wt + (size_t)q * (w_kt_stride / 2) + (size_t)(jj * NW * WROWS_PER_INST) * w_row_bytes;
         const uint32_t dst = lds0 + C::W_RING + hs * C::WH_BYTES + (jj * NW + wave) * 1024;
-        if constexpr (C::ALONE) dma16_nt(dw_off[0], src, dst);
+        if constexpr (C::W_ONCE) dma16_nt(dw_off[0], src, dst);
         else dma16(dw_off[0], src, dst);
     };
 
     // quarter-stage weight ring: this wave's instruction for quarter j of k-tile kt, into quarter q of the ring
     auto dma_wq = [&](int j, int kt, int q) __attribute__((always_inline)) {
-        const char* src = Wt + (size_t)kt * w_kt_stride + (W_FOLD ? (size_t)j * w_fold : (size_t)0);
-        const uint32_t dst = lds0 + C::W_RING + q * C::WQ_BYTES + wave * 1024;
-        if constexpr (C::ALONE) dma16_nt(dw_off[W_FOLD ? 0 : j], src, dst);
-        else dma16(dw_off[W_FOLD ? 0 : j], src, dst);
+        dma16(dw_off[W_FOLD ? 0 : j], Wt + (size_t)kt * w_kt_stride + (W_FOLD ? (size_t)j * w_fold : (size_t)0),
+              lds0 + C::W_RING + q * C::WQ_BYTES + wave * 1024);
     };
 
     if (C::EARLY_W) {
@@ -836,14 +841,14 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 if constexpr (STEADY) {
                     if constexpr (C::WQUART) dma_wq(j, kt + 2, quarter(j));
                     else if constexpr (C::WHALF) dma_wh(j, 2 * kt + 4, prevw);
-                    else dma_w(j, kt + 2, prevw, false, C::ALONE);
+                    else dma_w(j, kt + 2, prevw, false, C::W_ONCE);
                 }
             };
             auto wb = [&](int j) __attribute__((always_inline)) {
                 if constexpr (STEADY) {
                     if constexpr (C::WQUART) dma_wq(WH + j, kt + 2, quarter(WH + j));
                     else if constexpr (C::WHALF) dma_wh(j, 2 * kt + 5, curw);
-                    else dma_w(WH + j, kt + 2, prevw, false, C::ALONE);
+                    else dma_w(WH + j, kt + 2, prevw, false, C::W_ONCE);
                 }
             };
             // (quarters: slot 2 issues one weight instruction, and the last one, whose quarter slot 3 frees, follows the token rows)
@@ -864,7 +869,7 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
                 // After slot 1 nobody reads tile kt any more.  Slot 1 refills the weight stage freed one k-tile earlier,
                 // slot 2 the token stage just freed; at the wait only slot 1's weight instructions may be in flight.
                 auto wt = [&](int j) __attribute__((always_inline)) {
-                    if constexpr (STEADY) dma_w(j, kt + 2, prevw, false, C::ALONE);
+                    if constexpr (STEADY) dma_w(j, kt + 2, prevw, false, C::W_ONCE);
                 };
                 if constexpr (ROLE == 0) {
                     mma(integral_constant<int, WI>{}, wt);
@@ -1164,12 +1169,17 @@ __device__ __forceinline__ void pipe_tile(const GemmArgs& a, const int32_t* __re
             }
         }
         if constexpr (STAGED) {
-            // read the corner back row by row: cu 16-byte chunks per row, 64 / cu rows per instruction.  The stores are whole 128-byte lines
-            // that this launch does not read again, and go out non-temporally: kept in L2 they push out the weight panels and token rows that
+            // read the corner back row by row: cu 16-byte chunks per row, 64 / cu rows per instruction.  This launch does not read the outputs again,
+            // and they go out non-temporally: kept in L2 they push out the weight panels and token rows that
             // the workgroups share (a round of 256 tiles writes as much as all L2s hold), and what is still there at the end of the
-            // launch is written back then.  64 experts, 2048 -> 3072, plain / non-temporal, us: bf16 32 rows each 136 / 127, 128 rows 160 / 145,
-            // 256 rows 208 / 198, 512 rows 350 / 346; fp8 78 / 73, 97 / 91, 128 / 115, 205 / 201.  (Write-through without the hint is as good
-            // up to 128 rows and no better than plain stores beyond.)
+            // launch is written back then.  A wavefront writes a row in pieces of 128 bytes (64 columns each; 64 with the activation) or 64 bytes (32
+            // columns; 32 with it), of which two or four wavefronts fill a line.  Most still meet in L2 (WRITE_SIZE over the size of Y, 1.000 for plain
+            // stores: pieces of 128 bytes 1.003, of 64 1.11 and, 250 rows each with the activation, 1.14, of 32 1.03), and the
+            // hint gains for every length.  64 experts, 2048 -> 2816, even routing, plain / non-temporal, us: bf16, pieces of 64 bytes, 60 rows
+            // each 135 / 123, 130 rows 151 / 136; of 32, 60 rows 132 / 122, 73 rows 138 / 124; of 128, [E][N][K] 250 rows 208 / 189, 250 rows 208 / 199; of
+            // 64 with the activation, 250 rows 204 / 198; fp8, of 64, 73 rows 78 / 71, of 32, 77 / 71.  Skewed routings 0 to 4 % of it; the only loss
+            // is within the noise (8 experts, 4096 -> 14336, 128 x 128 tiles, pieces of 32, 40 rows 189 +- 3 / 194 +- 3).  (Write-through without the
+            // hint is as good up to 128 rows and no better than plain stores beyond.)
             wait_vmcnt<0>();   // the row ids, long since there; told here so that no wait lands between the stores
             const int cu = cu_;
             const int rpi = 64 / cu;
@@ -1413,7 +1423,7 @@ template <class C, class... Tails>
 struct TileFnsOnce : TileFns<C, Tails...> {
     static __device__ __forceinline__ void run(const GemmArgs& a, const int32_t* __restrict__ map, const MapLayout& L,
                                                const TileCoord& tc, char* smem) {
-        if (tc.m_tiles == 1 && tc.rows > C::BM / 2 && tc.streams >= kOnceTiles) pipe_tile<Alone<C>>(a, map, L, tc, smem);
+        if (tc.m_tiles == 1 && tc.rows > C::BM / 2 && tc.streams >= kOnceTiles) pipe_tile<WOnce<C>>(a, map, L, tc, smem);
         else run_tile<C, Tails...>(a, map, L, tc, smem);
     }
 };

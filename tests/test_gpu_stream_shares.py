@@ -23,14 +23,14 @@ CASES = [
     ("fp8", "nk", 128, 32, 64, 6, 512, 512, "uniform_topk", True, ()),
     ("fp8", "nk", 256, 50, 16, 2, 896, 512, "zipf", False, ()),
     ("fp8", "kn", 256, 50, 200, 2, 128, 512, "zipf", False, (8, 2)),         # one k-tile, four groups of task records
-    # K too short for the deep ring: resident in the two-wavefront form
+    # K too short for the deep ring: resident in the form of two workgroups per CU
     ("bf16", "kn", 256, 60, 32, 2, 128, 512, "gauss_topk", True, (8, 32, 2)),
     ("bf16", "kn", 128, 60, 32, 2, 320, 384, "zipf", False, (8, 32, 2)),
     ("fp8", "kn", 256, 60, 32, 2, 256, 512, "zipf", False, (8, 32, 2)),
     ("fp8", "kn", 128, 60, 32, 2, 512, 640, "gauss_topk", True, (8, 32, 2)),
     # ... with the most scales that a streaming launch holds (T + E = 2048)
     ("fp8", "kn", 128, 1984, 64, 1, 512, 384, "zipf", False, (8, 64, 2)),
-    # more tiles than CUs, one workgroup per tile in the two-wavefront form (more than 256 experts, or T + E > 2048)
+    # more tiles than CUs, one workgroup per tile, two per CU (more than 256 experts, or T + E > 2048)
     ("bf16", "kn", 256, 100, 300, 4, 192, 512, "gauss_topk", False, (2,)),
     ("bf16", "kn", 128, 100, 300, 4, 384, 256, "zipf", True, (2,)),
     ("fp8", "kn", 256, 100, 300, 4, 128, 512, "zipf", True, (2,)),
