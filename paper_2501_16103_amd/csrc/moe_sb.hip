@@ -541,6 +541,7 @@ int run_splitk(const void* X, const void* W, const void* task_map, void* Y, cons
                hipStream_t s) {
     if (!X || !W || !task_map || !Y || !ws) return MOE_ERR_INVALID_ARG;
     if (((uintptr_t)X & 15) || ((uintptr_t)W & 15) || ((uintptr_t)Y & 15) || ((uintptr_t)task_map & 15)) return MOE_ERR_INVALID_ARG;
+    if ((int64_t)d->T * d->K * 2 >= (int64_t)1 << 32) return MOE_ERR_UNSUPPORTED;   // (rows are addressed by 32-bit offsets)
     GemmArgs a{};
     a.X = X; a.W = W; a.map = static_cast<const int32_t*>(task_map); a.Y = Y;
     a.T = d->T; a.k = d->k; a.E = d->E; a.K = d->K; a.N = d->N;

@@ -150,6 +150,17 @@ def test_splitk_host_functions():
     assert lib.moe_grouped_gemm_splitk(16, 16, 16, 16, None, 2, 16, 1 << 30, None) == mb.MOE_ERR_INVALID_ARG
 
 
+def test_every_product_refuses_tokens_beyond_32_bit_offsets():
+    """X of 4 GiB: refused before any launch (the pointers are never read)."""
+    lib, T, K = mb.lib(), 1 << 17, 1 << 14
+    d = mb.GemmDesc(mb.MOE_DTYPE_BF16, T, 1, 8, K, 256, 256, 256).c_struct()
+    assert lib.moe_grouped_gemm(16, 16, None, 16, 16, ctypes.byref(d), None) == mb.MOE_ERR_UNSUPPORTED
+    assert lib.moe_grouped_gemm_tail_split(16, 16, 16, 16, ctypes.byref(d), 16, ctypes.c_size_t(1 << 30), None) == mb.MOE_ERR_UNSUPPORTED
+    assert lib.moe_grouped_gemm_splitk(16, 16, 16, 16, ctypes.byref(d), 2, 16, ctypes.c_size_t(1 << 30), None) == mb.MOE_ERR_UNSUPPORTED
+    d = mb.GemmDesc(mb.MOE_DTYPE_BF16, 1 << 14, 1, 8, 1 << 17, 256, 256, 256).c_struct()
+    assert lib.moe_grouped_gemm_splitk_static(16, 16, 16, 16, ctypes.byref(d), 2, None) in (mb.MOE_ERR_UNSUPPORTED, mb.MOE_ERR_HIP)   # (no GPU here)
+
+
 def test_default_tail_split():
     """Host-only: the rest of a round that a uniform routing leaves decides, for any number of experts."""
     cases = {  # R, E, K, N
