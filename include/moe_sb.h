@@ -308,8 +308,8 @@ enum { MOE_LAUNCH_AUTO = 0, MOE_LAUNCH_PER_TILE = 1, MOE_LAUNCH_RESIDENT = 2 };
  *   fp8: Y = (sum over e4m3 products in fp32) * x_scale[t] * w_scale[e].
  * Accumulation is fp32; the store rounds to bf16 (nearest even).
  * Requires K % 64 == 0 (bf16) / K % 128 == 0 (fp8) and N % tile_n == 0,
- * and a launch of less than 2^32 work items (2^23 tiles or more at 512
- * threads each would be too many), else MOE_ERR_UNSUPPORTED.  (tile_m, tile_n, dtype) must be a supported
+ * X of less than 4 GiB, and a launch of less than 2^32 work items (2^23
+ * tiles or more at 512 threads each would be too many), else MOE_ERR_UNSUPPORTED.  (tile_m, tile_n, dtype) must be a supported
  * combination: see moe_tile_supported.  A map whose header does not match
  * `desc`, or whose status is non-zero, makes the kernel a no-op.
  * topk_ids is accepted for symmetry with the problem statement and may be
@@ -348,7 +348,7 @@ int moe_pair_gemm_launches(int T, int k, int E, int N, const moe_tiling* tiling,
  *              (k_parts * T*k * N fp32); owned by the caller, contents undefined afterwards; calls that share a
  *              workspace must not overlap.
  * Supported: bf16, MOE_W_LAYOUT_KN, MOE_EPILOGUE_NONE, tile 256 x 256 without slack rows and with one tiling
- * strategy, k_parts 2 or 4 with (K / 64) % k_parts == 0 and K / 64 / k_parts >= 8, N % 256 == 0; anything else
+ * strategy, k_parts 2 or 4 with (K / 64) % k_parts == 0 and K / 64 / k_parts >= 8, N % 256 == 0, X of less than 4 GiB; anything else
  * returns MOE_ERR_UNSUPPORTED.  MOE_ERR_INVALID_ARG for NULL or misaligned pointers or a workspace that is too small.
  */
 int moe_grouped_gemm_splitk(const void* X, const void* W, const void* task_map, void* Y, const moe_gemm_desc* desc,

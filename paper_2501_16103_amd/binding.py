@@ -494,7 +494,7 @@ class MoeLayerPlan:
 
     @staticmethod
     def _streamed(g: Tiling, T: int, k: int, E: int, K: int, N: int) -> Tiling:
-        """A gate+up product of 9 to 32 rows per expert whose wide tiles are 1.75 to 4 rounds of the chip, and whose 16-row tiles the library would
+        """A gate+up product of 9 to 32 rows per expert whose wide tiles are at least one and a half rounds of the chip, and whose 16-row tiles the library would
         stream with up to 64 rows of an expert as one tile, is run that way instead of with one workgroup per 256 x 256 tile: the weights
         of such a launch are all it moves, and a round's start, end and remainder are a tenth of it.  What separates gain from loss is N: where
         the weight rows are a multiple of 2 KB long, the tiles read them at 5.7 to 6.0 TB/s, elsewhere at 6.2 to 6.4, what the
@@ -508,9 +508,11 @@ class MoeLayerPlan:
           17 to 32 rows, N a multiple of 1024: up to 16 experts 1.00 to 1.15 / 0.94 to 1.12, but with 449 to 512 tiles, two rounds without room for the
             busy experts' second tiles, 1.03 to 1.11 / 0.86 to 1.06; beyond 16 experts 0.98 to 1.11 / 0.84 to 1.08
           17 to 32 rows, others: 0.89 to 1.08 / 0.83 to 1.06
-        A few rows more than 8 on 448 to 511 tiles are not merged, as it would not save a round: with 448 still 1.09 to 1.11 / 1.00 to 1.04 (8 experts) and 1.06
-        / 0.97 (16), but 480 1.02 / 0.87 (12) and 32 experts 1.05 / 0.86.  Fewer tiles, 9 rows: 8 experts, 2048 -> 8192 48 / 46 us even, 47 / 69 skewed.
-        Beyond 1024 the gain fades (1280 tiles 1.01 to 1.09 / 0.99 to 1.06; 256 experts, 7168 -> 4096, 12 rows 0.97).  Beyond 256 experts nothing streams:
+        By tiles, 16 rows, K = 2048: 288 to 352 0.81 to 0.99 / 0.90 to 0.98, 384 1.06 to 1.08 / 1.02 to 1.05, 416 1.09 to 1.13 / 1.03 to 1.11 (8, 16 and 32 experts;
+        256, one round, 0.97 to 0.99 / 0.80 to 0.97); more than 1024, up to 32 experts, 1088 1.10 to 1.16 / 1.06 to 1.13, 1152 1.06 to 1.08 / 1.04 to 1.06, 1792 1.03
+        to 1.06 / 1.03 to 1.05 (2048, 8 experts, 1.10 / 1.08), beyond 32 experts 1.01 to 1.03 / 0.95 to 1.00 (256 experts, 7168 -> 4096, 12 rows 0.97).
+        A few rows more than 8 are not merged where it would not save one of two rounds: 416 and 448 tiles still 1.06 to 1.13 / 0.97 to 1.04 (8 and 16 experts), but
+        384, 12 rows, 1.03 to 1.05 / 0.86 to 0.94, 480 1.02 / 0.87 (12) and 448, 32 experts, 1.05 / 0.86.  Beyond 256 experts nothing streams:
         every 16-row tile would read its panel by itself (384 experts, 4096 -> 512, 9 rows 0.90 / 0.96, 24 rows 0.74 / 0.74)."""
         R, tiles = T * k, E * (N // 256)
         spare = not 448 < tiles <= 512       # room in the second round for a skewed routing's second tiles
@@ -518,10 +520,11 @@ class MoeLayerPlan:
             fits = N % (512 if E <= 48 else 1024) == 0
         else:
             fits = R <= 32 * E and E <= 16 and N % 1024 == 0 and spare
-        if not (fits and R > 8 * E and 448 <= tiles <= 1024 and g.tile_m == 256):
+        if not (fits and R > 8 * E and 384 <= tiles <= (2048 if E <= 32 else 1024) and g.tile_m == 256):
             return g
         form = moe_rows16_launch(MOE_DTYPE_BF16, 256, T, k, E, K, N)
-        return Tiling(16, 256) if form == MOE_ROWS16_STREAM_MERGED or (form == MOE_ROWS16_STREAM and E <= 16 and spare and K >= 1024) else g
+        single = form == MOE_ROWS16_STREAM and E <= 16 and 416 <= tiles <= 448 and K >= 1024
+        return Tiling(16, 256) if form == MOE_ROWS16_STREAM_MERGED or single else g
 
     def __init__(self, T: int, k: int, E: int, hidden: int, inter: int, device="cuda:0"):
         self.T, self.k, self.E, self.hidden, self.inter = T, k, E, hidden, inter

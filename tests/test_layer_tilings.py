@@ -10,16 +10,24 @@ from paper_2501_16103_amd import binding as mb
     (128, 2, 8, 4096, 14336, (16, 256)),
     (129, 2, 8, 4096, 14336, (256, 256)),
     (64, 2, 8, 4096, 7168, (16, 256)),      # 448 wide tiles
-    (64, 2, 8, 4096, 7040, (256, 256)),     # 440
+    (64, 2, 8, 4096, 7040, (256, 256)),     # 440, N a multiple of 256 only
+    (64, 2, 8, 4096, 6656, (16, 256)),      # 416
+    (64, 2, 8, 4096, 6144, (16, 256)),      # 384
+    (64, 2, 8, 4096, 5888, (256, 256)),     # 368
     (64, 2, 8, 3840, 14336, (16, 256)),     # any K from which the streamed tiles are merged on
     (64, 2, 8, 1024, 14336, (16, 256)),
     (64, 2, 8, 768, 14336, (256, 256)),
     (64, 4, 16, 4096, 8192, (16, 256)),     # 1024 wide tiles, 16 experts
     (128, 4, 16, 4096, 8192, (16, 256)),
-    (64, 4, 17, 4096, 8192, (256, 256)),    # 1088
+    (64, 4, 17, 4096, 8192, (16, 256)),     # 1088
+    (128, 4, 32, 2048, 8192, (16, 256)),    # 2048
+    (128, 4, 32, 2048, 8448, (256, 256)),   # 2112
+    (128, 4, 36, 4096, 4096, (256, 256)),   # 1152, more than 32 experts
     (102, 4, 24, 4096, 4096, (256, 256)),   # 17 rows per expert, more than 16 experts
     (96, 4, 24, 4096, 4096, (16, 256)),     # 16
     (36, 2, 8, 4096, 7168, (16, 256)),      # 9 rows: merging the 448 tiles would not save a round, but the second one has room
+    (36, 2, 8, 4096, 6656, (16, 256)),
+    (36, 2, 8, 4096, 6144, (256, 256)),     # ... 384
     (54, 2, 12, 2048, 5120, (256, 256)),    # ... 480: little room
     (76, 4, 32, 2048, 1792, (256, 256)),    # ... 448, more experts
     (36, 2, 8, 768, 7168, (256, 256)),
